@@ -53,6 +53,12 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   return v;
 }
 
+// Orders LDS accesses between the lanes of one wave.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 template <class T>
 __device__ __forceinline__ T ld_stream(const T* p) {
   return __builtin_nontemporal_load(p);

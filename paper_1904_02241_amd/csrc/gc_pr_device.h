@@ -14,6 +14,7 @@ namespace {
 
 
 using gcd::kWave;
+using gcd::wave_lds_fence;
 
 constexpr int kThreads = 256;
 
@@ -69,12 +70,6 @@ __device__ __forceinline__ double update_vertex(const Update& u, int32_t v, doub
 __device__ __forceinline__ double update_vertex(const Update& u, int32_t v, double sum, double D) {
   double dl = 0.0;
   return update_vertex(u, v, sum, D, dl);
-}
-
-// Orders LDS accesses between the lanes of one wave.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // Work-group sum of one double per thread (fixed reduction tree), returned

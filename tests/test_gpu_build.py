@@ -80,6 +80,51 @@ def test_partition_bit_exact(name, W, k, direction):
     np.testing.assert_array_equal(got["range_ptr"].reshape(R + 1, B).T, want.range_ptr)
 
 
+def _arcs(n, m, seed):
+    """A graph of exactly m arcs (distinct, no loops) over n vertices."""
+    rng = np.random.default_rng(seed)
+    keys = rng.choice(n * (n - 1), m, replace=False)
+    u, v = keys // (n - 1), keys % (n - 1)
+    return gg.from_edges(n, u, v + (v >= u), name=f"arcs{n}_{m}")
+
+
+# the edges of the radix passes: one arc, a head word (64 arcs) and an arc tile (8192) less, full and more; one
+# vertex bit, digits of equal and unequal width; one block, the largest one-pass block count and two passes;
+# rows and blocks far apart (long runs of empty rows)
+@pytest.mark.parametrize("n,m,W,k", [(2, 1, 1 << 10, 256), (2, 2, 1 << 10, 256), (300, 63, 1 << 10, 256),
+                                     (300, 64, 1 << 10, 256), (300, 65, 1 << 10, 512), (1025, 8191, 1 << 10, 256),
+                                     (1025, 8192, 1 << 10, 256), (1024, 8193, 1 << 10, 256),
+                                     (1 << 20, 20000, 1 << 10, 16384), ((1 << 20) + 1, 20000, 1 << 10, 16384),
+                                     (3000001, 5, 1 << 11, 16384), (200000, 16385, 1 << 17, 1024)])
+@pytest.mark.parametrize("direction", ["pull", "push"])
+def test_radix_edges_bit_exact(n, m, W, k, direction):
+    import paper_1904_02241_amd as gc
+    g = _arcs(n, m, seed=m)
+    g.with_weights(5)
+    print(f"radix n={n} m={m} W={W} k={k} {direction}", flush=True)
+    h = load(g, weights=True)
+    ar, ac, aw = oracle.transpose(g.n, g.rowptr, g.colidx, g.weights)
+    tr, tc, tw = np.empty(n + 1, np.int32), np.empty(m, np.int32), np.empty(m, np.int32)
+    gc.graph_export_transpose(h, tr, tc, tw)
+    gc.gc_sync()
+    for got, want in ((tr, ar), (tc, ac), (tw, aw)):
+        np.testing.assert_array_equal(got, want)
+    part = gc.tocab_partition(h, gc.GC_PULL if direction == "pull" else gc.GC_PUSH, W, k)
+    got, B, P, R = export_partition(part, g)
+    part.free()
+    h.free()
+    if direction == "push":
+        ar, ac, aw = g.rowptr, g.colidx, g.weights
+    want = oracle.partition(n, n, ar, ac, W, k, aw)
+    assert (B, P) == (want.B, want.P)
+    for name in ("blk_rowoff", "row_ptr"):
+        np.testing.assert_array_equal(got[name], getattr(want, name))
+    np.testing.assert_array_equal(got["id_map"][:P], want.id_map)
+    np.testing.assert_array_equal(got["col"], want.col)
+    np.testing.assert_array_equal(got["w"], want.w)
+    np.testing.assert_array_equal(got["range_ptr"].reshape(R + 1, B).T, want.range_ptr)
+
+
 def test_partition_rejects_bad_widths():
     import paper_1904_02241_amd as gc
     g = gg.rmat(12, 8, seed=1)
