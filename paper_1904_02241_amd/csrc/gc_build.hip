@@ -111,20 +111,22 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int32_t* __re
 // kRadixTile arcs (k_radix_count), scans the counts digit-major, then ranks
 // each tile's arcs in LDS and writes every digit's run to its place
 // (k_radix_move), so writes leave in runs of kRadixTile / digits arcs on
-// average. Digits have at most kRadixBits bits (1024 runs per tile of 8192
-// arcs: 32-byte runs); the transpose takes 8 (128-byte runs: a pass more,
-// but whole cache lines), the block of a column one pass of its own width up
-// to 1024 blocks. Measured on an R-MAT graph of 1.5 M vertices and 23 M
-// weighted arcs: a pass 0.27 ms (move 0.23, 2.4 TB/s; count 0.04), so the
-// transpose takes 0.82 ms (random scatter through atomics, in-degree atomics
+// average. Digits have at most kRadixBits bits (1024 runs per tile of 4096
+// arcs: 16-byte runs); the transpose takes at most 8 (64-byte runs: a pass
+// more, but whole sectors), the block of a column one pass of its own width
+// up to 1024 blocks. Measured on an R-MAT graph of 1.5 M vertices and 23 M
+// weighted arcs: a pass 0.20 ms (move 0.16, 3.4 TB/s; count 0.04), so the
+// transpose takes 0.62 ms (random scatter through atomics, in-degree atomics
 // and per-row sorts: 5.4 ms) and the partition into 46 blocks of 2^15 with
-// its local rows 0.45 ms (one wave per merge range walking its rows' blocks
+// its local rows 0.38 ms (one wave per merge range walking its rows' blocks
 // in order, twice, and a copy per row: 8.3 ms); loading, partitioning and
-// exporting the graph 14.4 -> 2.1 ms.
+// exporting the graph 14.4 -> 1.9 ms. Tile shapes tried (move, per pass):
+// 512 threads x 16 arcs 0.228 (132 registers: one work-group per CU), 1024 x
+// 8 0.180, 512 x 8 0.163, the last held to 80 registers 0.204 (spills).
 
 constexpr int kRadixThreads = 512;
 constexpr int kRadixWaves = kRadixThreads / kWave;
-constexpr int kRadixItems = 16;  // arcs per thread
+constexpr int kRadixItems = 8;  // arcs per thread
 constexpr int kRadixTile = kRadixThreads * kRadixItems;
 constexpr int kRadixBits = 10;
 constexpr int kTransposeBits = 8;
@@ -202,8 +204,8 @@ struct RadixArgs {
   int32_t low_mask;
 };
 
-// One pass. Thread t of wave v holds the arcs v * 1024 + r * 64 + lane,
-// r < 16, of its tile. Ranks: lanes with equal digits find each other with
+// One pass. Lane l of wave v holds the arcs 512 v + 64 r + l, r < 8, of its
+// tile (eight arcs per thread keep two work-groups per CU resident). Ranks: lanes with equal digits find each other with
 // one ballot per digit bit, the wave's counter of the digit (LDS) gives the
 // arcs of earlier rounds. The three arrays then go through one LDS stage,
 // one after another, into digit order, and out in that order.
@@ -219,13 +221,10 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_move(RadixArgs a) {
   const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kRadixTile;
   const int32_t len = static_cast<int32_t>(min<int64_t>(kRadixTile, a.m - e0));  // >= 1
   const int32_t p0 = wid * (kRadixTile / kRadixWaves) + lane;  // position of the thread's arc of round 0
-  int32_t key[kRadixItems], row[kRadixItems];
+  int32_t key[kRadixItems], row[kRadixItems];  // row: filled here only when it comes from rowptr
 #pragma unroll
   for (int r = 0; r < kRadixItems; ++r) key[r] = gcd::ld_stream(a.key + e0 + min(p0 + r * kWave, len - 1));
-  if (a.row) {  // uniform
-#pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) row[r] = gcd::ld_stream(a.row + e0 + min(p0 + r * kWave, len - 1));
-  } else {
+  if (!a.row) {  // uniform
     // rows of the tile's arcs: each row that starts inside the tile marks its
     // first arc (the last of several starting there wins), then a running
     // maximum
@@ -336,6 +335,10 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_move(RadixArgs a) {
       if (a.key_out) a.key_out[to[r]] = k;
       if (a.low_out) a.low_out[to[r]] = static_cast<uint16_t>(k & a.low_mask);
     }
+  }
+  if (a.row) {  // uniform
+#pragma unroll
+    for (int r = 0; r < kRadixItems; ++r) row[r] = gcd::ld_stream(a.row + e0 + min(p0 + r * kWave, len - 1));
   }
   __syncthreads();
 #pragma unroll
