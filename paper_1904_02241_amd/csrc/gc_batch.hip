@@ -128,12 +128,13 @@ __device__ bool grid_sync(const BatchArgs& a) {
   return ok;
 }
 
-__device__ __forceinline__ Update make_update(const BGraph& g, double d, const double* dtotal_in, float* rank_out) {
+__device__ __forceinline__ Update make_update(const BGraph& g, double d, const double* dtotal, float* rank_out) {
   Update u;
   u.base = (1.0 - d) / g.n;
   u.d = d;
   u.inv_n = 1.0 / g.n;
-  u.dtotal_in = dtotal_in;
+  u.din = dtotal;
+  u.dcount = 1;
   u.dpart = g.dpart;
   u.rowptr = g.rowptr;
   u.contrib = g.contrib;

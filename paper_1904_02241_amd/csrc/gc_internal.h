@@ -31,7 +31,9 @@ struct gc_graph_s {
   double* sums = nullptr;     // push accumulators (FP64 atomics)
   int32_t* tile_row_in = nullptr;  // pull tiles over the transposed graph
   int32_t n_tiles_in = 0;
-  double* dpart = nullptr;    // one slot per apply work-group
+  // one slot per update work-group; [1]: kDangSlots slots, used in turn with
+  // [0] by updates of at most that many work-groups
+  double* dpart[2] = {nullptr, nullptr};
   double* dtotal = nullptr;   // [2] ping-pong dangling totals
   unsigned* counter = nullptr;
   int32_t dpart_slots = 0;
@@ -229,12 +231,14 @@ struct Converge {
 // Device buffers an iteration writes besides rank_out: contributions (two,
 // used in turn by the forms that read one while writing the next), FP64
 // push sums (n), FP64 dangling partials (one per update work-group, at most
-// the graph's dpart_slots) and their two totals, and the pull partition's
-// partial sums (P + 8). By default the graph's and the partition's own.
+// the graph's dpart_slots; a second buffer of kDangSlots, or null: every
+// iteration's partials are then reduced by a kernel of their own) and their
+// two totals, and the pull partition's partial sums (P + 8). By default the graph's and the partition's own.
+constexpr int32_t kDangSlots = 1024;
 struct PrBuffers {
   float* contrib[2];
   double* sums;
-  double* dpart;
+  double* dpart[2];
   double* dtotal;
   float* partial;
 };

@@ -617,8 +617,8 @@ __global__ __launch_bounds__(kThreads) void k_pr_plain_pull(const int32_t* __res
   __shared__ float vals[kStageCap];
   const int32_t r0 = tile_row[blockIdx.x], r1 = tile_row[blockIdx.x + 1];
   double mine = 0.0, dl = 0.0;
-  if (r0 < r1) {
-    const double D = *u.dtotal_in;
+  if (r0 < r1) {  // uniform
+    const double D = dangling_total(u, dangling_share(u));
     pull_tile(t_rowptr, t_col, c_in, r0, r1, vals,
               [&](int32_t v, double s) { mine += update_vertex(u, v, s, D, dl); });
   }
@@ -633,9 +633,10 @@ __global__ __launch_bounds__(kThreads) void k_pr_merge(const int32_t* __restrict
                                                        const uint16_t* __restrict__ id16,
                                                        const float* __restrict__ partial, Update u) {
   __shared__ double acc[K];
+  const double share = dangling_share(u);
   merge_accumulate<K, kFlat>(range_ptr, B, id16, partial, blockIdx.x, acc);
   const int32_t v0 = blockIdx.x * K;
-  const double D = *u.dtotal_in;
+  const double D = dangling_total(u, share);
   double mine = 0.0, dl = 0.0;
   for (int i = threadIdx.x; i < K; i += kThreads) {
     const int32_t v = v0 + i;
@@ -752,7 +753,7 @@ __global__ __launch_bounds__(NT) void k_pr_merge_persist(const int32_t* __restri
         if (e0 + e >= a && e0 + e < z) atomicAdd(&acc[(id[k] >> (16 * e)) & 0xFFFFu], static_cast<double>(pv[e]));
     }
   };
-  const double D = *u.dtotal_in;
+  const double D = dangling_total<NT>(u, dangling_share<NT>(u));
   double mine = 0.0, dl = 0.0;
   const int32_t tid = threadIdx.x;
   int32_t j = blockIdx.x;
@@ -910,6 +911,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds(const int32_t* 
   extern __shared__ double acc[];  // the block's W sums
   const int32_t W = 1 << log2W;
   const int32_t v0 = static_cast<int32_t>(blockIdx.x) << log2W;
+  const double share = dangling_share<kPushLdsThreads>(u);
   for (int32_t i = threadIdx.x; i < W; i += kPushLdsThreads) acc[i] = 0.0;
   __syncthreads();
   const int32_t r0 = blk_rowoff[blockIdx.x], r1 = blk_rowoff[blockIdx.x + 1];
@@ -943,7 +945,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds(const int32_t* 
     }
   }
   __syncthreads();
-  const double D = *u.dtotal_in;
+  const double D = dangling_total<kPushLdsThreads>(u, share);
   double mine = 0.0, dl = 0.0;
   for (int32_t i = threadIdx.x; i < W; i += kPushLdsThreads) {
     const int32_t v = v0 + i;
@@ -1102,6 +1104,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
   const int32_t v0 = static_cast<int32_t>(blockIdx.x) << log2W;
   const int lane = threadIdx.x & (kWave - 1);
   const int32_t wid = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x) / kWave);
+  const double share = dangling_share<kPushLdsThreads>(u);
   for (int32_t i = threadIdx.x; i < W; i += kPushLdsThreads) acc[i] = 0.0;
   __syncthreads();
   const int32_t r0 = blk_rowoff[blockIdx.x], r1 = blk_rowoff[blockIdx.x + 1];
@@ -1133,7 +1136,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
     }
   }
   __syncthreads();
-  const double D = *u.dtotal_in;
+  const double D = dangling_total<kPushLdsThreads>(u, share);
   double mine = 0.0, dl = 0.0;
   // the block's out-degrees (and previous ranks) in registers first, then
   // the update on them (a load per vertex inside it is a round trip per step)
@@ -1171,7 +1174,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
 
 __global__ __launch_bounds__(kThreads) void k_pr_apply(double* __restrict__ sums, Update u) {
   const int32_t v = blockIdx.x * kThreads + threadIdx.x;
-  const double D = *u.dtotal_in;
+  const double D = dangling_total(u, dangling_share(u));
   double mine = 0.0, dl = 0.0;
   if (v < u.n) {
     const double s = sums[v];
@@ -1192,7 +1195,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_base(const int32_t* __restrict_
   const int32_t v = blockIdx.x * kThreads + threadIdx.x;
   double mine = 0.0, dl = 0.0;
   if (v < u.n) {
-    const double D = *u.dtotal_in;
+    const double D = *u.din;
     double s = 0.0;
     for (int32_t i = t_rowptr[v]; i < t_rowptr[v + 1]; ++i) s += static_cast<double>(c_in[t_col[i]]);
     mine = update_vertex(u, v, s, D, dl);
@@ -1210,7 +1213,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_vwc(const int32_t* __restrict__
                                                      const float* __restrict__ c_in, Update u) {
   constexpr int32_t kPerGroup = kThreads / VW;
   const int lane = threadIdx.x & (VW - 1);
-  const double D = *u.dtotal_in;
+  const double D = *u.din;
   double mine = 0.0, dl = 0.0;
   for (int32_t v0 = blockIdx.x * kPerGroup; v0 < u.n; v0 += gridDim.x * kPerGroup) {
     const int32_t v = v0 + static_cast<int32_t>(threadIdx.x) / VW;
@@ -1341,7 +1344,7 @@ hipError_t ladder_run(gc_graph g, gc_tocab t, int32_t method, float damping, int
   u.d = damping;
   u.base = (1.0 - static_cast<double>(damping)) / n;
   u.inv_n = dangling == GC_DANGLING_UNIFORM ? 1.0 / n : 0.0;
-  u.dpart = g->dpart;
+  u.dpart = g->dpart[0];
   u.rowptr = g->rowptr;
   u.n = n;
   u.rank_out = nullptr;
@@ -1352,14 +1355,15 @@ hipError_t ladder_run(gc_graph g, gc_tocab t, int32_t method, float damping, int
     GC_HIP_TRY(hipMemcpyAsync(rows.data(), t->blk_rowoff, sizeof(int32_t) * rows.size(), hipMemcpyDeviceToHost, s));
     GC_HIP_TRY(hipStreamSynchronize(s));
   }
-  u.dtotal_in = nullptr;
+  u.din = nullptr;
+  u.dcount = 1;
   u.contrib = g->contrib[0];
   k_pr_init<<<vgrid, kThreads, 0, s>>>(rank_in, u, cb ? g->sums : nullptr);
-  k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart, vgrid, g->dtotal, nullptr, nullptr);
+  k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart[0], vgrid, g->dtotal, nullptr, nullptr);
   GC_HIP_TRY(hipGetLastError());
   int cur = 0;
   for (int32_t it = 0; it < iters; ++it) {
-    u.dtotal_in = g->dtotal + (it & 1);
+    u.din = g->dtotal + (it & 1);
     u.rank_out = (it == iters - 1) ? rank_out : nullptr;
     if (cb) {
       {
@@ -1390,7 +1394,7 @@ hipError_t ladder_run(gc_graph g, gc_tocab t, int32_t method, float damping, int
     }
     {
       ProfScope prof("pr_dangling", s);
-      k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart, vgrid, g->dtotal + ((it + 1) & 1), nullptr, nullptr);
+      k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart[0], vgrid, g->dtotal + ((it + 1) & 1), nullptr, nullptr);
     }
     GC_HIP_TRY(hipGetLastError());
   }
@@ -1469,7 +1473,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
                         const float* rank_in, float* rank_out, int32_t iters, hipStream_t s, Converge* cv,
                         int32_t ladder, const PrBuffers* bufs) {
   const int32_t n = g->n;
-  const PrBuffers buf = bufs ? *bufs : PrBuffers{{g->contrib[0], g->contrib[1]}, g->sums, g->dpart, g->dtotal,
+  const PrBuffers buf = bufs ? *bufs : PrBuffers{{g->contrib[0], g->contrib[1]}, g->sums, {g->dpart[0], g->dpart[1]}, g->dtotal,
                                                  t ? t->partial : nullptr};
   if (cv) iters = cv->max_iters;
   if (iters == 0)
@@ -1482,14 +1486,15 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   u.d = damping;
   u.base = (1.0 - static_cast<double>(damping)) / n;
   u.inv_n = dangling == GC_DANGLING_UNIFORM ? 1.0 / n : 0.0;
-  u.dpart = buf.dpart;
+  u.dpart = buf.dpart[0];
   u.rowptr = g->rowptr;
   u.n = n;
   u.rank_out = nullptr;
   const int vgrid = (n + kThreads - 1) / kThreads;
 
   // contributions of rank_in and D of iteration 0 -> dtotal[0]
-  u.dtotal_in = nullptr;
+  u.din = nullptr;
+  u.dcount = 0;
   u.contrib = buf.contrib[0];
   const bool expanded = push && t && t->W <= kPushLdsMaxWidth && t->xc;
   {
@@ -1499,7 +1504,26 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
       k_pr_push_expand<<<t->n_sblk, kPushLdsThreads, push_x_lds(t->W, t->B), s>>>(push_x(t), t->log2W, n,
                                                                                  buf.contrib[0], t->xc);
   }
-  k_reduce_dangling<<<1, 1024, 0, s>>>(buf.dpart, vgrid, buf.dtotal, nullptr, nullptr);
+  // work-groups of the update kernel, one dangling partial each
+  int32_t parts = vgrid;
+  if (t && !push) parts = t->col16 ? merge_persist_grid(t->k, t->R) : t->R;
+  else if (!push) parts = g->n_tiles_in;
+  else if (t && t->W <= kPushLdsMaxWidth) parts = t->B;
+  // D of the next iteration from `count` partials in u.dpart: left to its
+  // kernels when they are few (the updates then write the two buffers in
+  // turn), else reduced to dtotal[slot], as in convergence mode, whose L1
+  // change needs that kernel anyway
+  const bool few = parts <= kDangFused && buf.dpart[1] && !cv;
+  auto hand_over = [&](int32_t count, int slot) {
+    const bool fused = few && count <= kDangFused;
+    if (!fused) {
+      ProfScope prof("pr_dangling", s);
+      k_reduce_dangling<<<1, 1024, 0, s>>>(u.dpart, count, buf.dtotal + slot, u.lpart, g->ltotal);
+    }
+    u.din = fused ? u.dpart : buf.dtotal + slot;
+    u.dcount = fused ? count : 1;
+  };
+  hand_over(vgrid, 0);
   GC_HIP_TRY(hipGetLastError());
 
   // convergence mode: iterates alternate between rank_out and rank_tmp,
@@ -1508,14 +1532,12 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   if (cv) u.lpart = g->lpart;
   int cur = 0;
   for (int32_t it = 0; it < iters; ++it) {
-    u.dtotal_in = buf.dtotal + (it & 1);
-    double* dtotal_out = buf.dtotal + ((it + 1) & 1);
     u.rank_out = (it == iters - 1) ? rank_out : nullptr;
     if (cv) {
       u.rank_out = iterate[it & 1];
       u.rank_prev = it == 0 ? rank_in : iterate[(it - 1) & 1];
     }
-    int32_t parts = vgrid;  // work-groups of the update kernel
+    u.dpart = few && u.din == buf.dpart[0] ? buf.dpart[1] : buf.dpart[0];
     if (t && !push) {
       if (t->col16) {
         {
@@ -1528,15 +1550,13 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
         }
         u.contrib = buf.contrib[0];
         ProfScope prof("pr_merge", s);
-        const int32_t mg = merge_persist_grid(t->k, t->R);
         switch (t->k) {
 #define GC_MERGE(K) \
-  case K: k_pr_merge_persist<K><<<mg, merge_threads<K>(), 0, s>>>(t->rstart, t->id16s, buf.partial, t->R, u); break;
+  case K: k_pr_merge_persist<K><<<parts, merge_threads<K>(), 0, s>>>(t->rstart, t->id16s, buf.partial, t->R, u); break;
           GC_MERGE(256) GC_MERGE(512) GC_MERGE(1024) GC_MERGE(2048) GC_MERGE(4096) GC_MERGE(8192) GC_MERGE(16384)
 #undef GC_MERGE
           default: return hipErrorInvalidValue;
         }
-        parts = mg;
       } else {
         {
           ProfScope prof("pr_tocab_pull", s);
@@ -1544,7 +1564,6 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
                                                           buf.partial);
         }
         u.contrib = buf.contrib[0];  // safe in place: the pull pass has finished reading c
-        parts = t->R;
         ProfScope prof("pr_merge", s);
         switch (t->k) {
           case 256: launch_merge<256>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
@@ -1559,14 +1578,12 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
       }
     } else if (!push) {
       u.contrib = buf.contrib[cur ^ 1];
-      parts = g->n_tiles_in;
       ProfScope prof("pr_plain_pull", s);
       k_pr_plain_pull<<<g->n_tiles_in, kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, g->tile_row_in,
                                                          buf.contrib[cur], u);
       cur ^= 1;
     } else if (expanded) {
       u.contrib = nullptr;  // the contributions go to the rows' expanded copies only
-      parts = t->B;
       ProfScope prof("pr_tocab_push", s);
       const int64_t P = push_xc_stride(t->P);
       k_pr_push_lds_x<<<t->B, kPushLdsThreads, push_x_lds(t->W, t->B), s>>>(
@@ -1574,7 +1591,6 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
           t->xc + ((it + 1) & 1) * P, u);
     } else if (t && t->W <= kPushLdsMaxWidth) {
       u.contrib = buf.contrib[cur ^ 1];
-      parts = t->B;
       ProfScope prof("pr_tocab_push", s);
       k_pr_push_lds<<<t->B, kPushLdsThreads, sizeof(double) * static_cast<size_t>(t->W), s>>>(
           t->blk_rowoff, t->row_ptr, t->id_map, t->col, t->log2W, buf.contrib[cur], u);
@@ -1595,10 +1611,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
       ProfScope prof("pr_apply", s);
       k_pr_apply<<<vgrid, kThreads, 0, s>>>(buf.sums, u);
     }
-    {
-      ProfScope prof("pr_dangling", s);
-      k_reduce_dangling<<<1, 1024, 0, s>>>(buf.dpart, parts, dtotal_out, u.lpart, g->ltotal);
-    }
+    hand_over(parts, (it + 1) & 1);
     GC_HIP_TRY(hipGetLastError());
     if (cv) {  // read this iteration's L1 change
       double delta = 0.0;

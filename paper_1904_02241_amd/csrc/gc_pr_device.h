@@ -8,6 +8,7 @@
 #include <cstdint>
 
 #include "gc_device.h"
+#include "gc_internal.h"
 #include "gc_merge.h"
 
 namespace {
@@ -29,7 +30,8 @@ struct Update {
   double base;      // (1 - d) / n
   double d;         // damping
   double inv_n;     // 1 / n, applied to D in uniform mode (0 in leak mode)
-  const double* dtotal_in;
+  const double* din;  // D of this iteration: the sum of din[0 .. dcount)
+  int32_t dcount;
   double* dpart;    // one dangling partial per work-group of the update kernel
   const int32_t* rowptr;  // out-arc CSR: outdeg(v) = rowptr[v+1] - rowptr[v]
   float* contrib;         // written for the next iteration
@@ -85,6 +87,29 @@ __device__ __forceinline__ double wg_sum(double x) {
   for (int w = 0; w < NT / kWave; ++w) t += part[w];
   __syncthreads();
   return t;
+}
+
+// This thread's share of D (its loads are issued before the caller's own),
+// and D itself, to every thread: up to kDangFused partials of the previous
+// update are added by each work-group in one fixed order, which costs a
+// few loads in the shadow of the tile's, where a reduction kernel between
+// two iterations costs its launch and two memory round trips (4.3 us each
+// on a 1000-vertex graph, more than the rest of its iteration needs).
+// Larger counts come reduced (dcount = 1): at 1024 partials and as many
+// work-groups the repeated reads are 8 MB of L2 traffic, and they grow with
+// the square.
+constexpr int32_t kDangFused = gcx::kDangSlots;
+
+template <int NT = kThreads>
+__device__ __forceinline__ double dangling_share(const Update& u) {
+  double x = 0.0;
+  for (int32_t i = threadIdx.x; i < u.dcount; i += NT) x += u.din[i];
+  return x;
+}
+
+template <int NT = kThreads>
+__device__ __forceinline__ double dangling_total(const Update& u, double share) {
+  return u.dcount == 1 ? *u.din : wg_sum<NT>(share);  // uniform
 }
 
 template <int NT = kThreads>

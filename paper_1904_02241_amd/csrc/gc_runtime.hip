@@ -71,7 +71,7 @@ bool is_device_ptr(const void* p) {
 void free_graph(gc_graph g) {
   if (!g) return;
   void* bufs[] = {g->rowptr, g->colidx, g->w, g->t_rowptr, g->t_colidx, g->t_w, g->contrib[0], g->contrib[1],
-                  g->sums, g->dpart, g->dtotal, g->counter, g->front, g->next, g->queue[0], g->queue[1],
+                  g->sums, g->dpart[0], g->dpart[1], g->dtotal, g->counter, g->front, g->next, g->queue[0], g->queue[1],
                   g->stats, g->tile_row_in, g->visited, g->mark, g->lpart, g->ltotal, g->rank_tmp, g->bc_sigma,
                   g->bc_coef, g->bc_depth, g->bc_order, g->arc_deg,
                   g->arc_pre};
@@ -263,7 +263,8 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
   g->contrib[0] = static_cast<float*>(gcx::dev_alloc(sizeof(float) * n, stream));
   g->contrib[1] = static_cast<float*>(gcx::dev_alloc(sizeof(float) * n, stream));
   g->sums = static_cast<double*>(gcx::dev_alloc(sizeof(double) * n, stream));
-  g->dpart = static_cast<double*>(gcx::dev_alloc(sizeof(double) * g->dpart_slots, stream));
+  g->dpart[0] = static_cast<double*>(gcx::dev_alloc(sizeof(double) * g->dpart_slots, stream));
+  g->dpart[1] = static_cast<double*>(gcx::dev_alloc(sizeof(double) * gcx::kDangSlots, stream));
   g->dtotal = static_cast<double*>(gcx::dev_alloc(sizeof(double) * 2, stream));
   g->counter = static_cast<unsigned*>(gcx::dev_alloc(sizeof(unsigned) * 4, stream));
   const size_t words = (static_cast<size_t>(n) + 31) / 32;
@@ -277,7 +278,7 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
   g->arc_deg = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * n, stream));
   g->arc_pre = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * (static_cast<size_t>(n) + 1), stream));
   bool ok = g->visited && g->mark && g->arc_deg && g->arc_pre && g->rowptr && g->colidx && g->t_rowptr && g->t_colidx && (!g->weighted || (g->w && g->t_w)) &&
-            g->contrib[0] && g->contrib[1] && g->sums && g->dpart && g->dtotal && g->counter && g->front &&
+            g->contrib[0] && g->contrib[1] && g->sums && g->dpart[0] && g->dpart[1] && g->dtotal && g->counter && g->front &&
             g->next && g->queue[0] && g->queue[1] && g->stats;
   if (ok && hipHostMalloc(reinterpret_cast<void**>(&g->stats_host), sizeof(int32_t) * gcx::kStatSlots,
                           hipHostMallocDefault) !=
@@ -512,7 +513,11 @@ int pagerank_iter_noalloc(gc_graph g, gc_tocab t, int32_t dir_if_plain, float da
   gcx::PrBuffers buf;
   buf.contrib[0] = reinterpret_cast<float*>(b + l.contrib0);
   buf.contrib[1] = reinterpret_cast<float*>(b + l.contrib1);
-  buf.dpart = reinterpret_cast<double*>(b + l.dpart);
+  buf.dpart[0] = reinterpret_cast<double*>(b + l.dpart);
+  // the second buffer of dangling partials when it fits beside the rest
+  buf.dpart[1] = l.total + sizeof(double) * gcx::kDangSlots <= kNoAllocScratchBytes
+                     ? reinterpret_cast<double*>(b + l.total)
+                     : nullptr;
   buf.dtotal = reinterpret_cast<double*>(b + l.dtotal);
   buf.sums = l.sums == SIZE_MAX ? nullptr : reinterpret_cast<double*>(b + l.sums);
   buf.partial = l.partial == SIZE_MAX ? nullptr : reinterpret_cast<float*>(b + l.partial);
