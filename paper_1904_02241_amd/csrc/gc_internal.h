@@ -246,6 +246,12 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
                         const float* rank_in, float* rank_out, int32_t iters, hipStream_t s,
                         Converge* cv = nullptr, int32_t ladder = -1, const PrBuffers* bufs = nullptr);
 
+// Small graphs (gc_pr_small.hip): whether all of g's iterations fit one
+// work-group's LDS, and that form of pagerank_run.
+bool pr_small_fits(gc_graph g, bool conv);
+hipError_t pr_small_run(gc_graph g, float damping, int32_t dangling, const float* rank_in, float* rank_out,
+                        int32_t iters, hipStream_t s, Converge* cv);
+
 // PageRank's working-set action among 0 push, 1 pull, 2 + i TOCAB over parts[i].
 int32_t pagerank_fallback_action(const gc_tocab* parts, int32_t n_parts);
 // Scheduler training rows for PageRank (see sched_collect, kind 2).

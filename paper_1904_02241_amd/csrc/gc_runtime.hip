@@ -635,7 +635,7 @@ int pagerank_converge(gc_graph g, gc_tocab t, int32_t dir_if_plain, float dampin
   if (!iters_out) return fail(GC_EINVAL, "pagerank_converge: NULL iters_out");
   if (!g->lpart) {  // first call on this graph: its convergence buffers
     g->lpart = static_cast<double*>(gcx::dev_alloc(sizeof(double) * g->dpart_slots, stream));
-    g->ltotal = static_cast<double*>(gcx::dev_alloc(sizeof(double), stream));
+    g->ltotal = static_cast<double*>(gcx::dev_alloc(2 * sizeof(double), stream));
     g->rank_tmp = static_cast<float*>(gcx::dev_alloc(sizeof(float) * std::max<int32_t>(g->n, 1), stream));
     if (!g->lpart || !g->ltotal || !g->rank_tmp) {
       for (void* p : {static_cast<void*>(g->lpart), static_cast<void*>(g->ltotal), static_cast<void*>(g->rank_tmp)})

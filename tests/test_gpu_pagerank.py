@@ -95,6 +95,28 @@ def test_pagerank_chained_calls_continue_the_iteration():
     h.free()
 
 
+# the one-work-group form of small graphs: one vertex, waves and row groups
+# of every width less, full and more, rows taken by a group and by a wave
+# (star: one row of all arcs), an even and an odd number of iterations, and
+# graphs just inside and just outside the LDS it may take. FP32 rounding of
+# ranks and contributions gives at most 2 * 2^-24 / (1 - 0.85) = 8e-7 in L1.
+@pytest.mark.parametrize("make", [lambda: graphs.edgeless(1), lambda: graphs.cycle(63), lambda: graphs.cycle(64),
+                                  lambda: graphs.cycle(65), lambda: graphs.cycle(257), lambda: graphs.star_in(2000),
+                                  lambda: graphs.star_out(130), lambda: gg.uniform(1025, 1025 * 4, seed=2),
+                                  lambda: gg.uniform(700, 700 * 12, seed=3), lambda: gg.rmat(11, 16, seed=4),
+                                  lambda: gg.uniform(4000, 24000, seed=5), lambda: gg.uniform(4000, 25000, seed=5)],
+                         ids=["one", "c63", "c64", "c65", "c257", "star_in", "star_out", "deg8", "deg24", "rmat11",
+                              "inside", "outside"])
+@pytest.mark.parametrize("form,iters", [("plain_pull", 1), ("plain_push", 2), ("tocab_pull", 7)])
+def test_pagerank_one_work_group(make, form, iters):
+    g = make()
+    print(f"small pagerank {g.name} n={g.n} m={g.m} {form} iters={iters}", flush=True)
+    for mode in (oracle.UNIFORM, oracle.LEAK):
+        got, r0 = pagerank_gpu(g, form, mode, iters=iters)
+        want = oracle.pagerank(g.n, g.rowptr, g.colidx, 0.85, iters, mode=mode, r0=r0)
+        assert l1(got, want) <= L1_TOL
+
+
 def test_pagerank_rejects_overlap_and_bad_args():
     import paper_1904_02241_amd as gc
     from tests.gpu_util import torch
