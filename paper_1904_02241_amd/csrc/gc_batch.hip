@@ -3,15 +3,15 @@
 // one-hot seed vectors on one graph, all iterations in ONE kernel launch.
 //
 // The grid holds at most as many work-groups as the GPU keeps resident, and
-// every phase hands out work items (pull tiles, merge ranges, PPR row
-// groups, dangling reductions) by striding over one flat item space built
-// from per-graph prefix tables. Phases are separated by a grid barrier
-// (atomic arrival counter + generation word, agent-scope fences around it so
-// writes of one XCD are visible to the others); a barrier that waits longer
-// than a spin limit sets an error flag that makes every work-group leave,
-// so the launch always ends. Nothing is allocated and no host
-// synchronisation happens inside batch_run, so it can be captured into a
-// HIP graph (batch_capture / batch_launch).
+// no more than a phase has items; every phase hands out work items (pull
+// tiles, merge ranges, PPR row runs, dangling reductions) by striding over
+// one flat item space built from per-graph prefix tables. An iteration has
+// two phases (pull, then merge), each ended by a grid barrier; dangling
+// totals are added inside the phase before the one that reads them. A
+// barrier that waits longer than a spin limit sets an error flag that makes
+// every work-group leave, so the launch always ends. Nothing is allocated
+// and no host synchronisation happens inside batch_run, so it can be
+// captured into a HIP graph (batch_capture / batch_launch).
 
 #include <algorithm>
 #include <vector>
@@ -24,7 +24,13 @@ namespace {
 constexpr int kBatchK = 1024;   // merge range of batched partitions
 constexpr int kPprLanes = 64;   // one lane per seed vector
 constexpr int kPprRows = 32;    // rows per PPR start item (8 per wave)
-constexpr int32_t kPprChunk = 2048;  // in-arcs per PPR chunk (one wave each, kWaves chunks per item)
+// Weight (in-arcs, and kPprRowCost per row finished) a PPR unit is cut at: a
+// wave each, kWaves units per item. Between the two bounds it is chosen so
+// that every wave the grid may hold has about two units: with 2048 arcs per
+// unit a graph of 1.6 M arcs kept 780 of 3000 waves busy, each 130 dependent
+// gathers deep.
+constexpr int32_t kPprUnitMin = 128, kPprUnitMax = 2048;
+constexpr int32_t kPprRowCost = 4;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kPprBatch = 16;   // 256-byte row gathers a wave keeps in flight
 constexpr unsigned long long kSpinLimit = 1ull << 21;
@@ -46,29 +52,33 @@ struct BGraph {
 
 // Personalised PageRank of up to 64 seeds, lane q of a wave = seed q. An
 // iteration gathers, per in-arc u -> v, the 256-byte row c[u][0..64) of the
-// current contributions. The in-arcs are cut into chunks of kPprChunk arcs
-// (one wave each) rather than handed out by rows, so every wave keeps
-// kPprBatch gathers in flight and a hub row's arcs spread over many waves:
-// a row whose arcs lie in one chunk is finished by that chunk's wave; a row
-// whose arcs span chunks leaves one FP64 piece per chunk (the sum of its
-// arcs there: piece_tail of the chunk it starts in, piece_head of the
-// others), and the next phase adds the pieces and finishes it.
+// current contributions. The rows are cut into units of about equal weight,
+// one wave each (rather than handed out one by one), so every wave keeps
+// kPprBatch gathers in flight: a run of whole rows, or a piece of one long
+// row, which leaves its FP64 sum for the next phase to add up.
+struct PprUnit {
+  int32_t a0, a1;  // in-arcs
+  int32_t r0, r1;  // rows [r0, r1), or (r0 < 0) piece ~r0 of a long row
+};
+struct PprLong {
+  int32_t row, p0, p1;  // pieces [p0, p1)
+};
 struct BPpr {
   int32_t n, S;
-  int64_t m;
-  int32_t init_items;        // start items: kPprRows rows each
-  int32_t n_chunks, items;   // iteration items: kWaves chunks each
-  int32_t n_split, fix_items;  // rows spanning chunks; finishing items: kWaves rows each
+  int32_t init_items;         // start items: kPprRows rows each
+  int32_t n_units, items;     // pull items: kWaves units each
+  int32_t n_long, fix_items;  // long rows; finishing items: kWaves rows each
   const int32_t* t_rowptr;
   const int32_t* t_col;
   const int32_t* rowptr;
   const int32_t* seeds;      // [S]
-  const int32_t* split;      // [n_split] rows spanning chunks
+  const PprUnit* units;
+  const PprLong* longs;
   float* c[2];               // [n][64]
-  double* piece_head;        // [n_chunks][64]
-  double* piece_tail;        // [n_chunks][64]
-  double* dpart;             // [max(init_items, items + fix_items)][64]
-  double* dtotal;            // [2][64]
+  double* piece;             // [pieces][64]
+  double* dpart;             // [max(init_items, items)][64]: dangling mass of the start / pull items
+  double* dfix[2];           // [fix_items][64]: of the finishing items, iterations in turn
+  double* dsum;              // [2][64]: dpart's total
 };
 
 struct BatchArgs {
@@ -84,9 +94,25 @@ struct BatchArgs {
   const float* rank_in;
   float* rank_out;
   float* ppr_out;            // [n][S]
-  unsigned* bar_count;
-  unsigned* bar_gen;
+  struct GridBar* bar;
   int32_t* err;
+};
+
+// State of the grid barrier, zeroed before every launch; one word per
+// 128-byte line.
+constexpr int kBarXcds = 16, kBarLine = 32;
+struct GridBar {
+  unsigned members[kBarXcds * kBarLine];  // work-groups on each XCD
+  unsigned arrived[kBarXcds * kBarLine];  // of them, arrivals so far
+  unsigned passed[kBarXcds * kBarLine];   // barriers the XCD has left
+  unsigned xcds[kBarLine], ready[kBarLine];
+  unsigned root[kBarLine], gen[kBarLine];  // XCD arrivals so far, barriers done
+};
+
+// What a work-group knows of the barrier: its XCD, the work-groups there, the
+// XCDs in use, and the barriers passed.
+struct BarSelf {
+  unsigned xcd, members, xcds, n;
 };
 
 // Item -> (graph, local index) by binary search in a prefix table.
@@ -100,29 +126,75 @@ __device__ __forceinline__ int32_t which(const int32_t* pre, int32_t G, int32_t 
   return lo;
 }
 
-__device__ bool grid_sync(const BatchArgs& a) {
-  __shared__ int ok;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned gen = __hip_atomic_load(a.bar_gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence();
-    const unsigned arrived = atomicAdd(a.bar_count, 1u);
-    if (arrived == gridDim.x - 1) {
-      __hip_atomic_store(a.bar_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __threadfence();
-      atomicAdd(a.bar_gen, 1u);
-    } else {
-      unsigned long long spins = 0;
-      while (__hip_atomic_load(a.bar_gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gen) {
-        if (++spins > kSpinLimit || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-          atomicExch(a.err, 1);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(4);
-      }
+__device__ __forceinline__ unsigned bar_load(const unsigned* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned bar_add(unsigned* p) {
+  return __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits (one thread) until *p reaches `target`; false after the spin limit
+// or when another work-group gave up.
+__device__ bool bar_wait(const BatchArgs& a, const unsigned* p, unsigned target) {
+  unsigned long long spins = 0;
+  while (bar_load(p) < target) {
+    if (++spins > kSpinLimit || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+      atomicExch(a.err, 1);
+      return false;
     }
-    __threadfence();
-    ok = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return true;
+}
+
+// Joins the barrier: counts the work-groups of each XCD (the hardware
+// register names the one this work-group runs on, for all of its life).
+__device__ bool grid_join(const BatchArgs& a, BarSelf* self) {
+  __shared__ BarSelf sh;
+  __shared__ int ok;
+  if (threadIdx.x == 0) {
+    constexpr int kXccId = 20 | ((4 - 1) << 11);  // hardware register XCC_ID, 4 bits from bit 0
+    sh.xcd = __builtin_amdgcn_s_getreg(kXccId) & (kBarXcds - 1);
+    if (bar_add(&a.bar->members[sh.xcd * kBarLine]) == 0) bar_add(a.bar->xcds);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // counted before this work-group is ready
+    bar_add(a.bar->ready);
+    ok = bar_wait(a, a.bar->ready, gridDim.x);
+    sh.members = bar_load(&a.bar->members[sh.xcd * kBarLine]);
+    sh.xcds = bar_load(a.bar->xcds);
+    sh.n = 0;
+  }
+  __syncthreads();
+  *self = sh;
+  return ok;
+}
+
+// Grid barrier. The writes of a work-group are in its XCD's L2 once its
+// waves have seen them complete; the last work-group of an XCD to arrive
+// writes that L2 back (one release per XCD), then the XCDs meet, and every
+// work-group drops its stale lines on the way out. With a release and an
+// acquire by each work-group, one after the other in its L2, a barrier of
+// 1024 work-groups took 25 us (43 us with two full fences and one counter);
+// with one release per XCD it takes 4.6 us at 256 work-groups, 6.9 at 512
+// and 9.5 at 768.
+__device__ bool grid_sync(const BatchArgs& a, BarSelf* self) {
+  __shared__ int ok;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every wave: its stores have reached the L2
+  __syncthreads();
+  const unsigned n = ++self->n;
+  if (threadIdx.x == 0) {
+    const unsigned x = self->xcd * kBarLine;
+    bool good;
+    if (bar_add(&a.bar->arrived[x]) == n * self->members - 1) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (bar_add(a.bar->root) == n * self->xcds - 1)
+        __hip_atomic_store(a.bar->gen, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      good = bar_wait(a, a.bar->gen, n);
+      __hip_atomic_store(&a.bar->passed[x], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      good = bar_wait(a, &a.bar->passed[x], n);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    ok = good;
   }
   __syncthreads();
   return ok;
@@ -166,22 +238,25 @@ __device__ __forceinline__ double ppr_finish(const BPpr& p, int32_t v, double s,
   return deg ? 0.0 : static_cast<double>(r32);
 }
 
-// One wave walks in-arc chunk c: arcs [c L, min(m, (c + 1) L)). It finishes
-// every row whose arcs all lie in the chunk (and the empty rows that start
-// in it; the last chunk also takes those starting at m), and leaves pieces
-// for rows that cross its ends. Returns the wave's dangling mass.
-__device__ double ppr_chunk(const BPpr& p, int32_t c, int32_t it, double d, double D, int32_t seed, float* out) {
+// The contributions c[u][lane] of kPprBatch in-arcs from a on (clamped to
+// the last before a1).
+__device__ __forceinline__ void ppr_gather(const BPpr& p, const float* cur, int32_t a, int32_t a1,
+                                           float (&x)[kPprBatch]) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int32_t u = p.t_col[min(a + min(lane, kPprBatch - 1), a1 - 1)];
+#pragma unroll
+  for (int k = 0; k < kPprBatch; ++k)
+    x[k] = cur[static_cast<int64_t>(__builtin_amdgcn_readlane(u, k)) * kPprLanes + lane];
+}
+
+// One wave takes a unit: it finishes the rows of a run, or leaves the sum of
+// a long row's piece. Returns the wave's dangling mass.
+__device__ double ppr_unit(const BPpr& p, const PprUnit& q, int32_t it, double d, double D, int32_t seed, float* out) {
   const int lane = threadIdx.x & (kWave - 1);
   const float* cur = p.c[it & 1];
-  const int64_t A0 = static_cast<int64_t>(c) * kPprChunk;
-  const int64_t A1 = min(p.m, A0 + kPprChunk);
-  const bool last_chunk = c == p.n_chunks - 1;
-  // rows starting in the chunk: [lo_row, hi_row); the row holding arc A0,
-  // if it started before A0, is the chunk's head row
-  const int32_t lo_row = gcd::lower_bound(p.t_rowptr, 0, p.n, static_cast<int32_t>(A0));
-  const int32_t hi_row = last_chunk ? p.n : gcd::lower_bound(p.t_rowptr, lo_row, p.n, static_cast<int32_t>(A1));
-  const bool head_split = A0 < A1 && lo_row > 0 && p.t_rowptr[lo_row] > A0;
-  int32_t v = head_split ? lo_row - 1 : lo_row;  // current row
+  const bool run = q.r0 >= 0;
+  int32_t v = run ? q.r0 : 0;  // current row
+  const int32_t last = run ? q.r1 : 0;
   // ends of rows base .. base + 63, one per lane
   int32_t base = v;
   int32_t ends = p.t_rowptr[min(base + 1 + lane, p.n)];
@@ -193,47 +268,38 @@ __device__ double ppr_chunk(const BPpr& p, int32_t c, int32_t it, double d, doub
     return __builtin_amdgcn_readlane(ends, r - base);
   };
   double s = 0.0, dang = 0.0;
-  int32_t vend = v < hi_row || head_split ? row_end(v) : 0;
+  int32_t vend = v < last ? row_end(v) : INT32_MAX;
   // rows that end at or before arc a (empty ones included) are finished
-  auto flush_to = [&](int64_t a) {
-    while (v < hi_row && vend <= a) {
-      if (head_split && v == lo_row - 1) {
-        p.piece_head[static_cast<int64_t>(c) * kPprLanes + lane] = s;
-      } else {
-        dang += ppr_finish(p, v, s, it, d, D, seed, out);
-      }
+  auto flush_to = [&](int32_t a) {
+    while (v < last && vend <= a) {
+      dang += ppr_finish(p, v, s, it, d, D, seed, out);
       s = 0.0;
       ++v;
-      if (v < hi_row) vend = row_end(v);
+      vend = v < last ? row_end(v) : INT32_MAX;
     }
   };
-  for (int64_t a = A0; a < A1; a += kPprBatch) {
-    const int32_t nb = static_cast<int32_t>(min<int64_t>(kPprBatch, A1 - a));
-    const int32_t u = p.t_col[a + min(lane, nb - 1)];
-    float x[kPprBatch];
-#pragma unroll
-    for (int k = 0; k < kPprBatch; ++k)
-      x[k] = cur[static_cast<int64_t>(__builtin_amdgcn_readlane(u, min(k, nb - 1))) * kPprLanes + lane];
+  // the next batch's gathers are in flight while one is added
+  float x[kPprBatch], y[kPprBatch];
+  if (q.a0 < q.a1) ppr_gather(p, cur, q.a0, q.a1, x);  // uniform
+  for (int32_t a = q.a0; a < q.a1; a += kPprBatch) {
+    ppr_gather(p, cur, min(a + kPprBatch, q.a1 - 1), q.a1, y);
 #pragma unroll
     for (int k = 0; k < kPprBatch; ++k) {
-      if (k < nb) {
+      if (a + k < q.a1) {
         flush_to(a + k);
         s += static_cast<double>(x[k]);
       }
     }
+#pragma unroll
+    for (int k = 0; k < kPprBatch; ++k) x[k] = y[k];
   }
-  flush_to(A1);
-  // what is left open crosses the chunk's end: the head row (when the whole
-  // chunk lies inside it) or the last row that started here
-  if (A0 < A1 && v < p.n && (v < hi_row || (head_split && v == lo_row - 1)) && vend > A1) {
-    if (head_split && v == lo_row - 1) p.piece_head[static_cast<int64_t>(c) * kPprLanes + lane] = s;
-    else p.piece_tail[static_cast<int64_t>(c) * kPprLanes + lane] = s;
-  }
+  flush_to(q.a1);
+  if (!run) p.piece[static_cast<int64_t>(~q.r0) * kPprLanes + lane] = s;
   return dang;
 }
 
-// Writes the work-group's dangling partial of item `slot` (one per seed).
-__device__ __forceinline__ void ppr_dangling(const BPpr& p, int32_t slot, double mine) {
+// Writes the work-group's dangling partial (one per seed).
+__device__ __forceinline__ void ppr_dangling(double* slot, double mine) {
   __shared__ double dp[kWaves][kPprLanes];
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
   dp[wid][lane] = mine;
@@ -242,38 +308,54 @@ __device__ __forceinline__ void ppr_dangling(const BPpr& p, int32_t slot, double
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) t += dp[w][lane];
-    p.dpart[static_cast<int64_t>(slot) * kPprLanes + lane] = t;
+    slot[lane] = t;
   }
   __syncthreads();
 }
 
-// Iteration item: chunks kWaves * item + wave.
-__device__ void ppr_chunks(const BPpr& p, int32_t item, int32_t it, double d, float* out) {
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const double D = p.dtotal[(it & 1) * kPprLanes + lane];
-  const int32_t seed = lane < p.S ? p.seeds[lane] : -1;
-  const int32_t c = item * kWaves + wid;
-  double mine = 0.0;
-  if (c < p.n_chunks) mine = ppr_chunk(p, c, it, d, D, seed, out);
-  ppr_dangling(p, item, mine);
+// Dangling mass of the ranks iteration `it` starts from, for this lane's
+// seed: the pull (or start) items' total and the finishing items' partials
+// of the iteration before.
+__device__ double ppr_mass(const BPpr& p, int32_t it) {
+  const int lane = threadIdx.x & (kWave - 1);
+  double D = p.dsum[(it & 1) * kPprLanes + lane];
+  if (it > 0) {
+    const double* f = p.dfix[(it - 1) & 1] + lane;
+    double t = 0.0;
+#pragma unroll 8
+    for (int32_t i = 0; i < p.fix_items; ++i) t += f[static_cast<int64_t>(i) * kPprLanes];
+    D += t;
+  }
+  return D;
 }
 
-// Finishing item (the phase after the chunks): rows that span chunks,
-// kWaves * item + wave, from their pieces.
-__device__ void ppr_split_rows(const BPpr& p, int32_t item, int32_t it, double d, float* out) {
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const double D = p.dtotal[(it & 1) * kPprLanes + lane];
+// Pull item: units kWaves * item + wave.
+__device__ void ppr_units(const BPpr& p, int32_t item, int32_t it, double d, double D, float* out) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int32_t seed = lane < p.S ? p.seeds[lane] : -1;
   const int32_t i = item * kWaves + wid;
   double mine = 0.0;
-  if (i < p.n_split) {
-    const int32_t v = p.split[i];
-    const int32_t c0 = p.t_rowptr[v] / kPprChunk, c1 = (p.t_rowptr[v + 1] - 1) / kPprChunk;
-    double s = p.piece_tail[static_cast<int64_t>(c0) * kPprLanes + lane];
-    for (int32_t c = c0 + 1; c <= c1; ++c) s += p.piece_head[static_cast<int64_t>(c) * kPprLanes + lane];
-    mine = ppr_finish(p, v, s, it, d, D, seed, out);
+  if (i < p.n_units) mine = ppr_unit(p, p.units[i], it, d, D, seed, out);
+  ppr_dangling(p.dpart + static_cast<int64_t>(item) * kPprLanes, mine);
+}
+
+// Finishing item (the phase after the pull): long rows, kWaves * item + wave,
+// from their pieces.
+__device__ void ppr_long_rows(const BPpr& p, int32_t item, int32_t it, double d, double D, float* out) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int32_t seed = lane < p.S ? p.seeds[lane] : -1;
+  const int32_t i = item * kWaves + wid;
+  double mine = 0.0;
+  if (i < p.n_long) {
+    const PprLong l = p.longs[i];
+    double s = 0.0;
+#pragma unroll 8
+    for (int32_t c = l.p0; c < l.p1; ++c) s += p.piece[static_cast<int64_t>(c) * kPprLanes + lane];
+    mine = ppr_finish(p, l.row, s, it, d, D, seed, out);
   }
-  ppr_dangling(p, p.items + item, mine);
+  ppr_dangling(p.dfix[it & 1] + static_cast<int64_t>(item) * kPprLanes, mine);
 }
 
 // PPR start: r0 = p (one-hot per seed), c0 = r0 / outdeg, dangling partials.
@@ -300,9 +382,17 @@ __device__ void ppr_init_rows(const BPpr& p, int32_t item) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kThreads) void k_batch_reset(unsigned* count, int32_t* err) {
-  *count = 0u;
-  *err = 0;
+__global__ __launch_bounds__(kThreads) void k_batch_reset(GridBar* bar, int32_t* err) {
+  unsigned* w = reinterpret_cast<unsigned*>(bar);
+  for (int i = threadIdx.x; i < static_cast<int>(sizeof(GridBar) / sizeof(unsigned)); i += kThreads) w[i] = 0u;
+  if (threadIdx.x == 0) *err = 0;
+}
+
+// Total of a graph's dangling partials.
+__device__ __forceinline__ void graph_mass(const BatchArgs& a, int32_t gi, int32_t it) {
+  const BGraph& g = a.graphs[gi];
+  const double t = sum_slots(g.dpart, it == 0 ? a.vert_pre[gi + 1] - a.vert_pre[gi] : g.R, 1);
+  if (threadIdx.x == 0) g.dtotal[it & 1] = t;
 }
 
 __global__ __launch_bounds__(kThreads) void k_batch(BatchArgs a) {
@@ -313,7 +403,9 @@ __global__ __launch_bounds__(kThreads) void k_batch(BatchArgs a) {
   const int32_t init_items = a.has_ppr ? a.ppr.init_items : 0;
   const int32_t pitems = a.has_ppr ? a.ppr.items : 0;
   const int32_t fitems = a.has_ppr ? a.ppr.fix_items : 0;
-  const int32_t red_items = G + (a.has_ppr ? kPprLanes : 0);
+  const int32_t lanes = a.has_ppr ? kPprLanes : 0;
+  BarSelf bar;
+  if (!grid_join(a, &bar)) return;
 
   // ---- start: contributions of the start vectors and their dangling mass
   for (int32_t item = blockIdx.x; item < verts + init_items; item += gridDim.x) {
@@ -334,43 +426,50 @@ __global__ __launch_bounds__(kThreads) void k_batch(BatchArgs a) {
       ppr_init_rows(a.ppr, item - verts);
     }
   }
-  if (!grid_sync(a)) return;
-  for (int32_t item = blockIdx.x; item < red_items; item += gridDim.x) {
-    if (item < G) {
-      const BGraph& g = a.graphs[item];
-      const double t = sum_slots(g.dpart, a.vert_pre[item + 1] - a.vert_pre[item], 1);
-      if (threadIdx.x == 0) g.dtotal[0] = t;
-    } else {
-      const int32_t q = item - G;
+  if (!grid_sync(a, &bar)) return;
+  if (a.has_ppr) {  // uniform over the grid
+    for (int32_t q = blockIdx.x; q < lanes; q += gridDim.x) {
       const double t = sum_slots(a.ppr.dpart + q, init_items, kPprLanes);
-      if (threadIdx.x == 0) a.ppr.dtotal[q] = t;
+      if (threadIdx.x == 0) a.ppr.dsum[q] = t;
     }
+    if (!grid_sync(a, &bar)) return;
   }
-  if (!grid_sync(a)) return;
 
   for (int32_t it = 0; it < a.iters; ++it) {
     const bool last = it == a.iters - 1;
-    // ---- pull tiles of every graph (Algorithm 4) and PPR row groups
-    for (int32_t item = blockIdx.x; item < tiles + pitems; item += gridDim.x) {
-      if (item < tiles) {
-        const int32_t gi = which(a.tile_pre, G, item);
+    double D = 0.0;  // PPR: the lane's dangling mass
+    if (a.has_ppr) D = ppr_mass(a.ppr, it);
+    // ---- PPR units, pull tiles of every graph (Algorithm 4), and the
+    // dangling totals that the merge phase reads
+    for (int32_t item = blockIdx.x; item < pitems + tiles + G; item += gridDim.x) {
+      if (item < pitems) {
+        ppr_units(a.ppr, item, it, a.damping, D, last ? a.ppr_out : nullptr);
+      } else if (item < pitems + tiles) {
+        const int32_t x = item - pitems;
+        const int32_t gi = which(a.tile_pre, G, x);
         const BGraph& g = a.graphs[gi];
-        const int32_t t = item - a.tile_pre[gi];
+        const int32_t t = x - a.tile_pre[gi];
         const int32_t r0 = g.tile_row[t], r1 = g.tile_row[t + 1];
         if (r0 < r1)
           pull_tile(g.row_ptr, g.col, g.contrib, r0, r1, vals,
                     [&](int32_t r, double s) { g.partial[r] = static_cast<float>(s); });
         __syncthreads();  // vals is reused by the next item
       } else {
-        ppr_chunks(a.ppr, item - tiles, it, a.damping, last ? a.ppr_out : nullptr);
+        graph_mass(a, item - pitems - tiles, it);
       }
     }
-    if (!grid_sync(a)) return;
-    // ---- merge ranges fused with the update (Figure 5), and the PPR rows
-    // whose arcs span chunks
-    for (int32_t item = blockIdx.x; item < ranges + fitems; item += gridDim.x) {
+    if (!grid_sync(a, &bar)) return;
+    // ---- merge ranges fused with the update (Figure 5), the long PPR rows,
+    // and the PPR mass of the pull items for the next iteration
+    for (int32_t item = blockIdx.x; item < ranges + fitems + (last ? 0 : lanes); item += gridDim.x) {
+      if (item >= ranges + fitems) {
+        const int32_t q = item - ranges - fitems;
+        const double t = sum_slots(a.ppr.dpart + q, pitems, kPprLanes);
+        if (threadIdx.x == 0) a.ppr.dsum[((it + 1) & 1) * kPprLanes + q] = t;
+        continue;
+      }
       if (item >= ranges) {
-        ppr_split_rows(a.ppr, item - ranges, it, a.damping, last ? a.ppr_out : nullptr);
+        ppr_long_rows(a.ppr, item - ranges, it, a.damping, D, last ? a.ppr_out : nullptr);
         continue;
       }
       const int32_t gi = which(a.range_pre, G, item);
@@ -378,30 +477,17 @@ __global__ __launch_bounds__(kThreads) void k_batch(BatchArgs a) {
       const int32_t j = item - a.range_pre[gi];
       merge_accumulate<kBatchK, true>(g.range_ptr, g.B, g.id16, g.partial, j, acc);
       const Update u = make_update(g, a.damping, g.dtotal + (it & 1), last ? a.rank_out + g.rank_off : nullptr);
-      const double D = g.dtotal[it & 1];
+      const double Dg = g.dtotal[it & 1];
       double mine = 0.0;
       for (int i = threadIdx.x; i < kBatchK; i += kThreads) {
         const int32_t v = j * kBatchK + i;
-        if (v < g.n) mine += update_vertex(u, v, acc[i], D);
+        if (v < g.n) mine += update_vertex(u, v, acc[i], Dg);
       }
       const double t = wg_sum(mine);
       if (threadIdx.x == 0) g.dpart[j] = t;
       __syncthreads();  // acc is reused by the next item
     }
-    if (!grid_sync(a)) return;
-    // ---- next dangling totals
-    for (int32_t item = blockIdx.x; item < red_items; item += gridDim.x) {
-      if (item < G) {
-        const BGraph& g = a.graphs[item];
-        const double t = sum_slots(g.dpart, g.R, 1);
-        if (threadIdx.x == 0) g.dtotal[(it + 1) & 1] = t;
-      } else {
-        const int32_t q = item - G;
-        const double t = sum_slots(a.ppr.dpart + q, pitems + fitems, kPprLanes);
-        if (threadIdx.x == 0) a.ppr.dtotal[((it + 1) & 1) * kPprLanes + q] = t;
-      }
-    }
-    if (!last && !grid_sync(a)) return;
+    if (!last && !grid_sync(a, &bar)) return;
   }
 }
 
@@ -465,6 +551,16 @@ int batch_create(const gc_graph* graphs, int32_t n_graphs, const int32_t* block_
     if (!graphs[i]) return bfail(GC_EINVAL, "batch_create: NULL graph");
   for (int32_t q = 0; q < n_seeds; ++q)
     if (seeds[q] < 0 || seeds[q] >= ppr_graph->n) return bfail(GC_EINVAL, "batch_create: seed out of range");
+  int32_t resident = 0;  // work-groups the GPU keeps resident
+  {
+    int per_cu = 0, dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_batch), kThreads, 0);
+    if (e != hipSuccess || per_cu < 1 || cus < 1) return bfail(GC_EHIP, "batch_create: device query failed");
+    resident = per_cu * cus;
+  }
   gc_batch b = new (std::nothrow) gc_batch_s;
   if (!b) return bfail(GC_ENOMEM, "batch_create: host allocation failed");
   std::vector<BGraph> hg(n_graphs);
@@ -532,57 +628,83 @@ int batch_create(const gc_graph* graphs, int32_t n_graphs, const int32_t* block_
     b->n_seeds = n_seeds;
     BPpr& p = a.ppr;
     p.n = pg->n;
-    p.m = pg->m;
     p.S = n_seeds;
     p.init_items = (pg->n + kPprRows - 1) / kPprRows;
-    p.n_chunks = static_cast<int32_t>(std::max<int64_t>(1, (pg->m + kPprChunk - 1) / kPprChunk));
-    p.items = (p.n_chunks + kWaves - 1) / kWaves;
     p.t_rowptr = pg->t_rowptr;
     p.t_col = pg->t_colidx;
     p.rowptr = pg->rowptr;
-    // rows whose in-arcs span chunks (finished from their pieces)
-    std::vector<int32_t> trp(static_cast<size_t>(pg->n) + 1), split;
+    // units of whole rows, long rows in pieces
+    std::vector<int32_t> trp(static_cast<size_t>(pg->n) + 1);
     if (hipMemcpy(trp.data(), pg->t_rowptr, sizeof(int32_t) * trp.size(), hipMemcpyDeviceToHost) != hipSuccess) {
       destroy(b);
       return bfail(GC_EHIP, "batch_create: copy failed");
     }
-    for (int32_t v = 0; v < pg->n; ++v)
-      if (trp[v + 1] > trp[v] && trp[v] / kPprChunk != (trp[v + 1] - 1) / kPprChunk) split.push_back(v);
-    p.n_split = static_cast<int32_t>(split.size());
-    p.fix_items = (p.n_split + kWaves - 1) / kWaves;
+    const int64_t weight = pg->m + kPprRowCost * static_cast<int64_t>(pg->n);
+    const int32_t unit = static_cast<int32_t>(
+        std::min<int64_t>(kPprUnitMax, std::max<int64_t>(kPprUnitMin, weight / (2 * kWaves * std::max(resident, 1)))));
+    std::vector<PprUnit> units;
+    std::vector<PprLong> longs;
+    int32_t pieces = 0;
+    for (int32_t v = 0; v < pg->n;) {
+      const int32_t a0 = trp[v], len = trp[v + 1] - a0;
+      if (len > 2 * unit) {
+        const int32_t k = (len + unit - 1) / unit, p0 = pieces;
+        for (int32_t i = 0; i < k; ++i)
+          units.push_back({a0 + static_cast<int32_t>(static_cast<int64_t>(len) * i / k),
+                           a0 + static_cast<int32_t>(static_cast<int64_t>(len) * (i + 1) / k), ~pieces++, 0});
+        longs.push_back({v, p0, pieces});
+        ++v;
+        continue;
+      }
+      int32_t r = v;
+      int64_t w = 0;
+      while (r < pg->n && w < unit && trp[r + 1] - trp[r] <= 2 * unit) {
+        w += trp[r + 1] - trp[r] + kPprRowCost;
+        ++r;
+      }
+      units.push_back({a0, trp[r], v, r});
+      v = r;
+    }
+    p.n_units = static_cast<int32_t>(units.size());
+    p.items = (p.n_units + kWaves - 1) / kWaves;
+    p.n_long = static_cast<int32_t>(longs.size());
+    p.fix_items = (p.n_long + kWaves - 1) / kWaves;
     const size_t lanes = kPprLanes;
     int32_t* ds = static_cast<int32_t*>(own(b, sizeof(int32_t) * n_seeds));
-    int32_t* sp = static_cast<int32_t*>(own(b, sizeof(int32_t) * std::max<size_t>(split.size(), 1)));
+    PprUnit* du = static_cast<PprUnit*>(own(b, sizeof(PprUnit) * units.size()));
+    PprLong* dl = static_cast<PprLong*>(own(b, sizeof(PprLong) * std::max<size_t>(longs.size(), 1)));
     p.c[0] = static_cast<float*>(own(b, sizeof(float) * lanes * static_cast<size_t>(pg->n)));
     p.c[1] = static_cast<float*>(own(b, sizeof(float) * lanes * static_cast<size_t>(pg->n)));
-    p.piece_head = static_cast<double*>(own(b, sizeof(double) * lanes * static_cast<size_t>(p.n_chunks)));
-    p.piece_tail = static_cast<double*>(own(b, sizeof(double) * lanes * static_cast<size_t>(p.n_chunks)));
-    const size_t slots = static_cast<size_t>(std::max(p.init_items, p.items + p.fix_items));
+    p.piece = static_cast<double*>(own(b, sizeof(double) * lanes * static_cast<size_t>(std::max(pieces, 1))));
+    const size_t slots = static_cast<size_t>(std::max(p.init_items, p.items));
     p.dpart = static_cast<double*>(own(b, sizeof(double) * lanes * slots));
-    p.dtotal = static_cast<double*>(own(b, sizeof(double) * 2 * lanes));
-    if (!ds || !sp || !p.c[0] || !p.c[1] || !p.piece_head || !p.piece_tail || !p.dpart || !p.dtotal) {
+    p.dfix[0] = static_cast<double*>(own(b, sizeof(double) * lanes * static_cast<size_t>(std::max(p.fix_items, 1))));
+    p.dfix[1] = static_cast<double*>(own(b, sizeof(double) * lanes * static_cast<size_t>(std::max(p.fix_items, 1))));
+    p.dsum = static_cast<double*>(own(b, sizeof(double) * 2 * lanes));
+    if (!ds || !du || !dl || !p.c[0] || !p.c[1] || !p.piece || !p.dpart || !p.dfix[0] || !p.dfix[1] || !p.dsum) {
       destroy(b);
       return bfail(GC_ENOMEM, "batch_create: allocation failed");
     }
     if (hipMemcpy(ds, seeds, sizeof(int32_t) * n_seeds, hipMemcpyDefault) != hipSuccess ||
-        (!split.empty() && hipMemcpy(sp, split.data(), sizeof(int32_t) * split.size(), hipMemcpyHostToDevice) !=
-                               hipSuccess)) {
+        hipMemcpy(du, units.data(), sizeof(PprUnit) * units.size(), hipMemcpyHostToDevice) != hipSuccess ||
+        (!longs.empty() &&
+         hipMemcpy(dl, longs.data(), sizeof(PprLong) * longs.size(), hipMemcpyHostToDevice) != hipSuccess)) {
       destroy(b);
       return bfail(GC_EHIP, "batch_create: copy failed");
     }
+    p.units = du;
+    p.longs = dl;
     p.seeds = ds;
-    p.split = sp;
   }
   BGraph* dg = static_cast<BGraph*>(own(b, sizeof(BGraph) * std::max(1, n_graphs)));
   int32_t* pre = static_cast<int32_t*>(own(b, sizeof(int32_t) * 3 * (n_graphs + 1)));
-  a.bar_count = static_cast<unsigned*>(own(b, sizeof(unsigned) * 2));
+  a.bar = static_cast<GridBar*>(own(b, sizeof(GridBar)));
   a.err = static_cast<int32_t*>(own(b, sizeof(int32_t)));
-  if (!dg || !pre || !a.bar_count || !a.err ||
+  if (!dg || !pre || !a.bar || !a.err ||
       hipHostMalloc(reinterpret_cast<void**>(&b->err_host), sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
     destroy(b);
     return bfail(GC_ENOMEM, "batch_create: allocation failed");
   }
-  a.bar_gen = a.bar_count + 1;
   hipError_t e = hipSuccess;
   if (n_graphs > 0) e = hipMemcpy(dg, hg.data(), sizeof(BGraph) * n_graphs, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(pre, tile_pre.data(), sizeof(int32_t) * (n_graphs + 1), hipMemcpyHostToDevice);
@@ -590,19 +712,18 @@ int batch_create(const gc_graph* graphs, int32_t n_graphs, const int32_t* block_
     e = hipMemcpy(pre + n_graphs + 1, range_pre.data(), sizeof(int32_t) * (n_graphs + 1), hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = hipMemcpy(pre + 2 * (n_graphs + 1), vert_pre.data(), sizeof(int32_t) * (n_graphs + 1), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemset(a.bar_count, 0, sizeof(unsigned) * 2);
-  // co-resident grid: every work-group must be live for the grid barrier
-  int per_cu = 0, dev = 0;
-  hipDeviceProp_t prop;
-  if (e == hipSuccess) e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
-  if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_batch), kThreads, 0);
-  if (e != hipSuccess || per_cu < 1) {
+  if (e != hipSuccess) {
     destroy(b);
-    return bfail(GC_EHIP, "batch_create: device query failed");
+    return bfail(GC_EHIP, "batch_create: copy failed");
   }
-  b->grid = per_cu * prop.multiProcessorCount;
+  // every work-group must be live for the grid barrier; no more of them than
+  // the largest phase has items (a barrier's cost grows with them)
+  const int64_t tiles = tile_pre[n_graphs], ranges = range_pre[n_graphs], verts = vert_pre[n_graphs];
+  int64_t most = std::max<int64_t>(tiles + n_graphs, std::max(ranges, verts));
+  if (n_seeds > 0)
+    most = std::max({static_cast<int64_t>(a.ppr.items) + tiles + n_graphs,
+                     ranges + a.ppr.fix_items + kPprLanes, verts + a.ppr.init_items});
+  b->grid = static_cast<int32_t>(std::min<int64_t>(resident, most));
   a.graphs = dg;
   a.tile_pre = pre;
   a.range_pre = pre + n_graphs + 1;
@@ -633,7 +754,7 @@ int batch_run(gc_batch b, float damping, int32_t iters, const float* ranks_in, f
   a.rank_out = ranks_out;
   a.ppr_out = ppr_out;
   gcx::ProfScope prof("batch", stream);
-  k_batch_reset<<<1, 1, 0, stream>>>(a.bar_count, a.err);
+  k_batch_reset<<<1, kThreads, 0, stream>>>(a.bar, a.err);
   k_batch<<<b->grid, kThreads, 0, stream>>>(a);
   return hipGetLastError() == hipSuccess ? GC_OK : bfail(GC_EHIP, "batch_run: launch failed");
 }

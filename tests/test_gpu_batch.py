@@ -107,6 +107,32 @@ def test_batch_ppr_only_and_graphs_only():
         h.free()
 
 
+# units of the personalised ranks: a row cut into pieces (more than twice a
+# unit's 128 arcs) alone and between short rows, rows without in-arcs, a row
+# of just twice a unit, one vertex; and a grid smaller than the GPU
+@pytest.mark.parametrize("make,count", [(lambda: graphs.star_in(9000), 3), (lambda: graphs.star_in(257), 2),
+                                        (lambda: graphs.star_in(258), 2), (lambda: graphs.star_out(300), 1),
+                                        (lambda: graphs.cycle(64), 64), (lambda: graphs.chain(131), 5),
+                                        (lambda: gg.rmat(13, 16, seed=9), 64)],
+                         ids=["piece9000", "row256", "row257", "star_out", "cycle", "chain", "rmat13"])
+def test_batch_ppr_units(make, count):
+    import paper_1904_02241_amd as gc
+    pg = make()
+    seeds = np.arange(count, dtype=np.int32) % pg.n
+    hp, hs = load(pg), load(graphs.dangling_mix())
+    print(f"ppr units {pg.name} seeds={count}", flush=True)
+    b = gc.batch_create([hs], [1 << 16], hp, seeds)
+    rin = dev(np.full(6, 1.0 / 6, np.float32))
+    rout = torch().empty(6, dtype=torch().float32, device="cuda")
+    pout = torch().empty((pg.n, count), dtype=torch().float32, device="cuda")
+    for iters in (1, 6):
+        gc.batch_run(b, 0.85, iters, rin, rout, pout)
+        check([graphs.dangling_mix()], pg, seeds, b, rout, pout, iters)
+    b.free()
+    hp.free()
+    hs.free()
+
+
 def test_batch_rejects_bad_arguments():
     import paper_1904_02241_amd as gc
     g = gg.rmat(10, 8, seed=1)
