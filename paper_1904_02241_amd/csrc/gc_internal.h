@@ -50,9 +50,12 @@ struct gc_graph_s {
   int32_t* queue[2] = {nullptr, nullptr};
   uint32_t* visited = nullptr;  // BFS: bitmap of vertices with a final depth
   int32_t* mark = nullptr;      // SSSP push: round in which a vertex was queued
-  int32_t* arc_deg = nullptr;   // out-degrees of a vertex list (arc-balanced push, BC backward)
-  int32_t* arc_pre = nullptr;   // [n+1] their exclusive scan
-  int32_t max_out_deg = -1;     // largest out-degree (-1: not found yet; set by the first traversal)
+  // arc prefixes of the two queues ([n], [n+1]); BC: in-degrees of the level
+  // order, and the prefixes of all its levels
+  int32_t* arc_deg = nullptr;
+  int32_t* arc_pre = nullptr;
+  bool bits_clean = false;      // front and next are all zero
+  int32_t level_seq = 0;        // number of the last level published to stats_host
   // betweenness centrality (allocated by the first bc_accumulate call):
   // path counts, two alternating arrays of (1 + delta) / sigma, BFS depths
   // and the vertices in level order of the current source
@@ -290,15 +293,17 @@ __host__ __device__ inline void level_features(int64_t n, int64_t m, int64_t n_f
   f[5] = static_cast<float>(log1p(prior_ms * 1e6 / static_cast<double>(prior_arcs > 1 ? prior_arcs : 1)));
 }
 
-// Device counters of one traversal level (int32 slots), copied once per
-// level to a pinned host mirror.
-constexpr int kStatQLen = 0;      // vertices appended to the next queue
-constexpr int kStatOverflow = 1;  // SSSP: a path length reached INT32_MAX
-constexpr int kStatDegLo = 2;     // out-arcs of the next frontier (64-bit: lo, hi)
+// Device counters of one traversal level (int32 slots), written once per
+// level to a pinned host mirror by the level's last kernel.
+constexpr int kStatArcs = 0;      // out-arcs of the next frontier, with
+constexpr int kStatQLen = 1;      // its vertices: one 64-bit word (below 2^31 each)
+constexpr int kStatOverflow = 2;  // SSSP: a path length reached INT32_MAX
+constexpr int kStatSeq = 3;       // host mirror: the level whose counters it holds
 constexpr int kStatT0 = 4;        // device wall clock at the level's start (64-bit)
 constexpr int kStatT1 = 6;        // device wall clock when its relaxation kernels have finished (64-bit)
 constexpr int kStatChoice = 8;    // learned scheduler: action for the next level (-1: no finite output)
 constexpr int kStatInDegLo = 10;  // in-arcs of the next frontier (64-bit: lo, hi)
+constexpr int kStatBuild = 12;    // the packed count of a queue built from status bits (64-bit)
 constexpr int kStatOut = 16;      // learned scheduler: its K outputs (FP32 bit patterns)
 constexpr int kStatSlots = kStatOut + GC_SCHED_HIDDEN;
 

@@ -52,19 +52,27 @@ __device__ __forceinline__ void mlp_decide(const float* __restrict__ p, const fl
   for (int i = 0; i < kIn; ++i) z += p[L.W1 + lane * kIn + i] * in[i];
   const float h1 = fmaxf(z, 0.0f);
   z = p[L.b2 + lane];
+#pragma unroll 16
   for (int i = 0; i < kHid; ++i)
     z += w2[lane * kPitch + i] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(h1), i));
   const float h2 = fmaxf(z, 0.0f);
-  int best = -1;
-  float bv = 0.0f;
-  bool bad = false;
-  for (int k = 0; k < K; ++k) {
-    const float o = p[L.b3 + k] + static_cast<float>(gcd::wave_sum(static_cast<double>(p[L.W3 + k * kHid + lane] * h2)));
-    if (out && lane == 0) out[k] = o;
-    bad |= !isfinite(o);
-    if (best < 0 || o < bv) {
+  // lane k takes output k (a wave-wide sum per output would pass through the
+  // lanes six times each)
+  const int32_t row = L.W3 + min(lane, K - 1) * kHid;
+  double acc = 0.0;
+#pragma unroll 16
+  for (int i = 0; i < kHid; ++i)
+    acc += static_cast<double>(p[row + i] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(h2), i)));
+  const float o = p[L.b3 + min(lane, K - 1)] + static_cast<float>(acc);
+  if (out && lane < K) out[lane] = o;
+  const bool bad = __any(lane < K && !isfinite(o));
+  int best = 0;
+  float bv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o), 0));
+  for (int k = 1; k < K; ++k) {
+    const float x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o), k));
+    if (x < bv) {
       best = k;
-      bv = o;
+      bv = x;
     }
   }
   if (lane == 0) *choice = bad ? -1 : best;

@@ -286,6 +286,7 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
     g->stats_host = nullptr;
     ok = false;
   }
+  if (g->stats_host) std::memset(g->stats_host, 0, sizeof(int32_t) * gcx::kStatSlots);
   if (!ok) {
     free_graph(g);
     return fail(GC_ENOMEM, "graph_load_csr: device allocation failed");

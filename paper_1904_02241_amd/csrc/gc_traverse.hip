@@ -17,7 +17,15 @@
 //         reduces them, updates depth / dist and builds the next frontier;
 //   push  data-driven from the queue: every frontier vertex relaxes its
 //         out-arcs with atomics (CAS on depth, atomicMin on dist).
-// The host reads the frontier size and its out-arc count once per level.
+// A push level appends the next frontier to a queue together with the arc
+// prefix of its out-degrees, so the next push finds its arcs without a scan of
+// its own; a pull level sets status bits. Where a level of one kind follows
+// the other, it builds what it needs (a pass over n bits or depths). Both
+// count the next frontier's vertices and out-arcs, which the host reads once
+// per level from pinned memory that the level's last kernel writes. Counters
+// take as few atomics as a launch allows: on one address they cost 25 ns
+// each on this GPU, whoever issues them (one per 256 vertices of a pull over
+// 2^23 vertices: 0.8 ms).
 
 #include <algorithm>
 #include <chrono>
@@ -41,115 +49,97 @@ constexpr int kThreads = 256;
 constexpr int32_t kInf = INT32_MAX;
 constexpr int kHeavy = 32;  // rows longer than this are scanned by the whole wave
 
-// stats slots (device int32[gcx::kStatSlots], copied to the pinned mirror once per level)
-constexpr int kQLen = gcx::kStatQLen;
+// stats slots (device int32[gcx::kStatSlots], written to the pinned mirror once per level)
 constexpr int kOverflow = gcx::kStatOverflow;
-constexpr int kDegLo = gcx::kStatDegLo;
 
-// Appends v to queue for every thread with take set, with one atomic on the
-// queue length per work-group (per-wave atomics on the one counter
-// serialise in L2 when most waves of a large grid append); positions follow
-// the thread order inside the work-group. Synchronises the work-group: every
+// Where a push puts the next frontier: its vertices, each one's first
+// position in the concatenation of their out-arcs, and (t_rowptr given) the
+// count of their in-arcs. `counter` is the slot of the packed count.
+struct Sink {
+  int32_t* queue;
+  int32_t* pre;
+  const int32_t* rowptr;
+  const int32_t* t_rowptr;
+  int32_t* stats;
+  int counter = gcx::kStatArcs;
+};
+
+__device__ __forceinline__ uint64_t one_vertex(int32_t deg) { return (1ull << 32) | static_cast<uint32_t>(deg); }
+
+// Adds every thread's vertices, mine = vertices << 32 | their out-arcs, to
+// the packed counter (and their in-arcs to theirs), one atomic per
+// work-group and counter. With kReserve returns the thread's first position
+// and arc, packed alike: both counts live in one 64-bit word, so positions
+// and arc prefixes ascend together. Synchronises the work-group: every
 // thread must reach each call.
-template <int NT = kThreads>
-__device__ __forceinline__ void block_append(bool take, int32_t v, int32_t* __restrict__ queue,
-                                             int32_t* __restrict__ qlen) {
-  __shared__ int32_t wave_cnt[NT / kWave];
-  __shared__ int32_t wave_off[NT / kWave];
-  const uint64_t mask = __ballot(take);
+template <int NT, bool kReserve>
+__device__ __forceinline__ uint64_t wg_count(uint64_t mine, uint64_t in_arcs, bool with_in, int32_t* stats,
+                                             int counter) {
+  __shared__ uint64_t tot[NT / kWave], base[NT / kWave], in_tot[NT / kWave];
+  const int lane = gcd::lane_id();
   const int wid = threadIdx.x / kWave;
-  if (gcd::lane_id() == 0) wave_cnt[wid] = __popcll(mask);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t tot = 0;
-    for (int w = 0; w < NT / kWave; ++w) {
-      wave_off[w] = tot;
-      tot += wave_cnt[w];
+  uint64_t incl = mine;  // inclusive sum over the wave's lanes
+  if (__any(mine != 0)) {
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint64_t y = __shfl_up(incl, o, kWave);
+      if (lane >= o) incl += y;
     }
-    const int32_t base = tot ? atomicAdd(qlen, tot) : 0;
-    for (int w = 0; w < NT / kWave; ++w) wave_off[w] += base;
+    if (with_in)  // uniform
+      for (int o = 32; o > 0; o >>= 1) in_arcs += __shfl_xor(in_arcs, o, kWave);
+  }
+  if (lane == kWave - 1) {
+    tot[wid] = incl;
+    in_tot[wid] = in_arcs;
   }
   __syncthreads();
-  if (take) queue[wave_off[wid] + __popcll(mask & gcd::lanemask_lt())] = v;
+  if (threadIdx.x == 0) {
+    uint64_t t = 0, ti = 0;
+    for (int w = 0; w < NT / kWave; ++w) {
+      base[w] = t;
+      t += tot[w];
+      ti += in_tot[w];
+    }
+    if (t) {
+      const uint64_t at = atomicAdd(reinterpret_cast<unsigned long long*>(stats + counter), t);
+      if (kReserve)
+        for (int w = 0; w < NT / kWave; ++w) base[w] += at;
+      if (with_in && ti) atomicAdd(reinterpret_cast<unsigned long long*>(stats + gcx::kStatInDegLo), ti);
+    }
+  }
+  if (!kReserve) return 0;
+  __syncthreads();
+  return base[wid] + incl - mine;
 }
 
-// Appends to the queue, with one atomic for the work-group, the vertices
-// vbase + u * stride of every thread for the set bits u of took (at most
-// 32 per thread). Every thread of the work-group calls it (it synchronises).
+__device__ __forceinline__ void sink_put(const Sink& s, uint64_t at, int32_t v) {
+  s.queue[at >> 32] = v;
+  s.pre[at >> 32] = static_cast<int32_t>(static_cast<uint32_t>(at));
+}
+
+// What a pull counts of the next frontier.
+struct Tally {
+  const int32_t* rowptr;
+  const int32_t* t_rowptr;  // null: in-arcs are not counted
+  int32_t* stats;
+};
+
+struct Counted {
+  uint64_t mine = 0, in = 0;
+  __device__ __forceinline__ void add(const Tally& t, int32_t v) {
+    mine += one_vertex(t.rowptr[v + 1] - t.rowptr[v]);
+    if (t.t_rowptr) in += static_cast<uint64_t>(t.t_rowptr[v + 1] - t.t_rowptr[v]);
+  }
+};
+
 template <int NT>
-__device__ __forceinline__ void block_append_bits(uint32_t took, int32_t vbase, int32_t stride,
-                                                  int32_t* __restrict__ queue, int32_t* __restrict__ qlen) {
-  __shared__ int32_t wave_cnt[NT / kWave];
-  __shared__ int32_t wave_off[NT / kWave];
-  const int lane = gcd::lane_id();
-  const int wid = threadIdx.x / kWave;
-  const int32_t c = __popc(took);
-  int32_t x = c;  // inclusive sum of the counts over the wave's lanes
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int32_t y = __shfl_up(x, o, kWave);
-    if (lane >= o) x += y;
-  }
-  if (lane == kWave - 1) wave_cnt[wid] = x;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t tot = 0;
-    for (int w = 0; w < NT / kWave; ++w) {
-      wave_off[w] = tot;
-      tot += wave_cnt[w];
-    }
-    const int32_t base = tot ? atomicAdd(qlen, tot) : 0;
-    for (int w = 0; w < NT / kWave; ++w) wave_off[w] += base;
-  }
-  __syncthreads();
-  int32_t pos = wave_off[wid] + x - c;
-  while (took) {
-    const int u = __ffs(took) - 1;
-    took &= took - 1u;
-    queue[pos++] = vbase + u * stride;
-  }
-}
-
-// Appends to the queue, with one atomic for the work-group, vals[u] of
-// every thread for the set bits u of took. Every thread of the work-group
-// calls it (it synchronises).
-template <int NT, int kN>
-__device__ __forceinline__ void block_append_list(uint32_t took, const int32_t (&vals)[kN],
-                                                  int32_t* __restrict__ queue, int32_t* __restrict__ qlen) {
-  __shared__ int32_t wave_cnt[NT / kWave];
-  __shared__ int32_t wave_off[NT / kWave];
-  const int lane = gcd::lane_id();
-  const int wid = threadIdx.x / kWave;
-  const int32_t c = __popc(took);
-  int32_t x = c;  // inclusive sum of the counts over the wave's lanes
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int32_t y = __shfl_up(x, o, kWave);
-    if (lane >= o) x += y;
-  }
-  if (lane == kWave - 1) wave_cnt[wid] = x;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t tot = 0;
-    for (int w = 0; w < NT / kWave; ++w) {
-      wave_off[w] = tot;
-      tot += wave_cnt[w];
-    }
-    const int32_t base = tot ? atomicAdd(qlen, tot) : 0;
-    for (int w = 0; w < NT / kWave; ++w) wave_off[w] += base;
-  }
-  __syncthreads();
-  int32_t pos = wave_off[wid] + x - c;
-#pragma unroll
-  for (int u = 0; u < kN; ++u)
-    if ((took >> u) & 1u) queue[pos++] = vals[u];
+__device__ __forceinline__ void publish_count(const Tally& t, const Counted& c) {
+  wg_count<NT, false>(c.mine, c.in, t.t_rowptr != nullptr, t.stats, gcx::kStatArcs);
 }
 
 __device__ __forceinline__ bool bit_test(const uint32_t* bits, int32_t v) {
   return (bits[v >> 5] >> (v & 31)) & 1u;
 }
-
-__device__ __forceinline__ void bit_set(uint32_t* bits, int32_t v) { atomicOr(&bits[v >> 5], 1u << (v & 31)); }
 
 // Sets bit v in `bits` for the lanes where `take` holds, one atomic per
 // 32-bit word: every lane of the wave calls it, and lane l holds vertex
@@ -168,27 +158,111 @@ __global__ void k_fill_i32(int32_t* __restrict__ a, int64_t n, int32_t x) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) a[i] = x;
 }
 
-__global__ void k_set_source(int32_t src, int32_t* __restrict__ value, uint32_t* __restrict__ front,
-                             int32_t* __restrict__ queue, uint32_t* __restrict__ visited) {
-  value[src] = 0;
-  front[src >> 5] |= 1u << (src & 31);
-  queue[0] = src;
-  if (visited) visited[src >> 5] |= 1u << (src & 31);
+// Writes the level's counters (the first 16 slots and `outs` scheduler
+// outputs) to the pinned mirror, then `seq`, which the host waits for. One
+// wave.
+__device__ __forceinline__ void publish_stats(const int32_t* stats, int32_t* host, int32_t seq, int outs) {
+  for (int i = gcd::lane_id(); i < gcx::kStatOut + outs; i += kWave)
+    if (i != gcx::kStatSeq)
+      __hip_atomic_store(host + i, __hip_atomic_load(stats + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  if (gcd::lane_id() == 0)
+    __hip_atomic_store(host + gcx::kStatSeq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Clears the old frontier's bitmap through its queue: every set bit belongs
-// to a queued vertex, so zeroing the words the queue touches clears it all.
-__global__ void k_clear_front(uint32_t* __restrict__ front, const int32_t* __restrict__ queue, int32_t qn) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < qn) front[queue[i] >> 5] = 0u;
+// Clears what the next level accumulates.
+__device__ __forceinline__ void reset_stats(int32_t* stats) {
+  if (gcd::lane_id() < gcx::kStatSeq) stats[gcd::lane_id()] = 0;
+  if (gcd::lane_id() < 2) stats[gcx::kStatInDegLo + gcd::lane_id()] = 0;
+  if (gcd::lane_id() < 2) stats[gcx::kStatBuild + gcd::lane_id()] = 0;
 }
 
-// Start of a level: clears the counters the level accumulates and stamps
-// the device wall clock.
-__global__ void k_level_begin(int32_t* __restrict__ stats) {
-  if (threadIdx.x < gcx::kStatT0) stats[threadIdx.x] = 0;
-  if (threadIdx.x < 2) stats[gcx::kStatInDegLo + threadIdx.x] = 0;
-  if (threadIdx.x == 0) *reinterpret_cast<uint64_t*>(stats + gcx::kStatT0) = wall_clock64();
+// Start of a traversal: values (and round stamps, path counts and
+// coefficients where given), the frontier {src} and its out-degree for the
+// host. Counters and source are handled by the first work-group.
+__global__ __launch_bounds__(kThreads) void k_start(int32_t n, int32_t src, const int32_t* __restrict__ rowptr,
+                                                    int32_t* __restrict__ value, int32_t* __restrict__ mark,
+                                                    double* __restrict__ sigma, double* __restrict__ coef,
+                                                    int32_t* __restrict__ queue, int32_t* __restrict__ pre,
+                                                    int32_t* __restrict__ stats, int32_t* __restrict__ host,
+                                                    int32_t seq) {
+  if (blockIdx.x == 0 && threadIdx.x < kWave) {
+    if (threadIdx.x == 0) {
+      queue[0] = src;
+      pre[0] = 0;
+      __hip_atomic_store(host + gcx::kStatArcs, rowptr[src + 1] - rowptr[src], __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(host + gcx::kStatSeq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    reset_stats(stats);
+  }
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n; i += stride) {
+    value[i] = i == src ? 0 : kInf;
+    if (mark) mark[i] = -1;
+    if (sigma) {
+      sigma[i] = i == src ? 1.0 : 0.0;
+      coef[i] = 0.0;
+      coef[n + i] = 0.0;
+    }
+  }
+}
+
+// Status bits of a pull level that follows a push: the frontier (depth ==
+// level) and the visited vertices, from the depths.
+__global__ __launch_bounds__(kThreads) void k_bits_from_depth(const int32_t* __restrict__ depth, int32_t n,
+                                                              int32_t level, uint32_t* __restrict__ front,
+                                                              uint32_t* __restrict__ visited) {
+  const int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  const int32_t d = v < n ? depth[v] : kInf;
+  const uint64_t f = __ballot(d == level), x = __ballot(d != kInf);
+  const int lane = gcd::lane_id();
+  if ((lane & 31) == 0 && v < n) {
+    front[v >> 5] = static_cast<uint32_t>(f >> (lane & 32));
+    visited[v >> 5] = static_cast<uint32_t>(x >> (lane & 32));
+  }
+}
+
+// The same for SSSP, whose frontier is known by its queue alone (front is
+// all zero on entry).
+__global__ __launch_bounds__(kThreads) void k_bits_from_queue(const int32_t* __restrict__ queue, int32_t qn,
+                                                              uint32_t* __restrict__ front) {
+  const int32_t i = blockIdx.x * kThreads + threadIdx.x;
+  if (i < qn) atomicOr(&front[queue[i] >> 5], 1u << (queue[i] & 31));
+}
+
+// The queue of a push level that follows a pull, from the status bits: a
+// thread takes kWords words, the queue comes out in vertex order within a
+// work-group.
+template <int kWords>
+__global__ __launch_bounds__(kThreads) void k_queue_from_bits(const uint32_t* __restrict__ front, int64_t words,
+                                                              Sink sink) {
+  const int64_t w0 = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) * kWords;
+  uint32_t bits[kWords];
+#pragma unroll
+  for (int k = 0; k < kWords; ++k) bits[k] = w0 + k < words ? front[w0 + k] : 0u;
+  uint64_t mine = 0;
+#pragma unroll
+  for (int k = 0; k < kWords; ++k)
+    for (uint32_t x = bits[k]; x; x &= x - 1u) {
+      const int32_t v = static_cast<int32_t>((w0 + k) << 5) + __ffs(x) - 1;
+      mine += one_vertex(sink.rowptr[v + 1] - sink.rowptr[v]);
+    }
+  uint64_t at = wg_count<kThreads, true>(mine, 0, false, sink.stats, sink.counter);
+#pragma unroll
+  for (int k = 0; k < kWords; ++k)
+    for (uint32_t x = bits[k]; x; x &= x - 1u) {
+      const int32_t v = static_cast<int32_t>((w0 + k) << 5) + __ffs(x) - 1;
+      sink_put(sink, at, v);
+      at += one_vertex(sink.rowptr[v + 1] - sink.rowptr[v]);
+    }
+}
+
+// Device wall clock at a level's start, by the first thread of each of its
+// kernels (the last one that runs first is the level's relaxation kernel).
+__device__ __forceinline__ void stamp_start(int32_t* stats) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<uint64_t*>(stats + gcx::kStatT0) = wall_clock64();
 }
 
 // What the learned scheduler needs to decide the next level on the device:
@@ -211,56 +285,6 @@ struct LevelDecide {
   double alpha = 0.0, beta = 0.0;
 };
 
-// Out-arc count of the queued vertices (for the direction heuristic). The
-// kernel runs right after the level's relaxation kernels on the same
-// stream, so its start stamps the end of the level.
-__global__ void k_queue_degree(const int32_t* __restrict__ queue, const int32_t* __restrict__ qlen,
-                               const int32_t* __restrict__ rowptr, const int32_t* __restrict__ t_rowptr,
-                               int32_t* __restrict__ stats) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *reinterpret_cast<uint64_t*>(stats + gcx::kStatT1) = wall_clock64();
-  const int32_t qn = *qlen;
-  uint64_t sum = 0, sum_in = 0;  // out-arcs and in-arcs of the queued vertices
-  // four queue entries per step, their loads issued together (one
-  // dependent pair of round trips per step, not per entry)
-  const int32_t stride = static_cast<int32_t>(gridDim.x * blockDim.x);
-  int32_t i = static_cast<int32_t>(blockIdx.x * blockDim.x + threadIdx.x);
-  for (; static_cast<int64_t>(i) + 3 * static_cast<int64_t>(stride) < qn; i += 4 * stride) {
-    int32_t v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = queue[i + k * stride];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      sum += static_cast<uint64_t>(rowptr[v[k] + 1] - rowptr[v[k]]);
-      if (t_rowptr) sum_in += static_cast<uint64_t>(t_rowptr[v[k] + 1] - t_rowptr[v[k]]);
-    }
-  }
-  for (; i < qn; i += stride) {
-    const int32_t v = queue[i];
-    sum += static_cast<uint64_t>(rowptr[v + 1] - rowptr[v]);
-    if (t_rowptr) sum_in += static_cast<uint64_t>(t_rowptr[v + 1] - t_rowptr[v]);
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    sum += __shfl_xor(sum, o, kWave);
-    sum_in += __shfl_xor(sum_in, o, kWave);
-  }
-  // one atomic per work-group (per-wave atomics on the one counter serialise)
-  __shared__ uint64_t part[kThreads / kWave], part_in[kThreads / kWave];
-  if (gcd::lane_id() == 0) {
-    part[threadIdx.x / kWave] = sum;
-    part_in[threadIdx.x / kWave] = sum_in;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t total = 0, total_in = 0;
-    for (int w = 0; w < kThreads / kWave; ++w) {
-      total += part[w];
-      total_in += part_in[w];
-    }
-    if (total) atomicAdd(reinterpret_cast<unsigned long long*>(stats + kDegLo), total);
-    if (total_in) atomicAdd(reinterpret_cast<unsigned long long*>(stats + gcx::kStatInDegLo), total_in);
-  }
-}
-
 // LDS the learned decision needs: the parameters, and W2 again at a pitch
 // of one word more than its rows.
 size_t level_decide_lds(int32_t K) {
@@ -268,18 +292,16 @@ size_t level_decide_lds(int32_t K) {
 }
 
 // The learned scheduler's decision for the next level, from the counters of
-// the level just ended (read after k_queue_degree): the next frontier's
-// size and out-arcs and the level's time from its clock stamps. The
-// network only picks the form of pull levels, so the kernel first applies
-// the working-set rule's direction test and stops on a push level. Else the
-// work-group stages the parameters in LDS (coalesced, all loads in flight
-// together; W2 at a pitch of kHid + 1, since each lane reads its own row)
-// and its first wave runs the network. Dynamic LDS: level_decide_lds(K).
-__global__ __launch_bounds__(kThreads) void k_level_decide(int32_t* __restrict__ stats, LevelDecide dec) {
-  extern __shared__ float sp[];
+// the level just ended: the next frontier's size and out-arcs and the
+// level's time from its clock stamps. The network only picks the form of
+// pull levels, so the work-group first applies the working-set rule's
+// direction test and stops on a push level. Else it stages the parameters in
+// LDS (coalesced, all loads in flight together; W2 at a pitch of kHid + 1,
+// since each lane reads its own row) and its first wave runs the network.
+// LDS: level_decide_lds(K) bytes at sp.
+__device__ void level_decide(int32_t* __restrict__ stats, const LevelDecide& dec, uint64_t t1, float* sp) {
   const int64_t n_f = stats[gcx::kStatQLen];
-  const int64_t m_f = static_cast<int64_t>(static_cast<uint32_t>(stats[kDegLo])) |
-                      (static_cast<int64_t>(stats[kDegLo + 1]) << 32);
+  const int64_t m_f = static_cast<uint32_t>(stats[gcx::kStatArcs]);
   const double mu = static_cast<double>(dec.sub_next ? dec.unexplored - m_f : dec.unexplored);
   const bool pull_next = dec.pulling ? !(static_cast<double>(n_f) < static_cast<double>(dec.n) / dec.beta)
                                      : static_cast<double>(m_f) > mu / dec.alpha;
@@ -289,16 +311,22 @@ __global__ __launch_bounds__(kThreads) void k_level_decide(int32_t* __restrict__
   }
   const gcmlp::Layout L(dec.K);
   float* w2 = sp + L.total;  // row r at r * (kHid + 1)
-  for (int32_t i = threadIdx.x; i < L.total; i += kThreads) {
-    const float x = dec.params[i];
-    const int32_t r = i - L.W2;
-    if (r >= 0 && r < gcmlp::kHid * gcmlp::kHid) w2[r + r / gcmlp::kHid] = x;
-    else sp[i] = x;
+  constexpr int kIn = 16;  // loads in flight per thread
+  for (int32_t i0 = threadIdx.x; i0 < L.total; i0 += kIn * kThreads) {
+    float x[kIn];
+#pragma unroll
+    for (int u = 0; u < kIn; ++u) x[u] = dec.params[min(i0 + u * kThreads, L.total - 1)];
+#pragma unroll
+    for (int u = 0; u < kIn; ++u) {
+      const int32_t i = i0 + u * kThreads, r = i - L.W2;
+      if (i >= L.total) break;
+      if (r >= 0 && r < gcmlp::kHid * gcmlp::kHid) w2[r + r / gcmlp::kHid] = x[u];
+      else sp[i] = x[u];
+    }
   }
   __syncthreads();
   if (threadIdx.x >= kWave) return;
   const uint64_t t0 = *reinterpret_cast<const uint64_t*>(stats + gcx::kStatT0);
-  const uint64_t t1 = *reinterpret_cast<const uint64_t*>(stats + gcx::kStatT1);
   const double prior_ms = t1 > t0 ? static_cast<double>(t1 - t0) / dec.clock_khz : 0.0;
   float in[GC_SCHED_INPUTS];
   gcx::level_features(dec.n, dec.m, n_f, m_f, dec.level, prior_ms, dec.prior_arcs, in);
@@ -306,23 +334,28 @@ __global__ __launch_bounds__(kThreads) void k_level_decide(int32_t* __restrict__
                                      reinterpret_cast<float*>(stats + gcx::kStatOut));
 }
 
-// Largest out-degree of the graph into *out (zero on entry): one atomic
-// per work-group.
-__global__ __launch_bounds__(kThreads) void k_max_out_degree(const int32_t* __restrict__ rowptr, int32_t n,
-                                                             int32_t* __restrict__ out) {
-  int32_t mx = 0;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
-  for (int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; v < n; v += stride)
-    mx = max(mx, rowptr[v + 1] - rowptr[v]);
-  for (int o = kWave / 2; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
-  __shared__ int32_t part[kThreads / kWave];
-  if (gcd::lane_id() == 0) part[threadIdx.x / kWave] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t top = 0;
-    for (int w = 0; w < kThreads / kWave; ++w) top = max(top, part[w]);
-    if (top) atomicMax(out, top);
+// End of a level: stamps the clock (the kernel runs right after the level's
+// relaxation kernels), takes the scheduler's decision when dec has a
+// network, hands the counters to the host and clears them (all by the first
+// work-group), and zeroes the status words of the frontier just expanded
+// when they are set.
+__global__ __launch_bounds__(kThreads) void k_level_end(int32_t* __restrict__ stats, int32_t* __restrict__ host,
+                                                        int32_t seq, LevelDecide dec, uint32_t* __restrict__ clear,
+                                                        int64_t words) {
+  extern __shared__ float sp[];
+  if (blockIdx.x == 0) {
+    const uint64_t t1 = wall_clock64();
+    if (dec.params) level_decide(stats, dec, t1, sp);  // uniform
+    if (threadIdx.x < kWave) {
+      if (threadIdx.x == 0) *reinterpret_cast<uint64_t*>(stats + gcx::kStatT1) = t1;
+      __threadfence();  // the wave reads back what its lanes have written
+      publish_stats(stats, host, seq, dec.params ? dec.K : 0);
+      reset_stats(stats);
+    }
   }
+  if (!clear) return;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < words; i += stride) clear[i] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -370,29 +403,38 @@ __device__ __forceinline__ bool scan_front(const int32_t* __restrict__ col, cons
   return found;
 }
 
-// Topology-driven pull over the whole transposed graph.
-__global__ __launch_bounds__(kThreads) void k_bfs_pull(const int32_t* __restrict__ t_rowptr,
-                                                       const int32_t* __restrict__ t_col, int32_t n,
-                                                       const uint32_t* __restrict__ front, int32_t* __restrict__ depth,
-                                                       int32_t level, uint32_t* __restrict__ next,
-                                                       uint32_t* __restrict__ visited, int32_t* __restrict__ queue,
-                                                       int32_t* __restrict__ stats) {
-  const int32_t v = blockIdx.x * kThreads + threadIdx.x;
-  // the visited word and the row bounds are loaded together (one memory
-  // round trip before the scan, not two)
-  uint32_t vw = ~0u;
-  int32_t b = 0, e = 0;
-  if (v < n) {
-    vw = visited[v >> 5];
-    b = t_rowptr[v];
-    e = t_rowptr[v + 1];
+// Topology-driven pull over the whole transposed graph. The work-groups
+// stride over the vertices (their waves by themselves, without barriers), so
+// the counters take one atomic per resident work-group.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bfs_pull(const int32_t* __restrict__ t_rowptr,
+                                                 const int32_t* __restrict__ t_col, int32_t n,
+                                                 const uint32_t* __restrict__ front, int32_t* __restrict__ depth,
+                                                 int32_t level, uint32_t* __restrict__ next,
+                                                 uint32_t* __restrict__ visited, Tally tally) {
+  stamp_start(tally.stats);
+  Counted cnt;
+  for (int64_t base = static_cast<int64_t>(blockIdx.x) * NT; base < n; base += static_cast<int64_t>(gridDim.x) * NT) {
+    const int32_t v = static_cast<int32_t>(min<int64_t>(base + threadIdx.x, INT32_MAX));
+    // the visited word and the row bounds are loaded together (one memory
+    // round trip before the scan, not two)
+    uint32_t vw = ~0u;
+    int32_t b = 0, e = 0;
+    if (v < n) {
+      vw = visited[v >> 5];
+      b = t_rowptr[v];
+      e = t_rowptr[v + 1];
+    }
+    const bool active = !((vw >> (v & 31)) & 1u);
+    const bool found = scan_front(t_col, front, active, b, e);
+    if (found) {
+      depth[v] = level + 1;
+      cnt.add(tally, v);
+    }
+    wave_bits_set(next, v, found);
+    wave_bits_set(visited, v, found);
   }
-  const bool active = !((vw >> (v & 31)) & 1u);
-  const bool found = scan_front(t_col, front, active, b, e);
-  if (found) depth[v] = level + 1;
-  wave_bits_set(next, v, found);
-  wave_bits_set(visited, v, found);
-  block_append(found, v, queue, stats + kQLen);
+  publish_count<NT>(tally, cnt);
 }
 
 // TOCAB pull, per block: flag[l] = 1 when local row l (an unvisited vertex)
@@ -402,7 +444,8 @@ __global__ __launch_bounds__(kThreads) void k_bfs_tocab(const int32_t* __restric
                                                         const int32_t* __restrict__ id_map, int64_t P,
                                                         const uint32_t* __restrict__ visited,
                                                         const uint32_t* __restrict__ front,
-                                                        uint8_t* __restrict__ flag) {
+                                                        uint8_t* __restrict__ flag, int32_t* __restrict__ stats) {
+  stamp_start(stats);
   // the stride is uniform over the work-group, so every wave of it runs the
   // same passes and the wave-wide scans inside stay convergent
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads; base < P;
@@ -429,8 +472,9 @@ __global__ __launch_bounds__(kThreads) void k_bfs_merge(const int32_t* __restric
                                                         const uint8_t* __restrict__ flag, int32_t n,
                                                         int32_t* __restrict__ depth, int32_t level,
                                                         uint32_t* __restrict__ next, uint32_t* __restrict__ visited,
-                                                        int32_t* __restrict__ queue, int32_t* __restrict__ stats) {
+                                                        Tally tally) {
   __shared__ uint8_t hit[K];
+  Counted cnt;
   const int32_t v0 = blockIdx.x * K;
   for (int i = threadIdx.x; i < K; i += kThreads) hit[i] = 0;
   gcm::merge_slices<kFlat, kThreads>(range_ptr, B, id16, flag, blockIdx.x, [&](uint32_t v, uint8_t f) {
@@ -439,67 +483,14 @@ __global__ __launch_bounds__(kThreads) void k_bfs_merge(const int32_t* __restric
   for (int i = threadIdx.x; i < K; i += kThreads) {
     const int32_t v = v0 + i;
     const bool found = v < n && hit[i] && !bit_test(visited, v);
-    if (found) depth[v] = level + 1;
+    if (found) {
+      depth[v] = level + 1;
+      cnt.add(tally, v);
+    }
     wave_bits_set(next, v, found);
     wave_bits_set(visited, v, found);
-    block_append(found, v, queue, stats + kQLen);
   }
-}
-
-// Data-driven push (Algorithm 3's CAS pattern): the work-group's 256 queued
-// vertices are laid end to end by a scan of their out-degrees and each lane
-// takes one arc at a time; the CAS on depth admits every vertex once.
-__global__ __launch_bounds__(kThreads) void k_bfs_push(const int32_t* __restrict__ queue_in, int32_t qn,
-                                                       const int32_t* __restrict__ rowptr,
-                                                       const int32_t* __restrict__ colidx,
-                                                       int32_t* __restrict__ depth, int32_t level,
-                                                       uint32_t* __restrict__ next, uint32_t* __restrict__ visited,
-                                                       int32_t* __restrict__ queue, int32_t* __restrict__ stats) {
-  __shared__ int32_t start[kThreads];
-  __shared__ int32_t first[kThreads];
-  __shared__ int32_t wave_tot[kThreads / kWave];
-  const int32_t i = blockIdx.x * kThreads + threadIdx.x;
-  int32_t b = 0, len = 0;
-  if (i < qn) {
-    const int32_t u = queue_in[i];
-    b = rowptr[u];
-    len = rowptr[u + 1] - b;
-  }
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int incl = gcd::wave_incl_scan(len);
-  if (lane == kWave - 1) wave_tot[wid] = incl;
-  __syncthreads();
-  int off = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / kWave; ++w) {
-    off += (w < wid) ? wave_tot[w] : 0;
-    total += wave_tot[w];
-  }
-  start[threadIdx.x] = off + incl - len;
-  first[threadIdx.x] = b;
-  __syncthreads();
-  // every thread runs the same number of rounds (block_append synchronises the work-group)
-  const int32_t rounds = (total + kThreads - 1) / kThreads;
-  for (int32_t r = 0; r < rounds; ++r) {
-    const int32_t a = r * kThreads + threadIdx.x;
-    bool disc = false;
-    int32_t v = 0;
-    if (a < total) {
-      int lo = 0, hi = kThreads - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (start[mid] <= a) lo = mid;
-        else hi = mid - 1;
-      }
-      v = colidx[first[lo] + (a - start[lo])];
-      if (depth[v] == kInf && atomicCAS(&depth[v], kInf, level + 1) == kInf) {
-        disc = true;
-        bit_set(next, v);
-        bit_set(visited, v);
-      }
-    }
-    block_append(disc, v, queue, stats + kQLen);
-  }
+  publish_count<kThreads>(tally, cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -564,28 +555,35 @@ __device__ __forceinline__ int64_t scan_min(const int32_t* __restrict__ col, con
   return min<int64_t>(best, kInf);
 }
 
-__global__ __launch_bounds__(kThreads) void k_sssp_pull(const int32_t* __restrict__ t_rowptr,
-                                                        const int32_t* __restrict__ t_col,
-                                                        const int32_t* __restrict__ t_w, int32_t n,
-                                                        const uint32_t* __restrict__ front, int32_t* __restrict__ dist,
-                                                        uint32_t* __restrict__ next, int32_t* __restrict__ queue,
-                                                        int32_t* __restrict__ stats) {
-  const int32_t v = blockIdx.x * kThreads + threadIdx.x;
-  int32_t b = 0, e = 0;
-  if (v < n) {
-    b = t_rowptr[v];
-    e = t_rowptr[v + 1];
+template <int NT>
+__global__ __launch_bounds__(NT) void k_sssp_pull(const int32_t* __restrict__ t_rowptr,
+                                                  const int32_t* __restrict__ t_col,
+                                                  const int32_t* __restrict__ t_w, int32_t n,
+                                                  const uint32_t* __restrict__ front, int32_t* __restrict__ dist,
+                                                  uint32_t* __restrict__ next, Tally tally) {
+  stamp_start(tally.stats);
+  Counted cnt;
+  bool any_over = false;
+  for (int64_t base = static_cast<int64_t>(blockIdx.x) * NT; base < n; base += static_cast<int64_t>(gridDim.x) * NT) {
+    const int32_t v = static_cast<int32_t>(min<int64_t>(base + threadIdx.x, INT32_MAX));
+    int32_t b = 0, e = 0;
+    if (v < n) {
+      b = t_rowptr[v];
+      e = t_rowptr[v + 1];
+    }
+    bool ovf;
+    const int64_t best = scan_min(t_col, t_w, front, dist, v < n, b, e, &ovf);
+    any_over |= ovf;
+    bool improved = false;
+    if (v < n && best < dist[v]) {
+      dist[v] = static_cast<int32_t>(best);
+      improved = true;
+      cnt.add(tally, v);
+    }
+    wave_bits_set(next, v, improved);
   }
-  bool ovf;
-  const int64_t best = scan_min(t_col, t_w, front, dist, v < n, b, e, &ovf);
-  if (ovf) stats[kOverflow] = 1;
-  bool improved = false;
-  if (v < n && best < dist[v]) {
-    dist[v] = static_cast<int32_t>(best);
-    improved = true;
-  }
-  wave_bits_set(next, v, improved);
-  block_append(improved, v, queue, stats + kQLen);
+  if (any_over) tally.stats[kOverflow] = 1;
+  publish_count<NT>(tally, cnt);
 }
 
 // TOCAB pull, per block: pmin[l] = min over active sources of this block of
@@ -596,6 +594,7 @@ __global__ __launch_bounds__(kThreads) void k_sssp_tocab(const int32_t* __restri
                                                          const uint32_t* __restrict__ front,
                                                          const int32_t* __restrict__ dist, int32_t* __restrict__ pmin,
                                                          int32_t* __restrict__ stats) {
+  stamp_start(stats);
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads; base < P;
        base += static_cast<int64_t>(gridDim.x) * kThreads) {  // uniform per work-group
     const int64_t l = base + threadIdx.x;
@@ -744,6 +743,7 @@ __global__ __launch_bounds__(kLdsRowThreads) void k_sssp_tocab_lds(
     const int2* __restrict__ seg, int32_t R, int32_t log2W, int32_t n, const uint32_t* __restrict__ front,
     const int32_t* __restrict__ dist, int32_t* __restrict__ pmin, uint32_t pmin_bytes, int32_t* __restrict__ stats) {
   extern __shared__ int32_t ad[];
+  stamp_start(stats);
   const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(pmin, 0, static_cast<int>(pmin_bytes), 0x00020000);
   const int32_t ch = blockIdx.x;
   const int32_t r0 = chunk_beg[ch], r1 = chunk_end[ch], b = chunk_blk[ch], j0 = chunk_j0[ch], ns = chunk_ns[ch];
@@ -963,9 +963,9 @@ __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restr
                                                           const uint16_t* __restrict__ id16s,
                                                           const int32_t* __restrict__ pmin, int32_t R, int32_t n,
                                                           int32_t* __restrict__ dist, uint32_t* __restrict__ next,
-                                                          int32_t* __restrict__ queue, int32_t* __restrict__ stats,
-                                                          int32_t level, uint32_t* __restrict__ visited) {
+                                                          Tally tally, int32_t level, uint32_t* __restrict__ visited) {
   __shared__ int32_t best[K];
+  Counted cnt;
   for (int i = threadIdx.x; i < K; i += NT) best[i] = kInf;
   __syncthreads();
   const ti32x4* p4 = reinterpret_cast<const ti32x4*>(pmin);
@@ -1067,9 +1067,30 @@ __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restr
       }
       took |= static_cast<uint32_t>(improved) << u;
     }
-    block_append_bits<NT>(took, v0 + tid, NT, queue, stats + kQLen);
+    if (__any(took)) {  // the new frontier's degrees, all loads together (others read the range's first vertex)
+      int32_t lo[kPer], hi[kPer];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int32_t o = (took >> u) & 1u ? tid + u * NT : 0;
+        lo[u] = tally.rowptr[v0 + o];
+        hi[u] = tally.rowptr[v0 + o + 1];
+      }
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) cnt.mine += (took >> u) & 1u ? one_vertex(hi[u] - lo[u]) : 0ull;
+      if (tally.t_rowptr) {  // uniform
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+          const int32_t o = (took >> u) & 1u ? tid + u * NT : 0;
+          lo[u] = tally.t_rowptr[v0 + o];
+          hi[u] = tally.t_rowptr[v0 + o + 1];
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) cnt.in += (took >> u) & 1u ? static_cast<uint64_t>(hi[u] - lo[u]) : 0ull;
+      }
+    }
     __syncthreads();
   }
+  publish_count<NT>(tally, cnt);
 }
 
 template <int K, bool kFlat>
@@ -1077,8 +1098,9 @@ __global__ __launch_bounds__(kThreads) void k_sssp_merge(const int32_t* __restri
                                                          const uint16_t* __restrict__ id16,
                                                          const int32_t* __restrict__ pmin, int32_t n,
                                                          int32_t* __restrict__ dist, uint32_t* __restrict__ next,
-                                                         int32_t* __restrict__ queue, int32_t* __restrict__ stats) {
+                                                         Tally tally) {
   __shared__ int32_t best[K];
+  Counted cnt;
   const int32_t v0 = blockIdx.x * K;
   for (int i = threadIdx.x; i < K; i += kThreads) best[i] = kInf;
   gcm::merge_slices<kFlat, kThreads>(range_ptr, B, id16, pmin, blockIdx.x, [&](uint32_t v, int32_t p) {
@@ -1090,90 +1112,18 @@ __global__ __launch_bounds__(kThreads) void k_sssp_merge(const int32_t* __restri
     if (v < n && best[i] < dist[v]) {
       dist[v] = best[i];
       improved = true;
+      cnt.add(tally, v);
     }
     wave_bits_set(next, v, improved);
-    block_append(improved, v, queue, stats + kQLen);
   }
+  publish_count<kThreads>(tally, cnt);
 }
-
-// Data-driven push relaxation: atomicMin on dist; a vertex whose distance
-// dropped enters the next frontier once (round stamp in mark).
-__global__ __launch_bounds__(kThreads) void k_sssp_push(const int32_t* __restrict__ queue_in, int32_t qn,
-                                                        const int32_t* __restrict__ rowptr,
-                                                        const int32_t* __restrict__ colidx,
-                                                        const int32_t* __restrict__ w, int32_t* __restrict__ dist,
-                                                        int32_t round, int32_t* __restrict__ mark,
-                                                        uint32_t* __restrict__ next, int32_t* __restrict__ queue,
-                                                        int32_t* __restrict__ stats) {
-  __shared__ int32_t start[kThreads];
-  __shared__ int32_t first[kThreads];
-  __shared__ int32_t du_s[kThreads];
-  __shared__ int32_t wave_tot[kThreads / kWave];
-  const int32_t i = blockIdx.x * kThreads + threadIdx.x;
-  int32_t b = 0, len = 0, du = 0;
-  if (i < qn) {
-    const int32_t u = queue_in[i];
-    b = rowptr[u];
-    len = rowptr[u + 1] - b;
-    du = dist[u];
-  }
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int incl = gcd::wave_incl_scan(len);
-  if (lane == kWave - 1) wave_tot[wid] = incl;
-  __syncthreads();
-  int off = 0, total = 0;
-#pragma unroll
-  for (int w2 = 0; w2 < kThreads / kWave; ++w2) {
-    off += (w2 < wid) ? wave_tot[w2] : 0;
-    total += wave_tot[w2];
-  }
-  start[threadIdx.x] = off + incl - len;
-  first[threadIdx.x] = b;
-  du_s[threadIdx.x] = du;
-  __syncthreads();
-  const int32_t rounds = (total + kThreads - 1) / kThreads;
-  for (int32_t r = 0; r < rounds; ++r) {
-    const int32_t a = r * kThreads + threadIdx.x;
-    bool fresh = false;
-    int32_t v = 0;
-    if (a < total) {
-      int lo = 0, hi = kThreads - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (start[mid] <= a) lo = mid;
-        else hi = mid - 1;
-      }
-      const int32_t e = first[lo] + (a - start[lo]);
-      v = colidx[e];
-      const int64_t nd = static_cast<int64_t>(du_s[lo]) + w[e];
-      if (nd >= kInf) {
-        stats[kOverflow] = 1;
-      } else if (static_cast<int32_t>(nd) < dist[v]) {
-        const int32_t old = atomicMin(&dist[v], static_cast<int32_t>(nd));
-        if (static_cast<int32_t>(nd) < old) {
-          bit_set(next, v);
-          fresh = atomicExch(&mark[v], round) != round;
-        }
-      }
-    }
-    block_append(fresh, v, queue, stats + kQLen);
-  }
-}
-
-// ---------------------------------------------------------------------------
 
 // ---------------------------------------------------------------------------
 // Betweenness centrality (Section 4's BC benchmark): the BFS levels above
 // also count shortest paths, sigma[v] = sum of sigma[u] over in-neighbours u
 // one level up (Algorithm 3's update); then the dependencies are
 // accumulated level by level backwards (Brandes).
-
-__global__ void k_set_sigma(int32_t src, double* __restrict__ sigma) { sigma[src] = 1.0; }
-
-__global__ void k_fill_f64(double* __restrict__ a, int64_t n) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) a[i] = 0.0;
-}
 
 // Sum of sigma[u] over in-arcs [b, e) from active sources u (FP64); rows
 // longer than kHeavy are summed by the whole wave.
@@ -1217,29 +1167,35 @@ __device__ __forceinline__ double scan_sigma(const int32_t* __restrict__ col, co
 
 // Topology-driven pull: an unvisited vertex with an active in-neighbour
 // joins the next level with the sum of their path counts.
-__global__ __launch_bounds__(kThreads) void k_bc_pull(const int32_t* __restrict__ t_rowptr,
-                                                      const int32_t* __restrict__ t_col, int32_t n,
-                                                      const uint32_t* __restrict__ front, int32_t* __restrict__ depth,
-                                                      int32_t level, double* __restrict__ sigma,
-                                                      uint32_t* __restrict__ next, uint32_t* __restrict__ visited,
-                                                      int32_t* __restrict__ queue, int32_t* __restrict__ stats) {
-  const int32_t v = blockIdx.x * kThreads + threadIdx.x;
-  bool active = false;
-  int32_t b = 0, e = 0;
-  if (v < n && !bit_test(visited, v)) {
-    active = true;
-    b = t_rowptr[v];
-    e = t_rowptr[v + 1];
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bc_pull(const int32_t* __restrict__ t_rowptr,
+                                                const int32_t* __restrict__ t_col, int32_t n,
+                                                const uint32_t* __restrict__ front, int32_t* __restrict__ depth,
+                                                int32_t level, double* __restrict__ sigma,
+                                                uint32_t* __restrict__ next, uint32_t* __restrict__ visited,
+                                                Tally tally) {
+  Counted cnt;
+  for (int64_t base = static_cast<int64_t>(blockIdx.x) * NT; base < n; base += static_cast<int64_t>(gridDim.x) * NT) {
+    const int32_t v = static_cast<int32_t>(min<int64_t>(base + threadIdx.x, INT32_MAX));
+    uint32_t vw = ~0u;
+    int32_t b = 0, e = 0;
+    if (v < n) {
+      vw = visited[v >> 5];
+      b = t_rowptr[v];
+      e = t_rowptr[v + 1];
+    }
+    const bool active = !((vw >> (v & 31)) & 1u);
+    const double sum = scan_sigma(t_col, front, sigma, active, b, e);
+    const bool found = active && sum > 0.0;  // every active vertex has sigma >= 1
+    if (found) {
+      depth[v] = level + 1;
+      sigma[v] = sum;
+      cnt.add(tally, v);
+    }
+    wave_bits_set(next, v, found);
+    wave_bits_set(visited, v, found);
   }
-  const double sum = scan_sigma(t_col, front, sigma, active, b, e);
-  const bool found = active && sum > 0.0;  // every active vertex has sigma >= 1
-  if (found) {
-    depth[v] = level + 1;
-    sigma[v] = sum;
-  }
-  wave_bits_set(next, v, found);
-  wave_bits_set(visited, v, found);
-  block_append(found, v, queue, stats + kQLen);
+  publish_count<NT>(tally, cnt);
 }
 
 // TOCAB pull, per block: part[l] = sum of sigma over the active sources of
@@ -1273,9 +1229,9 @@ __global__ __launch_bounds__(kThreads) void k_bc_merge(const int32_t* __restrict
                                                        const double* __restrict__ part, int32_t n,
                                                        int32_t* __restrict__ depth, int32_t level,
                                                        double* __restrict__ sigma, uint32_t* __restrict__ next,
-                                                       uint32_t* __restrict__ visited, int32_t* __restrict__ queue,
-                                                       int32_t* __restrict__ stats) {
+                                                       uint32_t* __restrict__ visited, Tally tally) {
   __shared__ double acc[K];
+  Counted cnt;
   gcm::merge_accumulate<K, kFlat, kThreads>(range_ptr, B, id16, part, blockIdx.x, acc);
   const int32_t v0 = blockIdx.x * K;
   for (int i = threadIdx.x; i < K; i += kThreads) {
@@ -1284,200 +1240,259 @@ __global__ __launch_bounds__(kThreads) void k_bc_merge(const int32_t* __restrict
     if (found) {
       depth[v] = level + 1;
       sigma[v] = acc[i];
+      cnt.add(tally, v);
     }
     wave_bits_set(next, v, found);
     wave_bits_set(visited, v, found);
-    block_append(found, v, queue, stats + kQLen);
   }
-}
-
-// Data-driven push (Algorithm 3): like the BFS push, plus sigma[v] +=
-// sigma[u] (FP64 atomic) for every arc u -> v that lands one level down.
-__global__ __launch_bounds__(kThreads) void k_bc_push(const int32_t* __restrict__ queue_in, int32_t qn,
-                                                      const int32_t* __restrict__ rowptr,
-                                                      const int32_t* __restrict__ colidx,
-                                                      int32_t* __restrict__ depth, int32_t level,
-                                                      double* __restrict__ sigma, uint32_t* __restrict__ next,
-                                                      uint32_t* __restrict__ visited, int32_t* __restrict__ queue,
-                                                      int32_t* __restrict__ stats) {
-  __shared__ int32_t start[kThreads];
-  __shared__ int32_t first[kThreads];
-  __shared__ double su[kThreads];
-  __shared__ int32_t wave_tot[kThreads / kWave];
-  const int32_t i = blockIdx.x * kThreads + threadIdx.x;
-  int32_t b = 0, len = 0;
-  double sg = 0.0;
-  if (i < qn) {
-    const int32_t u = queue_in[i];
-    b = rowptr[u];
-    len = rowptr[u + 1] - b;
-    sg = sigma[u];
-  }
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int incl = gcd::wave_incl_scan(len);
-  if (lane == kWave - 1) wave_tot[wid] = incl;
-  __syncthreads();
-  int off = 0, total = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / kWave; ++w) {
-    off += (w < wid) ? wave_tot[w] : 0;
-    total += wave_tot[w];
-  }
-  start[threadIdx.x] = off + incl - len;
-  first[threadIdx.x] = b;
-  su[threadIdx.x] = sg;
-  __syncthreads();
-  // every thread runs the same number of rounds (block_append synchronises the work-group)
-  const int32_t rounds = (total + kThreads - 1) / kThreads;
-  for (int32_t r = 0; r < rounds; ++r) {
-    const int32_t a = r * kThreads + threadIdx.x;
-    bool disc = false;
-    int32_t v = 0;
-    if (a < total) {
-      int lo = 0, hi = kThreads - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (start[mid] <= a) lo = mid;
-        else hi = mid - 1;
-      }
-      v = colidx[first[lo] + (a - start[lo])];
-      int32_t old = depth[v];
-      if (old == kInf) {
-        old = atomicCAS(&depth[v], kInf, level + 1);
-        if (old == kInf) {
-          disc = true;
-          bit_set(next, v);
-          bit_set(visited, v);
-        }
-      }
-      if (old == kInf || old == level + 1) atomicAdd(&sigma[v], su[lo]);
-    }
-    block_append(disc, v, queue, stats + kQLen);
-  }
+  publish_count<kThreads>(tally, cnt);
 }
 
 // ---------------------------------------------------------------------------
-// Data-driven push balanced over arcs, for frontiers with many arcs: pre is
-// the exclusive scan of the queued vertices' out-degrees, and each lane takes
-// kPushArcs consecutive arcs of their concatenated out-arc lists, so a hub's
-// arcs spread over many work-groups instead of one. The relaxation is a
-// functor: src(u) loads what u passes along its arcs, relax(v, e, x)
-// handles arc e into v and returns true when v enters the next frontier.
-constexpr int kPushArcs = 8;
+// Data-driven push, balanced over arcs. The queue's arc prefix cuts the
+// concatenated out-arcs of the frontier into equal pieces, one per
+// work-group, so a hub's arcs spread over many work-groups and a frontier of
+// any shape takes one launch. A work-group finds its first vertex with a
+// wave-wide search (64 probes per step), stages a window of the queue in
+// LDS, and every thread locates its kA arcs there. What bounds a small level
+// is the chain of dependent accesses (queue, row, column, value, atomic), so
+// each step is issued for all of a thread's arcs before the next; what
+// bounds a large one is the append, an atomic on one address, so a
+// work-group takes tiles in turn and collects what they find in LDS until
+// its buffer is full.
+// The relaxation is a functor: src(u) loads what u passes along its arcs, and
+// relax<kA>() does the atomics and returns the arcs whose target enters the
+// next frontier.
 
 struct BfsRelax {  // Algorithm 3's CAS on depth
+  using Src = int32_t;
   int32_t* depth;
   int32_t level;
-  uint32_t* next;
-  uint32_t* visited;
-  __device__ int32_t src(int32_t) const { return 0; }
-  __device__ bool relax(int32_t v, int64_t, int32_t) const {
-    if (depth[v] == kInf && atomicCAS(&depth[v], kInf, level + 1) == kInf) {
-      bit_set(next, v);
-      bit_set(visited, v);
-      return true;
+  __device__ Src src(int32_t) const { return 0; }
+  template <int kA>
+  __device__ uint32_t relax(uint32_t in, const int32_t (&v)[kA], const int32_t (&)[kA], const Src (&)[kA],
+                            int32_t*) const {
+    int32_t old[kA];
+#pragma unroll
+    for (int k = 0; k < kA; ++k) old[k] = (in >> k) & 1u ? depth[v[k]] : 0;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) {
+      const bool open = old[k] == kInf;
+      old[k] = 0;
+      if (open) old[k] = atomicCAS(&depth[v[k]], kInf, level + 1);
     }
-    return false;
+    uint32_t took = 0;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) took |= static_cast<uint32_t>(old[k] == kInf) << k;
+    return took;
   }
 };
 
 struct SsspRelax {  // atomicMin on dist; a vertex is queued once per round (stamp in mark)
+  using Src = int32_t;
   const int32_t* w;
   int32_t* dist;
   int32_t round;
   int32_t* mark;
-  uint32_t* next;
-  int32_t* stats;
-  __device__ int32_t src(int32_t u) const { return dist[u]; }
-  __device__ bool relax(int32_t v, int64_t e, int32_t du) const {
-    const int64_t nd = static_cast<int64_t>(du) + w[e];
-    if (nd >= kInf) {
-      stats[kOverflow] = 1;
-    } else if (static_cast<int32_t>(nd) < dist[v]) {
-      const int32_t old = atomicMin(&dist[v], static_cast<int32_t>(nd));
-      if (static_cast<int32_t>(nd) < old) {
-        bit_set(next, v);
-        return atomicExch(&mark[v], round) != round;
-      }
+  __device__ Src src(int32_t u) const { return dist[u]; }
+  template <int kA>
+  __device__ uint32_t relax(uint32_t in, const int32_t (&v)[kA], const int32_t (&e)[kA], const Src (&du)[kA],
+                            int32_t* stats) const {
+    int32_t nd[kA], old[kA];
+    bool over = false;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) {
+      nd[k] = (in >> k) & 1u ? w[e[k]] : 0;
+      old[k] = (in >> k) & 1u ? dist[v[k]] : 0;
     }
-    return false;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) {
+      const int64_t d = static_cast<int64_t>(du[k]) + nd[k];
+      const bool on = (in >> k) & 1u;
+      over |= on && d >= kInf;
+      nd[k] = on && d < kInf ? static_cast<int32_t>(d) : kInf;
+    }
+    if (over) stats[kOverflow] = 1;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) {
+      const bool better = nd[k] < old[k];
+      old[k] = INT32_MIN;
+      if (better) old[k] = atomicMin(&dist[v[k]], nd[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kA; ++k) {
+      const bool won = nd[k] < old[k];
+      old[k] = round;
+      if (won) old[k] = atomicExch(&mark[v[k]], round);
+    }
+    uint32_t took = 0;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) took |= static_cast<uint32_t>(old[k] != round) << k;
+    return took;
   }
 };
 
-struct BcRelax {  // the BFS CAS plus sigma[v] += sigma[u] for arcs that land one level down
+struct BcRelax {  // the BFS CAS plus sigma[v] += sigma[u] (FP64 atomic) for arcs that land one level down
+  using Src = double;
   int32_t* depth;
   int32_t level;
   double* sigma;
-  uint32_t* next;
-  uint32_t* visited;
-  __device__ double src(int32_t u) const { return sigma[u]; }
-  __device__ bool relax(int32_t v, int64_t, double su) const {
-    bool disc = false;
-    int32_t old = depth[v];
-    if (old == kInf) {
-      old = atomicCAS(&depth[v], kInf, level + 1);
-      if (old == kInf) {
-        disc = true;
-        bit_set(next, v);
-        bit_set(visited, v);
+  __device__ Src src(int32_t u) const { return sigma[u]; }
+  template <int kA>
+  __device__ uint32_t relax(uint32_t in, const int32_t (&v)[kA], const int32_t (&)[kA], const Src (&su)[kA],
+                            int32_t*) const {
+    int32_t old[kA];
+    uint32_t took = 0;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) old[k] = (in >> k) & 1u ? depth[v[k]] : 0;
+#pragma unroll
+    for (int k = 0; k < kA; ++k)
+      if (old[k] == kInf) {
+        old[k] = atomicCAS(&depth[v[k]], kInf, level + 1);
+        if (old[k] == kInf) took |= 1u << k;
       }
-    }
-    if (old == kInf || old == level + 1) atomicAdd(&sigma[v], su);
-    return disc;
+#pragma unroll
+    for (int k = 0; k < kA; ++k)
+      if (((in >> k) & 1u) && (old[k] == kInf || old[k] == level + 1)) atomicAdd(&sigma[v[k]], su[k]);
+    return took;
   }
 };
 
-template <class Relax>
-__global__ __launch_bounds__(kThreads) void k_push_arcs(const int32_t* __restrict__ queue_in,
-                                                        const int32_t* __restrict__ pre, int32_t qn,
-                                                        const int32_t* __restrict__ rowptr,
-                                                        const int32_t* __restrict__ colidx, Relax r,
-                                                        int32_t* __restrict__ queue, int32_t* __restrict__ stats) {
-  const int64_t end = pre[qn];
-  const int64_t a0 = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) * kPushArcs;
-  int32_t i = 0;
-  if (a0 < end) {  // the queued vertex whose arcs contain a0: the last i with pre[i] <= a0
-    int32_t h = qn - 1;
-    while (i < h) {
-      const int32_t mid = i + ((h - i + 1) >> 1);
-      if (pre[mid] <= a0) i = mid;
-      else h = mid - 1;
+// The last i in [0, qn) with pre[i] <= a (pre ascends, pre[0] <= a), by the
+// whole wave.
+__device__ __forceinline__ int32_t wave_owner(const int32_t* __restrict__ pre, int32_t qn, int32_t a) {
+  const int lane = gcd::lane_id();
+  int32_t lo = 0, hi = qn - 1;
+  while (lo < hi) {  // uniform
+    const int32_t step = (hi - lo + kWave - 1) / kWave;
+    const int32_t idx = static_cast<int32_t>(min<int64_t>(hi, lo + static_cast<int64_t>(lane + 1) * step));
+    const int cnt = __popcll(__ballot(pre[idx] <= a));  // a prefix of the lanes
+    const int32_t fail = static_cast<int32_t>(min<int64_t>(hi, lo + static_cast<int64_t>(cnt + 1) * step));
+    lo = static_cast<int32_t>(min<int64_t>(hi, lo + static_cast<int64_t>(cnt) * step));
+    if (cnt < kWave) hi = fail - 1;
+  }
+  return lo;
+}
+
+template <class Relax, int kA>
+__global__ __launch_bounds__(kThreads) void k_push(const int32_t* __restrict__ queue_in,
+                                                   const int32_t* __restrict__ pre, int32_t qn, int32_t arcs,
+                                                   const int32_t* __restrict__ rowptr,
+                                                   const int32_t* __restrict__ colidx, Relax r, Sink sink) {
+  constexpr int kWin = kA == 1 ? kThreads : 2 * kThreads;  // queue entries staged at a time
+  constexpr int kTile = kThreads * kA;                     // arcs
+  constexpr int kPer = kA == 1 ? 1 : 12;                   // buffered vertices per thread
+  constexpr int kBuf = kThreads * kPer;
+  static_assert(kBuf >= kTile, "a tile's vertices fit the empty buffer");
+  __shared__ int32_t w_pre[kWin], w_row[kWin], buf[kBuf];
+  __shared__ typename Relax::Src w_src[kWin];
+  __shared__ int32_t first, held;
+  const int tid = threadIdx.x;
+  stamp_start(sink.stats);
+  if (tid == 0) held = 0;
+  for (int64_t t0 = static_cast<int64_t>(blockIdx.x) * kTile; t0 < arcs;
+       t0 += static_cast<int64_t>(gridDim.x) * kTile) {  // uniform
+    const int32_t a0 = static_cast<int32_t>(t0);
+    const int32_t a1 = static_cast<int32_t>(min<int64_t>(arcs, t0 + kTile));
+    if (tid < kWave) {
+      const int32_t i = wave_owner(pre, qn, a0);
+      if (tid == 0) first = i;
     }
-  }
-  int64_t ub = 0, ue = 0, rb = 0;
-  auto x = r.src(0);
-  if (a0 < end) {
-    const int32_t u = queue_in[i];
-    ub = pre[i];
-    ue = pre[i + 1];
-    rb = rowptr[u];
-    x = r.src(u);
-  }
-  // the thread's kPushArcs arcs; the vertices they discover are appended
-  // together at the end (a work-group append per arc step kept the waves in
-  // lock-step through two barriers per step)
-  int32_t found[kPushArcs];
-  uint32_t took = 0;
+    __syncthreads();
+    int32_t v[kA];
+    uint32_t took = 0;
 #pragma unroll
-  for (int k = 0; k < kPushArcs; ++k) {
-    const int64_t a = a0 + k;
-    found[k] = 0;
-    if (a < end) {
-      while (a >= ue) {  // next queued vertex with an arc at a
-        ++i;
-        const int32_t u = queue_in[i];
-        ub = ue;
-        ue = pre[i + 1];
-        rb = rowptr[u];
-        x = r.src(u);
+    for (int k = 0; k < kA; ++k) v[k] = 0;
+    // one window nearly always; more where vertices without out-arcs stand between
+    for (int32_t base = first; base < qn; base += kWin) {  // uniform
+#pragma unroll
+      for (int t = tid; t < kWin; t += kThreads) {
+        const int32_t i = base + t;
+        int32_t p = INT32_MAX, row = 0;
+        typename Relax::Src x{};
+        if (i < qn) {
+          const int32_t u = queue_in[i];
+          p = pre[i];
+          row = rowptr[u] - p;
+          x = r.src(u);
+        }
+        w_pre[t] = p;
+        w_row[t] = row;
+        w_src[t] = x;
       }
-      const int64_t e = rb + (a - ub);
-      const int32_t v = colidx[e];
-      found[k] = v;
-      took |= static_cast<uint32_t>(r.relax(v, e, x)) << k;
+      const int32_t next = base + kWin < qn ? pre[base + kWin] : arcs;
+      __syncthreads();
+      const int32_t from = w_pre[0];
+      int32_t e[kA];
+      typename Relax::Src x[kA];
+      uint32_t in = 0;
+#pragma unroll
+      for (int k = 0; k < kA; ++k) {
+        const int64_t a = t0 + tid + k * kThreads;
+        const bool here = a >= from && a < next && a < a1;
+        int lo = 0;  // the last entry with w_pre <= a
+#pragma unroll
+        for (int step = kWin / 2; step > 0; step >>= 1)
+          if (w_pre[lo + step] <= a) lo += step;
+        e[k] = here ? static_cast<int32_t>(a) + w_row[lo] : 0;
+        x[k] = w_src[lo];
+        in |= static_cast<uint32_t>(here) << k;
+      }
+      int32_t to[kA];
+#pragma unroll
+      for (int k = 0; k < kA; ++k) to[k] = (in >> k) & 1u ? colidx[e[k]] : 0;
+      took |= r.template relax<kA>(in, to, e, x, sink.stats);
+#pragma unroll
+      for (int k = 0; k < kA; ++k) v[k] = (in >> k) & 1u ? to[k] : v[k];
+      if (next >= a1) break;
+      __syncthreads();  // the window is refilled
+    }
+    // what the tile found goes to the buffer, one LDS atomic per wave
+    int32_t total = 0, before[kA];
+#pragma unroll
+    for (int k = 0; k < kA; ++k) {
+      const uint64_t m = __ballot((took >> k) & 1u);
+      before[k] = total + __popcll(m & gcd::lanemask_lt());
+      total += __popcll(m);
+    }
+    if (total) {  // uniform over the wave
+      int32_t at = 0;
+      if (gcd::lane_id() == 0) at = atomicAdd(&held, total);
+      at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+      for (int k = 0; k < kA; ++k)
+        if ((took >> k) & 1u) buf[at + before[k]] = v[k];
+    }
+    __syncthreads();
+    const int32_t c = held;
+    const bool last = t0 + static_cast<int64_t>(gridDim.x) * kTile >= arcs;
+    if (c > 0 && (last || c + kTile > kBuf)) {  // uniform
+      int32_t u[kPer], deg[kPer];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) u[j] = buf[min(tid + j * kThreads, c - 1)];
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) deg[j] = sink.rowptr[u[j] + 1] - sink.rowptr[u[j]];
+      uint64_t mine = 0, in = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) mine += tid + j * kThreads < c ? one_vertex(deg[j]) : 0ull;
+      if (sink.t_rowptr) {  // uniform
+        int32_t di[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) di[j] = sink.t_rowptr[u[j] + 1] - sink.t_rowptr[u[j]];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) in += tid + j * kThreads < c ? static_cast<uint64_t>(di[j]) : 0ull;
+      }
+      uint64_t at = wg_count<kThreads, true>(mine, in, sink.t_rowptr != nullptr, sink.stats, sink.counter);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        if (tid + j * kThreads < c) {
+          sink_put(sink, at, u[j]);
+          at += one_vertex(deg[j]);
+        }
+      }
+      if (tid == 0) held = 0;  // added to again after the next tile's barriers
     }
   }
-  block_append_list<kThreads, kPushArcs>(took, found, queue, stats + kQLen);
 }
 
 __global__ void k_order_degree(const int32_t* __restrict__ order, int32_t cnt, const int32_t* __restrict__ rowptr,
@@ -1498,8 +1513,8 @@ __global__ void k_order_degree(const int32_t* __restrict__ order, int32_t cnt, c
 constexpr int kBackArcs = 8;  // consecutive arcs per lane
 
 // Sums for the vertices order[lo, hi) of one depth, balanced over arcs: the
-// level's out-arcs, concatenated in level order (pre = exclusive scan of the
-// degrees along order), are cut into kBackArcs-arc pieces, one per lane. A
+// level's `arcs` out-arcs, concatenated in level order (pre[lo, hi) = each
+// one's first position), are cut into kBackArcs-arc pieces, one per lane. A
 // lane adds the sum of coef_in over each vertex's arcs in its piece into
 // coef_out[v] (FP64 atomic), or stores it when the piece holds all of v's
 // arcs.
@@ -1507,10 +1522,10 @@ __global__ __launch_bounds__(kThreads) void k_bc_back_arcs(const int32_t* __rest
                                                            const int32_t* __restrict__ colidx,
                                                            const int32_t* __restrict__ order,
                                                            const int32_t* __restrict__ pre, int32_t lo, int32_t hi,
-                                                           const double* __restrict__ coef_in,
+                                                           int32_t arcs, const double* __restrict__ coef_in,
                                                            double* __restrict__ coef_out) {
-  const int64_t end = pre[hi];
-  const int64_t a0 = pre[lo] + (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) * kBackArcs;
+  const int64_t end = arcs;
+  const int64_t a0 = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) * kBackArcs;
   if (a0 >= end) return;
   const int64_t a1 = a0 + kBackArcs < end ? a0 + kBackArcs : end;
   // the vertex whose arcs contain a0: the last i in [lo, hi) with pre[i] <= a0
@@ -1528,7 +1543,7 @@ __global__ __launch_bounds__(kThreads) void k_bc_back_arcs(const int32_t* __rest
   {
     int32_t i = l;
     int32_t v = order[i];
-    int64_t vb = pre[i], ve = pre[i + 1];
+    int64_t vb = pre[i], ve = i + 1 < hi ? pre[i + 1] : arcs;
     int64_t rb = rowptr[v];
 #pragma unroll
     for (int k = 0; k < kBackArcs; ++k) {
@@ -1537,7 +1552,7 @@ __global__ __launch_bounds__(kThreads) void k_bc_back_arcs(const int32_t* __rest
         while (a >= ve) {  // next vertex with an arc at a (vertices without out-arcs are skipped)
           ++i;
           vb = ve;
-          ve = pre[i + 1];
+          ve = i + 1 < hi ? pre[i + 1] : arcs;
           v = order[i];
           rb = rowptr[v];
         }
@@ -1856,23 +1871,92 @@ hipError_t stream_weights(gc_tocab t, hipStream_t s) {
   return hipMemsetAsync(t->w_pad + t->m, 0, sizeof(int32_t) * (t->m_pad - t->m), s);
 }
 
-// Per-level bookkeeping: reads the next frontier's size and out-arc count,
-// clears the old frontier's status bytes, and swaps the buffers.
+// Waits until the pinned mirror holds level `seq`'s counters: it spins for
+// as long as a short level takes (a stream synchronisation costs more than
+// such a level's kernels), then leaves the waiting to the runtime.
+hipError_t wait_stats(gc_graph g, int32_t seq, hipStream_t s) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 1;; ++i) {
+    if (__atomic_load_n(g->stats_host + gcx::kStatSeq, __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+    if ((i & 63) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) break;
+  }
+  GC_HIP_TRY(hipStreamSynchronize(s));
+  return __atomic_load_n(g->stats_host + gcx::kStatSeq, __ATOMIC_ACQUIRE) == seq ? hipSuccess : hipErrorUnknown;
+}
+
+// Work-groups for a pass over `items`, each thread striding over them.
+inline int stride_grid(int64_t items) {
+  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((items + kThreads - 1) / kThreads, 8 * device_cus())));
+}
+
+// Per-level bookkeeping: the frontier's queue and status words, and the
+// counters of the next one.
 struct Frontier {
   gc_graph g;
   hipStream_t s;
+  int32_t* q[2];  // queues and their arc prefixes, the current and the next level's in turn
+  int32_t* p[2];
   int cur = 0;
   int32_t n_f = 1;
   int64_t m_f = 0;
   int64_t m_f_in = 0;  // in-arcs of the frontier when count_in (the source's are not counted)
   bool count_in = false;
+  bool queue_ok = true;            // queue and pre hold the current frontier
+  bool bits_ok = false;            // front (and visited) hold the current frontier
+  bool dirty[2] = {false, false};  // status words of [cur] / [cur ^ 1] may be set
+  Frontier(gc_graph gr, hipStream_t st)
+      : g(gr), s(st), q{gr->queue[0], gr->queue[1]}, p{gr->arc_pre, gr->arc_deg} {}
   uint32_t* front() { return cur == 0 ? g->front : g->next; }
   uint32_t* next() { return cur == 0 ? g->next : g->front; }
-  int32_t* queue() { return g->queue[cur]; }
-  int32_t* queue_next() { return g->queue[cur ^ 1]; }
+  int32_t* queue() { return q[cur]; }
+  int32_t* pre() { return p[cur]; }
+  int32_t* queue_next() { return q[cur ^ 1]; }
+  int64_t words() const { return (static_cast<int64_t>(g->n) + 31) / 32; }
+  Sink sink() {
+    return Sink{q[cur ^ 1], p[cur ^ 1], g->rowptr, count_in ? g->t_rowptr : nullptr, g->stats};
+  }
+  Tally tally() { return Tally{g->rowptr, count_in ? g->t_rowptr : nullptr, g->stats}; }
 
-  hipError_t begin_level() {
-    k_level_begin<<<1, kWave, 0, s>>>(g->stats);
+  // Start of a traversal from `src`: the value array (and what else is
+  // given), the frontier {src}; m_f = its out-degree.
+  hipError_t start(int32_t src, int32_t* value, int32_t* mark, double* sigma, double* coef) {
+    if (!g->bits_clean) {
+      k_fill_i32<<<stride_grid(words()), kThreads, 0, s>>>(reinterpret_cast<int32_t*>(g->front), words(), 0);
+      k_fill_i32<<<stride_grid(words()), kThreads, 0, s>>>(reinterpret_cast<int32_t*>(g->next), words(), 0);
+    }
+    g->bits_clean = false;  // until the traversal has ended well
+    const int32_t seq = ++g->level_seq;
+    k_start<<<stride_grid(g->n), kThreads, 0, s>>>(g->n, src, g->rowptr, value, mark, sigma, coef, q[0], p[0], g->stats,
+                                                   g->stats_host, seq);
+    GC_HIP_TRY(hipGetLastError());
+    GC_HIP_TRY(wait_stats(g, seq, s));
+    m_f = static_cast<uint32_t>(g->stats_host[gcx::kStatArcs]);
+    return hipSuccess;
+  }
+
+  // Before a pull level: the status words of the frontier (and, for BFS and
+  // BC, of the visited vertices) when the previous level was a push.
+  hipError_t need_bits(const int32_t* depth, int32_t level) {
+    if (bits_ok) return hipSuccess;
+    if (depth)
+      k_bits_from_depth<<<grid_for(g->n, kThreads), kThreads, 0, s>>>(depth, g->n, level, front(), g->visited);
+    else
+      k_bits_from_queue<<<grid_for(n_f, kThreads), kThreads, 0, s>>>(queue(), n_f, front());
+    dirty[cur] = true;
+    bits_ok = true;
+    return hipGetLastError();
+  }
+
+  // Before a push level: the queue, when the previous level was a pull.
+  hipError_t need_queue() {
+    if (queue_ok) return hipSuccess;
+    Sink to{q[cur], p[cur], g->rowptr, nullptr, g->stats, gcx::kStatBuild};
+    // up to 512 work-groups, an atomic each, at 2^22 vertices and 2^24
+    if (words() <= 512 * kThreads)
+      k_queue_from_bits<1><<<grid_for(words(), kThreads), kThreads, 0, s>>>(front(), words(), to);
+    else
+      k_queue_from_bits<4><<<grid_for(words(), 4 * kThreads), kThreads, 0, s>>>(front(), words(), to);
+    queue_ok = true;
     return hipGetLastError();
   }
 
@@ -1884,15 +1968,14 @@ struct Frontier {
     return t1 > t0 ? static_cast<double>(t1 - t0) / g->clock_khz : 0.0;
   }
 
-  // Ends a level: counts the next frontier's out-arcs, queues the learned
-  // scheduler's decision for the next level when `decide` is given (read
-  // back with the counters, so it costs no synchronisation of its own),
-  // and reads the counters.
-  hipError_t end_level(bool* overflow, gc_sched decide = nullptr, int32_t next_level = 0,
+  // Ends a level (pull: it set the next frontier's status words): queues the
+  // learned scheduler's decision for the next level when `decide` is given
+  // (read back with the counters, so it costs no synchronisation of its
+  // own), and reads the counters.
+  hipError_t end_level(bool pull, bool* overflow, gc_sched decide = nullptr, int32_t next_level = 0,
                        LevelDecide dec = LevelDecide()) {
     size_t lds = 0;
     if (decide) {
-      lds = level_decide_lds(gcx::sched_actions(decide));
       dec.params = gcx::sched_params(decide);
       dec.frange = gcx::sched_range(decide);
       dec.K = gcx::sched_actions(decide);
@@ -1901,69 +1984,58 @@ struct Frontier {
       dec.level = next_level;
       dec.prior_arcs = m_f;
       dec.clock_khz = g->clock_khz;
+      lds = level_decide_lds(dec.K);
     }
-    k_queue_degree<<<1024, kThreads, 0, s>>>(queue_next(), g->stats + kQLen, g->rowptr, count_in ? g->t_rowptr : nullptr,
-                                            g->stats);
-    if (decide) k_level_decide<<<1, kThreads, lds, s>>>(g->stats, dec);
+    const int32_t seq = ++g->level_seq;
+    const bool clear = dirty[cur];
+    k_level_end<<<clear ? stride_grid(words()) : 1, kThreads, lds, s>>>(g->stats, g->stats_host, seq, dec,
+                                                                        clear ? front() : nullptr, words());
+    dirty[cur] = false;
+    if (pull) dirty[cur ^ 1] = true;
+    bits_ok = pull;
+    queue_ok = !pull;
     GC_HIP_TRY(hipGetLastError());
-    GC_HIP_TRY(hipMemcpyAsync(g->stats_host, g->stats, sizeof(int32_t) * gcx::kStatSlots, hipMemcpyDeviceToHost, s));
-    if (n_f > 0) {
-      // the old frontier's bits: through its queue, or, for a frontier of at
-      // least one vertex per 16 words (one per 64-byte line), every word
-      const int64_t words = (static_cast<int64_t>(g->n) + 31) / 32;
-      if (16 * static_cast<int64_t>(n_f) >= words)
-        k_fill_i32<<<grid_for(words, kThreads), kThreads, 0, s>>>(reinterpret_cast<int32_t*>(front()), words, 0);
-      else
-        k_clear_front<<<grid_for(n_f, kThreads), kThreads, 0, s>>>(front(), queue(), n_f);
-    }
-    GC_HIP_TRY(hipGetLastError());
-    GC_HIP_TRY(hipStreamSynchronize(s));
-    n_f = g->stats_host[kQLen];
-    m_f = static_cast<int64_t>(static_cast<uint32_t>(g->stats_host[kDegLo])) |
-          (static_cast<int64_t>(g->stats_host[kDegLo + 1]) << 32);
+    GC_HIP_TRY(wait_stats(g, seq, s));
+    n_f = g->stats_host[gcx::kStatQLen];
+    m_f = static_cast<uint32_t>(g->stats_host[gcx::kStatArcs]);
     m_f_in = static_cast<int64_t>(static_cast<uint32_t>(g->stats_host[gcx::kStatInDegLo])) |
              (static_cast<int64_t>(g->stats_host[gcx::kStatInDegLo + 1]) << 32);
     if (overflow && g->stats_host[kOverflow]) *overflow = true;
     cur ^= 1;
     return hipSuccess;
   }
+
+  // End of a traversal whose last level found nothing: no status bit is set.
+  void finish() { g->bits_clean = n_f == 0; }
 };
 
-hipError_t init_state(gc_graph g, int32_t* value, int32_t source, bool bfs, hipStream_t s) {
-  const int32_t n = g->n;
-  k_fill_i32<<<grid_for(n, kThreads), kThreads, 0, s>>>(value, n, kInf);
-  const int64_t words = (static_cast<int64_t>(n) + 31) / 32;
-  k_fill_i32<<<grid_for(words, kThreads), kThreads, 0, s>>>(reinterpret_cast<int32_t*>(g->front), words, 0);
-  k_fill_i32<<<grid_for(words, kThreads), kThreads, 0, s>>>(reinterpret_cast<int32_t*>(g->next), words, 0);
-  k_fill_i32<<<grid_for(words, kThreads), kThreads, 0, s>>>(reinterpret_cast<int32_t*>(g->visited), words, 0);
-  if (!bfs) k_fill_i32<<<grid_for(n, kThreads), kThreads, 0, s>>>(g->mark, n, -1);
-  k_set_source<<<1, 1, 0, s>>>(source, value, g->front, g->queue[0], bfs ? g->visited : nullptr);
-  return hipGetLastError();
-}
+// Push of one level with relaxation r. One arc per thread up to 64 tiles of
+// them (the latency of a level is least, and so few appends cost little),
+// four beyond, in at most four work-groups per CU.
+constexpr int64_t kPushOneArc = 64 * kThreads;
 
-// Arc-balanced push of one level with relaxation r (see arc_balanced).
 template <class Relax>
-hipError_t push_arcs(gc_graph g, Frontier& f, Relax r, hipStream_t s) {
-  k_order_degree<<<grid_for(f.n_f, kThreads), kThreads, 0, s>>>(f.queue(), f.n_f, g->rowptr, g->arc_deg);
-  GC_HIP_TRY(hipGetLastError());
-  GC_HIP_TRY(gcx::scan_exclusive(g->arc_deg, g->arc_pre, f.n_f, s));
-  const int64_t pieces = (f.m_f + kPushArcs - 1) / kPushArcs;
-  k_push_arcs<<<grid_for(pieces, kThreads), kThreads, 0, s>>>(f.queue(), g->arc_pre, f.n_f, g->rowptr, g->colidx, r,
-                                                               f.queue_next(), g->stats);
+hipError_t push_level(gc_graph g, Frontier& f, Relax r, hipStream_t s) {
+  if (f.m_f == 0) return hipSuccess;
+  GC_HIP_TRY(f.need_queue());
+  const int32_t arcs = static_cast<int32_t>(f.m_f);
+  if (f.m_f <= kPushOneArc)
+    k_push<Relax, 1><<<grid_for(arcs, kThreads), kThreads, 0, s>>>(f.queue(), f.pre(), f.n_f, arcs, g->rowptr, g->colidx,
+                                                                   r, f.sink());
+  else
+    k_push<Relax, 4><<<std::min(grid_for(arcs, 4 * kThreads), 4 * device_cus()), kThreads, 0, s>>>(
+        f.queue(), f.pre(), f.n_f, arcs, g->rowptr, g->colidx, r, f.sink());
   return hipGetLastError();
 }
 
-// The vertex-parallel push kernels balance the arcs of each work-group's
-// kThreads vertices across its threads, so only the spread between
-// work-groups is left: on a graph whose out-degrees are all small a
-// frontier takes one launch instead of the five of the arc-balanced form
-// (degree order, scan, push), up to frontiers large enough for launches
-// not to matter.
-constexpr int32_t kBlockPushDegree = 64;
-constexpr int64_t kBlockPushArcs = int64_t{1} << 20;
-
-bool arc_balanced(const gc_graph_s* g, const Frontier& f) {
-  return f.m_f > kThreads * kPushArcs && (g->max_out_deg > kBlockPushDegree || f.m_f > kBlockPushArcs);
+// Grid of a pull over all vertices: two work-groups of 1024 threads per CU
+// (the most that are resident), smaller ones for graphs that would not give
+// every CU one.
+constexpr int kPullThreads = 1024;
+inline bool wide_pull(int32_t n) { return n >= 2 * kPullThreads * device_cus(); }
+inline int pull_grid(int32_t n) {
+  return wide_pull(n) ? std::min(grid_for(n, kPullThreads), 2 * device_cus())
+                      : std::min(grid_for(n, kThreads), 4 * device_cus());
 }
 
 // Enqueues one level (BFS depth `level` -> level+1, or SSSP round `level`)
@@ -1971,19 +2043,20 @@ bool arc_balanced(const gc_graph_s* g, const Frontier& f) {
 hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t level, Mode mode, gc_tocab t,
                      hipStream_t s) {
   const int32_t n = g->n;
+  const Tally tally = f.tally();
+  if (mode != Mode::kPush) GC_HIP_TRY(f.need_bits(bfs ? value : nullptr, level));
   if (bfs) {
-    if (mode == Mode::kPush && arc_balanced(g, f)) {
+    if (mode == Mode::kPush) {
       ProfScope prof("bfs_push", s);
-      GC_HIP_TRY(push_arcs(g, f, BfsRelax{value, level, f.next(), g->visited}, s));
-    } else if (mode == Mode::kPush) {
-      ProfScope prof("bfs_push", s);
-      k_bfs_push<<<grid_for(f.n_f, kThreads), kThreads, 0, s>>>(f.queue(), f.n_f, g->rowptr, g->colidx, value,
-                                                                 level, f.next(), g->visited, f.queue_next(),
-                                                                 g->stats);
+      GC_HIP_TRY(push_level(g, f, BfsRelax{value, level}, s));
     } else if (mode == Mode::kPull) {
       ProfScope prof("bfs_pull", s);
-      k_bfs_pull<<<grid_for(n, kThreads), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, n, f.front(), value, level,
-                                                             f.next(), g->visited, f.queue_next(), g->stats);
+      if (wide_pull(n))
+        k_bfs_pull<kPullThreads><<<pull_grid(n), kPullThreads, 0, s>>>(g->t_rowptr, g->t_colidx, n, f.front(), value,
+                                                                       level, f.next(), g->visited, tally);
+      else
+        k_bfs_pull<kThreads><<<pull_grid(n), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, n, f.front(), value, level,
+                                                               f.next(), g->visited, tally);
     } else if (t->col16) {
       // stream layout: the block's frontier bits (as 0 / INT32_MAX) in LDS,
       // per-(row, block) minima stored range-major (0: an in-neighbour of
@@ -2001,33 +2074,32 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
       GC_HIP_TRY((launch_by_k<BfsMergeStream>(t->k, t->R, s, static_cast<const int32_t*>(t->rstart),
                                               static_cast<const uint16_t*>(t->id16s),
                                               static_cast<const int32_t*>(t->pmin), t->R, n, value, f.next(),
-                                              f.queue_next(), g->stats, level, g->visited)));
+                                              tally, level, g->visited)));
     } else {
       uint8_t* flag = reinterpret_cast<uint8_t*>(t->pmin);
       {
         ProfScope prof("bfs_tocab", s);
         k_bfs_tocab<<<row_grid(t->P), kThreads, 0, s>>>(t->row_ptr, t->col, t->id_map, t->P, g->visited,
-                                                                   f.front(), flag);
+                                                                   f.front(), flag, g->stats);
       }
       ProfScope prof("bfs_merge", s);
       GC_HIP_TRY((launch_by_k<BfsMerge>(t->k, t->R, s, static_cast<const int32_t*>(t->range_ptr), t->B,
                                         static_cast<const uint16_t*>(t->id16),
                                         static_cast<const uint8_t*>(flag), n, value, level, f.next(), g->visited,
-                                        f.queue_next(), g->stats)));
+                                        tally)));
     }
   } else {
-    if (mode == Mode::kPush && arc_balanced(g, f)) {
+    if (mode == Mode::kPush) {
       ProfScope prof("sssp_push", s);
-      GC_HIP_TRY(push_arcs(g, f, SsspRelax{g->w, value, level, g->mark, f.next(), g->stats}, s));
-    } else if (mode == Mode::kPush) {
-      ProfScope prof("sssp_push", s);
-      k_sssp_push<<<grid_for(f.n_f, kThreads), kThreads, 0, s>>>(f.queue(), f.n_f, g->rowptr, g->colidx, g->w,
-                                                                  value, level, g->mark, f.next(), f.queue_next(),
-                                                                  g->stats);
+      GC_HIP_TRY(push_level(g, f, SsspRelax{g->w, value, level, g->mark}, s));
     } else if (mode == Mode::kPull) {
       ProfScope prof("sssp_pull", s);
-      k_sssp_pull<<<grid_for(n, kThreads), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, g->t_w, n, f.front(), value,
-                                                              f.next(), f.queue_next(), g->stats);
+      if (wide_pull(n))
+        k_sssp_pull<kPullThreads><<<pull_grid(n), kPullThreads, 0, s>>>(g->t_rowptr, g->t_colidx, g->t_w, n, f.front(),
+                                                                        value, f.next(), tally);
+      else
+        k_sssp_pull<kThreads><<<pull_grid(n), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, g->t_w, n, f.front(), value,
+                                                                f.next(), tally);
     } else {
       if (t->col16) {  // stream layout: the block's distances in LDS, partial minima range-major
         GC_HIP_TRY(stream_weights(t, s));
@@ -2047,7 +2119,7 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
         GC_HIP_TRY((launch_by_k<SsspMergeStream>(t->k, t->R, s, static_cast<const int32_t*>(t->rstart),
                                                  static_cast<const uint16_t*>(t->id16s),
                                                  static_cast<const int32_t*>(t->pmin), t->R, n, value, f.next(),
-                                                 f.queue_next(), g->stats, level, g->visited)));
+                                                 tally, level, g->visited)));
         return hipGetLastError();
       } else {
         ProfScope prof("sssp_tocab", s);
@@ -2057,8 +2129,7 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
       ProfScope prof("sssp_merge", s);
       GC_HIP_TRY((launch_by_k<SsspMerge>(t->k, t->R, s, static_cast<const int32_t*>(t->range_ptr), t->B,
                                          static_cast<const uint16_t*>(t->id16),
-                                         static_cast<const int32_t*>(t->pmin), n, value, f.next(), f.queue_next(),
-                                         g->stats)));
+                                         static_cast<const int32_t*>(t->pmin), n, value, f.next(), tally)));
     }
   }
   return hipGetLastError();
@@ -2066,25 +2137,6 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
 
 double now_ms() {
   return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
-}
-
-int64_t source_degree(gc_graph g, int32_t source, hipStream_t s, hipError_t* e) {
-  int32_t rp[3] = {0, 0, 0};
-  *e = hipMemcpyAsync(rp, g->rowptr + source, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s);
-  if (*e == hipSuccess && g->max_out_deg < 0) {
-    // once per graph: its largest out-degree (arc_balanced), through the
-    // first word of the push's degree scratch
-    k_fill_i32<<<1, kThreads, 0, s>>>(g->arc_deg, 1, 0);
-    k_max_out_degree<<<std::min<int64_t>(grid_for(g->n, kThreads), 1024), kThreads, 0, s>>>(g->rowptr, g->n,
-                                                                                           g->arc_deg);
-    *e = hipGetLastError();
-    if (*e == hipSuccess) *e = hipMemcpyAsync(rp + 2, g->arc_deg, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (*e == hipSuccess) *e = hipStreamSynchronize(s);
-    if (*e == hipSuccess) g->max_out_deg = rp[2];
-    return rp[1] - rp[0];
-  }
-  if (*e == hipSuccess) *e = hipStreamSynchronize(s);
-  return rp[1] - rp[0];
 }
 
 // Two HIP events released on scope exit.
@@ -2118,19 +2170,19 @@ int32_t mode_action(Mode m) { return m == Mode::kPush ? 0 : (m == Mode::kPull ? 
 // frontier, in the given mode.
 hipError_t run_bc_level(gc_graph g, Frontier& f, int32_t level, Mode mode, gc_tocab t, hipStream_t s) {
   const int32_t n = g->n;
-  if (mode == Mode::kPush && arc_balanced(g, f)) {
+  const Tally tally = f.tally();
+  if (mode != Mode::kPush) GC_HIP_TRY(f.need_bits(g->bc_depth, level));
+  if (mode == Mode::kPush) {
     ProfScope prof("bc_push", s);
-    GC_HIP_TRY(push_arcs(g, f, BcRelax{g->bc_depth, level, g->bc_sigma, f.next(), g->visited}, s));
-  } else if (mode == Mode::kPush) {
-    ProfScope prof("bc_push", s);
-    k_bc_push<<<grid_for(f.n_f, kThreads), kThreads, 0, s>>>(f.queue(), f.n_f, g->rowptr, g->colidx, g->bc_depth,
-                                                              level, g->bc_sigma, f.next(), g->visited,
-                                                              f.queue_next(), g->stats);
+    GC_HIP_TRY(push_level(g, f, BcRelax{g->bc_depth, level, g->bc_sigma}, s));
   } else if (mode == Mode::kPull) {
     ProfScope prof("bc_pull", s);
-    k_bc_pull<<<grid_for(n, kThreads), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, n, f.front(), g->bc_depth, level,
-                                                          g->bc_sigma, f.next(), g->visited, f.queue_next(),
-                                                          g->stats);
+    if (wide_pull(n))
+      k_bc_pull<kPullThreads><<<pull_grid(n), kPullThreads, 0, s>>>(g->t_rowptr, g->t_colidx, n, f.front(), g->bc_depth,
+                                                                    level, g->bc_sigma, f.next(), g->visited, tally);
+    else
+      k_bc_pull<kThreads><<<pull_grid(n), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, n, f.front(), g->bc_depth, level,
+                                                            g->bc_sigma, f.next(), g->visited, tally);
   } else {
     {
       ProfScope prof("bc_tocab", s);
@@ -2140,8 +2192,7 @@ hipError_t run_bc_level(gc_graph g, Frontier& f, int32_t level, Mode mode, gc_to
     ProfScope prof("bc_merge", s);
     GC_HIP_TRY((launch_by_k<BcMerge>(t->k, t->R, s, static_cast<const int32_t*>(t->range_ptr), t->B,
                                      static_cast<const uint16_t*>(t->id16), static_cast<const double*>(t->bc_part),
-                                     n, g->bc_depth, level, g->bc_sigma, f.next(), g->visited, f.queue_next(),
-                                     g->stats)));
+                                     n, g->bc_depth, level, g->bc_sigma, f.next(), g->visited, tally)));
   }
   return hipGetLastError();
 }
@@ -2158,11 +2209,8 @@ void sched_features(int64_t n, int64_t m, int64_t n_f, int64_t m_f, int32_t leve
 hipError_t traverse(gc_graph g, gc_tocab t, int32_t source, int32_t* value, int32_t* count, uint32_t policy,
                     hipStream_t s, bool bfs, bool* overflow) {
   const int32_t n = g->n;
-  GC_HIP_TRY(init_state(g, value, source, bfs, s));
-  Frontier f{g, s};
-  hipError_t e;
-  f.m_f = source_degree(g, source, s, &e);
-  GC_HIP_TRY(e);
+  Frontier f(g, s);
+  GC_HIP_TRY(f.start(source, value, bfs ? nullptr : g->mark, nullptr, nullptr));
   int64_t m_u = g->m - f.m_f;
   int64_t m_u_in = g->m;  // in-arcs of the unvisited vertices (the source's own few left in)
   Heuristic h;
@@ -2248,7 +2296,6 @@ hipError_t traverse(gc_graph g, gc_tocab t, int32_t source, int32_t* value, int3
       action = mode_action(mode);
     }
     const double t0 = now_ms();
-    GC_HIP_TRY(f.begin_level());
     GC_HIP_TRY(run_level(g, f, bfs, value, level, mode, lt, s));
     LevelDecide dec;
     if (learned) {
@@ -2258,7 +2305,7 @@ hipError_t traverse(gc_graph g, gc_tocab t, int32_t source, int32_t* value, int3
       dec.alpha = Heuristic::kAlpha;
       dec.beta = Heuristic::kBeta;
     }
-    GC_HIP_TRY(f.end_level(overflow, learned ? net : nullptr, level + 1, dec));
+    GC_HIP_TRY(f.end_level(mode != Mode::kPush, overflow, learned ? net : nullptr, level + 1, dec));
     const double wall_ms = now_ms() - t0;
     g->trace_action.push_back(action);
     g->trace_ms.push_back(static_cast<float>(wall_ms));
@@ -2269,6 +2316,7 @@ hipError_t traverse(gc_graph g, gc_tocab t, int32_t source, int32_t* value, int3
     }
     ++level;
   }
+  f.finish();
   if (count) *count = level;
   return hipSuccess;
 }
@@ -2309,25 +2357,23 @@ hipError_t bc_run(gc_graph g, gc_tocab t, const int32_t* sources, int32_t n_src,
     t->bc_part = static_cast<double*>(dev_alloc(sizeof(double) * std::max<int64_t>(t->P, 1), s));
     if (!t->bc_part) return hipErrorOutOfMemory;
   }
+  Buf pre_in(sizeof(int32_t) * (static_cast<size_t>(n) + 1), s);
+  if (!pre_in.p) return hipErrorOutOfMemory;
   g->trace_action.clear();
   g->trace_ms.clear();
   for (int32_t si = 0; si < n_src; ++si) {
     const int32_t src = sources[si];
-    GC_HIP_TRY(init_state(g, g->bc_depth, src, true, s));
-    k_fill_f64<<<grid_for(n, kThreads), kThreads, 0, s>>>(g->bc_sigma, n);
-    k_fill_f64<<<grid_for(2 * static_cast<int64_t>(n), kThreads), kThreads, 0, s>>>(g->bc_coef,
-                                                                                   2 * static_cast<int64_t>(n));
-    k_set_sigma<<<1, 1, 0, s>>>(src, g->bc_sigma);
-    GC_HIP_TRY(hipGetLastError());
     // order holds the vertices level by level (the source first); level d
-    // occupies [lv_off[d], lv_off[d + 1])
+    // occupies [lv_off[d], lv_off[d + 1]), and arc_pre each level's own arc
+    // prefix: both are the forward levels' queues
     std::vector<int32_t> lv_off{0, 1};
-    std::vector<int64_t> lv_arcs;  // out-arcs of each level's vertices
-    GC_HIP_TRY(hipMemcpyAsync(g->bc_order, g->queue[0], sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    Frontier f{g, s};
-    hipError_t e;
-    f.m_f = source_degree(g, src, s, &e);
-    GC_HIP_TRY(e);
+    std::vector<int64_t> lv_arcs;     // out-arcs of each level's vertices
+    std::vector<int64_t> lv_in{0};    // in-arcs (the source's are not needed)
+    Frontier f(g, s);
+    f.count_in = true;
+    f.q[0] = g->bc_order;
+    f.p[0] = g->arc_pre;
+    GC_HIP_TRY(f.start(src, g->bc_depth, nullptr, g->bc_sigma, g->bc_coef));
     int64_t m_u = g->m - f.m_f;
     lv_arcs.push_back(f.m_f);
     Heuristic h;
@@ -2338,47 +2384,42 @@ hipError_t bc_run(gc_graph g, gc_tocab t, const int32_t* sources, int32_t n_src,
       else if (policy == GC_POLICY_PULL) mode = t ? Mode::kTocab : Mode::kPull;
       else mode = h.pick(n, f.n_f, f.m_f, m_u, t != nullptr, true);
       const double t0 = now_ms();
-      GC_HIP_TRY(f.begin_level());
+      f.q[f.cur ^ 1] = g->bc_order + lv_off.back();
+      f.p[f.cur ^ 1] = g->arc_pre + lv_off.back();
       GC_HIP_TRY(run_bc_level(g, f, level, mode, t, s));
-      GC_HIP_TRY(f.end_level(nullptr));
+      GC_HIP_TRY(f.end_level(mode != Mode::kPush, nullptr));
       g->trace_action.push_back(mode_action(mode));
       g->trace_ms.push_back(static_cast<float>(now_ms() - t0));
       if (f.n_f > 0) {
-        GC_HIP_TRY(hipMemcpyAsync(g->bc_order + lv_off.back(), f.queue(), sizeof(int32_t) * f.n_f,
-                                  hipMemcpyDeviceToDevice, s));
+        GC_HIP_TRY(f.need_queue());  // the level order is its queues
         lv_off.push_back(lv_off.back() + f.n_f);
         lv_arcs.push_back(f.m_f);
+        lv_in.push_back(f.m_f_in);
       }
       m_u -= f.m_f;
       ++level;
     }
+    f.finish();
     // depths run 0 .. level-1 (level = lv_off.size() - 1). Each step d runs
     // in the direction with fewer arcs: pull over the out-arcs of depth d
-    // (arc_pre = exclusive scan of out-degrees along order) or push over
-    // the in-arcs of depth d + 1 (pre_in, the same for in-degrees). The
-    // deepest level's step only sets coef = 1 / sigma; the source (depth 0)
-    // takes no share.
+    // (arc_pre) or push over the in-arcs of depth d + 1 (pre_in = exclusive
+    // scan of the in-degrees along order). The deepest level's step only sets
+    // coef = 1 / sigma; the source (depth 0) takes no share.
     ProfScope prof("bc_back", s);
     const int32_t reached = lv_off.back();
-    Buf pre_in(sizeof(int32_t) * (static_cast<size_t>(reached) + 1), s);
-    if (!pre_in.p) return hipErrorOutOfMemory;
-    k_order_degree<<<grid_for(reached, kThreads), kThreads, 0, s>>>(g->bc_order, reached, g->rowptr, g->arc_deg);
-    GC_HIP_TRY(hipGetLastError());
-    GC_HIP_TRY(scan_exclusive(g->arc_deg, g->arc_pre, reached, s));
-    k_order_degree<<<grid_for(reached, kThreads), kThreads, 0, s>>>(g->bc_order, reached, g->t_rowptr, g->arc_deg);
-    GC_HIP_TRY(hipGetLastError());
-    GC_HIP_TRY(scan_exclusive(g->arc_deg, pre_in.as<int32_t>(), reached, s));
-    std::vector<int32_t> in_at(lv_off.size());  // in-arcs before each level's first vertex
-    for (size_t k = 0; k < lv_off.size(); ++k)
-      GC_HIP_TRY(hipMemcpyAsync(&in_at[k], pre_in.as<int32_t>() + lv_off[k], sizeof(int32_t),
-                                hipMemcpyDeviceToHost, s));
-    GC_HIP_TRY(hipStreamSynchronize(s));
+    bool push_any = false;
+    for (int32_t d = 1; d + 1 < level; ++d) push_any |= lv_in[d + 1] < lv_arcs[d];
+    if (push_any) {
+      k_order_degree<<<grid_for(reached, kThreads), kThreads, 0, s>>>(g->bc_order, reached, g->t_rowptr, g->arc_deg);
+      GC_HIP_TRY(hipGetLastError());
+      GC_HIP_TRY(scan_exclusive(g->arc_deg, pre_in.as<int32_t>(), reached, s));
+    }
     for (int32_t d = level - 1; d >= 1; --d) {
       const int32_t lo = lv_off[d], hi = lv_off[d + 1];
       double* coef_out = g->bc_coef + static_cast<size_t>(d & 1) * n;
       const double* coef_in = g->bc_coef + static_cast<size_t>((d + 1) & 1) * n;
       const int64_t out_arcs = lv_arcs[d];
-      const int64_t in_next = d + 1 < level ? static_cast<int64_t>(in_at[d + 2]) - in_at[d + 1] : 0;
+      const int64_t in_next = d + 1 < level ? lv_in[d + 1] : 0;
       if (d + 1 < level && in_next < out_arcs) {
         const int64_t pieces = (in_next + kBackArcs - 1) / kBackArcs;
         if (pieces > 0)
@@ -2389,7 +2430,8 @@ hipError_t bc_run(gc_graph g, gc_tocab t, const int32_t* sources, int32_t n_src,
         const int64_t pieces = (out_arcs + kBackArcs - 1) / kBackArcs;
         if (pieces > 0)
           k_bc_back_arcs<<<grid_for(pieces, kThreads), kThreads, 0, s>>>(g->rowptr, g->colidx, g->bc_order,
-                                                                         g->arc_pre, lo, hi, coef_in, coef_out);
+                                                                         g->arc_pre, lo, hi, static_cast<int32_t>(out_arcs),
+                                                                         coef_in, coef_out);
       }
       k_bc_finish<<<grid_for(hi - lo, kThreads), kThreads, 0, s>>>(g->bc_order + lo, hi - lo, g->bc_sigma, coef_out,
                                                                     bc);
@@ -2419,16 +2461,16 @@ hipError_t collect(gc_graph g, gc_tocab* parts, int32_t n_parts, bool bfs, const
   int32_t r = 0;
   hipError_t err = hipSuccess;
   for (int32_t si = 0; si < n_src && err == hipSuccess; ++si) {
-    err = init_state(g, value.as<int32_t>(), sources[si], bfs, s);
-    if (err != hipSuccess) break;
-    Frontier f{g, s};
-    f.m_f = source_degree(g, sources[si], s, &err);
+    Frontier f(g, s);
+    err = f.start(sources[si], value.as<int32_t>(), bfs ? nullptr : g->mark, nullptr, nullptr);
     int32_t level = 0;
     double prior_ms = 0.0;  // device time of the previous level (its fastest action), from the clock stamps
     int64_t prior_arcs = 0;
     bool overflow = false;
     std::vector<double> stamp_ms(static_cast<size_t>(K));
     while (err == hipSuccess && f.n_f > 0 && r < max_rows && !overflow) {
+      err = f.need_queue();
+      if (err != hipSuccess) break;
       sched_features(n, g->m, f.n_f, f.m_f, level, prior_ms, prior_arcs,
                      features + static_cast<size_t>(r) * GC_SCHED_INPUTS);
       // snapshot the state this level starts from
@@ -2456,12 +2498,12 @@ hipError_t collect(gc_graph g, gc_tocab* parts, int32_t n_parts, bool bfs, const
         gc_tocab lt;
         action_mode(a, parts, &mode, &lt);
         if (a > 0) err = restore();
-        if (err == hipSuccess) err = f.begin_level();
         if (err == hipSuccess) err = hipEventRecord(e0, s);
         if (err == hipSuccess) err = run_level(g, f, bfs, value.as<int32_t>(), level, mode, lt, s);
         if (err == hipSuccess) err = hipEventRecord(e1, s);
-        if (err == hipSuccess) err = f.end_level(&overflow);
+        if (err == hipSuccess) err = f.end_level(mode != Mode::kPush, &overflow);
         float ms = 0.0f;
+        if (err == hipSuccess) err = hipEventSynchronize(e1);
         if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
         row_t[a] = ms;
         stamp_ms[a] = f.level_ms();
@@ -2474,15 +2516,15 @@ hipError_t collect(gc_graph g, gc_tocab* parts, int32_t n_parts, bool bfs, const
         gc_tocab lt;
         action_mode(best, parts, &mode, &lt);
         err = restore();
-        if (err == hipSuccess) err = f.begin_level();
         if (err == hipSuccess) err = run_level(g, f, bfs, value.as<int32_t>(), level, mode, lt, s);
-        if (err == hipSuccess) err = f.end_level(&overflow);
+        if (err == hipSuccess) err = f.end_level(mode != Mode::kPush, &overflow);
       }
       prior_ms = stamp_ms[best];
       prior_arcs = start.m_f;
       ++r;
       ++level;
     }
+    if (err == hipSuccess && !overflow) f.finish();
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

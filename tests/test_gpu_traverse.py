@@ -228,3 +228,36 @@ def test_heuristic_bfs_tocab_arm():
             assert (2 in exp) == expect_tocab
         part.free()
         h.free()
+
+
+def _broom(leaves, every):
+    """0 -> 1 .. leaves; every `every`-th leaf has one child (and the others no out-arc)."""
+    kids = np.arange(every, leaves + 1, every)
+    src = np.concatenate([np.zeros(leaves, np.int64), kids])
+    dst = np.concatenate([np.arange(1, leaves + 1), leaves + 1 + np.arange(len(kids))])
+    return gg.from_edges(int(leaves + 1 + len(kids)), src, dst, name=f"broom{leaves}_{every}")
+
+
+# the push's pieces: a hub over one and four arcs per thread, queue windows
+# crossed by runs of vertices without out-arcs, fewer and more arcs than one
+# round of the grid (2^20), vertices found by a tile less than, at and beyond
+# the buffer's room; and, under the heuristic, pull levels after pushes and
+# pushes after pulls
+@pytest.mark.parametrize("make", [lambda: _broom(300, 1), lambda: _broom(9000, 700), lambda: _broom(70000, 3001),
+                                  lambda: gg.uniform(300001, 2000000, seed=6), lambda: graphs.chain(600),
+                                  lambda: gg.rmat(15, 16, seed=8)],
+                         ids=["broom300", "broom9000", "broom70000", "uniform", "chain", "rmat15"])
+@pytest.mark.parametrize("policy", ["push", "heuristic"])
+def test_push_levels_of_every_shape(make, policy):
+    import paper_1904_02241_amd as gc
+    g = make().with_weights(3)
+    print(f"push {g.name} n={g.n} m={g.m} {policy}", flush=True)
+    h = load(g, weights=True)
+    pol = gc.GC_POLICY_PUSH if policy == "push" else gc.GC_POLICY_HEURISTIC
+    d = torch().empty(g.n, dtype=torch().int32, device="cuda")
+    for s in (0, int(gg.sources(g, 1, seed=4)[0])):
+        gc.bfs_pull(h, None, s, d, pol)
+        np.testing.assert_array_equal(host(d), oracle.bfs(g.n, g.rowptr, g.colidx, s))
+        gc.sssp_pull(h, None, s, d, pol)
+        np.testing.assert_array_equal(host(d), oracle.dijkstra(g.n, g.rowptr, g.colidx, g.weights, s))
+    h.free()
