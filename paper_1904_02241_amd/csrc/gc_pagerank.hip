@@ -24,6 +24,7 @@
 #include "gc_internal.h"
 
 #include "gc_pr_device.h"
+#include "gc_stream.h"
 
 namespace {
 
@@ -113,18 +114,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_tocab_pull(const int32_t* __res
 // range-major index, so the merge reads every range as one stream. Loads
 // run two tiles ahead of the tile being reduced (all vector loads, which
 // complete in order, so waiting for one tile leaves the next in flight).
-constexpr int kLdsThreads = 1024;
-constexpr int kLdsWaves = kLdsThreads / kWave;
-constexpr int kArcsPerLane = 8;
-constexpr int kWaveTile = kArcsPerLane * kWave;  // 512 arcs, 8 head words
-constexpr int kStageRows = 384;                  // staged row sums per wave in the first pass
-constexpr int kTileRowsMax = 512;                // rows one tile can complete
-constexpr int kStageSpare = 16;                  // spare slots per wave for elements that end no staged row
-static_assert(kStageRows % kWave == 0 && (kTileRowsMax - kStageRows) % kWave == 0 &&
-              kTileRowsMax - kStageRows <= kStageRows, "staging passes of whole store instructions");
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using namespace gcs;
 
 struct WaveTile {
   u32x4 cols;  // this lane's 8 columns (16 bits each)
@@ -153,118 +143,6 @@ __device__ __forceinline__ WaveTile load_wave_tile(const uint16_t* __restrict__ 
 template <bool kVal>
 __device__ __forceinline__ float arc_value(const WaveTile& t, int e) {
   return kVal ? (e < 4 ? t.va[e] : t.vb[e - 4]) : 1.0f;
-}
-
-__device__ __forceinline__ uint64_t word_bits(const u32x4& w) {
-  return static_cast<uint64_t>(w[0]) | (static_cast<uint64_t>(w[1]) << 32);
-}
-
-// Merge-range index of local row r, searching forward from j: sb[j] is the
-// first row of the chunk's j-th merge range (ascending; sb[ns] lies past
-// the chunk and sb[ns+1..ns+3] hold INT32_MAX), four entries per step.
-__device__ __forceinline__ int32_t seek_range(const int32_t* sb, int32_t j, int32_t r) {
-  for (;;) {
-    const int32_t adv = (sb[j + 1] <= r) + (sb[j + 2] <= r) + (sb[j + 3] <= r) + (sb[j + 4] <= r);
-    j += adv;
-    if (adv < 4) return j;
-  }
-}
-constexpr int kSegPad = 4;  // LDS entries past the position table read by seek_range and the cursor
-
-// Buffer resource over the partial sums: a store whose offset lies past the
-// resource's size is dropped by the hardware, which lets every lane issue
-// the same number of stores per tile (no branch around a store, so the
-// compiler can count outstanding memory operations and keep the prefetched
-// tiles in flight while the stores drain).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t partial_rsrc(float* partial, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(partial, 0, static_cast<int>(bytes), 0x00020000);
-}
-
-__device__ __forceinline__ void partial_store(__amdgpu_buffer_rsrc_t out, uint32_t off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, off, 0, 0);
-}
-
-constexpr int kStoresPerTile = 6;  // stores of the first staging pass, issued by every tile
-
-// kStoresPerTile stores the hardware drops (offsets past any resource size
-// below 2^31, distinct so that none is a dead store of another).
-__device__ __forceinline__ void drop_stores(__amdgpu_buffer_rsrc_t out) {
-#pragma unroll
-  for (int i = 0; i < kStoresPerTile; ++i) __builtin_amdgcn_raw_buffer_store_b32(0u, out, 0x80000000u + 4u * i, 0, 0);
-}
-
-// Lanes of the wave selected by a mask held in scalar registers.
-__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-
-
-// Value a DPP control moves into each lane (lanes with no source get 0).
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ float dpp_moved(float a) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), kCtrl, kRowMask, 0xF, false));
-}
-
-// One step of a wave-wide segmented inclusive scan: a lane that has met no
-// head yet within the reach of the steps so far (not in F) adds the value
-// the DPP control moves in. F itself is kept as a lane mask in scalar
-// registers and widened by the caller after each step.
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ void seg_scan_step(float& A, uint64_t F) {
-  const float s = A + dpp_moved<kCtrl, kRowMask>(A);
-  A = lane_in(F) ? A : s;
-}
-
-// DPP controls (gfx9): shift right by n lanes inside each row of 16, copy
-// lane 15 / 31 into the following row(s), shift right by one lane across
-// the whole wave.
-constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
-constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143, kDppWaveShr1 = 0x138;
-
-// What a wave carries from one tile of its range to the next: the running
-// sum of the row still open at the tile's end (when that row is one the wave
-// must write), a window of 64 entries of the chunk's position table held one
-// per lane, and a cursor into it with the next boundaries and shifts in
-// scalar registers.
-struct PullCarry {
-  double open = 0.0;
-  int32_t open_row = -1;           // >= 0 when the wave owes that row's sum
-  int32_t jw = 0;                  // first table entry of the window
-  int32_t sbw, sdw;                // lane l: sb[jw + l], sd[jw + l] (past the table: its last spare)
-  int32_t jc = 0;                  // sb[jc] <= every row the wave still writes; jc - jw <= 60
-  int32_t b1, b2, b3, d0, d1, d2;  // sb[jc+1..jc+3], sd[jc..jc+2]
-};
-
-__device__ __forceinline__ void load_window(const int32_t* sb, const int32_t* sd, int32_t ns, int lane,
-                                            PullCarry& c) {
-  const int32_t i = min(c.jw + lane, ns + kSegPad - 1);
-  c.sbw = sb[i];
-  c.sdw = sd[i];
-}
-
-__device__ __forceinline__ void cursor_from_window(PullCarry& c) {
-  const int32_t o = c.jc - c.jw;
-  c.b1 = __builtin_amdgcn_readlane(c.sbw, o + 1);
-  c.b2 = __builtin_amdgcn_readlane(c.sbw, o + 2);
-  c.b3 = __builtin_amdgcn_readlane(c.sbw, o + 3);
-  c.d0 = __builtin_amdgcn_readlane(c.sdw, o);
-  c.d1 = __builtin_amdgcn_readlane(c.sdw, o + 1);
-  c.d2 = __builtin_amdgcn_readlane(c.sdw, o + 2);
-}
-
-// Moves the cursor to the range holding row r (r >= sb[jc]): the count of
-// window entries at or below r, restarting the window when the cursor and
-// the three boundaries after it would not fit in it.
-__device__ __forceinline__ void seek_cursor(const int32_t* sb, const int32_t* sd, int32_t ns, int lane, int32_t r,
-                                            PullCarry& c) {
-  for (;;) {
-    const int32_t cnt = __popcll(__ballot(c.sbw <= r));  // >= 1: sb[jw] <= r
-    if (cnt <= kWave - 3) {
-      c.jc = c.jw + cnt - 1;
-      break;
-    }
-    c.jw += cnt - 1;  // advances by at least 61; entries past the table are INT32_MAX, so this ends
-    load_window(sb, sd, ns, lane, c);
-  }
-  cursor_from_window(c);
 }
 
 // Sum over the tiles after tile q of the row open at q's end, up to its end
@@ -314,181 +192,6 @@ __device__ __forceinline__ void gather_tile(const WaveTile& t, float (&x)[kArcsP
     x[e] = *reinterpret_cast<lds_float*>(static_cast<uintptr_t>(col << 2));
     if (kVal) x[e] *= arc_value<kVal>(t, e);
   }
-}
-
-constexpr uint32_t kPushOut = 1u << 23;  // moves the staging slot of an arc that ends no row past every pass
-
-// Byte offsets (past the store's base) of the stores k < nk of a staging
-// pass: store k holds rows rs + i, i = lo + 64k + lane, written to index
-// i + D0 / D1 / D2 below / from / past the range boundaries i1 and i2
-// (kTwo: i2 lies among the rows written), dropped from iz on. The lane is
-// compared with scalar thresholds; the store's base offset 4(lo + 64k)
-// travels in the scalar offset operand, which the hardware leaves out of
-// its range check, so a dropped lane's offset alone is past the resource.
-template <bool kTwo>
-__device__ __forceinline__ void row_offsets(uint32_t (&off)[kStageRows / kWave], int nk, int lane, int32_t lo,
-                                            int32_t i1, int32_t i2, int32_t iz, int32_t D0, int32_t D1, int32_t D2) {
-  constexpr int32_t kDropIndex = 1 << 29;  // (lane + kDropIndex) * 4 >= 2^31
-#pragma unroll
-  for (int k = 0; k < kStageRows / kWave; ++k) {
-    if (k < nk) {
-      const int32_t base = lo + k * kWave;
-      const bool p1 = lane >= i1 - base, pz = lane >= iz - base;
-      int32_t d = p1 ? D1 : D0;
-      if (kTwo) d = lane >= i2 - base ? D2 : d;
-      d = pz ? kDropIndex : d;
-      off[k] = static_cast<uint32_t>(lane + d) << 2;
-    }
-  }
-}
-
-__device__ __forceinline__ void reduce_wave_tile(const WaveTile& t, const float (&x)[kArcsPerLane], int lane,
-                                                 const int32_t* sb, const int32_t* sd, int32_t ns, int32_t r0,
-                                                 int32_t r1, PullCarry& cr, __amdgpu_buffer_rsrc_t out,
-                                                 float* stage) {
-  const uint32_t wlo = t.hw[0], whi = t.hw[1];
-  const int32_t wrow = static_cast<int32_t>(t.hw[2]);
-  const int32_t ta = __builtin_amdgcn_readfirstlane(wrow);
-  const int32_t tz = __builtin_amdgcn_readlane(wrow + __popc(wlo) + __popc(whi), kWave - 1);
-  const uint32_t next_head = __builtin_amdgcn_readlane(static_cast<int32_t>(t.hw[3]), kWave - 1) & 1u;
-  // rows the wave writes from this tile: those whose head is here and that
-  // belong to the chunk, and the row left open by the previous tile
-  const int32_t rz = min(tz, r1);
-  const int32_t rmin = cr.open_row >= 0 ? cr.open_row : max(ta, r0);
-  if (rmin < rz && rmin >= cr.b1) seek_cursor(sb, sd, ns, lane, rmin, cr);
-  // this lane's 8 head bits and the head bit of the arc after them (bit 8)
-  const int sub = lane & 7;
-  const uint32_t wa = sub < 4 ? wlo : whi, wb = sub < 4 ? whi : t.hw[3];
-  const uint32_t my9 = __builtin_amdgcn_alignbit(wb, wa, 8 * (sub & 3)) & 0x1FFu;
-  const uint32_t my8 = my9 & 0xFFu;
-  const int32_t first = wrow + (sub < 4 ? 0 : __popc(wlo)) + __popc(wa & ((1u << (8 * (sub & 3))) - 1u));
-  // none[e]: all ones when arc e ends no row (the arc after it is no head)
-  uint32_t none[kArcsPerLane];
-#pragma unroll
-  for (int e = 0; e < kArcsPerLane; ++e)
-    none[e] = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int32_t>(~my9), e + 1, 1));
-  // The lane's open sum in FP32: a run over its 8 arcs from the row's start
-  // (or the lane's first arc) that carries over arc e - 1 (its bits masked
-  // to +0.0 otherwise) when that arc ends no row.
-  float run = x[0];
-#pragma unroll
-  for (int e = 1; e < kArcsPerLane; ++e) run = x[e] + __uint_as_float(__float_as_uint(run) & none[e - 1]);
-  // Segmented inclusive scan of the lanes' open sums across the wave (FP32;
-  // the flag of a lane is whether it holds a head). The flags live in a
-  // scalar lane mask, widened after each step the way the DPP moves data.
-  const uint64_t H = __ballot(my8 != 0u);
-  float A = run;
-  uint64_t F = H;
-  seg_scan_step<kDppRowShr1, 0xF>(A, F);
-  F |= (F << 1) & 0xFFFEFFFEFFFEFFFEull;
-  seg_scan_step<kDppRowShr2, 0xF>(A, F);
-  F |= (F << 2) & 0xFFFCFFFCFFFCFFFCull;
-  seg_scan_step<kDppRowShr4, 0xF>(A, F);
-  F |= (F << 4) & 0xFFF0FFF0FFF0FFF0ull;
-  seg_scan_step<kDppRowShr8, 0xF>(A, F);
-  F |= (F << 8) & 0xFF00FF00FF00FF00ull;
-  seg_scan_step<kDppRowBcast15, 0xA>(A, F);
-  F |= ((F & (1ull << 15)) ? 0x00000000FFFF0000ull : 0ull) | ((F & (1ull << 47)) ? 0xFFFF000000000000ull : 0ull);
-  seg_scan_step<kDppRowBcast31, 0xC>(A, F);
-  // lane l: the open sum at the end of lane l - 1, plus (in FP64) the sum
-  // carried from earlier tiles when no lane before l holds a head
-  const float c = dpp_moved<kDppWaveShr1, 0xF>(A);
-  const uint64_t past_head = H ? ((~0ull << __builtin_ctzll(H)) << 1) : 0ull;
-  const float with_open = static_cast<float>(static_cast<double>(c) + cr.open);
-  const float carry = lane_in(past_head) ? c : with_open;
-  // The rows this tile completes form one run [rs, re): the open row (if
-  // the wave owes it) and every row of the chunk with its head here, except
-  // the last one when it continues into the next tile. Their sums are
-  // staged in LDS by row and written back so that store k of the wave holds
-  // rows rs + 64k .. rs + 64k + 63 (coalesced); the position table turns a
-  // row into its range-major index. Every lane issues the same stores
-  // (unused ones get a dropped offset), so the compiler's count of
-  // outstanding memory operations stays exact.
-  const int32_t rs = rmin;
-  const int32_t re = min(rz, next_head ? tz : tz - 1);
-  // Staging slot of each arc: its row's offset from rs (as unsigned: rows
-  // before rs wrap to huge values) when the arc ends its row, pushed out by
-  // kPushOut otherwise. Every arc writes its run to the staging; those with
-  // no row of the pass go to one of the wave's spare slots.
-  uint32_t slot[kArcsPerLane];
-  {
-    uint32_t r = static_cast<uint32_t>(first - 1 - rs) + (my9 & 1u);  // offset of arc 0's row
-#pragma unroll
-    for (int e = 0; e < kArcsPerLane; ++e) {
-      slot[e] = (none[e] & kPushOut) | r;  // r < 512, or wrapped past 2^31: the OR acts as an add
-      r += 1u + none[e];
-    }
-  }
-  // The staged runs: the same masked run again, now starting from the
-  // carried sum unless arc 0 is a head (it reaches exactly the arcs before
-  // the lane's first head, i.e. the end of the row carried into the lane;
-  // an LDS atomic add of the carry to that row's slot costs more than these
-  // instructions).
-  float st[kArcsPerLane];
-  {
-    const uint32_t cont0 = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int32_t>(~my9), 0, 1));
-    float r = x[0] + __uint_as_float(__float_as_uint(carry) & cont0);
-    st[0] = r;
-#pragma unroll
-    for (int e = 1; e < kArcsPerLane; ++e) {
-      r = x[e] + __uint_as_float(__float_as_uint(r) & none[e - 1]);
-      st[e] = r;
-    }
-  }
-  // rows at or past the cached boundary b3 (three or more ranges in one tile)
-  // are stored on the slow path below; the others index with the cursor
-  const int32_t i1 = cr.b1 - rs, i2 = cr.b2 - rs, iz = min(re, cr.b3) - rs;
-  const int32_t D0 = rs + cr.d0, D1 = rs + cr.d1, D2 = rs + cr.d2;  // row rs + i goes to index i + D
-  const uint32_t spare = kStageRows + (lane & (kStageSpare - 1));
-  // Staging passes: rows [0, 384) of the run in every tile (6 stores),
-  // rows [384, 512) only in tiles that complete more rows (a tile completes
-  // at most 512). Every tile thus issues at least kStoresPerTile stores, the
-  // count the compiler's memory waits assume.
-  auto stage_pass = [&](auto pass_tag) {
-    constexpr int pass = decltype(pass_tag)::value;
-    constexpr uint32_t lo = pass == 0 ? 0u : static_cast<uint32_t>(kStageRows);
-    constexpr int n = pass == 0 ? kStageRows : kTileRowsMax - kStageRows;  // rows of this pass
-    // slots of the pass run [0, n); anything at or past n lands in
-    // [n, n + 16), which this pass does not read back
-    const uint32_t cap = spare - static_cast<uint32_t>(kStageRows - n);
-#pragma unroll
-    for (int e = 0; e < kArcsPerLane; ++e) stage[min(slot[e] - lo, cap)] = st[e];
-    wave_lds_fence();
-    float v[n / kWave];
-#pragma unroll
-    for (int k = 0; k < n / kWave; ++k) v[k] = stage[k * kWave + lane];
-    // the offsets take one of two branches; the stores follow unconditionally
-    // (stores inside the branches would leave the compiler unable to count
-    // them on every path)
-    uint32_t off[kStageRows / kWave];
-    if (i2 < iz) row_offsets<true>(off, n / kWave, lane, static_cast<int32_t>(lo), i1, i2, iz, D0, D1, D2);
-    else row_offsets<false>(off, n / kWave, lane, static_cast<int32_t>(lo), i1, i2, iz, D0, D1, D2);
-#pragma unroll
-    for (int k = 0; k < n / kWave; ++k)
-      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[k]), out, off[k], 4 * (static_cast<int32_t>(lo) + k * kWave), 0);
-    wave_lds_fence();  // the staging is rewritten next
-  };
-  stage_pass(std::integral_constant<int, 0>());
-  if (re - rs > kStageRows) stage_pass(std::integral_constant<int, 1>());  // uniform
-  if (re > cr.b3) {  // uniform, rare: store the rows at or past b3
-#pragma unroll
-    for (int e = 0; e < kArcsPerLane; ++e) {
-      const int32_t r = rs + static_cast<int32_t>(slot[e]);
-      if (slot[e] < static_cast<uint32_t>(re - rs) && r >= cr.b3) {
-        const int32_t j = seek_range(sb, cr.jc, r);
-        partial_store(out, 4u * static_cast<uint32_t>(r + sd[j]), st[e]);
-      }
-    }
-  }
-  // the row open at the tile's end, if the wave writes it (lane 63 holds its
-  // open sum; the earlier tiles' part joins in FP64)
-  const float run63 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(run), kWave - 1));
-  const float c63 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), kWave - 1));
-  const double tail = static_cast<double>((H >> 63) ? run63 : run63 + c63) + (H ? 0.0 : cr.open);
-  const int32_t ro = tz - 1;  // the row of the tile's last arc
-  const bool owe = !next_head && (tz > ta ? (ro >= r0 && ro < r1) : cr.open_row >= 0);
-  cr.open_row = owe ? ro : -1;
-  cr.open = owe ? tail : 0.0;
 }
 
 template <bool kVal>
@@ -548,7 +251,7 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
   const int32_t qa = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * wid / kLdsWaves);
   const int32_t qz = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * (wid + 1) / kLdsWaves) - 1;
   if (qa > qz) return;
-  PullCarry cr;
+  PullCarry<SumOp> cr;
   load_window(sb, sd, ns, lane, cr);
   cursor_from_window(cr);
   // Four tiles in registers: while one is reduced, the next one's gathers
@@ -577,7 +280,7 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
   // follow it.
 #define GC_PULL_STEP(cur, xcur, nxt, xnxt, k)                           \
   gather_tile<kVal>(nxt, xnxt);                                         \
-  reduce_wave_tile(cur, xcur, lane, sb, sd, ns, r0, r1, cr, out, stage); \
+  reduce_wave_tile<SumOp>(cur.hw, xcur, lane, sb, sd, ns, r0, r1, cr, out, stage); \
   hold_live<kVal>(cur, xcur);                                           \
   cur = load_wave_tile<kVal>(col16, heads, vals, min(q + (k + 4), qz), lane);
   const int32_t nw = qz - qa + 1;
@@ -591,13 +294,13 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
   const int32_t rest = nw % 4;
   if (rest > 0) {
     gather_tile<kVal>(t1, x1);
-    reduce_wave_tile(t0, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
+    reduce_wave_tile<SumOp>(t0.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
   }
   if (rest > 1) {
     gather_tile<kVal>(t2, x0);
-    reduce_wave_tile(t1, x1, lane, sb, sd, ns, r0, r1, cr, out, stage);
+    reduce_wave_tile<SumOp>(t1.hw, x1, lane, sb, sd, ns, r0, r1, cr, out, stage);
   }
-  if (rest > 2) reduce_wave_tile(t2, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
+  if (rest > 2) reduce_wave_tile<SumOp>(t2.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
 #undef GC_PULL_STEP
   if (cr.open_row >= 0) {  // the range's last row continues past it
     const double v = cr.open + finish_open_row<kVal>(col16, heads, vals, slice, qz, lane);

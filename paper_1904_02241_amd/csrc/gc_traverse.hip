@@ -38,6 +38,7 @@
 #include "gc_internal.h"
 #include "gc_mlp.h"
 #include "gc_merge.h"
+#include "gc_stream.h"
 
 namespace {
 
@@ -610,68 +611,36 @@ __global__ __launch_bounds__(kThreads) void k_sssp_tocab(const int32_t* __restri
   }
 }
 
-// TOCAB pull for SSSP over the stream layout (blocks up to 2^15 wide, the
-// layout the PageRank pull reads): the block's slice of the frontier's
-// distances lives in LDS, so the random reads of a round never leave the
-// CU. One work-group per chunk of the partition (rows [r0, r1) of block b);
-// it first stores ad[i] = dist[bW + i] for sources in the frontier and
-// INT32_MAX for the others, then each wave walks a contiguous range of
-// 512-arc tiles: a lane holds 8 consecutive arcs (16-bit columns, their
-// weights, the head bits of its head word), takes their candidates ad[col]
-// + w, and a segmented minimum (lane-local runs, then a wave-wide
-// segmented scan) gives the minimum of every row whose head lies in the
-// wave's range; the row open at a tile's end carries into the next tile,
-// and the one open at the range's end is finished by reading on. pmin[l]
-// (block-major, as the wide-block kernel writes it) is the minimum over
-// local row l's arcs, INT32_MAX when no source of the row is active.
-constexpr int kLdsRowThreads = 1024;
-// Buffer offset of a dropped store: past any partition's minima (whose
-// stream layout keeps 4 (P + 8) below 2^31 bytes).
-constexpr uint32_t kDropOff = 0x80000000u;
-constexpr int kSeekPad = 4;  // position-table entries past the chunk's ns ranges: sb[ns] (past the chunk), sentinels
-constexpr int kLdsRowWaves = kLdsRowThreads / kWave;
-constexpr int kRowTile = 512;  // arcs per wave tile: 8 per lane
-
-typedef uint32_t tu32x4 __attribute__((ext_vector_type(4)));
-typedef int32_t ti32x4 __attribute__((ext_vector_type(4)));
-
-// Value a DPP control moves into each lane; INT32_MAX (the identity of the
-// minimum) where the move has no source lane or the lane's row is masked off.
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ int32_t dpp_in(int32_t a) {
-  return __builtin_amdgcn_update_dpp(kInf, a, kCtrl, kRowMask, 0xF, false);
-}
-
-// Lanes of the wave selected by a mask held in scalar registers.
-__device__ __forceinline__ bool lane_in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-
-// One step of a wave-wide segmented inclusive minimum: a lane outside F
-// (no head met yet within the reach of the steps so far) takes the minimum
-// with the value the DPP control moves in. The move is made by every lane
-// before the select: under a narrower EXEC mask it could not read the
-// values of the lanes in F.
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ void seg_min_step(int32_t& A, uint64_t F) {
-  const int32_t m = min(A, dpp_in<kCtrl, kRowMask>(A));
-  A = lane_in_mask(F) ? A : m;
-}
-
-struct MinTile {
-  int32_t x[8];     // candidates of the lane's 8 arcs
-  uint32_t my9;     // head bits of the lane's arcs, bit 8: the arc after them
-  int32_t row0;     // local row holding the lane's arc 0 when it is no head (row before the first head)
-};
+// TOCAB pull for SSSP and BFS over the stream layout (blocks up to 2^15 wide,
+// the layout the PageRank pull reads): the block's slice of the frontier's
+// distances lives in LDS, so the random reads of a round never leave the CU.
+// Values are kept as INT32_MAX - distance, 0 for a source outside the
+// frontier, so that "none" is 0 and the minimum of a row is a maximum of
+// values whose lack is masked, like PageRank's sums: the same tile reduction
+// does both (BFS: 1 for a source in the frontier). One work-group per chunk
+// of the partition (rows [r0, r1) of block b) fills the slice, then each wave
+// walks a contiguous range of 512-arc tiles: a lane holds 8 consecutive arcs
+// (16-bit columns, their weights, the head bits of its head word) and takes
+// the candidates value[col] - w, saturating at 0. pmin gets every row's
+// result at its range-major index. What bounds it is the instruction path of
+// the tile reduction, not memory. Measured: 16 M weighted arcs of a uniform
+// graph 87 -> 57 us, the 15.6 M arcs of a 4 M-vertex grid's BFS 70 -> 45 us
+// (before: a minimum of its own with a store per arc and a walk over the
+// position table per tile).
+using namespace gcs;
 
 // Weights of a stream-layout partition in its arc order (kW): int32
 // (kW32), one byte each when every weight lies in [0, 255] (kW8), or none:
-// BFS, whose candidates are the sources' own values (0 when in the frontier).
+// BFS, whose candidates are the sources' own values.
 constexpr int kW32 = 0, kW8 = 1, kWNone = 2;
+typedef int32_t ti32x4 __attribute__((ext_vector_type(4)));
+
 // A tile's raw streams for one lane: its 8 columns, its head word and its
 // 8 weights (as loaded), so that the loads of later tiles can be issued
 // before an earlier tile is reduced.
 struct RawTile {
-  tu32x4 cols;
-  tu32x4 hw;
+  u32x4 cols;
+  u32x4 hw;
   ti32x4 wa, wb;  // int32 weights (kW32)
   uint64_t w8;    // byte weights (kW8)
 };
@@ -681,11 +650,9 @@ __device__ __forceinline__ RawTile load_raw_tile(const uint16_t* __restrict__ co
                                                  const gc_head_word* __restrict__ heads,
                                                  const void* __restrict__ w_arcs, int64_t q, int lane) {
   RawTile r;
-  const int64_t tb = q * kRowTile;
-  r.cols = gcd::ld_stream(reinterpret_cast<const tu32x4*>(col16 + tb) + lane);
-  r.w8 = 0;
-  r.wa = ti32x4{0, 0, 0, 0};
-  r.wb = ti32x4{0, 0, 0, 0};
+  const int64_t tb = q * kWaveTile;
+  r.cols = gcd::ld_stream(reinterpret_cast<const u32x4*>(col16 + tb) + lane);
+  r.hw = *reinterpret_cast<const u32x4*>(heads + (tb >> 6) + (lane >> 3));
   if (kW == kW8) {
     r.w8 = gcd::ld_stream(reinterpret_cast<const uint64_t*>(static_cast<const uint8_t*>(w_arcs) + tb) + lane);
   } else if (kW == kW32) {
@@ -693,257 +660,206 @@ __device__ __forceinline__ RawTile load_raw_tile(const uint16_t* __restrict__ co
     r.wa = gcd::ld_stream(reinterpret_cast<const ti32x4*>(w_pad + tb) + 2 * lane);
     r.wb = gcd::ld_stream(reinterpret_cast<const ti32x4*>(w_pad + tb) + 2 * lane + 1);
   }
-  r.hw = *reinterpret_cast<const tu32x4*>(heads + (tb >> 6) + (lane >> 3));
   return r;
 }
 
-// The lane's candidates ad[col] + w and its row structure from a raw tile.
+// Keeps a tile's registers and candidates allocated up to this point.
 template <int kW>
-__device__ __forceinline__ MinTile finish_min_tile(const RawTile& r, const int32_t* ad, int lane, bool* ovf) {
-  MinTile t;
-  const uint64_t bits = static_cast<uint64_t>(r.hw[0]) | (static_cast<uint64_t>(r.hw[1]) << 32);
-  const int sub = lane & 7;
-  const uint32_t after = sub < 7 ? static_cast<uint32_t>(bits >> (8 * sub + 8)) & 1u : r.hw[3] & 1u;
-  t.my9 = (static_cast<uint32_t>(bits >> (8 * sub)) & 0xFFu) | (after << 8);
-  const uint64_t below = sub ? (bits & ((1ull << (8 * sub)) - 1ull)) : 0ull;
-  t.row0 = static_cast<int32_t>(r.hw[2]) + __popcll(below) - 1;
+__device__ __forceinline__ void hold_raw(const RawTile& t, const uint32_t (&x)[kArcsPerLane]) {
+  asm volatile("" ::"v"(t.cols), "v"(t.hw));
+  if (kW == kW8) asm volatile("" ::"v"(t.w8));
+  if (kW == kW32) asm volatile("" ::"v"(t.wa), "v"(t.wb));
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const uint32_t c = (r.cols[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-    const int32_t a = ad[c];
-    if (kW == kWNone) {  // BFS: the source's own value
-      t.x[e] = a;
-      continue;
-    }
-    uint32_t w = 0;
-    if (kW == kW8) w = static_cast<uint32_t>(r.w8 >> (8 * e)) & 0xFFu;
-    else w = static_cast<uint32_t>(e < 4 ? r.wa[e] : r.wb[e - 4]);
-    // a <= INT32_MAX and 0 <= w <= INT32_MAX, so the sum fits in 32 unsigned bits
-    const uint32_t cand = static_cast<uint32_t>(a) + w;
-    const bool sat = cand >= static_cast<uint32_t>(kInf);
-    *ovf |= a != kInf && sat;
-    t.x[e] = (a == kInf || sat) ? kInf : static_cast<int32_t>(cand);
+  for (int e = 0; e < kArcsPerLane; ++e) asm volatile("" ::"v"(x[e]));
+}
+
+// The lane's candidates from the slice at ad. check (uniform): a path length
+// may reach INT32_MAX in this block; *ovf is set when one does.
+template <int kW>
+__device__ __forceinline__ void gather_min(const RawTile& r, const uint32_t* ad, bool check,
+                                           uint32_t (&x)[kArcsPerLane], bool* ovf) {
+#pragma unroll
+  for (int e = 0; e < kArcsPerLane; ++e) x[e] = ad[(r.cols[e >> 1] >> (16 * (e & 1))) & 0xFFFFu];
+  if (kW == kWNone) return;
+#pragma unroll
+  for (int e = 0; e < kArcsPerLane; ++e) {
+    const uint32_t w = kW == kW8 ? static_cast<uint32_t>(r.w8 >> (8 * e)) & 0xFFu
+                                 : static_cast<uint32_t>(e < 4 ? r.wa[e] : r.wb[e - 4]);
+    if (check) *ovf |= x[e] != 0u && w >= x[e];
+    x[e] = __builtin_elementwise_sub_sat(x[e], w);
   }
-  return t;
+}
+
+// Largest candidate over the tiles after tile q of the row open at q's end,
+// up to its end (the first head bit that follows).
+template <int kW>
+__device__ uint32_t finish_open_min(const uint16_t* __restrict__ col16, const gc_head_word* __restrict__ heads,
+                                    const void* __restrict__ w_arcs, const uint32_t* ad, bool check, int32_t q,
+                                    int lane, bool* ovf) {
+  uint32_t best = 0;
+  for (int64_t qq = static_cast<int64_t>(q) + 1;; ++qq) {
+    const RawTile r = load_raw_tile<kW>(col16, heads, w_arcs, qq, lane);
+    const uint32_t my8 = static_cast<uint32_t>(word_bits(r.hw) >> (8 * (lane & 7))) & 0xFFu;
+    const uint64_t hl = __ballot(my8 != 0u);
+    const int first_lane = hl ? __ffsll(static_cast<long long>(hl)) - 1 : kWave;
+    // the lane's arcs before the tile's first head
+    const int mine = lane < first_lane ? kArcsPerLane : (lane == first_lane ? __ffs(my8) - 1 : 0);
+    uint32_t x[kArcsPerLane];
+    bool o = false;
+    gather_min<kW>(r, ad, check && mine == kArcsPerLane, x, &o);
+    *ovf |= o;
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < kArcsPerLane; ++e) m = e < mine ? max(m, x[e]) : m;
+    best = max(best, static_cast<uint32_t>(gcd::wave_max(static_cast<int>(m))));  // below 2^31
+    if (hl) return best;  // bits past the last arc are set, so this ends
+  }
 }
 
 template <int kW>
-__device__ __forceinline__ MinTile load_min_tile(const uint16_t* __restrict__ col16,
-                                                 const gc_head_word* __restrict__ heads,
-                                                 const void* __restrict__ w_arcs, const int32_t* ad, int64_t q,
-                                                 int lane, bool* ovf) {
-  return finish_min_tile<kW>(load_raw_tile<kW>(col16, heads, w_arcs, q, lane), ad, lane, ovf);
-}
-
-template <int kW>
-__global__ __launch_bounds__(kLdsRowThreads) void k_sssp_tocab_lds(
+__global__ __launch_bounds__(kLdsThreads) void k_sssp_tocab_lds(
     const int32_t* __restrict__ row_ptr, const uint16_t* __restrict__ col16, const gc_head_word* __restrict__ heads,
-    const void* __restrict__ w_arcs, const int32_t* __restrict__ chunk_beg, const int32_t* __restrict__ chunk_end,
-    const int32_t* __restrict__ chunk_blk, const int32_t* __restrict__ chunk_j0, const int32_t* __restrict__ chunk_ns,
-    const int2* __restrict__ seg, int32_t R, int32_t log2W, int32_t n, const uint32_t* __restrict__ front,
-    const int32_t* __restrict__ dist, int32_t* __restrict__ pmin, uint32_t pmin_bytes, int32_t* __restrict__ stats) {
-  extern __shared__ int32_t ad[];
+    const void* __restrict__ w_arcs, uint32_t max_w, const int32_t* __restrict__ chunk_beg,
+    const int32_t* __restrict__ chunk_end, const int32_t* __restrict__ chunk_blk, const int32_t* __restrict__ chunk_j0,
+    const int32_t* __restrict__ chunk_ns, const int2* __restrict__ seg, int32_t R, int32_t log2W, int32_t n,
+    const uint32_t* __restrict__ front, const int32_t* __restrict__ dist, int32_t* __restrict__ pmin,
+    uint32_t pmin_bytes, int32_t* __restrict__ stats) {
+  extern __shared__ uint32_t ad[];
   stamp_start(stats);
-  const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(pmin, 0, static_cast<int>(pmin_bytes), 0x00020000);
+  const __amdgpu_buffer_rsrc_t out = partial_rsrc(pmin, pmin_bytes);
   const int32_t ch = blockIdx.x;
   const int32_t r0 = chunk_beg[ch], r1 = chunk_end[ch], b = chunk_blk[ch], j0 = chunk_j0[ch], ns = chunk_ns[ch];
   if (r0 >= r1) return;  // padding of the dispatch order (uniform)
   // Each wave streams a contiguous range [qa, qz] of the chunk's tiles. Its
-  // bounds, its first owned row and its first two tiles depend on the
-  // chunk alone, so their loads are issued before the block's LDS fill and
-  // overlap it.
-  const int lane = gcd::lane_id();
-  const int wid = static_cast<int>(threadIdx.x) / kWave;
-  const int32_t q0 = row_ptr[r0] / kRowTile, q1 = (row_ptr[r1] - 1) / kRowTile;
+  // bounds and its first tiles depend on the chunk alone, so their loads are
+  // issued before the block's LDS fill and overlap it.
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int32_t q0 = row_ptr[r0] / kWaveTile, q1 = (row_ptr[r1] - 1) / kWaveTile;
   const int32_t nt = q1 - q0 + 1;
-  const int32_t qa = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * wid / kLdsRowWaves);
-  const int32_t qz = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * (wid + 1) / kLdsRowWaves) - 1;
-  // rows this wave writes: heads at or after its first arc, inside the chunk
-  int32_t own0 = r0;
-  // the raw streams of the next two tiles are in flight while a tile is
-  // reduced (loads clamped to the wave's last tile, so every path issues them)
-  RawTile n1{}, n2{};
-  if (qa <= qz) {  // uniform over the wave
-    own0 = max(heads[static_cast<int64_t>(qa) * (kRowTile / 64)].row, r0);
-    n1 = load_raw_tile<kW>(col16, heads, w_arcs, qa, lane);
-    n2 = load_raw_tile<kW>(col16, heads, w_arcs, min(qa + 1, qz), lane);
+  const int32_t qa = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * wid / kLdsWaves);
+  const int32_t qz = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * (wid + 1) / kLdsWaves) - 1;
+  // Tiles in registers: four, as in the PageRank pull; two with weights,
+  // whose registers would otherwise spill, and a spill's reload waits for
+  // every tile load before it (68 -> 57 us on the uniform graph above).
+  constexpr int kDepth = kW == kWNone ? 4 : 2;
+  int32_t q = qa;
+  RawTile t0{}, t1{}, t2{}, t3{};
+  if (qa <= qz) {  // uniform over the wave; loads clamped to the wave's last tile
+    t0 = load_raw_tile<kW>(col16, heads, w_arcs, q, lane);
+    t1 = load_raw_tile<kW>(col16, heads, w_arcs, min(q + 1, qz), lane);
+    if (kDepth > 2) {
+      t2 = load_raw_tile<kW>(col16, heads, w_arcs, min(q + 2, qz), lane);
+      t3 = load_raw_tile<kW>(col16, heads, w_arcs, min(q + 3, qz), lane);
+    }
   }
   const int32_t W = 1 << log2W, v0 = b << log2W, cnt = min(W, n - v0);  // cnt >= 1
-  // The block's frontier values in LDS, in batches of kFill vertices per
-  // thread whose loads are all issued before the first is used: the status
-  // words first, then the distances, a load whose vertex lies outside the
-  // frontier's words (or past n) reading the block's first vertex instead,
-  // so that a sparse frontier costs no slice of distances.
+  uint32_t* stage = ad + W + wid * (kStageRows + kStageSpare);  // this wave's output staging and spare slots
+  int32_t* sb = reinterpret_cast<int32_t*>(ad + W + kLdsWaves * (kStageRows + kStageSpare));
+  int32_t* sd = sb + ns + kSegPad;
+  int32_t* near = sd + ns + kSegPad;  // [kLdsWaves]: the wave filled a value that a weight may exhaust
+  // The block's frontier values in LDS: thread t fills vertices t + 1024 u.
+  // A wave's vertices need 64 status words, one per lane and one load, handed
+  // out by lane reads; then the distances, kFill loads in flight, a vertex
+  // outside the frontier reading the block's first one instead (so a sparse
+  // frontier costs no slice of distances).
   constexpr int kFill = 16;
-  for (int32_t k0 = 0; k0 < W; k0 += kFill * kLdsRowThreads) {
-    uint32_t wd[kFill];
+  bool exhaust = false;
+  const int32_t nu = W / kLdsThreads;  // 1 .. 32
+  uint32_t word = 0;
+  {
+    const int32_t wi = (lane >> 1) * (kLdsThreads / 32) + 2 * wid + (lane & 1);
+    if (32 * wi < cnt) word = front[(v0 >> 5) + wi];
+  }
+  for (int32_t u0 = 0; u0 < nu; u0 += kFill) {
     int32_t dv[kFill];
+    uint32_t on = 0;
 #pragma unroll
-    for (int u = 0; u < kFill; ++u) {
-      const int32_t i = min(k0 + u * kLdsRowThreads + static_cast<int32_t>(threadIdx.x), cnt - 1);
-      wd[u] = front[(v0 + i) >> 5];
+    for (int k = 0; k < kFill; ++k) {
+      const int32_t u = min(u0 + k, nu - 1);
+      const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(word), 2 * u);
+      const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(word), 2 * u + 1);
+      const uint32_t bit = ((lane < 32 ? lo : hi) >> (lane & 31)) & 1u;
+      on |= bit << k;
+      if (kW != kWNone) dv[k] = dist[v0 + (bit ? u * kLdsThreads + static_cast<int32_t>(threadIdx.x) : 0)];
     }
 #pragma unroll
-    for (int u = 0; u < kFill; ++u) {
-      const int32_t i = k0 + u * kLdsRowThreads + static_cast<int32_t>(threadIdx.x);
-      dv[u] = 0;
-      if (kW != kWNone) dv[u] = dist[v0 + ((wd[u] != 0u && i < cnt) ? i : 0)];
-    }
-#pragma unroll
-    for (int u = 0; u < kFill; ++u) {
-      const int32_t i = k0 + u * kLdsRowThreads + static_cast<int32_t>(threadIdx.x);
-      const bool on = i < cnt && ((wd[u] >> ((v0 + i) & 31)) & 1u);
-      if (i < W) ad[i] = on ? dv[u] : kInf;
+    for (int k = 0; k < kFill; ++k) {
+      const int32_t u = min(u0 + k, nu - 1);
+      uint32_t y = (on >> k) & 1u;
+      if (kW != kWNone) {
+        y = y ? static_cast<uint32_t>(kInf - dv[k]) : 0u;
+        exhaust |= y != 0u && y <= max_w;
+      }
+      ad[u * kLdsThreads + threadIdx.x] = y;
     }
   }
   // the chunk's part of the position table: sb[i] = first row of merge range
   // j0 + i, sd[i] = its shift to the range-major index; sb[ns] lies past the
   // chunk, then sentinels
-  int32_t* sb = ad + W;
-  int32_t* sd = sb + ns + kSeekPad;
   {
     const int2* sg = seg + static_cast<int64_t>(b) * (R + 1) + j0;
-    for (int32_t i = threadIdx.x; i < ns + kSeekPad; i += kLdsRowThreads) {
+    for (int32_t i = threadIdx.x; i < ns + kSegPad; i += kLdsThreads) {
       const int2 e = i <= ns ? sg[i] : make_int2(INT32_MAX, 0);
       sb[i] = e.x;
       sd[i] = e.y;
     }
   }
+  exhaust = __any(exhaust);
+  if (lane == 0) near[wid] = exhaust ? 1 : 0;
   __syncthreads();
   if (qa > qz) return;  // no barrier follows
+  const bool check = kW != kWNone && __any(near[lane & (kLdsWaves - 1)] != 0);
   bool ovf = false;
-  int32_t carry = kInf;  // minimum so far of the row open at the previous tile's end
-  int32_t open_row = -1;
-  int32_t jw = 0;  // merge range of the wave's rows so far (ranges ascend with rows)
-  // window of the position table's row boundaries: lane l holds sb[jwin + l]
-  // (past the table: its last sentinel)
-  int32_t jwin = 0;
-  int32_t sbw = sb[min(lane, ns + kSeekPad - 1)];
-  for (int32_t q = qa; q <= qz; ++q) {
-    const RawTile cur = n1;
-    n1 = n2;
-    n2 = load_raw_tile<kW>(col16, heads, w_arcs, min(q + 2, qz), lane);
-    const MinTile t = finish_min_tile<kW>(cur, ad, lane, &ovf);
-    // lane-local runs: reset at every head; lane 0 starts from the carry
-    int32_t run = (lane == 0) ? carry : kInf;
-    int32_t rv[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      run = ((t.my9 >> e) & 1u) ? t.x[e] : min(run, t.x[e]);
-      rv[e] = run;
+  PullCarry<MaxOp> cr;
+  load_window(sb, sd, ns, lane, cr);
+  cursor_from_window(cr);
+  uint32_t x0[kArcsPerLane], x1[kArcsPerLane];
+  gather_min<kW>(t0, ad, check, x0, &ovf);
+#define GC_MIN_STEP(cur, xcur, nxt, xnxt, k)                                       \
+  gather_min<kW>(nxt, ad, check, xnxt, &ovf);                                      \
+  reduce_wave_tile<MaxOp>(cur.hw, xcur, lane, sb, sd, ns, r0, r1, cr, out, stage); \
+  hold_raw<kW>(cur, xcur);                                                         \
+  cur = load_raw_tile<kW>(col16, heads, w_arcs, min(q + (k + kDepth), qz), lane);
+  // whole rounds of kDepth tiles in the loop, the rest after it
+  const int32_t nw = qz - qa + 1;
+  for (int32_t round = 0; round < nw / kDepth; ++round) {
+    if constexpr (kDepth == 4) {
+      GC_MIN_STEP(t0, x0, t1, x1, 0)
+      GC_MIN_STEP(t1, x1, t2, x0, 1)
+      GC_MIN_STEP(t2, x0, t3, x1, 2)
+      GC_MIN_STEP(t3, x1, t0, x0, 3)
+    } else {
+      GC_MIN_STEP(t0, x0, t1, x1, 0)
+      GC_MIN_STEP(t1, x1, t0, x0, 1)
     }
-    // Wave-wide segmented inclusive minimum of the lanes' open runs, with DPP
-    // lane moves: a lane that has met a head within the reach of the steps
-    // so far (a lane mask in scalar registers, widened after each step the
-    // way the moves carry data) keeps its value, the others take the minimum
-    // with the value moved in (INT32_MAX where a move has no source).
-    const uint64_t H = __ballot((t.my9 & 0xFFu) != 0u);
-    int32_t A = run;
-    uint64_t F = H;
-    seg_min_step<0x111, 0xF>(A, F);  // row_shr:1
-    F |= (F << 1) & 0xFFFEFFFEFFFEFFFEull;
-    seg_min_step<0x112, 0xF>(A, F);  // row_shr:2
-    F |= (F << 2) & 0xFFFCFFFCFFFCFFFCull;
-    seg_min_step<0x114, 0xF>(A, F);  // row_shr:4
-    F |= (F << 4) & 0xFFF0FFF0FFF0FFF0ull;
-    seg_min_step<0x118, 0xF>(A, F);  // row_shr:8
-    F |= (F << 8) & 0xFF00FF00FF00FF00ull;
-    seg_min_step<0x142, 0xA>(A, F);  // row_bcast:15 into rows 1 and 3
-    F |= ((F & (1ull << 15)) ? 0x00000000FFFF0000ull : 0ull) | ((F & (1ull << 47)) ? 0xFFFF000000000000ull : 0ull);
-    seg_min_step<0x143, 0xC>(A, F);  // row_bcast:31 into rows 2 and 3
-    const int32_t lin = dpp_in<0x138, 0xF>(A);  // wave_shr:1, the row flowing into this lane (lane 0: none)
-    // Merge range of the rows this lane may store (those of its arcs 0 .. 7,
-    // rows rlo .. rhi). The range boundaries inside the tile's rows are
-    // counted from the register window (a ballot gives how many lie at or
-    // below the tile's last row) and walked through scalar registers, each
-    // lane counting those at or below its first and last row; the window
-    // moves on when the tile's rows run past its last entry. A lane's rows
-    // cross at most one boundary when the block's ranges hold 8 rows or
-    // more (tens to hundreds here): the row's shift is then one of the two
-    // read below, and only a lane crossing several looks each row's range up.
-    const int32_t rlo = t.row0 + static_cast<int32_t>(t.my9 & 1u);
-    const int32_t rhi = t.row0 + __popc(t.my9 & 0xFFu);
-    const int32_t maxrow = __builtin_amdgcn_readlane(rhi, kWave - 1);
-    int32_t cf = 0, cl = 0, jz = jw;
-    for (;;) {  // uniform
-      if (jz + 1 - jwin >= kWave) {
-        jwin = jz;
-        sbw = sb[min(jwin + lane, ns + kSeekPad - 1)];
-      }
-      const int32_t cnt = __popcll(__ballot(sbw <= maxrow));  // a prefix: the table ascends
-      const int32_t jend = jwin + cnt - 1;
-      for (int32_t jj = jz + 1; jj <= jend; ++jj) {
-        const int32_t bnd = __builtin_amdgcn_readlane(sbw, jj - jwin);
-        cf += rlo >= bnd;
-        cl += rhi >= bnd;
-      }
-      jz = max(jz, jend);
-      if (cnt < kWave) break;
-    }
-    // jz <= ns (sb[ns + 1 ..] are sentinels above every row), so jf + 1 lies
-    // inside the table
-    const int32_t jf = jw + cf;
-    const int32_t nx = cl - cf;  // boundaries inside the lane's rows
-    const int32_t d0 = sd[jf], b1 = sb[jf + 1], d1 = sd[jf + 1];
-    jw = jz;
-    // Every lane issues its 8 stores, one per arc: an arc that ends a row
-    // the wave writes stores the row's minimum at its range-major index, any
-    // other store gets an offset past the buffer and is dropped (no branch
-    // around a store: the loads of the next tiles stay in flight). Lanes
-    // crossing several boundaries store on the path below instead.
-    const bool slow = nx > 1;
-    int32_t row = t.row0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      row += static_cast<int32_t>((t.my9 >> e) & 1u);
-      const bool ends = (t.my9 >> (e + 1)) & 1u;  // arc e ends its row
-      const bool started_here = (t.my9 & ((2u << e) - 1u)) != 0u;
-      const int32_t v = started_here ? rv[e] : min(rv[e], lin);
-      const int32_t d = row >= b1 ? d1 : d0;
-      const bool ok = ends && !slow && row >= own0 && row < r1;
-      const uint32_t off = ok ? 4u * static_cast<uint32_t>(row + d) : kDropOff + 4u * e;
-      __builtin_amdgcn_raw_buffer_store_b32(static_cast<uint32_t>(v), out, off, 0, 0);
-    }
-    if (__any(slow)) {
-      row = t.row0;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        row += static_cast<int32_t>((t.my9 >> e) & 1u);
-        if (slow && ((t.my9 >> (e + 1)) & 1u) && row >= own0 && row < r1) {
-          const bool started_here = (t.my9 & ((2u << e) - 1u)) != 0u;
-          int32_t j = jf;
-          while (sb[j + 1] <= row) ++j;
-          pmin[row + sd[j]] = started_here ? rv[e] : min(rv[e], lin);
-        }
-      }
-    }
-    carry = __builtin_amdgcn_readlane(A, kWave - 1);
-    open_row = __builtin_amdgcn_readlane(row, kWave - 1);
+    q += kDepth;
   }
-  // the row open at the range's end, if the wave owns it: read on to its end
-  const int64_t end_arc = static_cast<int64_t>(qz + 1) * kRowTile;
-  const bool continues = !((heads[end_arc >> 6].bits) & 1ull);
-  if (continues && open_row >= own0 && open_row < r1) {
-    for (int64_t q = qz + 1;; ++q) {
-      const MinTile t = load_min_tile<kW>(col16, heads, w_arcs, ad, q, lane, &ovf);
-      // arcs before the tile's first head belong to the open row
-      const int fh = (t.my9 & 0xFFu) ? __ffs(t.my9 & 0xFFu) - 1 : 8;  // first head in the lane
-      const uint64_t hl = __ballot(fh < 8);
-      const int first_lane = hl ? __ffsll(static_cast<long long>(hl)) - 1 : kWave;
-      int32_t mine = kInf;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (lane < first_lane || (lane == first_lane && e < fh)) mine = min(mine, t.x[e]);
-      carry = min(carry, gcd::wave_min(mine));
-      if (first_lane < kWave) break;  // bits past the last arc are set, so this ends
-    }
-    if (lane == 0) {
-      int32_t j = jw;
-      while (sb[j + 1] <= open_row) ++j;
-      pmin[open_row + sd[j]] = carry;
-    }
+  const int32_t rest = nw % kDepth;
+  if (rest > 0) {
+    if (kDepth > 2) gather_min<kW>(t1, ad, check, x1, &ovf);
+    reduce_wave_tile<MaxOp>(t0.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
   }
-  if (__any(ovf) && lane == 0) stats[kOverflow] = 1;
+  if constexpr (kDepth == 4) {
+    if (rest > 1) {
+      gather_min<kW>(t2, ad, check, x0, &ovf);
+      reduce_wave_tile<MaxOp>(t1.hw, x1, lane, sb, sd, ns, r0, r1, cr, out, stage);
+    }
+    if (rest > 2) reduce_wave_tile<MaxOp>(t2.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
+  }
+#undef GC_MIN_STEP
+  if (cr.open_row >= 0) {  // the range's last row continues past it
+    const uint32_t v = max(cr.open, finish_open_min<kW>(col16, heads, w_arcs, ad, check, qz, lane, &ovf));
+    if (lane == 0) pmin[cr.open_row + sd[seek_range(sb, cr.jc, cr.open_row)]] = static_cast<int32_t>(v);
+  }
+  if (kW != kWNone && __any(ovf) && lane == 0) stats[kOverflow] = 1;
+}
+
+// Dynamic LDS of k_sssp_tocab_lds for partition t: the PageRank pull's, plus
+// a word per wave.
+inline size_t tocab_lds_bytes(const gc_tocab_s* t) {
+  return sizeof(int32_t) * (static_cast<size_t>(t->W) + 2 * static_cast<size_t>(t->seg_max) + 2 * kSegPad + kLdsWaves) +
+         gcx::kLdsStageBytes;
 }
 
 // Size in bytes of the partial minima of a stream-layout partition (P + 8
@@ -955,9 +871,9 @@ inline uint32_t pmin_bytes(const gc_tocab_s* t) { return static_cast<uint32_t>(s
 // rstart[j+1]) of pmin / id16s (the position table's range-major order). A
 // persistent work-group (two per CU) walks ranges j = blockIdx.x,
 // blockIdx.x + gridDim.x, ...: 16-byte / 8-byte loads of 4 entries, LDS
-// minima, then the range's vertices are updated (distance, next status
-// bit, queue) and the minima reset for the next range, whose first loads
-// are issued before that update.
+// maxima of the inverted values, then the range's vertices are updated
+// (distance, next status bit, counts) and the maxima reset for the next
+// range, whose first loads are issued before that update.
 template <int K, int NT, bool kBfs>
 __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restrict__ rstart,
                                                           const uint16_t* __restrict__ id16s,
@@ -966,7 +882,7 @@ __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restr
                                                           Tally tally, int32_t level, uint32_t* __restrict__ visited) {
   __shared__ int32_t best[K];
   Counted cnt;
-  for (int i = threadIdx.x; i < K; i += NT) best[i] = kInf;
+  for (int i = threadIdx.x; i < K; i += NT) best[i] = 0;
   __syncthreads();
   const ti32x4* p4 = reinterpret_cast<const ti32x4*>(pmin);
   const uint64_t* i4 = reinterpret_cast<const uint64_t*>(id16s);
@@ -997,7 +913,7 @@ __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restr
       const int32_t e0 = 4 * (g + k * NT);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (e0 + e >= a && e0 + e < z && p[k][e] != kInf) atomicMin(&best[(id[k] >> (16 * e)) & 0xFFFFu], p[k][e]);
+        if (e0 + e >= a && e0 + e < z && p[k][e] != 0) atomicMax(&best[(id[k] >> (16 * e)) & 0xFFFFu], p[k][e]);
     }
   };
   const int32_t tid = threadIdx.x;
@@ -1029,12 +945,12 @@ __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restr
     for (int u = 0; u < kPer; ++u) {
       const int32_t i = tid + u * NT;
       bi[u] = best[i];
-      best[i] = kInf;
+      best[i] = 0;
     }
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
       const uint32_t o = static_cast<uint32_t>(tid + u * NT);
-      const bool need = o <= last && (kBfs ? bi[u] == 0 : bi[u] != kInf);
+      const bool need = o <= last && bi[u] != 0;
       const uint32_t oo = need ? o : 0u;
       cur[u] = kBfs ? static_cast<int32_t>(visited[(static_cast<uint32_t>(v0) + oo) >> 5]) : dist[v0 + oo];
     }
@@ -1052,11 +968,12 @@ __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restr
       const int32_t v = v0 + tid + u * NT;
       bool improved;
       if (kBfs) {  // depth: a vertex not yet reached with an in-neighbour in the frontier
-        improved = v < n && bi[u] == 0 && !((static_cast<uint32_t>(cur[u]) >> (v & 31)) & 1u);
+        improved = v < n && bi[u] != 0 && !((static_cast<uint32_t>(cur[u]) >> (v & 31)) & 1u);
         if (improved) dist[v] = level + 1;
       } else {
-        improved = v < n && bi[u] != kInf && bi[u] < cur[u];
-        if (improved) dist[v] = bi[u];
+        const int32_t nd = kInf - bi[u];
+        improved = v < n && bi[u] != 0 && nd < cur[u];
+        if (improved) dist[v] = nd;
       }
       const uint64_t m = __ballot(improved);
       const int lane = tid & (kWave - 1);
@@ -1833,7 +1750,7 @@ int32_t* g_range_flag() {
 // its chunk's position table).
 hipError_t stream_pull_setup() {
   static const hipError_t attr = [] {
-    const int lds = gcx::lds_budget(gcx::kLdsMaxWidth);
+    const int lds = gcx::lds_budget(gcx::kLdsMaxWidth) + static_cast<int>(sizeof(int32_t)) * kLdsWaves;
     hipError_t e = hipSuccess;
     for (const void* k : {reinterpret_cast<const void*>(&k_sssp_tocab_lds<kW32>),
                           reinterpret_cast<const void*>(&k_sssp_tocab_lds<kW8>),
@@ -2064,10 +1981,9 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
       GC_HIP_TRY(stream_pull_setup());
       {
         ProfScope prof("bfs_tocab", s);
-        const size_t lds = sizeof(int32_t) * (static_cast<size_t>(t->W) + 2 * (t->seg_max + kSeekPad));
         if (t->n_chunks > 0)
-          k_sssp_tocab_lds<kWNone><<<t->n_chunks, kLdsRowThreads, lds, s>>>(
-              t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
+          k_sssp_tocab_lds<kWNone><<<t->n_chunks, kLdsThreads, tocab_lds_bytes(t), s>>>(
+              t->row_ptr, t->col16, t->heads, nullptr, 0u, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
               t->chunk_ns, t->seg, t->R, t->log2W, n, f.front(), nullptr, t->pmin, pmin_bytes(t), g->stats);
       }
       ProfScope prof("bfs_merge", s);
@@ -2105,14 +2021,14 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
         GC_HIP_TRY(stream_weights(t, s));
         {
           ProfScope prof("sssp_tocab", s);
-          const size_t lds = sizeof(int32_t) * (static_cast<size_t>(t->W) + 2 * (t->seg_max + kSeekPad));
+          const size_t lds = tocab_lds_bytes(t);
           if (t->n_chunks > 0 && t->w8)
-            k_sssp_tocab_lds<kW8><<<t->n_chunks, kLdsRowThreads, lds, s>>>(
-                t->row_ptr, t->col16, t->heads, t->w8, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
+            k_sssp_tocab_lds<kW8><<<t->n_chunks, kLdsThreads, lds, s>>>(
+                t->row_ptr, t->col16, t->heads, t->w8, 255u, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
                 t->chunk_ns, t->seg, t->R, t->log2W, n, f.front(), value, t->pmin, pmin_bytes(t), g->stats);
           else if (t->n_chunks > 0)
-            k_sssp_tocab_lds<kW32><<<t->n_chunks, kLdsRowThreads, lds, s>>>(
-                t->row_ptr, t->col16, t->heads, t->w_pad, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
+            k_sssp_tocab_lds<kW32><<<t->n_chunks, kLdsThreads, lds, s>>>(
+                t->row_ptr, t->col16, t->heads, t->w_pad, static_cast<uint32_t>(kInf), t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
                 t->chunk_ns, t->seg, t->R, t->log2W, n, f.front(), value, t->pmin, pmin_bytes(t), g->stats);
         }
         ProfScope prof("sssp_merge", s);
