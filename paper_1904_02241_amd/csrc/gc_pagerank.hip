@@ -255,7 +255,8 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
   load_window(sb, sd, ns, lane, cr);
   cursor_from_window(cr);
   // Four tiles in registers: while one is reduced, the next one's gathers
-  // and the two after it's loads are in flight; the tile just reduced is
+  // and the two after it's loads are in flight (loading them before the
+  // slice's fill gains nothing: 310 against 312 us at R-MAT 24); the tile just reduced is
   // refilled once its stores are issued, so the youngest memory operations
   // at every wait are tile loads. Its registers (and its gathered values)
   // are held live until then, so the compiler cannot hand them to the
@@ -264,43 +265,57 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
   // kStoresPerTile stores, and dropped stores after the prologue's loads
   // give the compiler's count of memory operations after each load at
   // least its steady-state value on entry.
+  // The valued pull holds two tiles: with four its registers spill, and a
+  // spill's reload waits for every tile load before it (FP32 values, R-MAT
+  // of 2^22 vertices and 64 M arcs: 202 -> 153 us).
+  constexpr int kDepth = kVal ? 2 : 4;
   int32_t q = qa;
   WaveTile t0 = load_wave_tile<kVal>(col16, heads, vals, q, lane);
   WaveTile t1 = load_wave_tile<kVal>(col16, heads, vals, min(q + 1, qz), lane);
-  WaveTile t2 = load_wave_tile<kVal>(col16, heads, vals, min(q + 2, qz), lane);
-  WaveTile t3 = load_wave_tile<kVal>(col16, heads, vals, min(q + 3, qz), lane);
+  WaveTile t2{}, t3{};
+  if constexpr (kDepth == 4) {
+    t2 = load_wave_tile<kVal>(col16, heads, vals, min(q + 2, qz), lane);
+    t3 = load_wave_tile<kVal>(col16, heads, vals, min(q + 3, qz), lane);
+  }
   drop_stores(out);
   drop_stores(out);
   drop_stores(out);
   float x0[kArcsPerLane], x1[kArcsPerLane];
   gather_tile<kVal>(t0, x0);
-  // Whole rounds of four tiles run in a loop with no exit inside (an exit
+  // Whole rounds of kDepth tiles run in a loop with no exit inside (an exit
   // merged into the loop's back edge would make the compiler assume a path
-  // with fewer memory operations and wait longer); the last nt % 4 tiles
-  // follow it.
-#define GC_PULL_STEP(cur, xcur, nxt, xnxt, k)                           \
-  gather_tile<kVal>(nxt, xnxt);                                         \
-  reduce_wave_tile<SumOp>(cur.hw, xcur, lane, sb, sd, ns, r0, r1, cr, out, stage); \
-  hold_live<kVal>(cur, xcur);                                           \
-  cur = load_wave_tile<kVal>(col16, heads, vals, min(q + (k + 4), qz), lane);
+  // with fewer memory operations and wait longer); the last nt % kDepth
+  // tiles follow it.
+#define GC_PULL_STEP(cur, xcur, nxt, xnxt, k)                                             \
+  gather_tile<kVal>(nxt, xnxt);                                                           \
+  reduce_wave_tile<SumOp>(cur.hw, xcur, lane, sb, sd, ns, r0, r1, cr, out, stage);        \
+  hold_live<kVal>(cur, xcur);                                                             \
+  cur = load_wave_tile<kVal>(col16, heads, vals, min(q + (k + kDepth), qz), lane);
   const int32_t nw = qz - qa + 1;
-  for (int32_t round = 0; round < nw / 4; ++round) {
-    GC_PULL_STEP(t0, x0, t1, x1, 0)
-    GC_PULL_STEP(t1, x1, t2, x0, 1)
-    GC_PULL_STEP(t2, x0, t3, x1, 2)
-    GC_PULL_STEP(t3, x1, t0, x0, 3)
-    q += 4;
+  for (int32_t round = 0; round < nw / kDepth; ++round) {
+    if constexpr (kDepth == 4) {
+      GC_PULL_STEP(t0, x0, t1, x1, 0)
+      GC_PULL_STEP(t1, x1, t2, x0, 1)
+      GC_PULL_STEP(t2, x0, t3, x1, 2)
+      GC_PULL_STEP(t3, x1, t0, x0, 3)
+    } else {
+      GC_PULL_STEP(t0, x0, t1, x1, 0)
+      GC_PULL_STEP(t1, x1, t0, x0, 1)
+    }
+    q += kDepth;
   }
-  const int32_t rest = nw % 4;
+  const int32_t rest = nw % kDepth;
   if (rest > 0) {
-    gather_tile<kVal>(t1, x1);
+    if (kDepth > 2) gather_tile<kVal>(t1, x1);
     reduce_wave_tile<SumOp>(t0.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
   }
-  if (rest > 1) {
-    gather_tile<kVal>(t2, x0);
-    reduce_wave_tile<SumOp>(t1.hw, x1, lane, sb, sd, ns, r0, r1, cr, out, stage);
+  if constexpr (kDepth == 4) {
+    if (rest > 1) {
+      gather_tile<kVal>(t2, x0);
+      reduce_wave_tile<SumOp>(t1.hw, x1, lane, sb, sd, ns, r0, r1, cr, out, stage);
+    }
+    if (rest > 2) reduce_wave_tile<SumOp>(t2.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
   }
-  if (rest > 2) reduce_wave_tile<SumOp>(t2.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
 #undef GC_PULL_STEP
   if (cr.open_row >= 0) {  // the range's last row continues past it
     const double v = cr.open + finish_open_row<kVal>(col16, heads, vals, slice, qz, lane);
