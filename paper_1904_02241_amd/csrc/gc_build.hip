@@ -183,6 +183,17 @@ __device__ __forceinline__ int32_t wave_owner_row(const int32_t* __restrict__ ro
   return lo;
 }
 
+// Tile of this work-group of k_radix_move: consecutive tiles run on one XCD
+// (the GPU hands consecutive work-groups to its kXcds XCDs in turn), since a
+// digit's runs of consecutive tiles share cache lines, which one L2 can put
+// together and several write back in parts.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int32_t xcd_tile(int32_t tiles) {
+  const int32_t per = (tiles + kXcds - 1) / kXcds;
+  return static_cast<int32_t>(blockIdx.x % kXcds) * per + static_cast<int32_t>(blockIdx.x / kXcds);
+}
+inline int32_t xcd_grid(int32_t tiles) { return (tiles + kXcds - 1) / kXcds * kXcds; }
+
 // LDS bytes of k_radix_move.
 constexpr size_t radix_lds(int32_t bins) {
   return sizeof(int32_t) * (kRadixTile + static_cast<size_t>(bins) * (kRadixWaves + 1));
@@ -218,7 +229,9 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_move(RadixArgs a) {
   __shared__ int32_t row_first, row_last;
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
-  const int64_t e0 = static_cast<int64_t>(blockIdx.x) * kRadixTile;
+  const int32_t tile = xcd_tile(a.tiles);
+  if (tile >= a.tiles) return;  // uniform
+  const int64_t e0 = static_cast<int64_t>(tile) * kRadixTile;
   const int32_t len = static_cast<int32_t>(min<int64_t>(kRadixTile, a.m - e0));  // >= 1
   const int32_t p0 = wid * (kRadixTile / kRadixWaves) + lane;  // position of the thread's arc of round 0
   int32_t key[kRadixItems], row[kRadixItems];  // row: filled here only when it comes from rowptr
@@ -308,7 +321,7 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_move(RadixArgs a) {
     }
     carry += all;
     if (d < bins) {
-      off[d] = a.base[static_cast<int64_t>(d) * a.tiles + blockIdx.x] - start;
+      off[d] = a.base[static_cast<int64_t>(d) * a.tiles + tile] - start;
       for (int w = 0; w < kRadixWaves; ++w) {
         const int32_t c = cnt[w * bins + d];
         cnt[w * bins + d] = start;
@@ -548,11 +561,57 @@ __global__ void k_seg_table(const int32_t* __restrict__ range_ptr, const int32_t
   if (b == 0) rstart[j] = j < R ? rm_start[jb] : static_cast<int32_t>(P);
 }
 
-// First arc of every (block, range) boundary row.
-__global__ void k_seg_arcs(const int2* __restrict__ seg, int64_t count, const int32_t* __restrict__ row_ptr,
-                           int32_t* __restrict__ out) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < count) out[i] = row_ptr[seg[i].x];
+// Chunks of the stream-layout pull, one wave per block: a block's ranges are
+// cut into chunks of about equal arc counts (near `target`, at most `cap`
+// ranges each). From range j0 a chunk runs to the first boundary that gives
+// it its share of the block's arcs, found with 64 probes per step. out[0]
+// counts the chunks; chunk i follows at out + kChunkInts (i + 1): first row,
+// end row, block, first range, ranges, arcs.
+constexpr int kChunkInts = 8;
+__global__ __launch_bounds__(256) void k_cut_chunks(const int32_t* __restrict__ range_ptr,
+                                                    const int32_t* __restrict__ row_ptr, int32_t B, int32_t R,
+                                                    int64_t target, int32_t cap, int32_t most,
+                                                    int32_t* __restrict__ out) {
+  const int32_t b = static_cast<int32_t>(blockIdx.x) * (256 / kWave) + static_cast<int32_t>(threadIdx.x) / kWave;
+  if (b >= B) return;  // uniform over the wave
+  const int lane = gcd::lane_id();
+  auto arc_at = [&](int32_t j) { return row_ptr[range_ptr[static_cast<int64_t>(j) * B + b]]; };
+  const int64_t mb = arc_at(R) - arc_at(0);
+  if (mb == 0) return;
+  const int64_t pieces = max<int64_t>(1, (mb + target - 1) / target);
+  const int64_t per = (mb + pieces - 1) / pieces;  // arcs per chunk of this block
+  for (int32_t ja = 0; ja < R;) {
+    const int32_t a0 = arc_at(ja), top = min(R, ja + cap);
+    int32_t lo = ja + 1, hi = top;  // first j in (ja, top] with per arcs or more, else top
+    while (lo < hi) {  // uniform
+      const int32_t step = (hi - lo + kWave - 1) / kWave;
+      const int32_t j = min(hi, lo + lane * step);
+      const int cnt = __popcll(__ballot(arc_at(j) - a0 < per));  // a prefix of the lanes
+      const int32_t fail = lo + cnt * step;  // the first probe with enough (past hi: none)
+      if (cnt == 0) {
+        hi = lo;
+      } else {
+        lo = min(hi, lo + (cnt - 1) * step + 1);
+        hi = min(hi, fail);
+      }
+    }
+    if (lane == 0) {
+      const int32_t r0 = range_ptr[static_cast<int64_t>(ja) * B + b], r1 = range_ptr[static_cast<int64_t>(lo) * B + b];
+      if (r1 > r0) {
+        const int32_t i = atomicAdd(out, 1);
+        if (i < most) {
+          int32_t* c = out + kChunkInts * (static_cast<int64_t>(i) + 1);
+          c[0] = r0;
+          c[1] = r1;
+          c[2] = b;
+          c[3] = ja;
+          c[4] = lo - ja;
+          c[5] = arc_at(lo) - a0;
+        }
+      }
+    }
+    ja = lo;
+  }
 }
 
 // id16 of every local row, scattered to the row's range-major index.
@@ -609,29 +668,35 @@ inline int key_bits(int64_t values) {  // bits of the largest of `values` values
   return b;
 }
 
-// Scratch of a radix pass: digit counts, their scan and its tile sums.
+// Scratch of a radix pass in a slab: digit counts, their scan and its tile
+// sums.
 struct RadixScratch {
-  gcx::Buf counts, base, tile;
+  size_t i_counts, i_base, i_tile;
+  int32_t *counts = nullptr, *base = nullptr, *tile = nullptr;
   int32_t tiles;
-  RadixScratch(int64_t m, int width, hipStream_t s)
-      : counts(sizeof(int32_t) * entries(m, width), s),
-        base(sizeof(int32_t) * (entries(m, width) + 1), s),
-        tile(sizeof(int32_t) * std::max<int64_t>(scan_tiles(entries(m, width)), 1), s),
-        tiles(static_cast<int32_t>((m + kRadixTile - 1) / kRadixTile)) {}
-  static int64_t entries(int64_t m, int width) { return ((m + kRadixTile - 1) / kRadixTile) << width; }
-  bool ok() const { return counts.p && base.p && tile.p; }
+  RadixScratch(int64_t m, int width, gcx::Slab& slab) {
+    tiles = static_cast<int32_t>((m + kRadixTile - 1) / kRadixTile);
+    const int64_t entries = static_cast<int64_t>(tiles) << width;
+    i_counts = slab.reserve(sizeof(int32_t) * entries);
+    i_base = slab.reserve(sizeof(int32_t) * (entries + 1));
+    i_tile = slab.reserve(sizeof(int32_t) * scan_tiles(entries));
+  }
+  void take(const gcx::Slab& slab, void* p) {
+    counts = slab.take<int32_t>(p, i_counts);
+    base = slab.take<int32_t>(p, i_base);
+    tile = slab.take<int32_t>(p, i_tile);
+  }
 };
 
 // Queues one pass (m > 0).
 hipError_t radix_pass(RadixArgs a, const RadixScratch& r, hipStream_t s) {
   const int32_t bins = 1 << a.bits;
   a.tiles = r.tiles;
-  a.base = r.base.as<int32_t>();
-  k_radix_count<<<r.tiles, kRadixThreads, 0, s>>>(a.key, a.m, a.shift, bins, r.tiles, r.counts.as<int32_t>());
+  a.base = r.base;
+  k_radix_count<<<r.tiles, kRadixThreads, 0, s>>>(a.key, a.m, a.shift, bins, r.tiles, r.counts);
   GC_HIP_TRY(hipGetLastError());
-  GC_HIP_TRY(scan_queue(r.counts.as<int32_t>(), r.base.as<int32_t>(), static_cast<int64_t>(r.tiles) << a.bits,
-                        r.tile.as<int32_t>(), s));
-  k_radix_move<<<r.tiles, kRadixThreads, radix_lds(bins), s>>>(a);
+  GC_HIP_TRY(scan_queue(r.counts, r.base, static_cast<int64_t>(r.tiles) << a.bits, r.tile, s));
+  k_radix_move<<<xcd_grid(r.tiles), kRadixThreads, radix_lds(bins), s>>>(a);
   return hipGetLastError();
 }
 
@@ -691,12 +756,17 @@ hipError_t build_transpose(int32_t n, int64_t m, const int32_t* rowptr, const in
   GC_HIP_TRY(radix_setup());
   const Digits dg(key_bits(n), kTransposeBits);
   const size_t mb = sizeof(int32_t) * static_cast<size_t>(m);
-  Buf k0(mb, s), k1(dg.passes > 1 ? mb : 0, s), r1(dg.passes > 1 ? mb : 0, s), w1(dg.passes > 1 && w ? mb : 0, s);
-  RadixScratch scratch(m, dg.width, s);
-  if (!k0.p || !k1.p || !r1.p || !w1.p || !scratch.ok()) return hipErrorOutOfMemory;
-  int32_t* const keys[2] = {k0.as<int32_t>(), k1.as<int32_t>()};
-  int32_t* const rows[2] = {t_colidx, r1.as<int32_t>()};
-  int32_t* const ws[2] = {t_w, w1.as<int32_t>()};
+  const bool many = dg.passes > 1;
+  Slab slab;
+  const size_t k0 = slab.reserve(mb), k1 = slab.reserve(many ? mb : 0), r1 = slab.reserve(many ? mb : 0),
+               w1 = slab.reserve(many && w ? mb : 0);
+  RadixScratch scratch(m, dg.width, slab);
+  Buf mem(slab.total, s);
+  if (!mem.p) return hipErrorOutOfMemory;
+  scratch.take(slab, mem.p);
+  int32_t* const keys[2] = {slab.take<int32_t>(mem.p, k0), slab.take<int32_t>(mem.p, k1)};
+  int32_t* const rows[2] = {t_colidx, slab.take<int32_t>(mem.p, r1)};
+  int32_t* const ws[2] = {t_w, slab.take<int32_t>(mem.p, w1)};
   RadixArgs a{};
   a.key = colidx;
   a.rowptr = rowptr;
@@ -715,9 +785,9 @@ hipError_t build_transpose(int32_t n, int64_t m, const int32_t* rowptr, const in
     a.row = rows[o];
     if (w) a.w = ws[o];
   }
-  k_row_offsets<<<grid_for(m, kOffsetTile), 256, 0, s>>>(k0.as<int32_t>(), m, n, t_rowptr);
+  k_row_offsets<<<grid_for(m, kOffsetTile), 256, 0, s>>>(keys[0], m, n, t_rowptr);
   GC_HIP_TRY(hipGetLastError());
-  return hipStreamSynchronize(s);  // the Bufs are released on return
+  return hipStreamSynchronize(s);  // the Buf is released on return
 }
 
 // Stream layout of an LDS-resident pull partition: padded 16-bit columns,
@@ -738,57 +808,56 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   // range-major start of every (range j, block b) slice: exclusive scan of
   // the slice sizes in j-major order
   const int64_t BR = static_cast<int64_t>(B) * R;
-  Buf cnt(sizeof(int32_t) * std::max<int64_t>(BR, 1), s), rm(sizeof(int32_t) * (BR + 1), s);
-  Buf arcs(sizeof(int32_t) * entries, s);
-  if (!cnt.p || !rm.p || !arcs.p) return hipErrorOutOfMemory;
-  k_seg_counts<<<grid_for(BR, 256, INT_MAX), 256, 0, s>>>(t->range_ptr, B, R, cnt.as<int32_t>());
+  const int64_t target = std::max<int64_t>(kLdsChunkArcs, m / 1024);
+  const int32_t cap = lds_seg_cap(t->W);
+  // no block has more chunks than its share of target-sized pieces, one cut
+  // short by `cap` per cap ranges, and one more
+  const int64_t most = m / target + static_cast<int64_t>(B) * ((R + cap - 1) / cap + 2);
+  Slab slab;
+  const size_t i_cnt = slab.reserve(sizeof(int32_t) * BR), i_rm = slab.reserve(sizeof(int32_t) * (BR + 1)),
+               i_tile = slab.reserve(sizeof(int32_t) * scan_tiles(BR)),
+               i_chunks = slab.reserve(sizeof(int32_t) * kChunkInts * (most + 1));
+  Buf mem(slab.total, s);
+  if (!mem.p) return hipErrorOutOfMemory;
+  int32_t* const cnt = slab.take<int32_t>(mem.p, i_cnt);
+  int32_t* const rm = slab.take<int32_t>(mem.p, i_rm);
+  int32_t* const dch = slab.take<int32_t>(mem.p, i_chunks);
+  GC_HIP_TRY(hipMemsetAsync(dch, 0, sizeof(int32_t) * kChunkInts, s));
+  k_cut_chunks<<<grid_for(B, 256 / kWave), 256, 0, s>>>(t->range_ptr, t->row_ptr, B, R, target, cap,
+                                                        static_cast<int32_t>(most), dch);
+  k_seg_counts<<<grid_for(BR, 256, INT_MAX), 256, 0, s>>>(t->range_ptr, B, R, cnt);
   GC_HIP_TRY(hipGetLastError());
-  GC_HIP_TRY(scan_exclusive(cnt.as<int32_t>(), rm.as<int32_t>(), BR, s));
-  k_seg_table<<<grid_for(entries, 256, INT_MAX), 256, 0, s>>>(t->range_ptr, rm.as<int32_t>(), B, R, P, t->seg,
-                                                              t->rstart);
+  // (the pageable copies wait for the kernels before them)
+  std::vector<int32_t> hch(kChunkInts);
+  GC_HIP_TRY(hipMemcpyAsync(hch.data(), dch, sizeof(int32_t) * kChunkInts, hipMemcpyDeviceToHost, s));
+  GC_HIP_TRY(hipStreamSynchronize(s));
+  const int32_t found = hch[0];
+  if (found > most) return hipErrorUnknown;
+  hch.resize(static_cast<size_t>(kChunkInts) * found);
+  GC_HIP_TRY(scan_queue(cnt, rm, BR, slab.take<int32_t>(mem.p, i_tile), s));
+  k_seg_table<<<grid_for(entries, 256, INT_MAX), 256, 0, s>>>(t->range_ptr, rm, B, R, P, t->seg, t->rstart);
   if (P > 0)
     k_id16_stream<<<grid_for(P, 256, 65536), 256, 0, s>>>(t->id_map, P, t->blk_rowoff, B, R, t->log2k, t->seg,
                                                           t->id16s);
-  k_seg_arcs<<<grid_for(entries, 256, INT_MAX), 256, 0, s>>>(t->seg, entries, t->row_ptr, arcs.as<int32_t>());
   GC_HIP_TRY(hipGetLastError());
-
-  // chunks on the host from the boundary rows and their first arcs
-  std::vector<int2> hseg(entries);
-  std::vector<int32_t> harc(entries);
-  GC_HIP_TRY(hipMemcpyAsync(hseg.data(), t->seg, sizeof(int2) * entries, hipMemcpyDeviceToHost, s));
-  GC_HIP_TRY(hipMemcpyAsync(harc.data(), arcs.p, sizeof(int32_t) * entries, hipMemcpyDeviceToHost, s));
+  if (found > 0)
+    GC_HIP_TRY(hipMemcpyAsync(hch.data(), dch + kChunkInts, sizeof(int32_t) * hch.size(), hipMemcpyDeviceToHost, s));
   GC_HIP_TRY(hipStreamSynchronize(s));
-  // A block's ranges are cut into chunks of about equal arc counts (near
-  // `target`, at most `cap` ranges each); chunks are launched largest first,
-  // so the work-groups that start last are the short ones.
-  const int64_t target = std::max<int64_t>(kLdsChunkArcs, m / 1024);
-  const int32_t cap = lds_seg_cap(t->W);
   struct Chunk {
     int32_t beg, end, blk, j0, ns;
     int64_t arcs;
   };
-  std::vector<Chunk> ch;
+  std::vector<Chunk> ch(static_cast<size_t>(found));
   int32_t seg_max = 1;
-  for (int32_t b = 0; b < B; ++b) {
-    const int64_t o = static_cast<int64_t>(b) * (R + 1);
-    const int64_t mb = harc[o + R] - harc[o];
-    const int64_t pieces = std::max<int64_t>(1, (mb + target - 1) / target);
-    const int64_t per = (mb + pieces - 1) / pieces;  // arcs per chunk of this block
-    int32_t j = 0;
-    while (j < R) {
-      const int32_t ja = j;
-      int64_t a = 0;
-      while (j < R && j - ja < cap && (j == ja || a < per)) {
-        a += harc[o + j + 1] - harc[o + j];
-        ++j;
-      }
-      const int32_t r0 = hseg[o + ja].x, r1 = hseg[o + j].x;
-      if (r1 > r0) {
-        ch.push_back({r0, r1, b, ja, j - ja, a});
-        seg_max = std::max(seg_max, j - ja);
-      }
-    }
+  for (int32_t i = 0; i < found; ++i) {
+    const int32_t* c = hch.data() + static_cast<size_t>(kChunkInts) * i;
+    ch[i] = {c[0], c[1], c[2], c[3], c[4], c[5]};
+    seg_max = std::max(seg_max, c[4]);
   }
+  // the blocks' waves append in any order
+  std::sort(ch.begin(), ch.end(), [](const Chunk& x, const Chunk& y) {
+    return x.blk != y.blk ? x.blk < y.blk : x.j0 < y.j0;
+  });
   // Dispatch order, XCD aware: the GPU hands consecutive work-groups to its
   // kXcds XCDs in turn (work-group i to XCD i mod kXcds), and each XCD has
   // its own L2. All chunks of a block go to one XCD, next to each other in
@@ -796,7 +865,6 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   // from that L2 for the block's other chunks. Blocks are dealt largest
   // first, each to the XCD with the fewest arcs so far; within a block the
   // largest chunk runs first; shorter lists are padded with empty chunks.
-  constexpr int kXcds = 8;
   std::vector<int64_t> blk_arcs(static_cast<size_t>(B), 0);
   for (const Chunk& c : ch) blk_arcs[c.blk] += c.arcs;
   std::vector<int32_t> order(static_cast<size_t>(B));
@@ -837,20 +905,19 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   const int32_t nch = static_cast<int32_t>(beg.size());
   t->n_chunks = nch;
   t->seg_max = seg_max;
-  const size_t cb = sizeof(int32_t) * std::max(nch, 1);
-  t->chunk_beg = static_cast<int32_t*>(dev_alloc(cb, s));
-  t->chunk_end = static_cast<int32_t*>(dev_alloc(cb, s));
-  t->chunk_blk = static_cast<int32_t*>(dev_alloc(cb, s));
-  t->chunk_j0 = static_cast<int32_t*>(dev_alloc(cb, s));
-  t->chunk_ns = static_cast<int32_t*>(dev_alloc(cb, s));
-  if (!t->chunk_beg || !t->chunk_end || !t->chunk_blk || !t->chunk_j0 || !t->chunk_ns) return hipErrorOutOfMemory;
-  t->bytes += 5 * static_cast<int64_t>(cb);
+  const size_t room = static_cast<size_t>(std::max(nch, 1));
+  t->chunk_beg = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * 5 * room, s));
+  if (!t->chunk_beg) return hipErrorOutOfMemory;
+  t->chunk_end = t->chunk_beg + room;
+  t->chunk_blk = t->chunk_end + room;
+  t->chunk_j0 = t->chunk_blk + room;
+  t->chunk_ns = t->chunk_j0 + room;
+  t->bytes += 5 * static_cast<int64_t>(sizeof(int32_t) * room);
+  std::vector<int32_t> all;
   if (nch > 0) {
-    GC_HIP_TRY(hipMemcpyAsync(t->chunk_beg, beg.data(), sizeof(int32_t) * nch, hipMemcpyHostToDevice, s));
-    GC_HIP_TRY(hipMemcpyAsync(t->chunk_end, end.data(), sizeof(int32_t) * nch, hipMemcpyHostToDevice, s));
-    GC_HIP_TRY(hipMemcpyAsync(t->chunk_blk, blk.data(), sizeof(int32_t) * nch, hipMemcpyHostToDevice, s));
-    GC_HIP_TRY(hipMemcpyAsync(t->chunk_j0, j0v.data(), sizeof(int32_t) * nch, hipMemcpyHostToDevice, s));
-    GC_HIP_TRY(hipMemcpyAsync(t->chunk_ns, nsv.data(), sizeof(int32_t) * nch, hipMemcpyHostToDevice, s));
+    all.reserve(5 * room);
+    for (const auto* v : {&beg, &end, &blk, &j0v, &nsv}) all.insert(all.end(), v->begin(), v->end());
+    GC_HIP_TRY(hipMemcpyAsync(t->chunk_beg, all.data(), sizeof(int32_t) * all.size(), hipMemcpyHostToDevice, s));
   }
   return hipStreamSynchronize(s);  // host vectors and Bufs are released on return
 }
@@ -975,12 +1042,19 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
   const Digits dg(key_bits(B), kRadixBits);
   const size_t mb = sizeof(int32_t) * mn;
   const bool two = dg.passes > 1;  // at most 32768 blocks: two passes
-  Buf row(mb, s), k1(two ? mb : 0, s), r1(two ? mb : 0, s), w1(two && t->weighted ? mb : 0, s);
-  RadixScratch scratch(m, dg.width, s);
-  Buf bits(sizeof(uint64_t) * std::max<int64_t>(words, 1), s), wcnt(sizeof(int32_t) * std::max<int64_t>(words, 1), s),
-      wrow(sizeof(int32_t) * (words + 1), s), wtile(sizeof(int32_t) * std::max<int64_t>(scan_tiles(words), 1), s);
-  if (!row.p || !k1.p || !r1.p || !w1.p || !scratch.ok() || !bits.p || !wcnt.p || !wrow.p || !wtile.p)
-    return hipErrorOutOfMemory;
+  Slab slab;
+  const size_t i_row = slab.reserve(mb), i_k1 = slab.reserve(two ? mb : 0), i_r1 = slab.reserve(two ? mb : 0),
+               i_w1 = slab.reserve(two && t->weighted ? mb : 0), i_bits = slab.reserve(sizeof(uint64_t) * words),
+               i_wcnt = slab.reserve(sizeof(int32_t) * words), i_wrow = slab.reserve(sizeof(int32_t) * (words + 1)),
+               i_wtile = slab.reserve(sizeof(int32_t) * scan_tiles(words));
+  RadixScratch scratch(m, dg.width, slab);
+  Buf mem(slab.total, s);
+  if (!mem.p) return hipErrorOutOfMemory;
+  scratch.take(slab, mem.p);
+  int32_t* const row = slab.take<int32_t>(mem.p, i_row);
+  uint64_t* const bits = slab.take<uint64_t>(mem.p, i_bits);
+  int32_t* const wcnt = slab.take<int32_t>(mem.p, i_wcnt);
+  int32_t* const wrow = slab.take<int32_t>(mem.p, i_wrow);
   if (m > 0) {
     RadixArgs a{};
     a.key = a_col;
@@ -991,31 +1065,31 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
     a.bits = dg.width;
     a.shift = t->log2W;
     if (two) {
-      a.key_out = k1.as<int32_t>();
-      a.row_out = r1.as<int32_t>();
-      a.w_out = w1.as<int32_t>();
+      a.key_out = slab.take<int32_t>(mem.p, i_k1);
+      a.row_out = slab.take<int32_t>(mem.p, i_r1);
+      a.w_out = slab.take<int32_t>(mem.p, i_w1);
       GC_HIP_TRY(radix_pass(a, scratch, s));
-      a.key = k1.as<int32_t>();
-      a.row = r1.as<int32_t>();
-      if (a.w) a.w = w1.as<int32_t>();
+      a.key = a.key_out;
+      a.row = a.row_out;
+      if (a.w) a.w = a.w_out;
       a.shift += dg.width;
     }
     a.key_out = t->col;
-    a.row_out = row.as<int32_t>();
+    a.row_out = row;
     a.w_out = t->w;
     a.low_out = col16;
     a.low_mask = t->W - 1;
     GC_HIP_TRY(radix_pass(a, scratch, s));
-    k_head_bits<<<grid_for(words, 4, 16384), 256, 0, s>>>(row.as<int32_t>(), t->col, m, t->log2W, words,
-                                                          bits.as<uint64_t>(), wcnt.as<int32_t>());
+    k_head_bits<<<grid_for(words, 4, 16384), 256, 0, s>>>(row, t->col, m, t->log2W, words,
+                                                          bits, wcnt);
     GC_HIP_TRY(hipGetLastError());
   }
-  GC_HIP_TRY(scan_queue(wcnt.as<int32_t>(), wrow.as<int32_t>(), words, wtile.as<int32_t>(), s));
-  k_block_rows<<<grid_for(B + 1, 256), 256, 0, s>>>(t->col, m, t->log2W, B, bits.as<uint64_t>(), wrow.as<int32_t>(),
+  GC_HIP_TRY(scan_queue(wcnt, wrow, words, slab.take<int32_t>(mem.p, i_wtile), s));
+  k_block_rows<<<grid_for(B + 1, 256), 256, 0, s>>>(t->col, m, t->log2W, B, bits, wrow,
                                                     words, t->blk_rowoff);
   GC_HIP_TRY(hipGetLastError());
   int32_t P32 = 0;
-  GC_HIP_TRY(hipMemcpyAsync(&P32, wrow.as<int32_t>() + words, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  GC_HIP_TRY(hipMemcpyAsync(&P32, wrow + words, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   GC_HIP_TRY(hipStreamSynchronize(s));
   const int64_t P = P32;
   t->P = P;
@@ -1032,7 +1106,7 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
                                 mn * (t->weighted ? 2 : 1)) +
              static_cast<int64_t>(sizeof(uint16_t)) * P;
   k_local_rows<<<grid_for(heads ? head_words : words, 4, 16384), 256, 0, s>>>(
-      row.as<int32_t>(), m, words, bits.as<uint64_t>(), wrow.as<int32_t>(), t->k - 1, t->id_map, t->row_ptr, t->id16,
+      row, m, words, bits, wrow, t->k - 1, t->id_map, t->row_ptr, t->id16,
       heads, head_words);
   k_range_rows<<<grid_for(static_cast<int64_t>(R + 1) * B, 256, 65536), 256, 0, s>>>(t->id_map, t->blk_rowoff, B, R,
                                                                                      t->log2k, t->range_ptr);
@@ -1049,7 +1123,7 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
     t->m_pad = 0;
   }
   if (push_stream) GC_HIP_TRY(build_push_expand(t, s));
-  return hipStreamSynchronize(s);  // the Bufs are released on return
+  return hipStreamSynchronize(s);  // the Buf is released on return
 }
 
 }  // namespace gcx

@@ -25,6 +25,7 @@ struct gc_graph_s {
   int32_t* t_rowptr = nullptr;
   int32_t* t_colidx = nullptr;
   int32_t* t_w = nullptr;
+  void* scratch = nullptr;  // holds the arrays from contrib to arc_pre (but not those allocated later)
   // PageRank scratch: contributions (two buffers for the fused plain pull),
   // push accumulators, FP64 dangling partials / totals and a done counter
   float* contrib[2] = {nullptr, nullptr};
@@ -117,7 +118,7 @@ struct gc_tocab_s {
   int2* seg = nullptr;            // [B][R+1]: first local row of block b in range j, shift to range-major index
   int32_t* rstart = nullptr;      // [R+1] range-major start of merge range j
   uint16_t* id16s = nullptr;      // [P] id16 in range-major order
-  int32_t* chunk_beg = nullptr;   // [n_chunks] first local row
+  int32_t* chunk_beg = nullptr;   // [n_chunks] first local row (one buffer holds the five chunk arrays)
   int32_t* chunk_end = nullptr;   // [n_chunks] one past the last local row
   int32_t* chunk_blk = nullptr;   // [n_chunks] block
   int32_t* chunk_j0 = nullptr;    // [n_chunks] first merge range the chunk's rows fall in
@@ -169,6 +170,21 @@ struct Buf {
   Buf& operator=(const Buf&) = delete;
   template <class T> T* as() const { return static_cast<T*>(p); }
   void* release() { void* q = p; p = nullptr; return q; }
+};
+
+// Several arrays in one buffer of the library allocator (an allocation goes
+// through the caller's hook): reserve() every array, allocate once, take().
+struct Slab {
+  std::vector<size_t> at;
+  size_t total = 0;
+  size_t reserve(size_t bytes) {
+    at.push_back(total);
+    total += (std::max<size_t>(bytes, 1) + 255) & ~size_t(255);
+    return at.size() - 1;
+  }
+  template <class T> T* take(void* base, size_t i) const {
+    return reinterpret_cast<T*>(static_cast<char*>(base) + at[i]);
+  }
 };
 
 // ---- construction kernels (gc_build.hip) ----

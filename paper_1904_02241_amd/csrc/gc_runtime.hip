@@ -68,24 +68,57 @@ bool is_device_ptr(const void* p) {
   return attr.type == hipMemoryTypeDevice || attr.type == hipMemoryTypeManaged;
 }
 
+// Pinned mirrors of the traversal counters, one per graph. Allocating and
+// freeing one costs 80 us, most of what the host does to load a small graph,
+// so up to kMirrorsKept of them wait here for the next graph (a graph is
+// freed after the device has finished with it).
+constexpr size_t kMirrorsKept = 64;
+std::mutex g_mirror_mu;
+std::vector<int32_t*> g_mirrors;
+
+int32_t* mirror_get() {
+  {
+    std::lock_guard<std::mutex> lk(g_mirror_mu);
+    if (!g_mirrors.empty()) {
+      int32_t* p = g_mirrors.back();
+      g_mirrors.pop_back();
+      return p;
+    }
+  }
+  void* p = nullptr;
+  if (hipHostMalloc(&p, sizeof(int32_t) * gcx::kStatSlots, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return static_cast<int32_t*>(p);
+}
+
+void mirror_put(int32_t* p) {
+  {
+    std::lock_guard<std::mutex> lk(g_mirror_mu);
+    if (g_mirrors.size() < kMirrorsKept) {
+      g_mirrors.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
 void free_graph(gc_graph g) {
   if (!g) return;
-  void* bufs[] = {g->rowptr, g->colidx, g->w, g->t_rowptr, g->t_colidx, g->t_w, g->contrib[0], g->contrib[1],
-                  g->sums, g->dpart[0], g->dpart[1], g->dtotal, g->counter, g->front, g->next, g->queue[0], g->queue[1],
-                  g->stats, g->tile_row_in, g->visited, g->mark, g->lpart, g->ltotal, g->rank_tmp, g->bc_sigma,
-                  g->bc_coef, g->bc_depth, g->bc_order, g->arc_deg,
-                  g->arc_pre};
+  void* bufs[] = {g->rowptr, g->colidx, g->w, g->t_rowptr, g->t_colidx, g->t_w, g->scratch, g->tile_row_in,
+                  g->lpart, g->ltotal, g->rank_tmp, g->bc_sigma, g->bc_coef, g->bc_depth, g->bc_order};
   for (void* p : bufs)
     if (p) gcx::dev_free(p, nullptr);
-  if (g->stats_host) (void)hipHostFree(g->stats_host);
+  if (g->stats_host) mirror_put(g->stats_host);
   delete g;
 }
 
 void free_tocab(gc_tocab t) {
   if (!t) return;
   void* bufs[] = {t->blk_rowoff, t->row_ptr, t->id_map, t->col, t->w, t->range_ptr, t->partial, t->pmin,
-                  t->tile_row, t->col16, t->chunk_beg, t->chunk_end, t->chunk_blk, t->wtile_row, t->id16,
-                  t->heads, t->seg, t->rstart, t->id16s, t->chunk_j0, t->chunk_ns, t->bc_part,
+                  t->tile_row, t->col16, t->chunk_beg, t->wtile_row, t->id16,
+                  t->heads, t->seg, t->rstart, t->id16s, t->bc_part,
                   t->val32, t->w_pad, t->w8, t->xid16, t->xperm, t->xstart, t->xc, t->pcol16, t->pheads};
   for (void* p : bufs)
     if (p) gcx::dev_free(p, nullptr);
@@ -260,31 +293,37 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
     g->w = static_cast<int32_t*>(gcx::dev_alloc(mb, stream));
     g->t_w = static_cast<int32_t*>(gcx::dev_alloc(mb, stream));
   }
-  g->contrib[0] = static_cast<float*>(gcx::dev_alloc(sizeof(float) * n, stream));
-  g->contrib[1] = static_cast<float*>(gcx::dev_alloc(sizeof(float) * n, stream));
-  g->sums = static_cast<double*>(gcx::dev_alloc(sizeof(double) * n, stream));
-  g->dpart[0] = static_cast<double*>(gcx::dev_alloc(sizeof(double) * g->dpart_slots, stream));
-  g->dpart[1] = static_cast<double*>(gcx::dev_alloc(sizeof(double) * gcx::kDangSlots, stream));
-  g->dtotal = static_cast<double*>(gcx::dev_alloc(sizeof(double) * 2, stream));
-  g->counter = static_cast<unsigned*>(gcx::dev_alloc(sizeof(unsigned) * 4, stream));
-  const size_t words = (static_cast<size_t>(n) + 31) / 32;
-  g->front = static_cast<uint32_t*>(gcx::dev_alloc(sizeof(uint32_t) * words, stream));
-  g->next = static_cast<uint32_t*>(gcx::dev_alloc(sizeof(uint32_t) * words, stream));
-  g->queue[0] = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * n, stream));
-  g->queue[1] = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * n, stream));
-  g->stats = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * gcx::kStatSlots, stream));
-  g->visited = static_cast<uint32_t*>(gcx::dev_alloc(sizeof(uint32_t) * ((static_cast<size_t>(n) + 31) / 32), stream));
-  g->mark = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * n, stream));
-  g->arc_deg = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * n, stream));
-  g->arc_pre = static_cast<int32_t*>(gcx::dev_alloc(sizeof(int32_t) * (static_cast<size_t>(n) + 1), stream));
-  bool ok = g->visited && g->mark && g->arc_deg && g->arc_pre && g->rowptr && g->colidx && g->t_rowptr && g->t_colidx && (!g->weighted || (g->w && g->t_w)) &&
-            g->contrib[0] && g->contrib[1] && g->sums && g->dpart[0] && g->dpart[1] && g->dtotal && g->counter && g->front &&
-            g->next && g->queue[0] && g->queue[1] && g->stats;
-  if (ok && hipHostMalloc(reinterpret_cast<void**>(&g->stats_host), sizeof(int32_t) * gcx::kStatSlots,
-                          hipHostMallocDefault) !=
-                hipSuccess) {
-    g->stats_host = nullptr;
-    ok = false;
+  const size_t words = (static_cast<size_t>(n) + 31) / 32, nn = static_cast<size_t>(n);
+  gcx::Slab slab;
+  const size_t contrib0 = slab.reserve(sizeof(float) * nn), contrib1 = slab.reserve(sizeof(float) * nn),
+               sums = slab.reserve(sizeof(double) * nn), dpart0 = slab.reserve(sizeof(double) * g->dpart_slots),
+               dpart1 = slab.reserve(sizeof(double) * gcx::kDangSlots), dtotal = slab.reserve(sizeof(double) * 2),
+               counter = slab.reserve(sizeof(unsigned) * 4), front = slab.reserve(sizeof(uint32_t) * words),
+               next = slab.reserve(sizeof(uint32_t) * words), queue0 = slab.reserve(sizeof(int32_t) * nn),
+               queue1 = slab.reserve(sizeof(int32_t) * nn), stats = slab.reserve(sizeof(int32_t) * gcx::kStatSlots),
+               visited = slab.reserve(sizeof(uint32_t) * words), mark = slab.reserve(sizeof(int32_t) * nn),
+               arc_deg = slab.reserve(sizeof(int32_t) * nn), arc_pre = slab.reserve(sizeof(int32_t) * (nn + 1));
+  g->scratch = gcx::dev_alloc(slab.total, stream);
+  bool ok = g->rowptr && g->colidx && g->t_rowptr && g->t_colidx && (!g->weighted || (g->w && g->t_w)) && g->scratch;
+  if (ok) {
+    g->contrib[0] = slab.take<float>(g->scratch, contrib0);
+    g->contrib[1] = slab.take<float>(g->scratch, contrib1);
+    g->sums = slab.take<double>(g->scratch, sums);
+    g->dpart[0] = slab.take<double>(g->scratch, dpart0);
+    g->dpart[1] = slab.take<double>(g->scratch, dpart1);
+    g->dtotal = slab.take<double>(g->scratch, dtotal);
+    g->counter = slab.take<unsigned>(g->scratch, counter);
+    g->front = slab.take<uint32_t>(g->scratch, front);
+    g->next = slab.take<uint32_t>(g->scratch, next);
+    g->queue[0] = slab.take<int32_t>(g->scratch, queue0);
+    g->queue[1] = slab.take<int32_t>(g->scratch, queue1);
+    g->stats = slab.take<int32_t>(g->scratch, stats);
+    g->visited = slab.take<uint32_t>(g->scratch, visited);
+    g->mark = slab.take<int32_t>(g->scratch, mark);
+    g->arc_deg = slab.take<int32_t>(g->scratch, arc_deg);
+    g->arc_pre = slab.take<int32_t>(g->scratch, arc_pre);
+    g->stats_host = mirror_get();
+    ok = g->stats_host != nullptr;
   }
   if (g->stats_host) std::memset(g->stats_host, 0, sizeof(int32_t) * gcx::kStatSlots);
   if (!ok) {
