@@ -220,8 +220,9 @@ int pagerank_iter_noalloc(gc_graph g, gc_tocab t, int32_t dir_if_plain, float da
  * stopping after the first k with delta_k <= tol, or after max_iters.
  * rank_in, rank_out: device float[n], must not overlap; rank_out receives
  * the last iterate. *iters_out (host) = iterations run; *delta_out (host,
- * NULL to skip) = the last delta. Synchronises `stream` once per iteration
- * to read delta_k. The first call on a graph allocates its convergence
+ * NULL to skip) = the last delta. Waits for `stream` once per iteration to
+ * read delta_k, with the next iteration already queued (its kernels leave at
+ * once when delta_k ended the run). The first call on a graph allocates its convergence
  * buffers (an FP32 iterate and one FP64 slot per update work-group), freed
  * by graph_free. Errors: GC_EINVAL for bad arguments (tol < 0 or NaN,
  * max_iters < 1, NULL iters_out, plus pagerank_iter's checks), GC_ENOMEM. */
@@ -271,8 +272,8 @@ int spmv(gc_graph g, gc_tocab t, const float* x, float* y, hipStream_t stream);
  * stream layout (blocks up to 2^15), where a pull level runs as TOCAB on
  * graphs with at most 10 arcs per vertex while at least 1/64 of the arcs
  * end at unvisited vertices, as plain pull otherwise). levels (host,
- * nullable) receives the number of levels run. Synchronises `stream` once
- * per level to read the frontier size. */
+ * nullable) receives the number of levels run. Waits for `stream` once per
+ * level to read the frontier size. */
 int bfs_pull(gc_graph g, gc_tocab t, int32_t source, int32_t* depth, int32_t* levels,
              uint32_t policy, hipStream_t stream);
 
@@ -284,7 +285,7 @@ int bfs_pull(gc_graph g, gc_tocab t, int32_t source, int32_t* depth, int32_t* le
  * unreachable. Requires a weighted graph (GC_EINVAL otherwise). Distances
  * are int32: if a finite distance would reach INT32_MAX the call returns
  * GC_EOVERFLOW (dist is then not meaningful). rounds (host, nullable)
- * receives the number of rounds. Synchronises once per round. */
+ * receives the number of rounds. Waits for `stream` once per round. */
 int sssp_pull(gc_graph g, gc_tocab t, int32_t source, int32_t* dist, int32_t* rounds,
               uint32_t policy, hipStream_t stream);
 
@@ -302,7 +303,7 @@ int sssp_pull(gc_graph g, gc_tocab t, int32_t source, int32_t* dist, int32_t* ro
  * partition t with FP64 per-block partials and the Figure 5 merge, or plain
  * pull with t == NULL; GC_POLICY_PUSH; GC_POLICY_HEURISTIC); GC_POLICY_LEARNED
  * is refused. The first call allocates 20 bytes per vertex on g (and 8 per
- * local row on t), freed with them. Synchronises `stream` once per level;
+ * local row on t), freed with them. Waits for `stream` once per level;
  * returns after the last source's work is complete. The per-level record of
  * traversal_trace covers the forward levels of every source in turn.
  * Errors: GC_EINVAL for bad arguments (NULL or host bc, a source out of

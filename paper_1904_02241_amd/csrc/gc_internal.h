@@ -56,7 +56,7 @@ struct gc_graph_s {
   int32_t* arc_deg = nullptr;
   int32_t* arc_pre = nullptr;
   bool bits_clean = false;      // front and next are all zero
-  int32_t level_seq = 0;        // number of the last level published to stats_host
+  uint32_t level_seq = 0;       // number of the last level (or convergence step) published to stats_host
   // betweenness centrality (allocated by the first bc_accumulate call):
   // path counts, two alternating arrays of (1 + delta) / sigma, BFS depths
   // and the vertices in level order of the current source
@@ -293,6 +293,11 @@ hipError_t collect(gc_graph g, gc_tocab* parts, int32_t n_parts, bool bfs, const
                    float* features, float* times, int32_t max_rows, int32_t* rows, hipStream_t s);
 void sched_features(int64_t n, int64_t m, int64_t n_f, int64_t m_f, int32_t level, double prior_ms,
                     int64_t prior_arcs, float* f);
+
+// Waits until the pinned word holds `seq`, which a kernel queued on s writes:
+// it spins for as long as short work takes (a stream synchronisation costs
+// more than such kernels), then leaves the waiting to the runtime.
+hipError_t wait_mirror(const int32_t* word, int32_t seq, hipStream_t s);
 
 // The scheduler's 6 inputs for a level (the same arithmetic on the host and
 // in the device-side decision): log1p(frontier vertices), log1p(frontier

@@ -16,6 +16,7 @@
 
 #include <climits>
 #include <cstdlib>
+#include <cstring>
 
 #include <type_traits>
 #include <vector>
@@ -29,6 +30,17 @@
 namespace {
 
 int g_cus = 256;  // compute units of the GPU (read once by pagerank_setup)
+
+// Convergence mode: an iteration's L1 change, from its partials to the host
+// (two words of the FP64 value, then `seq`, in pinned memory) and to the
+// stop flag.
+struct Change {
+  const double* lpart = nullptr;  // null: clear the flag (when given)
+  double tol = 0.0;
+  int32_t* stop = nullptr;
+  int32_t* host = nullptr;
+  int32_t seq = 0;
+};
 
 // D for the next iteration: the partials summed in index order by one
 // work-group (deterministic).
@@ -47,15 +59,22 @@ __device__ __forceinline__ double reduce_slots(const double* __restrict__ slots,
 // Total of the per-work-group dangling partials (and, in convergence mode,
 // of the L1-change partials), in a fixed order.
 __global__ __launch_bounds__(1024) void k_reduce_dangling(const double* __restrict__ dpart, int32_t count,
-                                                          double* __restrict__ dtotal,
-                                                          const double* __restrict__ lpart,
-                                                          double* __restrict__ ltotal) {
+                                                          double* __restrict__ dtotal, Change ch) {
+  if (ch.lpart && stopped(ch.stop)) return;  // uniform
   __shared__ double part[1024 / kWave];
   const double t = reduce_slots(dpart, count, part);
   if (threadIdx.x == 0) *dtotal = t;
-  if (lpart) {
-    const double l = reduce_slots(lpart, count, part);
-    if (threadIdx.x == 0) *ltotal = l;
+  if (ch.lpart) {
+    const double l = reduce_slots(ch.lpart, count, part);
+    if (threadIdx.x == 0) {
+      if (l <= ch.tol) *ch.stop = 1;
+      const uint64_t b = static_cast<uint64_t>(__double_as_longlong(l));
+      for (int i = 0; i < 2; ++i)
+        __hip_atomic_store(ch.host + i, static_cast<int32_t>(b >> (32 * i)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(ch.host + 2, ch.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  } else if (ch.stop && threadIdx.x == 0) {
+    *ch.stop = 0;  // before the first iteration
   }
 }
 
@@ -83,7 +102,9 @@ __global__ __launch_bounds__(kThreads) void k_pr_tocab_pull(const int32_t* __res
                                                             const int32_t* __restrict__ col,
                                                             const int32_t* __restrict__ tile_row,
                                                             const float* __restrict__ c,
-                                                            float* __restrict__ partial) {
+                                                            float* __restrict__ partial,
+                                                            const int32_t* __restrict__ stop) {
+  if (stopped(stop)) return;
   __shared__ float vals[kStageCap];
   const int32_t r0 = tile_row[blockIdx.x], r1 = tile_row[blockIdx.x + 1];
   if (r0 >= r1) return;
@@ -201,8 +222,9 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
     const int32_t* __restrict__ chunk_end, const int32_t* __restrict__ chunk_blk,
     const int32_t* __restrict__ chunk_j0, const int32_t* __restrict__ chunk_ns, const int2* __restrict__ seg,
     int32_t R, int32_t log2W, int32_t n, const float* __restrict__ c, float* __restrict__ partial,
-    uint32_t partial_bytes) {
+    uint32_t partial_bytes, const int32_t* __restrict__ stop) {
   extern __shared__ float lds[];
+  if (stopped(stop)) return;
   const int32_t W = 1 << log2W;
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
@@ -332,6 +354,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_plain_pull(const int32_t* __res
                                                             const int32_t* __restrict__ t_col,
                                                             const int32_t* __restrict__ tile_row,
                                                             const float* __restrict__ c_in, Update u) {
+  if (stopped(u.stop)) return;
   __shared__ float vals[kStageCap];
   const int32_t r0 = tile_row[blockIdx.x], r1 = tile_row[blockIdx.x + 1];
   double mine = 0.0, dl = 0.0;
@@ -350,6 +373,7 @@ template <int K, bool kFlat>
 __global__ __launch_bounds__(kThreads) void k_pr_merge(const int32_t* __restrict__ range_ptr, int32_t B,
                                                        const uint16_t* __restrict__ id16,
                                                        const float* __restrict__ partial, Update u) {
+  if (stopped(u.stop)) return;
   __shared__ double acc[K];
   const double share = dangling_share(u);
   merge_accumulate<K, kFlat>(range_ptr, B, id16, partial, blockIdx.x, acc);
@@ -435,6 +459,7 @@ template <int K, int NT = merge_threads<K>()>
 __global__ __launch_bounds__(NT) void k_pr_merge_persist(const int32_t* __restrict__ rstart,
                                                          const uint16_t* __restrict__ id16s,
                                                          const float* __restrict__ partial, int32_t R, Update u) {
+  if (stopped(u.stop)) return;
   __shared__ double acc[K];
   for (int i = threadIdx.x; i < K; i += NT) acc[i] = 0.0;
   __syncthreads();
@@ -571,7 +596,8 @@ __global__ __launch_bounds__(kThreads) void k_pr_push(const int32_t* __restrict_
                                                       const int32_t* __restrict__ id_map,
                                                       const int32_t* __restrict__ col,
                                                       const float* __restrict__ c, double* __restrict__ sums,
-                                                      int64_t rows) {
+                                                      int64_t rows, const int32_t* __restrict__ stop) {
+  if (stopped(stop)) return;
   __shared__ int32_t start[kThreads];
   __shared__ int32_t first[kThreads];
   __shared__ float val[kThreads];
@@ -626,6 +652,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds(const int32_t* 
                                                                  const int32_t* __restrict__ id_map,
                                                                  const int32_t* __restrict__ col, int32_t log2W,
                                                                  const float* __restrict__ c, Update u) {
+  if (stopped(u.stop)) return;
   extern __shared__ double acc[];  // the block's W sums
   const int32_t W = 1 << log2W;
   const int32_t v0 = static_cast<int32_t>(blockIdx.x) << log2W;
@@ -815,6 +842,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
     const int32_t* __restrict__ blk_rowoff, const int32_t* __restrict__ row_ptr,
     const uint16_t* __restrict__ pcol16, const gc_head_word* __restrict__ pheads, int32_t log2W,
     const float* __restrict__ xc_in, PushX x, float* __restrict__ xc_out, Update u) {
+  if (stopped(u.stop)) return;
   extern __shared__ double acc[];  // the block's W sums, then (as FP32) its W new contributions
   constexpr int kPer = kPushLdsMaxWidth / kPushLdsThreads;
   constexpr int kWaves = kPushLdsThreads / kWave;
@@ -891,6 +919,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
 }
 
 __global__ __launch_bounds__(kThreads) void k_pr_apply(double* __restrict__ sums, Update u) {
+  if (stopped(u.stop)) return;
   const int32_t v = blockIdx.x * kThreads + threadIdx.x;
   const double D = dangling_total(u, dangling_share(u));
   double mine = 0.0, dl = 0.0;
@@ -1020,11 +1049,11 @@ hipError_t spmv_stream(gc_graph g, gc_tocab t, const float* x, const float* vals
       if (vals)
         k_pr_tocab_pull_lds<true><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, vals, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->R, t->log2W, g->n, x, t->partial, bytes);
+            t->chunk_ns, t->seg, t->R, t->log2W, g->n, x, t->partial, bytes, nullptr);
       else
         k_pr_tocab_pull_lds<false><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->R, t->log2W, g->n, x, t->partial, bytes);
+            t->chunk_ns, t->seg, t->R, t->log2W, g->n, x, t->partial, bytes, nullptr);
     }
   }
   ProfScope prof("spmv_merge", s);
@@ -1077,7 +1106,7 @@ hipError_t ladder_run(gc_graph g, gc_tocab t, int32_t method, float damping, int
   u.dcount = 1;
   u.contrib = g->contrib[0];
   k_pr_init<<<vgrid, kThreads, 0, s>>>(rank_in, u, cb ? g->sums : nullptr);
-  k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart[0], vgrid, g->dtotal, nullptr, nullptr);
+  k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart[0], vgrid, g->dtotal, Change());
   GC_HIP_TRY(hipGetLastError());
   int cur = 0;
   for (int32_t it = 0; it < iters; ++it) {
@@ -1112,7 +1141,7 @@ hipError_t ladder_run(gc_graph g, gc_tocab t, int32_t method, float damping, int
     }
     {
       ProfScope prof("pr_dangling", s);
-      k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart[0], vgrid, g->dtotal + ((it + 1) & 1), nullptr, nullptr);
+      k_reduce_dangling<<<1, 1024, 0, s>>>(g->dpart[0], vgrid, g->dtotal + ((it + 1) & 1), Change());
     }
     GC_HIP_TRY(hipGetLastError());
   }
@@ -1234,11 +1263,16 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   // turn), else reduced to dtotal[slot], as in convergence mode, whose L1
   // change needs that kernel anyway
   const bool few = parts <= kDangFused && buf.dpart[1] && !cv;
+  Change change;
+  if (cv) {
+    change.tol = cv->tol;
+    change.stop = reinterpret_cast<int32_t*>(g->ltotal + 2);
+  }
   auto hand_over = [&](int32_t count, int slot) {
     const bool fused = few && count <= kDangFused;
     if (!fused) {
       ProfScope prof("pr_dangling", s);
-      k_reduce_dangling<<<1, 1024, 0, s>>>(u.dpart, count, buf.dtotal + slot, u.lpart, g->ltotal);
+      k_reduce_dangling<<<1, 1024, 0, s>>>(u.dpart, count, buf.dtotal + slot, change);
     }
     u.din = fused ? u.dpart : buf.dtotal + slot;
     u.dcount = fused ? count : 1;
@@ -1249,7 +1283,26 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   // convergence mode: iterates alternate between rank_out and rank_tmp,
   // each compared with the one before it
   float* const iterate[2] = {rank_out, cv ? g->rank_tmp : nullptr};
-  if (cv) u.lpart = g->lpart;
+  if (cv) {
+    u.lpart = g->lpart;
+    u.stop = change.stop;
+    change.lpart = g->lpart;
+  }
+  // Iteration `it` is queued before the host waits for the change of the one
+  // before it (in a ring of four pinned slots), so the GPU does not idle
+  // while the host is told; past the last iteration its kernels find the stop
+  // flag set and leave. The change of iteration j: its slot, and the number
+  // that marks it.
+  auto slot_of = [&](int32_t j) { return g->stats_host + kStatOut + 4 * (j & 3); };
+  const uint32_t seq0 = g->level_seq + 1;
+  auto seq_of = [&](int32_t j) { return static_cast<int32_t>(seq0 + static_cast<uint32_t>(j)); };
+  auto converged = [&](int32_t j, bool* done) -> hipError_t {
+    GC_HIP_TRY(wait_mirror(slot_of(j) + 2, seq_of(j), s));
+    std::memcpy(&cv->delta, slot_of(j), sizeof(double));
+    cv->iters = j + 1;
+    *done = cv->delta <= cv->tol;
+    return hipSuccess;
+  };
   int cur = 0;
   for (int32_t it = 0; it < iters; ++it) {
     u.rank_out = (it == iters - 1) ? rank_out : nullptr;
@@ -1266,7 +1319,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
             k_pr_tocab_pull_lds<false><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
                 t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
                 t->chunk_ns, t->seg, t->R, t->log2W, n, buf.contrib[0], buf.partial,
-                static_cast<uint32_t>(sizeof(float) * (t->P + 8)));
+                static_cast<uint32_t>(sizeof(float) * (t->P + 8)), u.stop);
         }
         u.contrib = buf.contrib[0];
         ProfScope prof("pr_merge", s);
@@ -1281,7 +1334,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
         {
           ProfScope prof("pr_tocab_pull", s);
           k_pr_tocab_pull<<<t->n_tiles, kThreads, 0, s>>>(t->row_ptr, t->col, t->tile_row, buf.contrib[0],
-                                                          buf.partial);
+                                                          buf.partial, u.stop);
         }
         u.contrib = buf.contrib[0];  // safe in place: the pull pass has finished reading c
         ProfScope prof("pr_merge", s);
@@ -1321,25 +1374,31 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
         if (P > 0) {
           ProfScope prof("pr_tocab_push", s);
           k_pr_push<<<static_cast<uint32_t>((P + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-              t->row_ptr, t->id_map, t->col, buf.contrib[0], buf.sums, P);
+              t->row_ptr, t->id_map, t->col, buf.contrib[0], buf.sums, P, u.stop);
         }
       } else {
         ProfScope prof("pr_plain_push", s);
-        k_pr_push<<<vgrid, kThreads, 0, s>>>(g->rowptr, nullptr, g->colidx, buf.contrib[0], buf.sums, n);
+        k_pr_push<<<vgrid, kThreads, 0, s>>>(g->rowptr, nullptr, g->colidx, buf.contrib[0], buf.sums, n, u.stop);
       }
       u.contrib = buf.contrib[0];
       ProfScope prof("pr_apply", s);
       k_pr_apply<<<vgrid, kThreads, 0, s>>>(buf.sums, u);
     }
+    if (cv) {
+      change.host = slot_of(it);
+      change.seq = seq_of(it);
+      ++g->level_seq;
+    }
     hand_over(parts, (it + 1) & 1);
     GC_HIP_TRY(hipGetLastError());
-    if (cv) {  // read this iteration's L1 change
-      double delta = 0.0;
-      GC_HIP_TRY(hipMemcpyAsync(&delta, g->ltotal, sizeof(double), hipMemcpyDeviceToHost, s));
-      GC_HIP_TRY(hipStreamSynchronize(s));
-      cv->iters = it + 1;
-      cv->delta = delta;
-      if (delta <= cv->tol) break;
+    if (cv && it > 0) {
+      bool done = false;
+      GC_HIP_TRY(converged(it - 1, &done));
+      if (done) break;
+    }
+    if (cv && it == iters - 1) {
+      bool done = false;
+      GC_HIP_TRY(converged(it, &done));
     }
   }
   if (cv && (cv->iters & 1) == 0)  // the last iterate is in rank_tmp

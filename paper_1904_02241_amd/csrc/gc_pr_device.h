@@ -38,8 +38,13 @@ struct Update {
   float* rank_out;        // written on the last iteration only (else null)
   const float* rank_prev = nullptr;  // convergence mode: the previous iterate
   double* lpart = nullptr;           // convergence mode: L1 change per work-group
+  const int32_t* stop = nullptr;     // convergence mode: set once an iterate has converged
   int32_t n;
 };
+
+// Convergence mode queues an iteration before it knows the change of the one
+// before; the kernels of an iteration past the last do nothing.
+__device__ __forceinline__ bool stopped(const int32_t* stop) { return stop && *stop; }
 
 // r'[v] from the neighbour sum; writes c'[v] (and r'[v] on the last pass),
 // returns r'[v] when v has no out-arcs (its share of the next D), else 0.

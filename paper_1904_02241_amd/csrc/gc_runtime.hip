@@ -2,6 +2,7 @@
 // argument validation (done before anything is queued), handle lifetime.
 
 #include <algorithm>
+#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdint>
@@ -145,6 +146,17 @@ void* dev_alloc(size_t bytes, hipStream_t s) {
     return nullptr;
   }
   return p;
+}
+
+hipError_t wait_mirror(const int32_t* word, int32_t seq, hipStream_t s) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 1;; ++i) {
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+    if ((i & 63) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) break;
+  }
+  const hipError_t e = hipStreamSynchronize(s);
+  if (e != hipSuccess) return e;
+  return __atomic_load_n(word, __ATOMIC_ACQUIRE) == seq ? hipSuccess : hipErrorUnknown;
 }
 
 void dev_free(void* p, hipStream_t s) {
@@ -675,7 +687,7 @@ int pagerank_converge(gc_graph g, gc_tocab t, int32_t dir_if_plain, float dampin
   if (!iters_out) return fail(GC_EINVAL, "pagerank_converge: NULL iters_out");
   if (!g->lpart) {  // first call on this graph: its convergence buffers
     g->lpart = static_cast<double*>(gcx::dev_alloc(sizeof(double) * g->dpart_slots, stream));
-    g->ltotal = static_cast<double*>(gcx::dev_alloc(2 * sizeof(double), stream));
+    g->ltotal = static_cast<double*>(gcx::dev_alloc(3 * sizeof(double), stream));
     g->rank_tmp = static_cast<float*>(gcx::dev_alloc(sizeof(float) * std::max<int32_t>(g->n, 1), stream));
     if (!g->lpart || !g->ltotal || !g->rank_tmp) {
       for (void* p : {static_cast<void*>(g->lpart), static_cast<void*>(g->ltotal), static_cast<void*>(g->rank_tmp)})

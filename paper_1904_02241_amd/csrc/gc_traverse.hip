@@ -1788,17 +1788,9 @@ hipError_t stream_weights(gc_tocab t, hipStream_t s) {
   return hipMemsetAsync(t->w_pad + t->m, 0, sizeof(int32_t) * (t->m_pad - t->m), s);
 }
 
-// Waits until the pinned mirror holds level `seq`'s counters: it spins for
-// as long as a short level takes (a stream synchronisation costs more than
-// such a level's kernels), then leaves the waiting to the runtime.
+// Waits until the pinned mirror holds level `seq`'s counters.
 hipError_t wait_stats(gc_graph g, int32_t seq, hipStream_t s) {
-  const auto t0 = std::chrono::steady_clock::now();
-  for (int i = 1;; ++i) {
-    if (__atomic_load_n(g->stats_host + gcx::kStatSeq, __ATOMIC_ACQUIRE) == seq) return hipSuccess;
-    if ((i & 63) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) break;
-  }
-  GC_HIP_TRY(hipStreamSynchronize(s));
-  return __atomic_load_n(g->stats_host + gcx::kStatSeq, __ATOMIC_ACQUIRE) == seq ? hipSuccess : hipErrorUnknown;
+  return gcx::wait_mirror(g->stats_host + gcx::kStatSeq, seq, s);
 }
 
 // Work-groups for a pass over `items`, each thread striding over them.
@@ -1842,7 +1834,7 @@ struct Frontier {
       k_fill_i32<<<stride_grid(words()), kThreads, 0, s>>>(reinterpret_cast<int32_t*>(g->next), words(), 0);
     }
     g->bits_clean = false;  // until the traversal has ended well
-    const int32_t seq = ++g->level_seq;
+    const int32_t seq = static_cast<int32_t>(++g->level_seq);
     k_start<<<stride_grid(g->n), kThreads, 0, s>>>(g->n, src, g->rowptr, value, mark, sigma, coef, q[0], p[0], g->stats,
                                                    g->stats_host, seq);
     GC_HIP_TRY(hipGetLastError());
@@ -1903,7 +1895,7 @@ struct Frontier {
       dec.clock_khz = g->clock_khz;
       lds = level_decide_lds(dec.K);
     }
-    const int32_t seq = ++g->level_seq;
+    const int32_t seq = static_cast<int32_t>(++g->level_seq);
     const bool clear = dirty[cur];
     k_level_end<<<clear ? stride_grid(words()) : 1, kThreads, lds, s>>>(g->stats, g->stats_host, seq, dec,
                                                                         clear ? front() : nullptr, words());
