@@ -561,8 +561,54 @@ __global__ void k_seg_table(const int32_t* __restrict__ range_ptr, const int32_t
   if (b == 0) rstart[j] = j < R ? rm_start[jb] : static_cast<int32_t>(P);
 }
 
+// Arcs per chunk, of kSizes sizes from `base` up in steps of 1/16: the one
+// that costs least. The pull runs a round of 256 chunks (one per CU) in its
+// longest chunk's time and `fill` (in arcs: loading the slice, and the waves
+// that end early), so a few chunks past a multiple of 256 cost as much as 256
+// more: 300,007 vertices of 16 arcs took 487 us for 20 iterations in 264
+// chunks, 389 in 248. Lane i of each wave counts size i's chunks over the
+// wave's share of the blocks; a block has at least one chunk per cap ranges.
+constexpr int kSizes = 64;
+__global__ __launch_bounds__(1024) void k_chunk_size(const int32_t* __restrict__ range_ptr,
+                                                     const int32_t* __restrict__ row_ptr, int32_t B, int32_t R,
+                                                     int32_t cap, int32_t base, int32_t fill,
+                                                     int32_t* __restrict__ out) {
+  __shared__ int32_t count[kSizes], longest[kSizes];
+  const int lane = gcd::lane_id(), wave = static_cast<int>(threadIdx.x) / kWave;
+  if (wave == 0) count[lane] = longest[lane] = 0;
+  __syncthreads();
+  const uint32_t size = static_cast<uint32_t>(fminf(base * exp2f(lane * 0.0875f), 2147483647.f));
+  int32_t mine = 0;
+  uint32_t top = 0;
+  const uint32_t least = static_cast<uint32_t>((R + cap - 1) / cap);
+  for (int32_t b0 = wave * kWave; b0 < B; b0 += 1024) {
+    const int32_t b = min(b0 + lane, B - 1);
+    const int32_t arcs =
+        b0 + lane < B ? row_ptr[range_ptr[static_cast<int64_t>(R) * B + b]] - row_ptr[range_ptr[b]] : 0;
+    for (int l = 0; l < kWave; ++l) {
+      const uint32_t a = __shfl(arcs, l);
+      const uint32_t pieces = a ? max((a + size - 1) / size, least) : 0u;
+      mine += pieces;
+      top = max(top, pieces ? (a + pieces - 1) / pieces : 0u);
+    }
+  }
+  atomicAdd(&count[lane], mine);
+  atomicMax(&longest[lane], static_cast<int32_t>(top));
+  __syncthreads();
+  if (wave == 0) {
+    float best = static_cast<float>((count[lane] + 255) / 256) * (static_cast<float>(longest[lane]) + fill);
+    int at = lane;
+    for (int d = 1; d < kWave; d *= 2) {
+      const float o = __shfl_xor(best, d);
+      const int oa = __shfl_xor(at, d);
+      if (o < best || (o == best && oa < at)) best = o, at = oa;
+    }
+    if (lane == at) out[1] = static_cast<int32_t>(size);
+  }
+}
+
 // Chunks of the stream-layout pull, one wave per block: a block's ranges are
-// cut into chunks of about equal arc counts (near `target`, at most `cap`
+// cut into chunks of about equal arc counts (at most out[1], at most `cap`
 // ranges each). From range j0 a chunk runs to the first boundary that gives
 // it its share of the block's arcs, found with 64 probes per step. out[0]
 // counts the chunks; chunk i follows at out + kChunkInts (i + 1): first row,
@@ -570,15 +616,14 @@ __global__ void k_seg_table(const int32_t* __restrict__ range_ptr, const int32_t
 constexpr int kChunkInts = 8;
 __global__ __launch_bounds__(256) void k_cut_chunks(const int32_t* __restrict__ range_ptr,
                                                     const int32_t* __restrict__ row_ptr, int32_t B, int32_t R,
-                                                    int64_t target, int32_t cap, int32_t most,
-                                                    int32_t* __restrict__ out) {
+                                                    int32_t cap, int32_t most, int32_t* __restrict__ out) {
   const int32_t b = static_cast<int32_t>(blockIdx.x) * (256 / kWave) + static_cast<int32_t>(threadIdx.x) / kWave;
   if (b >= B) return;  // uniform over the wave
   const int lane = gcd::lane_id();
   auto arc_at = [&](int32_t j) { return row_ptr[range_ptr[static_cast<int64_t>(j) * B + b]]; };
-  const int64_t mb = arc_at(R) - arc_at(0);
+  const int64_t mb = arc_at(R) - arc_at(0), target = out[1];
   if (mb == 0) return;
-  const int64_t pieces = max<int64_t>(1, (mb + target - 1) / target);
+  const int64_t pieces = max<int64_t>((R + cap - 1) / cap, (mb + target - 1) / target);
   const int64_t per = (mb + pieces - 1) / pieces;  // arcs per chunk of this block
   for (int32_t ja = 0; ja < R;) {
     const int32_t a0 = arc_at(ja), top = min(R, ja + cap);
@@ -808,11 +853,15 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   // range-major start of every (range j, block b) slice: exclusive scan of
   // the slice sizes in j-major order
   const int64_t BR = static_cast<int64_t>(B) * R;
-  const int64_t target = std::max<int64_t>(kLdsChunkArcs, m / 1024);
+  // Sizes from four chunks per CU (but kLdsChunkArcs) up.
+  // A round costs 8 us more than its arcs at 2^14 vertices per block
+  // (32 M arcs in one round 79 us an iteration, in two 87): about 24 K arcs.
+  const int32_t base = static_cast<int32_t>(std::max<int64_t>(m / 1024, kLdsChunkArcs));
+  const int32_t fill = 16384 + t->W / 2;
   const int32_t cap = lds_seg_cap(t->W);
-  // no block has more chunks than its share of target-sized pieces, one cut
-  // short by `cap` per cap ranges, and one more
-  const int64_t most = m / target + static_cast<int64_t>(B) * ((R + cap - 1) / cap + 2);
+  // no block has more chunks than its share of base-sized pieces (or the
+  // least that cap allows), one cut short by `cap` per cap ranges, and two more
+  const int64_t most = m / base + static_cast<int64_t>(B) * (2 * ((R + cap - 1) / cap) + 2);
   Slab slab;
   const size_t i_cnt = slab.reserve(sizeof(int32_t) * BR), i_rm = slab.reserve(sizeof(int32_t) * (BR + 1)),
                i_tile = slab.reserve(sizeof(int32_t) * scan_tiles(BR)),
@@ -823,7 +872,8 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   int32_t* const rm = slab.take<int32_t>(mem.p, i_rm);
   int32_t* const dch = slab.take<int32_t>(mem.p, i_chunks);
   GC_HIP_TRY(hipMemsetAsync(dch, 0, sizeof(int32_t) * kChunkInts, s));
-  k_cut_chunks<<<grid_for(B, 256 / kWave), 256, 0, s>>>(t->range_ptr, t->row_ptr, B, R, target, cap,
+  k_chunk_size<<<1, 1024, 0, s>>>(t->range_ptr, t->row_ptr, B, R, cap, base, fill, dch);
+  k_cut_chunks<<<grid_for(B, 256 / kWave), 256, 0, s>>>(t->range_ptr, t->row_ptr, B, R, cap,
                                                         static_cast<int32_t>(most), dch);
   k_seg_counts<<<grid_for(BR, 256, INT_MAX), 256, 0, s>>>(t->range_ptr, B, R, cnt);
   GC_HIP_TRY(hipGetLastError());
@@ -849,10 +899,12 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   };
   std::vector<Chunk> ch(static_cast<size_t>(found));
   int32_t seg_max = 1;
+  int64_t top = 1;
   for (int32_t i = 0; i < found; ++i) {
     const int32_t* c = hch.data() + static_cast<size_t>(kChunkInts) * i;
     ch[i] = {c[0], c[1], c[2], c[3], c[4], c[5]};
     seg_max = std::max(seg_max, c[4]);
+    top = std::max<int64_t>(top, c[5] + 1);
   }
   // the blocks' waves append in any order
   std::sort(ch.begin(), ch.end(), [](const Chunk& x, const Chunk& y) {
@@ -860,27 +912,30 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   });
   // Dispatch order, XCD aware: the GPU hands consecutive work-groups to its
   // kXcds XCDs in turn (work-group i to XCD i mod kXcds), and each XCD has
-  // its own L2. All chunks of a block go to one XCD, next to each other in
-  // its sequence, so the block's slice of c comes from memory once and
-  // from that L2 for the block's other chunks. Blocks are dealt largest
-  // first, each to the XCD with the fewest arcs so far; within a block the
-  // largest chunk runs first; shorter lists are padded with empty chunks.
-  std::vector<int64_t> blk_arcs(static_cast<size_t>(B), 0);
-  for (const Chunk& c : ch) blk_arcs[c.blk] += c.arcs;
-  std::vector<int32_t> order(static_cast<size_t>(B));
-  for (int32_t b = 0; b < B; ++b) order[b] = b;
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return blk_arcs[x] > blk_arcs[y]; });
-  std::stable_sort(ch.begin(), ch.end(), [](const Chunk& x, const Chunk& y) { return x.arcs > y.arcs; });
-  std::vector<std::vector<int32_t>> blk_chunks(static_cast<size_t>(B));  // chunk ids per block, largest first
-  for (int32_t i = 0; i < static_cast<int32_t>(ch.size()); ++i) blk_chunks[ch[i].blk].push_back(i);
+  // its own L2. The chunks in block order are cut into one run of about
+  // equal arcs per XCD, so a block's slice of c comes from memory once (twice
+  // where the cut falls inside it) and from that L2 for its other chunks;
+  // whole blocks dealt to the XCDs left 20 to 30 % of the CUs without a chunk
+  // where blocks are few. Longer chunks run first, in eighths of the longest
+  // (equal ones keep their order: neighbours share a slice and write
+  // neighbouring partials); shorter lists are padded with empty chunks.
   std::vector<std::vector<int32_t>> xcd(kXcds);
-  std::vector<int64_t> load(kXcds, 0);
-  for (int32_t b : order) {
-    if (blk_chunks[b].empty()) continue;
-    const int x = static_cast<int>(std::min_element(load.begin(), load.end()) - load.begin());
-    load[x] += blk_arcs[b];
-    for (int32_t i : blk_chunks[b]) xcd[x].push_back(i);
+  // no XCD takes more chunks than its CUs run in the least number of rounds,
+  // or leaves the XCDs after it more than that
+  const size_t full = (ch.size() + 255) / 256 * (256 / kXcds);
+  int64_t before = 0;
+  int x = 0;
+  for (size_t i = 0; i < ch.size(); ++i) {
+    // past its share of the arcs (the chunk's middle decides): the next XCD
+    while (x + 1 < kXcds && (xcd[x].size() >= full || (2 * before + ch[i].arcs > 2 * m / kXcds * (x + 1) &&
+                                                       ch.size() - i <= full * static_cast<size_t>(kXcds - 1 - x))))
+      ++x;
+    xcd[x].push_back(static_cast<int32_t>(i));
+    before += ch[i].arcs;
   }
+  for (auto& l : xcd)
+    std::stable_sort(l.begin(), l.end(),
+                     [&](int32_t a, int32_t b) { return ch[a].arcs * 8 / top > ch[b].arcs * 8 / top; });
   size_t longest = 0;
   for (const auto& l : xcd) longest = std::max(longest, l.size());
   std::vector<int32_t> beg, end, blk, j0v, nsv;

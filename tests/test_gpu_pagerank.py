@@ -117,6 +117,24 @@ def test_pagerank_one_work_group(make, form, iters):
         assert l1(got, want) <= L1_TOL
 
 
+@pytest.mark.parametrize("make,W,k", [(lambda: graphs.star_out(70000), 1 << 13, 256),
+                                      (lambda: gg.uniform(5000, 4095, seed=1), 1 << 12, 256),
+                                      (lambda: gg.uniform(5000, 40960, seed=2), 1 << 13, 256),
+                                      (lambda: gg.uniform(230001, 3 * 230001, seed=3), 1 << 15, 256),
+                                      (lambda: gg.uniform(270000, 2 * 270000, seed=4), 1 << 10, 1024),
+                                      (lambda: gg.rmat(16, 16, seed=5, permute=False), 1 << 10, 256)],
+                         ids=["empty_blocks", "below_least", "one_block", "range_cap", "many_blocks", "skewed"])
+def test_pagerank_chunk_cuts(make, W, k):
+    """Chunk sizes: blocks without arcs, fewer arcs than the least chunk, one
+    block, more ranges than a chunk's table holds (899 against 828), more
+    blocks than CUs, blocks of very different sizes."""
+    g = make()
+    print(f"chunk cuts {g.name} n={g.n} m={g.m} W={W} k={k}", flush=True)
+    got, r0 = pagerank_gpu(g, "tocab_pull", oracle.LEAK, iters=3, W=W, k=k)
+    want = oracle.pagerank(g.n, g.rowptr, g.colidx, 0.85, 3, mode=oracle.LEAK, r0=r0)
+    assert l1(got, want) <= L1_TOL
+
+
 def test_pagerank_rejects_overlap_and_bad_args():
     import paper_1904_02241_amd as gc
     from tests.gpu_util import torch
