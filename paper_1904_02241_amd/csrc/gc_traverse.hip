@@ -1291,6 +1291,10 @@ __device__ __forceinline__ int32_t wave_owner(const int32_t* __restrict__ pre, i
   return lo;
 }
 
+// One arc per thread up to 64 tiles of them (the latency of a level is
+// least, and so few appends cost little), four beyond.
+constexpr int64_t kPushOneArc = 64 * kThreads;
+
 template <class Relax, int kA>
 __global__ __launch_bounds__(kThreads) void k_push(const int32_t* __restrict__ queue_in,
                                                    const int32_t* __restrict__ pre, int32_t qn, int32_t arcs,
@@ -1427,143 +1431,165 @@ __global__ void k_order_degree(const int32_t* __restrict__ order, int32_t cnt, c
 // (an arc from depth d reaches depth d + 1 at most), so the sum over all
 // out-arcs of coef needs no depth test; the array it writes is zero at the
 // vertices of depth d.
-constexpr int kBackArcs = 8;  // consecutive arcs per lane
-
-// Sums for the vertices order[lo, hi) of one depth, balanced over arcs: the
-// level's `arcs` out-arcs, concatenated in level order (pre[lo, hi) = each
-// one's first position), are cut into kBackArcs-arc pieces, one per lane. A
-// lane adds the sum of coef_in over each vertex's arcs in its piece into
-// coef_out[v] (FP64 atomic), or stores it when the piece holds all of v's
-// arcs.
-__global__ __launch_bounds__(kThreads) void k_bc_back_arcs(const int32_t* __restrict__ rowptr,
-                                                           const int32_t* __restrict__ colidx,
-                                                           const int32_t* __restrict__ order,
-                                                           const int32_t* __restrict__ pre, int32_t lo, int32_t hi,
-                                                           int32_t arcs, const double* __restrict__ coef_in,
-                                                           double* __restrict__ coef_out) {
-  const int64_t end = arcs;
-  const int64_t a0 = (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) * kBackArcs;
-  if (a0 >= end) return;
-  const int64_t a1 = a0 + kBackArcs < end ? a0 + kBackArcs : end;
-  // the vertex whose arcs contain a0: the last i in [lo, hi) with pre[i] <= a0
-  int32_t l = lo, h = hi - 1;
-  while (l < h) {
-    const int32_t mid = l + ((h - l + 1) >> 1);
-    if (pre[mid] <= a0) l = mid;
-    else h = mid - 1;
+//
+// A step walks the arcs of the vertices order[lo, hi), concatenated in level
+// order (pre = their prefix), in tiles of one work-group, cut like k_push's:
+// the tile's first vertex by a wave-wide search, a window of the level in
+// LDS, every thread's arcs located there.
+//
+// kPush false: over the out-arcs of the level at depth d, coef_in of the
+// targets is added up per vertex in LDS and stored, or added with one FP64
+// atomic where the vertex's arcs go on in another tile.
+// kPush true, chosen where the next level's in-arcs are few: over the
+// in-arcs v -> w of the vertices at depth d + 1, coef_in[w] is added into
+// coef_out[v] for every v of depth d (FP64 atomic).
+// The sums are bound by the gathers (110 G arcs/s: 11.7 M arcs of an R-MAT
+// graph of 2^20 vertices 106 us), the pushes by the atomics on hubs (4.2 M
+// arcs 194 us). 1.5 M arcs of 255 K vertices took 75 us when each lane
+// searched the level for its eight arcs alone and loaded their vertices one
+// after the other, 19 us so.
+template <bool kPush, int kA>
+__global__ __launch_bounds__(kThreads) void k_bc_back(const int32_t* __restrict__ rowptr,
+                                                      const int32_t* __restrict__ colidx,
+                                                      const int32_t* __restrict__ order,
+                                                      const int32_t* __restrict__ pre, int32_t qn, int32_t arcs,
+                                                      const int32_t* __restrict__ depth, int32_t d,
+                                                      const double* __restrict__ coef_in,
+                                                      double* __restrict__ coef_out) {
+  constexpr int kWin = kA == 1 ? kThreads : 2 * kThreads;
+  constexpr int kTile = kThreads * kA;
+  constexpr int kPad = kPush ? 1 : kTile + kTile / 32;  // a word apart every 32: a thread's kA are neighbours
+  __shared__ int32_t w_pre[kWin], w_row[kWin];
+  __shared__ double w_sum[kWin];  // kPush: coefficient of the entry, else its sum
+  __shared__ double val[kPad];
+  __shared__ int16_t own[kPad];
+  __shared__ int32_t first;
+  const int tid = threadIdx.x;
+  const int32_t off = pre[0];
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kTile;  // the tile's arcs, from the level's first
+  const int32_t a0 = static_cast<int32_t>(t0);
+  const int32_t a1 = static_cast<int32_t>(min<int64_t>(arcs, t0 + kTile));
+  if (tid < kWave) {
+    const int32_t i = wave_owner(pre, qn, a0 + off);
+    if (tid == 0) first = i;
   }
-  // owner and position of each of the lane's arcs, then all column loads,
-  // then all coefficient gathers, so that kBackArcs gathers are in flight
-  int64_t pos[kBackArcs];
-  int32_t vid[kBackArcs];
-  bool whole[kBackArcs];
-  {
-    int32_t i = l;
-    int32_t v = order[i];
-    int64_t vb = pre[i], ve = i + 1 < hi ? pre[i + 1] : arcs;
-    int64_t rb = rowptr[v];
+  __syncthreads();
+  for (int32_t base = first; base < qn; base += kWin) {  // uniform; one window nearly always
 #pragma unroll
-    for (int k = 0; k < kBackArcs; ++k) {
-      const int64_t a = a0 + k;
-      if (a < a1) {
-        while (a >= ve) {  // next vertex with an arc at a (vertices without out-arcs are skipped)
-          ++i;
-          vb = ve;
-          ve = i + 1 < hi ? pre[i + 1] : arcs;
-          v = order[i];
-          rb = rowptr[v];
+    for (int t = tid; t < kWin; t += kThreads) {
+      const int32_t i = base + t;
+      int32_t p = INT32_MAX, row = 0;
+      double x = 0.0;
+      if (i < qn) {
+        const int32_t u = order[i];
+        p = pre[i] - off;
+        row = rowptr[u] - p;
+        if constexpr (kPush) x = coef_in[u];
+      }
+      w_pre[t] = p;
+      w_row[t] = row;
+      w_sum[t] = x;
+    }
+    const int32_t next = base + kWin < qn ? pre[base + kWin] - off : arcs;
+    __syncthreads();
+    const int32_t from = w_pre[0];
+    int32_t e[kA], at[kA];
+    uint32_t in = 0;
+#pragma unroll
+    for (int k = 0; k < kA; ++k) {
+      const int64_t a = t0 + tid + k * kThreads;
+      const bool here = a >= from && a < next && a < a1;
+      int lo = 0;  // the last entry with w_pre <= a
+#pragma unroll
+      for (int step = kWin / 2; step > 0; step >>= 1)
+        if (w_pre[lo + step] <= a) lo += step;
+      at[k] = lo;
+      e[k] = here ? static_cast<int32_t>(a) + w_row[lo] : 0;
+      in |= static_cast<uint32_t>(here) << k;
+    }
+    int32_t to[kA];
+#pragma unroll
+    for (int k = 0; k < kA; ++k) to[k] = (in >> k) & 1u ? colidx[e[k]] : 0;
+    if constexpr (kPush) {
+      int32_t dv[kA];
+#pragma unroll
+      for (int k = 0; k < kA; ++k) dv[k] = (in >> k) & 1u ? depth[to[k]] : d + 1;
+#pragma unroll
+      for (int k = 0; k < kA; ++k)
+        if (dv[k] == d) atomicAdd(&coef_out[to[k]], w_sum[at[k]]);
+    } else {
+      double c[kA];
+#pragma unroll
+      for (int k = 0; k < kA; ++k) c[k] = (in >> k) & 1u ? coef_in[to[k]] : 0.0;
+#pragma unroll
+      for (int k = 0; k < kA; ++k) {
+        const int i = tid + k * kThreads;
+        val[i + i / 32] = c[k];
+        own[i + i / 32] = (in >> k) & 1u ? static_cast<int16_t>(at[k]) : int16_t{-1};
+      }
+      __syncthreads();
+      // kA neighbouring arcs per thread: one LDS atomic per run of a vertex,
+      // one per wave where a vertex has all its arcs
+      double sum = 0.0;
+      const int l0 = tid * kA + tid * kA / 32;
+      int who = own[l0];
+      bool one = who >= 0;
+#pragma unroll
+      for (int k = 0; k < kA; ++k) {
+        const int i = tid * kA + k;
+        const int o = own[i + i / 32];
+        if (o != who) {
+          if (who >= 0) atomicAdd(&w_sum[who], sum);
+          sum = 0.0;
+          who = o;
+          one = false;
         }
-        pos[k] = rb + (a - vb);
-        vid[k] = v;
-        whole[k] = vb >= a0 && ve <= a1;
-      } else {
-        pos[k] = pos[0];
-        vid[k] = -1;
-        whole[k] = false;
+        sum += val[i + i / 32];
+      }
+      const int lead = __builtin_amdgcn_readfirstlane(who);
+      if (__all(one && who == lead)) {
+        sum = gcd::wave_sum(sum);
+        if (gcd::lane_id() == 0) atomicAdd(&w_sum[who], sum);
+      } else if (who >= 0) {
+        atomicAdd(&w_sum[who], sum);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int t = tid; t < kWin; t += kThreads) {
+        const int32_t i = base + t;
+        if (i >= qn) break;
+        const int32_t p = w_pre[t], q = t + 1 < kWin && i + 1 < qn ? w_pre[t + 1] : next;
+        if (p >= a1 || q <= a0 || p == q) continue;  // no arc in the tile
+        if (p >= a0 && q <= a1) coef_out[order[i]] = w_sum[t];
+        else if (w_sum[t] != 0.0) atomicAdd(&coef_out[order[i]], w_sum[t]);
       }
     }
-  }
-  int32_t w[kBackArcs];
-#pragma unroll
-  for (int k = 0; k < kBackArcs; ++k) w[k] = colidx[pos[k]];
-  double c[kBackArcs];
-#pragma unroll
-  for (int k = 0; k < kBackArcs; ++k) c[k] = coef_in[w[k]];
-  // sums per vertex run: a plain store when the lane holds all of v's arcs
-  double sum = 0.0;
-#pragma unroll
-  for (int k = 0; k < kBackArcs; ++k) {
-    if (vid[k] < 0) break;
-    sum += c[k];
-    if (k == kBackArcs - 1 || vid[k + 1] != vid[k]) {
-      if (whole[k]) coef_out[vid[k]] = sum;
-      else if (sum != 0.0) atomicAdd(&coef_out[vid[k]], sum);
-      sum = 0.0;
-    }
+    if (next >= a1) break;
+    __syncthreads();  // the window is refilled
   }
 }
 
-// The same step in the push direction, chosen when the next level's in-arcs
-// are fewer than this level's out-arcs: over the in-arcs v -> w of the
-// vertices w = order[lo, hi) of depth d + 1 (pre = exclusive scan of their
-// in-degrees along order), balanced like k_bc_back_arcs, coef_in[w] is
-// added into coef_out[v] for every v of depth d (FP64 atomic).
-__global__ __launch_bounds__(kThreads) void k_bc_back_push(const int32_t* __restrict__ t_rowptr,
-                                                           const int32_t* __restrict__ t_colidx,
-                                                           const int32_t* __restrict__ order,
-                                                           const int32_t* __restrict__ pre, int32_t lo, int32_t hi,
-                                                           const int32_t* __restrict__ depth, int32_t d,
-                                                           const double* __restrict__ coef_in,
-                                                           double* __restrict__ coef_out) {
-  const int64_t end = pre[hi];
-  const int64_t a0 = pre[lo] + (static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x) * kBackArcs;
-  if (a0 >= end) return;
-  const int64_t a1 = a0 + kBackArcs < end ? a0 + kBackArcs : end;
-  int32_t l = lo, h = hi - 1;  // the vertex whose in-arcs contain a0
-  while (l < h) {
-    const int32_t mid = l + ((h - l + 1) >> 1);
-    if (pre[mid] <= a0) l = mid;
-    else h = mid - 1;
-  }
-  // position and coefficient of each of the lane's arcs, then all column
-  // loads, then all depth gathers
-  int64_t pos[kBackArcs];
-  double cw[kBackArcs];
-  {
-    int32_t i = l;
-    int32_t w = order[i];
-    int64_t wb = pre[i], we = pre[i + 1];
-    int64_t rb = t_rowptr[w];
-    double c = coef_in[w];
-#pragma unroll
-    for (int k = 0; k < kBackArcs; ++k) {
-      const int64_t a = a0 + k;
-      if (a < a1) {
-        while (a >= we) {  // next vertex with an in-arc at a
-          ++i;
-          wb = we;
-          we = pre[i + 1];
-          w = order[i];
-          rb = t_rowptr[w];
-          c = coef_in[w];
-        }
-        pos[k] = rb + (a - wb);
-        cw[k] = c;
-      } else {
-        pos[k] = pos[0];
-        cw[k] = 0.0;
-      }
-    }
-  }
-  int32_t v[kBackArcs];
-#pragma unroll
-  for (int k = 0; k < kBackArcs; ++k) v[k] = t_colidx[pos[k]];
-  bool on[kBackArcs];
-#pragma unroll
-  for (int k = 0; k < kBackArcs; ++k) on[k] = a0 + k < a1 && depth[v[k]] == d;
-#pragma unroll
-  for (int k = 0; k < kBackArcs; ++k)
-    if (on[k]) atomicAdd(&coef_out[v[k]], cw[k]);
+// The step of depth d is pushed where the in-arcs below are fewer than a
+// sixth of the level's out-arcs: an arc costs 50 to 70 ps pushed, 9 ps pulled
+// (4.2 M against 11.7 M: 194 us pushed, 106 pulled; 0.9 M against 13.6 M: 62
+// and 114; 41 K against 4.1 M: 14 and 43).
+inline bool back_pushes(int64_t in_next, int64_t out_arcs) { return 6 * in_next < out_arcs; }
+
+// One step: the arcs of the qn vertices at `order`, one per thread up to
+// kPushOneArc of them (k_push's reason), four beyond.
+template <bool kPush>
+hipError_t bc_back(const int32_t* rowptr, const int32_t* colidx, const int32_t* order, const int32_t* pre, int32_t qn,
+                   int64_t arcs, const int32_t* depth, int32_t d, const double* coef_in, double* coef_out,
+                   hipStream_t s) {
+  const int32_t m = static_cast<int32_t>(arcs);
+  if (m == 0) return hipSuccess;
+  if (arcs <= kPushOneArc)
+    k_bc_back<kPush, 1><<<(m + kThreads - 1) / kThreads, kThreads, 0, s>>>(rowptr, colidx, order, pre, qn, m, depth, d,
+                                                                           coef_in, coef_out);
+  else
+    k_bc_back<kPush, 4><<<static_cast<int32_t>((arcs + 4 * kThreads - 1) / (4 * kThreads)), kThreads, 0, s>>>(
+        rowptr, colidx, order, pre, qn, m, depth, d, coef_in, coef_out);
+  return hipGetLastError();
 }
 
 // delta[v] = sigma[v] * (sum held in coef[v]) is added into bc[v], and
@@ -1918,11 +1944,7 @@ struct Frontier {
   void finish() { g->bits_clean = n_f == 0; }
 };
 
-// Push of one level with relaxation r. One arc per thread up to 64 tiles of
-// them (the latency of a level is least, and so few appends cost little),
-// four beyond, in at most four work-groups per CU.
-constexpr int64_t kPushOneArc = 64 * kThreads;
-
+// Push of one level with relaxation r, in at most four work-groups per CU.
 template <class Relax>
 hipError_t push_level(gc_graph g, Frontier& f, Relax r, hipStream_t s) {
   if (f.m_f == 0) return hipSuccess;
@@ -2309,14 +2331,14 @@ hipError_t bc_run(gc_graph g, gc_tocab t, const int32_t* sources, int32_t n_src,
     }
     f.finish();
     // depths run 0 .. level-1 (level = lv_off.size() - 1). Each step d runs
-    // in the direction with fewer arcs: pull over the out-arcs of depth d
+    // in the cheaper direction: pull over the out-arcs of depth d
     // (arc_pre) or push over the in-arcs of depth d + 1 (pre_in = exclusive
     // scan of the in-degrees along order). The deepest level's step only sets
     // coef = 1 / sigma; the source (depth 0) takes no share.
     ProfScope prof("bc_back", s);
     const int32_t reached = lv_off.back();
     bool push_any = false;
-    for (int32_t d = 1; d + 1 < level; ++d) push_any |= lv_in[d + 1] < lv_arcs[d];
+    for (int32_t d = 1; d + 1 < level; ++d) push_any |= back_pushes(lv_in[d + 1], lv_arcs[d]);
     if (push_any) {
       k_order_degree<<<grid_for(reached, kThreads), kThreads, 0, s>>>(g->bc_order, reached, g->t_rowptr, g->arc_deg);
       GC_HIP_TRY(hipGetLastError());
@@ -2328,19 +2350,12 @@ hipError_t bc_run(gc_graph g, gc_tocab t, const int32_t* sources, int32_t n_src,
       const double* coef_in = g->bc_coef + static_cast<size_t>((d + 1) & 1) * n;
       const int64_t out_arcs = lv_arcs[d];
       const int64_t in_next = d + 1 < level ? lv_in[d + 1] : 0;
-      if (d + 1 < level && in_next < out_arcs) {
-        const int64_t pieces = (in_next + kBackArcs - 1) / kBackArcs;
-        if (pieces > 0)
-          k_bc_back_push<<<grid_for(pieces, kThreads), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, g->bc_order,
-                                                                         pre_in.as<int32_t>(), hi, lv_off[d + 2],
-                                                                         g->bc_depth, d, coef_in, coef_out);
-      } else if (d + 1 < level) {
-        const int64_t pieces = (out_arcs + kBackArcs - 1) / kBackArcs;
-        if (pieces > 0)
-          k_bc_back_arcs<<<grid_for(pieces, kThreads), kThreads, 0, s>>>(g->rowptr, g->colidx, g->bc_order,
-                                                                         g->arc_pre, lo, hi, static_cast<int32_t>(out_arcs),
-                                                                         coef_in, coef_out);
-      }
+      if (d + 1 < level && back_pushes(in_next, out_arcs))
+        GC_HIP_TRY(bc_back<true>(g->t_rowptr, g->t_colidx, g->bc_order + hi, pre_in.as<int32_t>() + hi,
+                                 lv_off[d + 2] - hi, in_next, g->bc_depth, d, coef_in, coef_out, s));
+      else if (d + 1 < level)
+        GC_HIP_TRY(bc_back<false>(g->rowptr, g->colidx, g->bc_order + lo, g->arc_pre + lo, hi - lo, out_arcs,
+                                  g->bc_depth, d, coef_in, coef_out, s));
       k_bc_finish<<<grid_for(hi - lo, kThreads), kThreads, 0, s>>>(g->bc_order + lo, hi - lo, g->bc_sigma, coef_out,
                                                                     bc);
     }

@@ -95,6 +95,29 @@ def test_bc_tocab_widths(W, k):
     h.free()
 
 
+@pytest.mark.parametrize("mid,hubs,leaves", [(1, 1, 1), (255, 3, 1023), (4096, 2, 1025), (4097, 70, 300),
+                                             (9000, 1, 16385)])
+@pytest.mark.parametrize("policy", ["pull", "push", "heuristic"])
+def test_bc_hub_rows_and_tile_edges(mid, hubs, leaves, policy):
+    """0 -> mid vertices -> each of the hubs -> the leaves, every second of
+    which goes on to one last vertex: rows around the length left to the
+    whole work-group, more of them than it notes, and backward steps of one
+    arc, around 256, 1024 and 16384, with vertices without out-arcs between."""
+    import paper_1904_02241_amd as gc
+    h0, l0 = 1 + mid, 1 + mid + hubs
+    end = l0 + leaves
+    a, b, c = np.arange(1, h0), np.arange(h0, l0), np.arange(l0, end)
+    src = np.concatenate([np.zeros(mid, np.int64), np.repeat(a, hubs), np.repeat(b, leaves), c[::2]])
+    dst = np.concatenate([a, np.tile(b, mid), np.tile(c, hubs), np.full(len(c[::2]), end)])
+    g = gg.from_edges(end + 1, src, dst, name="hub_layers")
+    print(f"bc hubs mid={mid} hubs={hubs} leaves={leaves} {policy}", flush=True)
+    h = load(g)
+    bc = torch().zeros(g.n, dtype=torch().float64, device="cuda")
+    gc.bc_accumulate(h, None, [0, 1], bc, _policy(gc, policy))
+    _check(host(bc), oracle.bc(g.n, g.rowptr, g.colidx, [0, 1]))
+    h.free()
+
+
 def test_bc_accumulates_and_matches_single_sources():
     """bc is added into: two calls over disjoint source sets equal one call
     over their union, and the sum over single-source calls."""
