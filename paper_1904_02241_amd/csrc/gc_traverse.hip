@@ -1042,48 +1042,76 @@ __global__ __launch_bounds__(kThreads) void k_sssp_merge(const int32_t* __restri
 // one level up (Algorithm 3's update); then the dependencies are
 // accumulated level by level backwards (Brandes).
 
-// Sum of sigma[u] over in-arcs [b, e) from active sources u (FP64); rows
-// longer than kHeavy are summed by the whole wave.
+// One wave's rows in LDS.
+struct SigmaRows {
+  double sum[kWave];
+  int32_t pre[kWave], off[kWave];
+};
+
+// Sum of sigma[u] over in-arcs [b, e) of each lane's row (none unless active)
+// from active sources u (FP64), balanced over arcs: the wave walks its rows'
+// arcs end to end, 64 x kU at a time, each lane finding its arcs' rows in
+// LDS. What bounds it is the chain column, frontier bit, sigma of one
+// step, so a lane has kU of them in flight; a row per lane, and the whole
+// wave for each row of more than 32 arcs in turn, paid that chain once per
+// row.
 __device__ __forceinline__ double scan_sigma(const int32_t* __restrict__ col, const uint32_t* __restrict__ front,
-                                             const double* __restrict__ sigma, bool active, int32_t b, int32_t e) {
+                                             const double* __restrict__ sigma, bool active, int32_t b, int32_t e,
+                                             SigmaRows& rows) {
+  constexpr int kU = 4;
   const int lane = gcd::lane_id();
-  const bool heavy = active && (e - b) > kHeavy;
-  double s = 0.0;
-  if (active && !heavy) {
-    int32_t i = b;
-    for (; i + 4 <= e; i += 4) {  // four arcs' loads in flight at a time
-      int32_t u[4];
-      bool on[4];
+  const int32_t len = active ? e - b : 0;
+  const int32_t incl = gcd::wave_incl_scan(len);
+  const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+  if (total == 0) return 0.0;  // uniform
+  rows.pre[lane] = incl - len;
+  rows.off[lane] = b - (incl - len);
+  rows.sum[lane] = 0.0;
+  gcd::wave_lds_fence();
+  for (int64_t a0 = 0; a0 < total; a0 += kWave * kU) {  // uniform
+    int at[kU];
+    int32_t u[kU];
+    uint32_t in = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) u[k] = col[i + k];
+    for (int k = 0; k < kU; ++k) {
+      const int64_t a = a0 + lane + k * kWave;
+      int lo = 0;  // the last row with pre <= a
 #pragma unroll
-      for (int k = 0; k < 4; ++k) on[k] = bit_test(front, u[k]);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) s += on[k] ? sigma[u[k]] : 0.0;
+      for (int step = kWave / 2; step > 0; step >>= 1)
+        if (rows.pre[lo + step] <= a) lo += step;
+      at[k] = lo;
+      in |= static_cast<uint32_t>(a < total) << k;
+      u[k] = a < total ? col[static_cast<int32_t>(a) + rows.off[lo]] : 0;
     }
-    for (; i < e; ++i) {
-      const int32_t u = col[i];
-      if (bit_test(front, u)) s += sigma[u];
+#pragma unroll
+    for (int k = 0; k < kU; ++k) in &= ~(static_cast<uint32_t>(!bit_test(front, u[k])) << k);
+    double x[kU];
+#pragma unroll
+    for (int k = 0; k < kU; ++k) x[k] = (in >> k) & 1u ? sigma[u[k]] : 0.0;
+    if (__all(at[kU - 1] == at[0] && at[0] == __builtin_amdgcn_readfirstlane(at[0]))) {  // one row has them all
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < kU; ++k) t += x[k];
+      t = gcd::wave_sum(t);
+      if (lane == 0 && t != 0.0) atomicAdd(&rows.sum[at[0]], t);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kU; ++k)
+        if ((in >> k) & 1u) atomicAdd(&rows.sum[at[k]], x[k]);
     }
   }
-  uint64_t pending = __ballot(heavy);
-  while (pending) {
-    const int owner = __ffsll(static_cast<long long>(pending)) - 1;
-    pending &= pending - 1;
-    const int32_t hb = __shfl(b, owner, kWave), he = __shfl(e, owner, kWave);
-    double m = 0.0;
-    for (int32_t i = hb + lane; i < he; i += kWave) {
-      const int32_t u = col[i];
-      if (bit_test(front, u)) m += sigma[u];
-    }
-    m = gcd::wave_sum(m);
-    if (lane == owner) s = m;
-  }
+  gcd::wave_lds_fence();
+  const double s = rows.sum[lane];
+  gcd::wave_lds_fence();  // before the next rows are written
   return s;
 }
 
 // Topology-driven pull: an unvisited vertex with an active in-neighbour
-// joins the next level with the sum of their path counts.
+// joins the next level with the sum of their path counts. Rows of more than
+// kHugeRow arcs (kHuges of them at most) are left for the whole work-group:
+// one wave would walk a hub's row for longer than the level's other rows
+// take together.
+constexpr int kHugeRow = 4096, kHuges = 64;
 template <int NT>
 __global__ __launch_bounds__(NT) void k_bc_pull(const int32_t* __restrict__ t_rowptr,
                                                 const int32_t* __restrict__ t_col, int32_t n,
@@ -1091,6 +1119,10 @@ __global__ __launch_bounds__(NT) void k_bc_pull(const int32_t* __restrict__ t_ro
                                                 int32_t level, double* __restrict__ sigma,
                                                 uint32_t* __restrict__ next, uint32_t* __restrict__ visited,
                                                 Tally tally) {
+  __shared__ SigmaRows rows[NT / kWave];
+  __shared__ int32_t huge[kHuges], huges;
+  if (threadIdx.x == 0) huges = 0;
+  __syncthreads();
   Counted cnt;
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * NT; base < n; base += static_cast<int64_t>(gridDim.x) * NT) {
     const int32_t v = static_cast<int32_t>(min<int64_t>(base + threadIdx.x, INT32_MAX));
@@ -1101,8 +1133,15 @@ __global__ __launch_bounds__(NT) void k_bc_pull(const int32_t* __restrict__ t_ro
       b = t_rowptr[v];
       e = t_rowptr[v + 1];
     }
-    const bool active = !((vw >> (v & 31)) & 1u);
-    const double sum = scan_sigma(t_col, front, sigma, active, b, e);
+    bool active = !((vw >> (v & 31)) & 1u);
+    if (active && e - b > kHugeRow) {
+      const int at = atomicAdd(&huges, 1);
+      if (at < kHuges) {
+        huge[at] = v;
+        active = false;
+      }
+    }
+    const double sum = scan_sigma(t_col, front, sigma, active, b, e, rows[threadIdx.x / kWave]);
     const bool found = active && sum > 0.0;  // every active vertex has sigma >= 1
     if (found) {
       depth[v] = level + 1;
@@ -1111,6 +1150,38 @@ __global__ __launch_bounds__(NT) void k_bc_pull(const int32_t* __restrict__ t_ro
     }
     wave_bits_set(next, v, found);
     wave_bits_set(visited, v, found);
+  }
+  __syncthreads();
+  const int left = min(huges, kHuges);
+  for (int i = 0; i < left; ++i) {  // uniform
+    const int32_t v = huge[i];
+    const int32_t b = t_rowptr[v], e = t_rowptr[v + 1];
+    double part = 0.0;
+    for (int64_t a0 = b; a0 < e; a0 += 4 * NT) {
+      int32_t u[4];
+      bool on[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u[k] = t_col[static_cast<int32_t>(min<int64_t>(a0 + threadIdx.x + k * NT, e - 1))];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) on[k] = a0 + threadIdx.x + k * NT < e && bit_test(front, u[k]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part += on[k] ? sigma[u[k]] : 0.0;
+    }
+    part = gcd::wave_sum(part);
+    __syncthreads();  // rows[] is read no more
+    if (gcd::lane_id() == 0) rows[threadIdx.x / kWave].sum[0] = part;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double sum = 0.0;
+      for (int w = 0; w < NT / kWave; ++w) sum += rows[w].sum[0];
+      if (sum > 0.0) {
+        depth[v] = level + 1;
+        sigma[v] = sum;
+        cnt.add(tally, v);
+        atomicOr(&next[v >> 5], 1u << (v & 31));
+        atomicOr(&visited[v >> 5], 1u << (v & 31));
+      }
+    }
   }
   publish_count<NT>(tally, cnt);
 }
@@ -1123,6 +1194,7 @@ __global__ __launch_bounds__(kThreads) void k_bc_tocab(const int32_t* __restrict
                                                        const uint32_t* __restrict__ visited,
                                                        const uint32_t* __restrict__ front,
                                                        const double* __restrict__ sigma, double* __restrict__ part) {
+  __shared__ SigmaRows rows[kThreads / kWave];
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads; base < P;
        base += static_cast<int64_t>(gridDim.x) * kThreads) {  // uniform per work-group
     const int64_t l = base + threadIdx.x;
@@ -1133,7 +1205,7 @@ __global__ __launch_bounds__(kThreads) void k_bc_tocab(const int32_t* __restrict
       b = row_ptr[l];
       e = row_ptr[l + 1];
     }
-    const double sum = scan_sigma(col, front, sigma, active, b, e);
+    const double sum = scan_sigma(col, front, sigma, active, b, e, rows[threadIdx.x / kWave]);
     if (l < P) part[l] = sum;
   }
 }
