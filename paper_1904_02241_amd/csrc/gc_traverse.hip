@@ -48,7 +48,6 @@ using gcx::ProfScope;
 
 constexpr int kThreads = 256;
 constexpr int32_t kInf = INT32_MAX;
-constexpr int kHeavy = 32;  // rows longer than this are scanned by the whole wave
 
 // stats slots (device int32[gcx::kStatSlots], written to the pinned mirror once per level)
 constexpr int kOverflow = gcx::kStatOverflow;
@@ -362,57 +361,98 @@ __global__ __launch_bounds__(kThreads) void k_level_end(int32_t* __restrict__ st
 // ---------------------------------------------------------------------------
 // BFS
 
-// Scans in-arcs [b, e) for an active source; rows longer than kHeavy are
-// taken by the whole wave, which stops as soon as any lane hits.
-__device__ __forceinline__ bool scan_front(const int32_t* __restrict__ col, const uint32_t* __restrict__ front,
-                                           bool active, int32_t b, int32_t e) {
+// One wave's rows in LDS.
+struct WaveRows {
+  int32_t pre[kWave], off[kWave];
+};
+
+// Walks the rows of a wave (each lane's starts at b and has len arcs) end to
+// end, 64 x kU arcs a step, so that the step's chain (column, frontier bit,
+// value) is paid once for all rows and a lane has kU arcs in flight: a row per
+// lane, and the whole wave for each row of more than 32 arcs in turn, paid it
+// once per row. (The kernels' bound of 8 waves per SIMD keeps their registers
+// at 64, so that both work-groups of 1024 threads are resident.) step(at, e, in) gets each arc's row (lane) and index, and a
+// mask of those that exist.
+template <int kU, class Step>
+__device__ __forceinline__ void walk_rows(WaveRows& rows, int32_t b, int32_t len, Step&& step) {
   const int lane = gcd::lane_id();
-  const bool heavy = active && (e - b) > kHeavy;
+  const int32_t incl = gcd::wave_incl_scan(len);
+  const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
+  if (total == 0) return;  // uniform
+  rows.pre[lane] = incl - len;
+  rows.off[lane] = b - (incl - len);
+  gcd::wave_lds_fence();
+  for (int64_t a0 = 0; a0 < total; a0 += kWave * kU) {  // uniform
+    int at[kU];
+    int32_t e[kU];
+    uint32_t in = 0;
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {
+      const int64_t a = a0 + lane + k * kWave;
+      int lo = 0;  // the last row with pre <= a
+#pragma unroll
+      for (int d = kWave / 2; d > 0; d >>= 1)
+        if (rows.pre[lo + d] <= a) lo += d;
+      at[k] = lo;
+      e[k] = static_cast<int32_t>(a) + rows.off[lo];
+      in |= static_cast<uint32_t>(a < total) << k;
+    }
+    step(at, e, in);
+  }
+  gcd::wave_lds_fence();
+}
+
+// Whether in-arcs [b, e) of each lane's row (none unless active) have an active
+// source. Most rows of a level that is pulled end within their first
+// kFirst arcs, which every lane looks at alone, four at a time; the wave then
+// walks what is left of the others (no further for a row that was hit in an
+// earlier step). BFS of an R-MAT graph of 8 M vertices and 64 M arcs 377 us
+// with whole rows per lane (up to 32 arcs), 333 so; 335 with kFirst 4, 343
+// with 16; a uniform graph of 4 M vertices and 64 M arcs 466, 473, 502, 479.
+struct FrontRows : WaveRows {
+  int32_t hit[kWave];
+};
+__device__ __forceinline__ bool scan_front(const int32_t* __restrict__ col, const uint32_t* __restrict__ front,
+                                           bool active, int32_t b, int32_t e, FrontRows& rows) {
+  constexpr int kFirst = 8;
+  const int lane = gcd::lane_id();
   bool found = false;
-  if (active && !heavy) {
-    int32_t i = b;
-    for (; i + 4 <= e; i += 4) {  // four arcs' loads in flight at a time
-      int32_t u[4];
+  if (!active) e = b;
+  const int32_t own = min(e, b + kFirst);
+  for (int32_t i = b; i < own && !found; i += 4) {
+    int32_t u[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) u[k] = col[i + k];
-      uint32_t any = 0;  // all four tests, no short circuit
+    for (int k = 0; k < 4; ++k) u[k] = col[min(i + k, e - 1)];
+    uint32_t any = 0;  // all tests, no short circuit
 #pragma unroll
-      for (int k = 0; k < 4; ++k) any |= (front[u[k] >> 5] >> (u[k] & 31)) & 1u;
-      if (any) {
-        found = true;
-        break;
-      }
-    }
-    for (; !found && i < e; ++i) found = bit_test(front, col[i]);
+    for (int k = 0; k < 4; ++k) any |= (front[u[k] >> 5] >> (u[k] & 31)) & 1u;
+    found = any;
   }
-  uint64_t pending = __ballot(heavy);
-  while (pending) {
-    const int owner = __ffsll(static_cast<long long>(pending)) - 1;
-    pending &= pending - 1;
-    const int32_t hb = __shfl(b, owner, kWave), he = __shfl(e, owner, kWave);
-    bool hit = false;
-    for (int32_t base = hb; base < he; base += kWave) {
-      const int32_t i = base + lane;
-      const bool h = i < he && bit_test(front, col[i]);
-      if (__any(h)) {
-        hit = true;
-        break;
-      }
-    }
-    if (lane == owner) found = hit;
-  }
-  return found;
+  rows.hit[lane] = 0;
+  walk_rows<4>(rows, own, found ? 0 : e - own, [&](const int(&at)[4], const int32_t(&i)[4], uint32_t in) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) in &= ~(static_cast<uint32_t>(rows.hit[at[k]] != 0) << k);
+    int32_t u[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u[k] = (in >> k) & 1u ? col[i[k]] : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (((in >> k) & 1u) && bit_test(front, u[k])) rows.hit[at[k]] = 1;
+    gcd::wave_lds_fence();
+  });
+  return found || rows.hit[lane];
 }
 
 // Topology-driven pull over the whole transposed graph. The work-groups
 // stride over the vertices (their waves by themselves, without barriers), so
 // the counters take one atomic per resident work-group.
 template <int NT>
-__global__ __launch_bounds__(NT) void k_bfs_pull(const int32_t* __restrict__ t_rowptr,
+__global__ __launch_bounds__(NT, 8) void k_bfs_pull(const int32_t* __restrict__ t_rowptr,
                                                  const int32_t* __restrict__ t_col, int32_t n,
                                                  const uint32_t* __restrict__ front, int32_t* __restrict__ depth,
                                                  int32_t level, uint32_t* __restrict__ next,
                                                  uint32_t* __restrict__ visited, Tally tally) {
+  __shared__ FrontRows rows[NT / kWave];
   stamp_start(tally.stats);
   Counted cnt;
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * NT; base < n; base += static_cast<int64_t>(gridDim.x) * NT) {
@@ -427,7 +467,7 @@ __global__ __launch_bounds__(NT) void k_bfs_pull(const int32_t* __restrict__ t_r
       e = t_rowptr[v + 1];
     }
     const bool active = !((vw >> (v & 31)) & 1u);
-    const bool found = scan_front(t_col, front, active, b, e);
+    const bool found = scan_front(t_col, front, active, b, e, rows[threadIdx.x / kWave]);
     if (found) {
       depth[v] = level + 1;
       cnt.add(tally, v);
@@ -446,6 +486,7 @@ __global__ __launch_bounds__(kThreads) void k_bfs_tocab(const int32_t* __restric
                                                         const uint32_t* __restrict__ visited,
                                                         const uint32_t* __restrict__ front,
                                                         uint8_t* __restrict__ flag, int32_t* __restrict__ stats) {
+  __shared__ FrontRows rows[kThreads / kWave];
   stamp_start(stats);
   // the stride is uniform over the work-group, so every wave of it runs the
   // same passes and the wave-wide scans inside stay convergent
@@ -459,7 +500,7 @@ __global__ __launch_bounds__(kThreads) void k_bfs_tocab(const int32_t* __restric
       b = row_ptr[l];
       e = row_ptr[l + 1];
     }
-    const bool found = scan_front(col, front, active, b, e);
+    const bool found = scan_front(col, front, active, b, e, rows[threadIdx.x / kWave]);
     if (l < P) flag[l] = found ? 1 : 0;
   }
 }
@@ -497,71 +538,60 @@ __global__ __launch_bounds__(kThreads) void k_bfs_merge(const int32_t* __restric
 // ---------------------------------------------------------------------------
 // SSSP (synchronous Bellman-Ford rounds over the vertices changed last round)
 
-// Minimum of dist[u] + w over in-arcs [b, e) from active sources u (kInf if
-// none); rows longer than kHeavy are reduced by the whole wave. *ovf is set
-// when a candidate path length reaches INT32_MAX.
-__device__ __forceinline__ int64_t scan_min(const int32_t* __restrict__ col, const int32_t* __restrict__ w,
+// Minimum of dist[u] + w over in-arcs [b, e) of each lane's row from active
+// sources u (kInf if none). *ovf is set when a candidate path length reaches
+// INT32_MAX. Shortest paths by pull alone, 10^6 vertices of an R-MAT graph,
+// 16 arcs each: 3840 us with a row per lane, 2660 so (4110 without the case
+// of one row, whose lanes all met on one LDS word).
+struct MinRows : WaveRows {
+  int32_t best[kWave];
+};
+__device__ __forceinline__ int32_t scan_min(const int32_t* __restrict__ col, const int32_t* __restrict__ w,
                                             const uint32_t* __restrict__ front, const int32_t* __restrict__ dist,
-                                            bool active, int32_t b, int32_t e, bool* ovf) {
+                                            bool active, int32_t b, int32_t e, bool* ovf, MinRows& rows) {
   const int lane = gcd::lane_id();
-  const bool heavy = active && (e - b) > kHeavy;
-  int64_t best = kInf;
   bool over = false;
-  if (active && !heavy) {
-    int32_t i = b;
-    for (; i + 4 <= e; i += 4) {  // four arcs' loads in flight at a time
-      int32_t u[4], wk[4];
-      bool on[4];
+  rows.best[lane] = kInf;
+  walk_rows<4>(rows, b, active ? e - b : 0, [&](const int(&at)[4], const int32_t(&i)[4], uint32_t in) {
+    int32_t u[4], wk[4], du[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        u[k] = col[i + k];
-        wk[k] = w[i + k];
-      }
+    for (int k = 0; k < 4; ++k) u[k] = (in >> k) & 1u ? col[i[k]] : 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) on[k] = bit_test(front, u[k]);
+    for (int k = 0; k < 4; ++k) in &= ~(static_cast<uint32_t>(!bit_test(front, u[k])) << k);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int64_t cand = on[k] ? static_cast<int64_t>(dist[u[k]]) + wk[k] : static_cast<int64_t>(kInf);
-        over |= on[k] && cand >= kInf;
-        best = min(best, cand);
-      }
+    for (int k = 0; k < 4; ++k) {
+      wk[k] = (in >> k) & 1u ? w[i[k]] : 0;
+      du[k] = (in >> k) & 1u ? dist[u[k]] : 0;
     }
-    for (; i < e; ++i) {
-      const int32_t u = col[i];
-      if (bit_test(front, u)) {
-        const int64_t cand = static_cast<int64_t>(dist[u]) + w[i];
-        over |= cand >= kInf;
-        best = min(best, cand);
-      }
+    int32_t cand[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool on = (in >> k) & 1u, past = wk[k] >= kInf - du[k];  // du[k] + wk[k] >= kInf
+      over |= on && past;
+      cand[k] = on && !past ? du[k] + wk[k] : kInf;
     }
-  }
-  uint64_t pending = __ballot(heavy);
-  while (pending) {
-    const int owner = __ffsll(static_cast<long long>(pending)) - 1;
-    pending &= pending - 1;
-    const int32_t hb = __shfl(b, owner, kWave), he = __shfl(e, owner, kWave);
-    int64_t m = kInf;
-    for (int32_t i = hb + lane; i < he; i += kWave) {
-      const int32_t u = col[i];
-      if (bit_test(front, u)) {
-        const int64_t cand = static_cast<int64_t>(dist[u]) + w[i];
-        over |= cand >= kInf;
-        m = min(m, cand);
-      }
+    if (__builtin_amdgcn_readfirstlane(at[0]) == __builtin_amdgcn_readlane(at[3], kWave - 1)) {  // one row has them all
+      int32_t m = min(min(cand[0], cand[1]), min(cand[2], cand[3]));
+      for (int o = 32; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o, kWave));
+      if (lane == 0 && m != kInf) atomicMin(&rows.best[at[0]], m);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (cand[k] != kInf) atomicMin(&rows.best[at[k]], cand[k]);
     }
-    for (int o = 32; o > 0; o >>= 1) m = min(m, static_cast<int64_t>(__shfl_xor(m, o, kWave)));
-    if (lane == owner) best = m;
-  }
+  });
+  gcd::wave_lds_fence();
   *ovf = over;
-  return min<int64_t>(best, kInf);
+  return rows.best[lane];
 }
 
 template <int NT>
-__global__ __launch_bounds__(NT) void k_sssp_pull(const int32_t* __restrict__ t_rowptr,
+__global__ __launch_bounds__(NT, 8) void k_sssp_pull(const int32_t* __restrict__ t_rowptr,
                                                   const int32_t* __restrict__ t_col,
                                                   const int32_t* __restrict__ t_w, int32_t n,
                                                   const uint32_t* __restrict__ front, int32_t* __restrict__ dist,
                                                   uint32_t* __restrict__ next, Tally tally) {
+  __shared__ MinRows rows[NT / kWave];
   stamp_start(tally.stats);
   Counted cnt;
   bool any_over = false;
@@ -573,11 +603,11 @@ __global__ __launch_bounds__(NT) void k_sssp_pull(const int32_t* __restrict__ t_
       e = t_rowptr[v + 1];
     }
     bool ovf;
-    const int64_t best = scan_min(t_col, t_w, front, dist, v < n, b, e, &ovf);
+    const int32_t best = scan_min(t_col, t_w, front, dist, v < n, b, e, &ovf, rows[threadIdx.x / kWave]);
     any_over |= ovf;
     bool improved = false;
     if (v < n && best < dist[v]) {
-      dist[v] = static_cast<int32_t>(best);
+      dist[v] = best;
       improved = true;
       cnt.add(tally, v);
     }
@@ -595,6 +625,7 @@ __global__ __launch_bounds__(kThreads) void k_sssp_tocab(const int32_t* __restri
                                                          const uint32_t* __restrict__ front,
                                                          const int32_t* __restrict__ dist, int32_t* __restrict__ pmin,
                                                          int32_t* __restrict__ stats) {
+  __shared__ MinRows rows[kThreads / kWave];
   stamp_start(stats);
   for (int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads; base < P;
        base += static_cast<int64_t>(gridDim.x) * kThreads) {  // uniform per work-group
@@ -605,9 +636,9 @@ __global__ __launch_bounds__(kThreads) void k_sssp_tocab(const int32_t* __restri
       e = row_ptr[l + 1];
     }
     bool ovf;
-    const int64_t best = scan_min(col, w, front, dist, l < P, b, e, &ovf);
+    const int32_t best = scan_min(col, w, front, dist, l < P, b, e, &ovf, rows[threadIdx.x / kWave]);
     if (ovf) stats[kOverflow] = 1;
-    if (l < P) pmin[l] = static_cast<int32_t>(best);
+    if (l < P) pmin[l] = best;
   }
 }
 
@@ -1042,68 +1073,37 @@ __global__ __launch_bounds__(kThreads) void k_sssp_merge(const int32_t* __restri
 // one level up (Algorithm 3's update); then the dependencies are
 // accumulated level by level backwards (Brandes).
 
-// One wave's rows in LDS.
-struct SigmaRows {
-  double sum[kWave];
-  int32_t pre[kWave], off[kWave];
-};
-
 // Sum of sigma[u] over in-arcs [b, e) of each lane's row (none unless active)
-// from active sources u (FP64), balanced over arcs: the wave walks its rows'
-// arcs end to end, 64 x kU at a time, each lane finding its arcs' rows in
-// LDS. What bounds it is the chain column, frontier bit, sigma of one
-// step, so a lane has kU of them in flight; a row per lane, and the whole
-// wave for each row of more than 32 arcs in turn, paid that chain once per
-// row.
+// from active sources u (FP64). The first pull level of an R-MAT graph of
+// 2^20 vertices (16 M arcs) took 186 us with a row per lane, 118 so.
+struct SigmaRows : WaveRows {
+  double sum[kWave];
+};
 __device__ __forceinline__ double scan_sigma(const int32_t* __restrict__ col, const uint32_t* __restrict__ front,
                                              const double* __restrict__ sigma, bool active, int32_t b, int32_t e,
                                              SigmaRows& rows) {
-  constexpr int kU = 4;
   const int lane = gcd::lane_id();
-  const int32_t len = active ? e - b : 0;
-  const int32_t incl = gcd::wave_incl_scan(len);
-  const int32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
-  if (total == 0) return 0.0;  // uniform
-  rows.pre[lane] = incl - len;
-  rows.off[lane] = b - (incl - len);
   rows.sum[lane] = 0.0;
-  gcd::wave_lds_fence();
-  for (int64_t a0 = 0; a0 < total; a0 += kWave * kU) {  // uniform
-    int at[kU];
-    int32_t u[kU];
-    uint32_t in = 0;
+  walk_rows<4>(rows, b, active ? e - b : 0, [&](const int(&at)[4], const int32_t(&i)[4], uint32_t in) {
+    int32_t u[4];
+    double x[4];
 #pragma unroll
-    for (int k = 0; k < kU; ++k) {
-      const int64_t a = a0 + lane + k * kWave;
-      int lo = 0;  // the last row with pre <= a
+    for (int k = 0; k < 4; ++k) u[k] = (in >> k) & 1u ? col[i[k]] : 0;
 #pragma unroll
-      for (int step = kWave / 2; step > 0; step >>= 1)
-        if (rows.pre[lo + step] <= a) lo += step;
-      at[k] = lo;
-      in |= static_cast<uint32_t>(a < total) << k;
-      u[k] = a < total ? col[static_cast<int32_t>(a) + rows.off[lo]] : 0;
-    }
+    for (int k = 0; k < 4; ++k) in &= ~(static_cast<uint32_t>(!bit_test(front, u[k])) << k);
 #pragma unroll
-    for (int k = 0; k < kU; ++k) in &= ~(static_cast<uint32_t>(!bit_test(front, u[k])) << k);
-    double x[kU];
-#pragma unroll
-    for (int k = 0; k < kU; ++k) x[k] = (in >> k) & 1u ? sigma[u[k]] : 0.0;
-    if (__all(at[kU - 1] == at[0] && at[0] == __builtin_amdgcn_readfirstlane(at[0]))) {  // one row has them all
-      double t = 0.0;
-#pragma unroll
-      for (int k = 0; k < kU; ++k) t += x[k];
-      t = gcd::wave_sum(t);
+    for (int k = 0; k < 4; ++k) x[k] = (in >> k) & 1u ? sigma[u[k]] : 0.0;
+    if (__builtin_amdgcn_readfirstlane(at[0]) == __builtin_amdgcn_readlane(at[3], kWave - 1)) {  // one row has them all
+      const double t = gcd::wave_sum((x[0] + x[1]) + (x[2] + x[3]));
       if (lane == 0 && t != 0.0) atomicAdd(&rows.sum[at[0]], t);
     } else {
 #pragma unroll
-      for (int k = 0; k < kU; ++k)
+      for (int k = 0; k < 4; ++k)
         if ((in >> k) & 1u) atomicAdd(&rows.sum[at[k]], x[k]);
     }
-  }
+  });
   gcd::wave_lds_fence();
-  const double s = rows.sum[lane];
-  gcd::wave_lds_fence();  // before the next rows are written
-  return s;
+  return rows.sum[lane];
 }
 
 // Topology-driven pull: an unvisited vertex with an active in-neighbour
@@ -1113,7 +1113,7 @@ __device__ __forceinline__ double scan_sigma(const int32_t* __restrict__ col, co
 // take together.
 constexpr int kHugeRow = 4096, kHuges = 64;
 template <int NT>
-__global__ __launch_bounds__(NT) void k_bc_pull(const int32_t* __restrict__ t_rowptr,
+__global__ __launch_bounds__(NT, 8) void k_bc_pull(const int32_t* __restrict__ t_rowptr,
                                                 const int32_t* __restrict__ t_col, int32_t n,
                                                 const uint32_t* __restrict__ front, int32_t* __restrict__ depth,
                                                 int32_t level, double* __restrict__ sigma,

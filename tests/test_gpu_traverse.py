@@ -261,3 +261,35 @@ def test_push_levels_of_every_shape(make, policy):
         gc.sssp_pull(h, None, s, d, pol)
         np.testing.assert_array_equal(host(d), oracle.dijkstra(g.n, g.rowptr, g.colidx, g.weights, s))
     h.free()
+
+
+# a wave's rows walked end to end: vertex i of 1..64 has rows[(i - 1) % len]
+# in-arcs from the middle layer, of which the source reaches one vertex only,
+# so that one arc (the first, one inside, the last) of every row counts
+@pytest.mark.parametrize("rows", [(0, 1, 8, 9), (7, 255, 0, 64), (256, 257), (1025, 0, 3), (4096, 8, 4097)],
+                         ids=lambda r: "-".join(map(str, r)))
+@pytest.mark.parametrize("at", [0.0, 0.5, 1.0])
+@pytest.mark.parametrize("W", [None, 1 << 16])
+def test_pull_rows_of_every_length(rows, at, W):
+    import paper_1904_02241_amd as gc
+    most = max(rows)
+    src, dst = [], []
+    for i in range(64):
+        n_in = rows[i % len(rows)]
+        hot = int(at * (n_in - 1)) if n_in else 0
+        src.append(65 + (np.arange(n_in) - hot) % most)  # the active vertex (65) stands at `hot`
+        dst.append(np.full(n_in, 1 + i))
+    src.append([0])
+    dst.append([65])
+    g = gg.from_edges(65 + most, np.concatenate(src), np.concatenate(dst), name="pull_rows").with_weights(5)
+    print(f"pull rows {rows} at={at} W={W} m={g.m}", flush=True)
+    h = load(g, weights=True)
+    part = gc.tocab_partition(h, gc.GC_PULL, W, 256) if W else None
+    d = torch().empty(g.n, dtype=torch().int32, device="cuda")
+    gc.bfs_pull(h, part, 0, d, gc.GC_POLICY_PULL)
+    np.testing.assert_array_equal(host(d), oracle.bfs(g.n, g.rowptr, g.colidx, 0))
+    gc.sssp_pull(h, part, 0, d, gc.GC_POLICY_PULL)
+    np.testing.assert_array_equal(host(d), oracle.dijkstra(g.n, g.rowptr, g.colidx, g.weights, 0))
+    if part is not None:
+        part.free()
+    h.free()
