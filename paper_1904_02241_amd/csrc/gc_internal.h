@@ -115,9 +115,10 @@ struct gc_tocab_s {
   int64_t m_pad = 0;              // multiple of wave_tile_arcs(), >= m + wave_tile_arcs()
   int32_t* wtile_row = nullptr;   // unused by the stream layout
   int32_t n_wtiles = 0;
-  int2* seg = nullptr;            // [B][R+1]: first local row of block b in range j, shift to range-major index
-  int32_t* rstart = nullptr;      // [R+1] range-major start of merge range j
-  uint16_t* id16s = nullptr;      // [P] id16 in range-major order
+  int32_t sk = 0, sR = 0;         // width and number of the layout's own merge ranges (stream_range)
+  int2* seg = nullptr;            // [B][sR+1]: first local row of block b in range j, shift to range-major index
+  int32_t* rstart = nullptr;      // [sR+1] range-major start of merge range j
+  uint16_t* id16s = nullptr;      // [P] id_map mod sk in range-major order
   int32_t* chunk_beg = nullptr;   // [n_chunks] first local row (one buffer holds the five chunk arrays)
   int32_t* chunk_end = nullptr;   // [n_chunks] one past the last local row
   int32_t* chunk_blk = nullptr;   // [n_chunks] block

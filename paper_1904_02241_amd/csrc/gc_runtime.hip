@@ -489,7 +489,7 @@ int tocab_layout(gc_tocab t, int32_t* stream_layout, int32_t* chunks, int64_t* t
   const bool st = t->col16 != nullptr;
   if (stream_layout) *stream_layout = st ? 1 : 0;
   if (chunks) *chunks = st ? t->n_chunks : 0;
-  if (table_bytes) *table_bytes = st ? static_cast<int64_t>(sizeof(int2)) * t->B * (t->R + 1) : 0;
+  if (table_bytes) *table_bytes = st ? static_cast<int64_t>(sizeof(int2)) * t->B * (t->sR + 1) : 0;
   return GC_OK;
 }
 
