@@ -594,18 +594,18 @@ int batch_create(const gc_graph* graphs, int32_t n_graphs, const int32_t* block_
     BGraph& d = hg[i];
     d.n = g->n;
     d.n_tiles = t->n_tiles;
-    d.R = t->R;
+    d.R = t->mR;
     d.B = t->B;
     d.rowptr = g->rowptr;
     d.row_ptr = t->row_ptr;
     d.col = t->col;
     d.tile_row = t->tile_row;
-    d.range_ptr = t->range_ptr;
+    d.range_ptr = t->mrange;
     d.id16 = t->id16;
     d.partial = t->partial;
     const int32_t vgrid = (g->n + kThreads - 1) / kThreads;
     d.contrib = static_cast<float*>(own(b, sizeof(float) * g->n));
-    d.dpart = static_cast<double*>(own(b, sizeof(double) * std::max(vgrid, t->R)));
+    d.dpart = static_cast<double*>(own(b, sizeof(double) * std::max(vgrid, t->mR)));
     d.dtotal = static_cast<double*>(own(b, sizeof(double) * 2));
     d.rank_off = off;
     if (!d.contrib || !d.dpart || !d.dtotal) {
@@ -615,7 +615,7 @@ int batch_create(const gc_graph* graphs, int32_t n_graphs, const int32_t* block_
     b->rank_off.push_back(off);
     off += g->n;
     tile_pre[i + 1] = tile_pre[i] + t->n_tiles;
-    range_pre[i + 1] = range_pre[i] + t->R;
+    range_pre[i + 1] = range_pre[i] + t->mR;
     vert_pre[i + 1] = vert_pre[i] + vgrid;
   }
   b->rank_off.push_back(off);

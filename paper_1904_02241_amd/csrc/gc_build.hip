@@ -835,27 +835,12 @@ hipError_t build_transpose(int32_t n, int64_t m, const int32_t* rowptr, const in
   return hipStreamSynchronize(s);  // the Buf is released on return
 }
 
-// Merge ranges of the stream layout: the partition's, halved until there are
-// kStreamRanges of them (or they are 256 vertices wide), since the merge gives
-// each one work-group. PageRank, 20 iterations, with the partition's own, with
-// 64, 128 and 256: 10^6 vertices of 16 arcs, ranges of 2^14: 1461, 1081, 887,
-// 894 us; 300,007 of 16, 2^14: 657, 386, 361, 385; of 4, 2^12: 312, 312, 296,
-// 331 (a tile of the pull that meets more ranges takes longer).
-constexpr int32_t kStreamRanges = 128;
-int32_t stream_range(int32_t n, int32_t k) {
-  while (k > 256 && (static_cast<int64_t>(n) + k - 1) / k < kStreamRanges) k /= 2;
-  return k;
-}
-
 // Stream layout of an LDS-resident pull partition: padded 16-bit columns,
 // head bits, wave-tile rows, the range-major position table, range-major
 // id16, and chunks (one work-group each) cut at merge-range boundaries so
 // a chunk's slice of the position table fits in LDS beside the block's slice.
 hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
-  t->sk = stream_range(t->n_rows, t->k);
-  t->sR = (t->n_rows + t->sk - 1) / t->sk;
-  const int32_t log2k = __builtin_ctz(static_cast<uint32_t>(t->sk));
-  const int32_t B = t->B, R = t->sR;
+  const int32_t B = t->B, R = t->mR;
   const int64_t P = t->P, m = t->m;
   const int64_t entries = static_cast<int64_t>(B) * (R + 1);
   t->seg = static_cast<int2*>(dev_alloc(sizeof(int2) * entries, s));
@@ -878,8 +863,6 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   // least that cap allows), one cut short by `cap` per cap ranges, and two more
   const int64_t most = m / base + static_cast<int64_t>(B) * (2 * ((R + cap - 1) / cap) + 2);
   Slab slab;
-  const bool own = t->sk != t->k;  // ranges of its own
-  const size_t i_rp = slab.reserve(own ? sizeof(int32_t) * entries : 0);
   const size_t i_cnt = slab.reserve(sizeof(int32_t) * BR), i_rm = slab.reserve(sizeof(int32_t) * (BR + 1)),
                i_tile = slab.reserve(sizeof(int32_t) * scan_tiles(BR)),
                i_chunks = slab.reserve(sizeof(int32_t) * kChunkInts * (most + 1));
@@ -888,12 +871,7 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   int32_t* const cnt = slab.take<int32_t>(mem.p, i_cnt);
   int32_t* const rm = slab.take<int32_t>(mem.p, i_rm);
   int32_t* const dch = slab.take<int32_t>(mem.p, i_chunks);
-  const int32_t* range_ptr = t->range_ptr;
-  if (own) {
-    int32_t* const rp = slab.take<int32_t>(mem.p, i_rp);
-    k_range_rows<<<grid_for(entries, 256, 65536), 256, 0, s>>>(t->id_map, t->blk_rowoff, B, R, log2k, rp);
-    range_ptr = rp;
-  }
+  const int32_t* const range_ptr = t->mrange;
   GC_HIP_TRY(hipMemsetAsync(dch, 0, sizeof(int32_t) * kChunkInts, s));
   k_chunk_size<<<1, 1024, 0, s>>>(range_ptr, t->row_ptr, B, R, cap, base, fill, dch);
   k_cut_chunks<<<grid_for(B, 256 / kWave), 256, 0, s>>>(range_ptr, t->row_ptr, B, R, cap,
@@ -910,7 +888,7 @@ hipError_t build_lds_stream(gc_tocab t, hipStream_t s) {
   GC_HIP_TRY(scan_queue(cnt, rm, BR, slab.take<int32_t>(mem.p, i_tile), s));
   k_seg_table<<<grid_for(entries, 256, INT_MAX), 256, 0, s>>>(range_ptr, rm, B, R, P, t->seg, t->rstart);
   if (P > 0)
-    k_id16_stream<<<grid_for(P, 256, 65536), 256, 0, s>>>(t->id_map, P, t->blk_rowoff, B, R, log2k, t->seg,
+    k_id16_stream<<<grid_for(P, 256, 65536), 256, 0, s>>>(t->id_map, P, t->blk_rowoff, B, R, __builtin_ctz(t->mk), t->seg,
                                                           t->id16s);
   GC_HIP_TRY(hipGetLastError());
   if (found > 0)
@@ -1082,6 +1060,26 @@ hipError_t build_push_expand(gc_tocab t, hipStream_t s) {
   return hipSuccess;
 }
 
+// Width of the ranges that the merges of a pull partition work in, since a
+// merge gives each range one work-group: k, halved as follows while the range
+// table stays below an eighth of the arcs.
+// Stream layout: until there are 128 (or they are 256 wide). PageRank, 20
+// iterations, with ranges of k, with 64, 128 and 256: 10^6 vertices of 16
+// arcs, k = 2^14: 1461, 1081, 887, 894 us; 300,007 of 16, 2^14: 657, 386, 361,
+// 385; of 4, 2^12: 312, 312, 296, 331 (a tile of the pull that meets more
+// ranges takes longer).
+// Wider blocks: until they are 2048 wide, and on to 1024 while there are
+// fewer than 512. The merge of 256 threads holds a range's FP64 sums in LDS,
+// so 2048 of them let a CU run its work-groups: 2.5 M vertices of 16 arcs with
+// k = 2^13 5552 us, 4815 with 4096, 4501 with 2048, 4557 with 1024; 10^6 of 16,
+// k = 2^14: 3381, 2119, 1940, 1861.
+int32_t merge_width(int32_t n, int64_t m, int32_t B, int32_t k, bool stream) {
+  auto ranges = [&](int32_t w) { return (static_cast<int64_t>(n) + w - 1) / w; };
+  auto wanted = [&] { return stream ? k > 256 && ranges(k) < 128 : k > 2048 || (k > 1024 && ranges(k) < 512); };
+  while (wanted() && B * (ranges(k / 2) + 1) <= m / 8 + 65536) k /= 2;
+  return k;
+}
+
 hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a_col, const int32_t* a_w,
                            hipStream_t s) {
   const int32_t B = t->B, R = t->R;
@@ -1094,6 +1092,8 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
                            static_cast<int64_t>(B) * (R + 1) <= (int64_t(1) << 25) && m + 1024 < INT32_MAX;
   const bool push_stream = t->dir == GC_PUSH && t->W <= kPushLdsMaxWidth && t->k <= t->W && m > 0 &&
                            m + 1024 < INT32_MAX && B <= kPushExpandMaxBlocks;
+  t->mk = t->dir == GC_PULL ? merge_width(t->n_rows, m, B, t->k, t->W <= kLdsMaxWidth) : t->k;
+  t->mR = (t->n_rows + t->mk - 1) / t->mk;
   const int64_t tile = wave_tile_arcs();
   const int64_t m_pad = (m / tile + 2) * tile, head_words = m_pad / 64 + 1;
   t->col = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * mn, s));
@@ -1101,6 +1101,10 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
   t->range_ptr = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (R + 1) * static_cast<size_t>(B), s));
   t->blk_rowoff = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (B + 1), s));
   if (!t->col || (t->weighted && !t->w) || !t->range_ptr || !t->blk_rowoff) return hipErrorOutOfMemory;
+  t->mrange = t->range_ptr;
+  if (t->mk != t->k)
+    t->mrange = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (t->mR + 1) * static_cast<size_t>(B), s));
+  if (!t->mrange) return hipErrorOutOfMemory;
   uint16_t* col16 = nullptr;
   gc_head_word* heads = nullptr;
   if (pull_stream || push_stream) {
@@ -1180,14 +1184,17 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
   t->pmin = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (Pn + 8), s));  // padded for 16-byte reads
   t->id16 = static_cast<uint16_t*>(dev_alloc(sizeof(uint16_t) * Pn, s));
   if (!t->id_map || !t->row_ptr || !t->partial || !t->pmin || !t->id16) return hipErrorOutOfMemory;
-  t->bytes = sizeof(int32_t) * ((R + 1) * static_cast<int64_t>(B) + B + 1 + 4 * static_cast<int64_t>(Pn) + 1 +
+  t->bytes = sizeof(int32_t) * ((R + 1 + (t->mk != t->k ? t->mR + 1 : 0)) * static_cast<int64_t>(B) + B + 1 + 4 * static_cast<int64_t>(Pn) + 1 +
                                 mn * (t->weighted ? 2 : 1)) +
              static_cast<int64_t>(sizeof(uint16_t)) * P;
   k_local_rows<<<grid_for(heads ? head_words : words, 4, 16384), 256, 0, s>>>(
-      row, m, words, bits, wrow, t->k - 1, t->id_map, t->row_ptr, t->id16,
+      row, m, words, bits, wrow, t->mk - 1, t->id_map, t->row_ptr, t->id16,
       heads, head_words);
   k_range_rows<<<grid_for(static_cast<int64_t>(R + 1) * B, 256, 65536), 256, 0, s>>>(t->id_map, t->blk_rowoff, B, R,
                                                                                      t->log2k, t->range_ptr);
+  if (t->mk != t->k)
+    k_range_rows<<<grid_for(static_cast<int64_t>(t->mR + 1) * B, 256, 65536), 256, 0, s>>>(
+        t->id_map, t->blk_rowoff, B, t->mR, __builtin_ctz(t->mk), t->mrange);
   GC_HIP_TRY(hipGetLastError());
   GC_HIP_TRY(build_tiles(t->row_ptr, P, m, pull_tile_arcs(), &t->tile_row, &t->n_tiles, s));
   if (pull_stream && 4 * (P + 8) < (int64_t(1) << 31)) {

@@ -102,8 +102,12 @@ struct gc_tocab_s {
   int32_t* col = nullptr;         // [m]
   int32_t* w = nullptr;           // [m] or null
   int32_t* range_ptr = nullptr;   // [(R+1)*B], j-major
+  // Ranges the merges of a GC_PULL partition work in: k, R and range_ptr, or
+  // narrower ones where those are few (merge_width).
+  int32_t mk = 0, mR = 0;
+  int32_t* mrange = nullptr;      // [(mR+1)*B], j-major; range_ptr itself when mk = k
   float* partial = nullptr;       // [P] pull partial sums (Algorithm 4)
-  uint16_t* id16 = nullptr;       // [P] id_map mod k: position inside the merge range
+  uint16_t* id16 = nullptr;       // [P] id_map mod mk: position inside the merge range
   int32_t* tile_row = nullptr;    // [n_tiles+1] first local row of each pull tile
   int32_t n_tiles = 0;
   // Stream layout of an LDS-resident pull partition (W <= kLdsMaxWidth):
@@ -115,10 +119,9 @@ struct gc_tocab_s {
   int64_t m_pad = 0;              // multiple of wave_tile_arcs(), >= m + wave_tile_arcs()
   int32_t* wtile_row = nullptr;   // unused by the stream layout
   int32_t n_wtiles = 0;
-  int32_t sk = 0, sR = 0;         // width and number of the layout's own merge ranges (stream_range)
-  int2* seg = nullptr;            // [B][sR+1]: first local row of block b in range j, shift to range-major index
-  int32_t* rstart = nullptr;      // [sR+1] range-major start of merge range j
-  uint16_t* id16s = nullptr;      // [P] id_map mod sk in range-major order
+  int2* seg = nullptr;            // [B][mR+1]: first local row of block b in range j, shift to range-major index
+  int32_t* rstart = nullptr;      // [mR+1] range-major start of merge range j
+  uint16_t* id16s = nullptr;      // [P] id16 in range-major order
   int32_t* chunk_beg = nullptr;   // [n_chunks] first local row (one buffer holds the five chunk arrays)
   int32_t* chunk_end = nullptr;   // [n_chunks] one past the last local row
   int32_t* chunk_blk = nullptr;   // [n_chunks] block

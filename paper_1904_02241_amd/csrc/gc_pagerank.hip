@@ -1049,22 +1049,22 @@ hipError_t spmv_stream(gc_graph g, gc_tocab t, const float* x, const float* vals
       if (vals)
         k_pr_tocab_pull_lds<true><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, vals, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->sR, t->log2W, g->n, x, t->partial, bytes, nullptr);
+            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, nullptr);
       else
         k_pr_tocab_pull_lds<false><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->sR, t->log2W, g->n, x, t->partial, bytes, nullptr);
+            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, nullptr);
     }
   }
   ProfScope prof("spmv_merge", s);
-  switch (t->sk) {
-    case 256: k_spmv_merge_stream<256><<<t->sR, merge_threads<256>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
-    case 512: k_spmv_merge_stream<512><<<t->sR, merge_threads<512>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
-    case 1024: k_spmv_merge_stream<1024><<<t->sR, merge_threads<1024>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
-    case 2048: k_spmv_merge_stream<2048><<<t->sR, merge_threads<2048>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
-    case 4096: k_spmv_merge_stream<4096><<<t->sR, merge_threads<4096>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
-    case 8192: k_spmv_merge_stream<8192><<<t->sR, merge_threads<8192>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
-    case 16384: k_spmv_merge_stream<16384><<<t->sR, merge_threads<16384>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
+  switch (t->mk) {
+    case 256: k_spmv_merge_stream<256><<<t->mR, merge_threads<256>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
+    case 512: k_spmv_merge_stream<512><<<t->mR, merge_threads<512>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
+    case 1024: k_spmv_merge_stream<1024><<<t->mR, merge_threads<1024>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
+    case 2048: k_spmv_merge_stream<2048><<<t->mR, merge_threads<2048>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
+    case 4096: k_spmv_merge_stream<4096><<<t->mR, merge_threads<4096>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
+    case 8192: k_spmv_merge_stream<8192><<<t->mR, merge_threads<8192>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
+    case 16384: k_spmv_merge_stream<16384><<<t->mR, merge_threads<16384>(), 0, s>>>(t->rstart, t->id16s, t->partial, g->n, y); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1255,7 +1255,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   }
   // work-groups of the update kernel, one dangling partial each
   int32_t parts = vgrid;
-  if (t && !push) parts = t->col16 ? merge_persist_grid(t->sk, t->sR) : t->R;
+  if (t && !push) parts = t->col16 ? merge_persist_grid(t->mk, t->mR) : t->mR;
   else if (!push) parts = g->n_tiles_in;
   else if (t && t->W <= kPushLdsMaxWidth) parts = t->B;
   // D of the next iteration from `count` partials in u.dpart: left to its
@@ -1318,14 +1318,14 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
           if (t->n_chunks > 0)
             k_pr_tocab_pull_lds<false><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
                 t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-                t->chunk_ns, t->seg, t->sR, t->log2W, n, buf.contrib[0], buf.partial,
+                t->chunk_ns, t->seg, t->mR, t->log2W, n, buf.contrib[0], buf.partial,
                 static_cast<uint32_t>(sizeof(float) * (t->P + 8)), u.stop);
         }
         u.contrib = buf.contrib[0];
         ProfScope prof("pr_merge", s);
-        switch (t->sk) {
+        switch (t->mk) {
 #define GC_MERGE(K) \
-  case K: k_pr_merge_persist<K><<<parts, merge_threads<K>(), 0, s>>>(t->rstart, t->id16s, buf.partial, t->sR, u); break;
+  case K: k_pr_merge_persist<K><<<parts, merge_threads<K>(), 0, s>>>(t->rstart, t->id16s, buf.partial, t->mR, u); break;
           GC_MERGE(256) GC_MERGE(512) GC_MERGE(1024) GC_MERGE(2048) GC_MERGE(4096) GC_MERGE(8192) GC_MERGE(16384)
 #undef GC_MERGE
           default: return hipErrorInvalidValue;
@@ -1338,14 +1338,14 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
         }
         u.contrib = buf.contrib[0];  // safe in place: the pull pass has finished reading c
         ProfScope prof("pr_merge", s);
-        switch (t->k) {
-          case 256: launch_merge<256>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
-          case 512: launch_merge<512>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
-          case 1024: launch_merge<1024>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
-          case 2048: launch_merge<2048>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
-          case 4096: launch_merge<4096>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
-          case 8192: launch_merge<8192>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
-          case 16384: launch_merge<16384>(t->R, s, t->range_ptr, t->B, t->id16, buf.partial, u); break;
+        switch (t->mk) {
+          case 256: launch_merge<256>(t->mR, s, t->mrange, t->B, t->id16, buf.partial, u); break;
+          case 512: launch_merge<512>(t->mR, s, t->mrange, t->B, t->id16, buf.partial, u); break;
+          case 1024: launch_merge<1024>(t->mR, s, t->mrange, t->B, t->id16, buf.partial, u); break;
+          case 2048: launch_merge<2048>(t->mR, s, t->mrange, t->B, t->id16, buf.partial, u); break;
+          case 4096: launch_merge<4096>(t->mR, s, t->mrange, t->B, t->id16, buf.partial, u); break;
+          case 8192: launch_merge<8192>(t->mR, s, t->mrange, t->B, t->id16, buf.partial, u); break;
+          case 16384: launch_merge<16384>(t->mR, s, t->mrange, t->B, t->id16, buf.partial, u); break;
           default: return hipErrorInvalidValue;
         }
       }

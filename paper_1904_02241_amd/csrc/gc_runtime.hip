@@ -117,7 +117,8 @@ void free_graph(gc_graph g) {
 
 void free_tocab(gc_tocab t) {
   if (!t) return;
-  void* bufs[] = {t->blk_rowoff, t->row_ptr, t->id_map, t->col, t->w, t->range_ptr, t->partial, t->pmin,
+  if (t->mrange == t->range_ptr) t->mrange = nullptr;
+  void* bufs[] = {t->blk_rowoff, t->mrange, t->row_ptr, t->id_map, t->col, t->w, t->range_ptr, t->partial, t->pmin,
                   t->tile_row, t->col16, t->chunk_beg, t->wtile_row, t->id16,
                   t->heads, t->seg, t->rstart, t->id16s, t->bc_part,
                   t->val32, t->w_pad, t->w8, t->xid16, t->xperm, t->xstart, t->xc, t->pcol16, t->pheads};
@@ -489,7 +490,7 @@ int tocab_layout(gc_tocab t, int32_t* stream_layout, int32_t* chunks, int64_t* t
   const bool st = t->col16 != nullptr;
   if (stream_layout) *stream_layout = st ? 1 : 0;
   if (chunks) *chunks = st ? t->n_chunks : 0;
-  if (table_bytes) *table_bytes = st ? static_cast<int64_t>(sizeof(int2)) * t->B * (t->sR + 1) : 0;
+  if (table_bytes) *table_bytes = st ? static_cast<int64_t>(sizeof(int2)) * t->B * (t->mR + 1) : 0;
   return GC_OK;
 }
 

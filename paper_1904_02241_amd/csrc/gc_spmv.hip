@@ -95,14 +95,14 @@ hipError_t spmv_run(gc_graph g, gc_tocab t, const float* x, float* y, hipStream_
     if (t->n_tiles > 0) k_spmv_tocab<<<t->n_tiles, kThreads, 0, s>>>(t->row_ptr, t->col, t->tile_row, x, arc, t->partial);
   }
   ProfScope prof("spmv_merge", s);
-  switch (t->k) {
-    case 256: launch_spmv_merge<256>(t->R, s, t->range_ptr, t->B, t->id16, t->partial, g->n, y); break;
-    case 512: launch_spmv_merge<512>(t->R, s, t->range_ptr, t->B, t->id16, t->partial, g->n, y); break;
-    case 1024: launch_spmv_merge<1024>(t->R, s, t->range_ptr, t->B, t->id16, t->partial, g->n, y); break;
-    case 2048: launch_spmv_merge<2048>(t->R, s, t->range_ptr, t->B, t->id16, t->partial, g->n, y); break;
-    case 4096: launch_spmv_merge<4096>(t->R, s, t->range_ptr, t->B, t->id16, t->partial, g->n, y); break;
-    case 8192: launch_spmv_merge<8192>(t->R, s, t->range_ptr, t->B, t->id16, t->partial, g->n, y); break;
-    case 16384: launch_spmv_merge<16384>(t->R, s, t->range_ptr, t->B, t->id16, t->partial, g->n, y); break;
+  switch (t->mk) {
+    case 256: launch_spmv_merge<256>(t->mR, s, t->mrange, t->B, t->id16, t->partial, g->n, y); break;
+    case 512: launch_spmv_merge<512>(t->mR, s, t->mrange, t->B, t->id16, t->partial, g->n, y); break;
+    case 1024: launch_spmv_merge<1024>(t->mR, s, t->mrange, t->B, t->id16, t->partial, g->n, y); break;
+    case 2048: launch_spmv_merge<2048>(t->mR, s, t->mrange, t->B, t->id16, t->partial, g->n, y); break;
+    case 4096: launch_spmv_merge<4096>(t->mR, s, t->mrange, t->B, t->id16, t->partial, g->n, y); break;
+    case 8192: launch_spmv_merge<8192>(t->mR, s, t->mrange, t->B, t->id16, t->partial, g->n, y); break;
+    case 16384: launch_spmv_merge<16384>(t->mR, s, t->mrange, t->B, t->id16, t->partial, g->n, y); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

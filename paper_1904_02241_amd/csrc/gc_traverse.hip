@@ -2070,12 +2070,12 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
         if (t->n_chunks > 0)
           k_sssp_tocab_lds<kWNone><<<t->n_chunks, kLdsThreads, tocab_lds_bytes(t), s>>>(
               t->row_ptr, t->col16, t->heads, nullptr, 0u, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-              t->chunk_ns, t->seg, t->sR, t->log2W, n, f.front(), nullptr, t->pmin, pmin_bytes(t), g->stats);
+              t->chunk_ns, t->seg, t->mR, t->log2W, n, f.front(), nullptr, t->pmin, pmin_bytes(t), g->stats);
       }
       ProfScope prof("bfs_merge", s);
-      GC_HIP_TRY((launch_by_k<BfsMergeStream>(t->sk, t->sR, s, static_cast<const int32_t*>(t->rstart),
+      GC_HIP_TRY((launch_by_k<BfsMergeStream>(t->mk, t->mR, s, static_cast<const int32_t*>(t->rstart),
                                               static_cast<const uint16_t*>(t->id16s),
-                                              static_cast<const int32_t*>(t->pmin), t->sR, n, value, f.next(),
+                                              static_cast<const int32_t*>(t->pmin), t->mR, n, value, f.next(),
                                               tally, level, g->visited)));
     } else {
       uint8_t* flag = reinterpret_cast<uint8_t*>(t->pmin);
@@ -2085,7 +2085,7 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
                                                                    f.front(), flag, g->stats);
       }
       ProfScope prof("bfs_merge", s);
-      GC_HIP_TRY((launch_by_k<BfsMerge>(t->k, t->R, s, static_cast<const int32_t*>(t->range_ptr), t->B,
+      GC_HIP_TRY((launch_by_k<BfsMerge>(t->mk, t->mR, s, static_cast<const int32_t*>(t->mrange), t->B,
                                         static_cast<const uint16_t*>(t->id16),
                                         static_cast<const uint8_t*>(flag), n, value, level, f.next(), g->visited,
                                         tally)));
@@ -2111,16 +2111,16 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
           if (t->n_chunks > 0 && t->w8)
             k_sssp_tocab_lds<kW8><<<t->n_chunks, kLdsThreads, lds, s>>>(
                 t->row_ptr, t->col16, t->heads, t->w8, 255u, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-                t->chunk_ns, t->seg, t->sR, t->log2W, n, f.front(), value, t->pmin, pmin_bytes(t), g->stats);
+                t->chunk_ns, t->seg, t->mR, t->log2W, n, f.front(), value, t->pmin, pmin_bytes(t), g->stats);
           else if (t->n_chunks > 0)
             k_sssp_tocab_lds<kW32><<<t->n_chunks, kLdsThreads, lds, s>>>(
                 t->row_ptr, t->col16, t->heads, t->w_pad, static_cast<uint32_t>(kInf), t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-                t->chunk_ns, t->seg, t->sR, t->log2W, n, f.front(), value, t->pmin, pmin_bytes(t), g->stats);
+                t->chunk_ns, t->seg, t->mR, t->log2W, n, f.front(), value, t->pmin, pmin_bytes(t), g->stats);
         }
         ProfScope prof("sssp_merge", s);
-        GC_HIP_TRY((launch_by_k<SsspMergeStream>(t->sk, t->sR, s, static_cast<const int32_t*>(t->rstart),
+        GC_HIP_TRY((launch_by_k<SsspMergeStream>(t->mk, t->mR, s, static_cast<const int32_t*>(t->rstart),
                                                  static_cast<const uint16_t*>(t->id16s),
-                                                 static_cast<const int32_t*>(t->pmin), t->sR, n, value, f.next(),
+                                                 static_cast<const int32_t*>(t->pmin), t->mR, n, value, f.next(),
                                                  tally, level, g->visited)));
         return hipGetLastError();
       } else {
@@ -2129,7 +2129,7 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
                                                          t->pmin, g->stats);
       }
       ProfScope prof("sssp_merge", s);
-      GC_HIP_TRY((launch_by_k<SsspMerge>(t->k, t->R, s, static_cast<const int32_t*>(t->range_ptr), t->B,
+      GC_HIP_TRY((launch_by_k<SsspMerge>(t->mk, t->mR, s, static_cast<const int32_t*>(t->mrange), t->B,
                                          static_cast<const uint16_t*>(t->id16),
                                          static_cast<const int32_t*>(t->pmin), n, value, f.next(), tally)));
     }
@@ -2192,7 +2192,7 @@ hipError_t run_bc_level(gc_graph g, Frontier& f, int32_t level, Mode mode, gc_to
                                                                 f.front(), g->bc_sigma, t->bc_part);
     }
     ProfScope prof("bc_merge", s);
-    GC_HIP_TRY((launch_by_k<BcMerge>(t->k, t->R, s, static_cast<const int32_t*>(t->range_ptr), t->B,
+    GC_HIP_TRY((launch_by_k<BcMerge>(t->mk, t->mR, s, static_cast<const int32_t*>(t->mrange), t->B,
                                      static_cast<const uint16_t*>(t->id16), static_cast<const double*>(t->bc_part),
                                      n, g->bc_depth, level, g->bc_sigma, f.next(), g->visited, tally)));
   }

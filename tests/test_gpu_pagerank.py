@@ -136,12 +136,13 @@ def test_pagerank_chunk_cuts(make, W, k):
 
 
 @pytest.mark.parametrize("n", [255, 16385, 32768, 130000, 2 * 127 * 1024 + 1, 128 * 2048])
-@pytest.mark.parametrize("k", [256, 2048, 16384])
-def test_pagerank_split_merge_ranges(n, k):
-    """Merge ranges as wide as given, halved once, or down to 256 vertices."""
+@pytest.mark.parametrize("W,k", [(1 << 13, 256), (1 << 13, 2048), (1 << 13, 16384), (1 << 16, 512), (1 << 16, 2048),
+                                 (1 << 16, 16384)])
+def test_pagerank_split_merge_ranges(n, W, k):
+    """Merge ranges as wide as given, halved once, or down to the least width."""
     g = gg.uniform(n, 6 * n, seed=n)
-    print(f"split ranges n={n} k={k}", flush=True)
-    got, r0 = pagerank_gpu(g, "tocab_pull", oracle.UNIFORM, iters=2, W=1 << 13, k=k)
+    print(f"split ranges n={n} W={W} k={k}", flush=True)
+    got, r0 = pagerank_gpu(g, "tocab_pull", oracle.UNIFORM, iters=2, W=W, k=k)
     want = oracle.pagerank(g.n, g.rowptr, g.colidx, 0.85, 2, r0=r0)
     assert l1(got, want) <= L1_TOL
 
