@@ -1090,7 +1090,7 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
   // once (pull), and 32-bit arc indices past the padded end
   const bool pull_stream = t->dir == GC_PULL && t->W <= kLdsMaxWidth &&
                            static_cast<int64_t>(B) * (R + 1) <= (int64_t(1) << 25) && m + 1024 < INT32_MAX;
-  const bool push_stream = t->dir == GC_PUSH && t->W <= kPushLdsMaxWidth && t->k <= t->W && m > 0 &&
+  const bool push_stream = t->dir == GC_PUSH && !t->inner && t->W <= kPushLdsMaxWidth && t->k <= t->W && m > 0 &&
                            m + 1024 < INT32_MAX && B <= kPushExpandMaxBlocks;
   t->mk = t->dir == GC_PULL ? merge_width(t->n_rows, m, B, t->k, t->W <= kLdsMaxWidth) : t->k;
   t->mR = (t->n_rows + t->mk - 1) / t->mk;

@@ -134,6 +134,9 @@ struct gc_tocab_s {
   float* val32 = nullptr;         // [m_pad] FP32 arc values in stream order (first valued SpMV)
   int32_t* w_pad = nullptr;       // [m_pad] integer weights in stream order, 0 past m (first SSSP over the stream layout)
   uint8_t* w8 = nullptr;          // [m_pad] the same as bytes, instead of w_pad when every weight lies in [0, 255]
+  // GC_PUSH: the same arcs in blocks of the width that PageRank is fastest
+  // over (push_width), which it takes instead; null: W itself.
+  gc_tocab inner = nullptr;
   // Expanded contributions of a GC_PUSH partition with block sums in LDS
   // (W <= kPushLdsMaxWidth, B <= kPushExpandMaxBlocks): the work-group that
   // updates source block s writes the new contribution of each local row
@@ -216,6 +219,19 @@ int32_t wave_tile_arcs();
 constexpr int32_t kLdsMaxWidth = 1 << 15;
 // Largest block width of a TOCAB push whose block sums (FP64) sit in LDS.
 constexpr int32_t kPushLdsMaxWidth = 1 << 14;
+// Width of the blocks that the push with block sums in LDS runs over:
+// kPushLdsMaxWidth, halved until there are kPushBlocks of them (or they are
+// 1024 wide), one work-group each; wider blocks hold a source's arcs in fewer
+// rows. PageRank, 20 iterations at 2^14, 13, 12, 11, 10: R-MAT of 16 arcs and
+// 20,000 vertices 1420, 954, 592, 477, 370 us; 300,007: 1690, 1073, 812, 698,
+// 725; 10^6: 2398, 1884, 1652, 2043, 2654; 3 M: 3182, 3799, 4334, 5062, 7938.
+constexpr int32_t kPushBlocks = 128;
+inline int32_t push_width(int32_t n, int32_t W) {
+  if (W > kPushLdsMaxWidth) return W;
+  W = kPushLdsMaxWidth;
+  while (W > 1024 && (static_cast<int64_t>(n) + W - 1) / W < kPushBlocks) W /= 2;
+  return W;
+}
 // Most blocks of a push partition with expanded contributions (a work-group
 // keeps two run bounds per block in LDS).
 constexpr int32_t kPushExpandMaxBlocks = 4096;

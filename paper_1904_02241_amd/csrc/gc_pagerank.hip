@@ -1231,6 +1231,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   if (pr_small_fits(g, cv != nullptr))
     return pr_small_run(g, damping, dangling, rank_in, rank_out, iters, s, cv);
   const bool push = t ? (t->dir == GC_PUSH) : (dir == GC_PUSH);
+  if (t && t->inner) t = t->inner;
   Update u;
   u.d = damping;
   u.base = (1.0 - static_cast<double>(damping)) / n;

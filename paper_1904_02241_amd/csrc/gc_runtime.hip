@@ -117,6 +117,7 @@ void free_graph(gc_graph g) {
 
 void free_tocab(gc_tocab t) {
   if (!t) return;
+  free_tocab(t->inner);
   if (t->mrange == t->range_ptr) t->mrange = nullptr;
   void* bufs[] = {t->blk_rowoff, t->mrange, t->row_ptr, t->id_map, t->col, t->w, t->range_ptr, t->partial, t->pmin,
                   t->tile_row, t->col16, t->chunk_beg, t->wtile_row, t->id16,
@@ -435,29 +436,45 @@ int tocab_partition(gc_graph g, int32_t dir, int32_t block_width, int32_t merge_
     return fail(GC_EUNSUPPORTED, "tocab_partition: %lld x %lld range table too large; widen block or merge range",
                 (long long)B, (long long)(R + 1));
 
-  gc_tocab t = new (std::nothrow) gc_tocab_s;
+  auto make = [&](int32_t W, int32_t k) -> gc_tocab {
+    gc_tocab t = new (std::nothrow) gc_tocab_s;
+    if (!t) return nullptr;
+    t->g = g;
+    t->dir = dir;
+    t->W = W;
+    t->log2W = ilog2(W);
+    t->k = k;
+    t->log2k = ilog2(k);
+    t->B = static_cast<int32_t>((static_cast<int64_t>(g->n) + W - 1) / W);
+    t->R = static_cast<int32_t>((static_cast<int64_t>(g->n) + k - 1) / k);
+    t->n_rows = g->n;
+    t->n_cols = g->n;
+    t->m = g->m;
+    return t;
+  };
+  gc_tocab t = make(block_width, merge_range);
   if (!t) return fail(GC_ENOMEM, "tocab_partition: host allocation failed");
-  t->g = g;
-  t->dir = dir;
-  t->W = block_width;
-  t->log2W = ilog2(block_width);
-  t->k = merge_range;
-  t->log2k = ilog2(merge_range);
-  t->B = static_cast<int32_t>(B);
-  t->R = static_cast<int32_t>(R);
-  t->n_rows = g->n;
-  t->n_cols = g->n;
-  t->m = g->m;
   t->weighted = g->weighted;
   const int32_t* a_rowptr = dir == GC_PULL ? g->t_rowptr : g->rowptr;
   const int32_t* a_col = dir == GC_PULL ? g->t_colidx : g->colidx;
   const int32_t* a_w = dir == GC_PULL ? g->t_w : g->w;
+  // (graphs that run in one work-group need no second layout)
+  const int32_t push_w =
+      dir == GC_PUSH && !gcx::pr_small_fits(g, true) ? gcx::push_width(g->n, block_width) : block_width;
+  if (push_w != block_width && (t->inner = make(push_w, push_w)) != nullptr &&
+      gcx::build_partition(t->inner, a_rowptr, a_col, nullptr, stream) != hipSuccess) {
+    (void)hipGetLastError();  // no memory for a second layout: PageRank runs over the blocks as given
+    (void)hipStreamSynchronize(stream);
+    free_tocab(t->inner);
+    t->inner = nullptr;
+  }
   hipError_t e = gcx::build_partition(t, a_rowptr, a_col, a_w, stream);
   if (e != hipSuccess) {
     (void)hipStreamSynchronize(stream);
     free_tocab(t);
     return hip_fail(e, "tocab_partition");
   }
+  if (t->inner) t->bytes += t->inner->bytes;
   *out = t;
   return GC_OK;
 }

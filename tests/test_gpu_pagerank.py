@@ -147,6 +147,27 @@ def test_pagerank_split_merge_ranges(n, W, k):
     assert l1(got, want) <= L1_TOL
 
 
+@pytest.mark.parametrize("n,W,k", [(9000, 1 << 14, 16384), (16385, 1 << 11, 256), (127 * 1024, 1 << 10, 1024),
+                                   (128 * 1024 + 1, 1 << 14, 4096), (300001, 1 << 13, 256),
+                                   (2100000, 1 << 11, 1024)])
+@pytest.mark.parametrize("mode", [oracle.UNIFORM, oracle.LEAK])
+def test_pagerank_push_inner_blocks(n, W, k, mode):
+    """Push over narrower and wider blocks than the partition's: the least
+    width, one short of enough blocks, ranges wider than the inner blocks; and
+    the partition itself is still as asked for."""
+    import paper_1904_02241_amd as gc
+    g = gg.uniform(n, 5 * n, seed=n)
+    print(f"push inner n={n} W={W} k={k} mode={mode}", flush=True)
+    got, r0 = pagerank_gpu(g, "tocab_push", mode, iters=3, W=W, k=k)
+    want = oracle.pagerank(g.n, g.rowptr, g.colidx, 0.85, 3, mode=mode, r0=r0)
+    assert l1(got, want) <= L1_TOL
+    h = load(g)
+    part = gc.tocab_partition(h, gc.GC_PUSH, W, k)
+    assert (part.info["W"], part.info["k"], part.info["B"]) == (W, k, (n + W - 1) // W)
+    part.free()
+    h.free()
+
+
 def test_pagerank_rejects_overlap_and_bad_args():
     import paper_1904_02241_amd as gc
     from tests.gpu_util import torch
