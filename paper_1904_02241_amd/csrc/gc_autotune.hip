@@ -28,6 +28,14 @@ bool allowed(int64_t n, int32_t W, int32_t k) {
   return B <= 32768 && B * (R + 1) <= (int64_t(1) << 28);
 }
 
+// Whether the partitions of width W with merge ranges k and j run alike.
+bool same_ranges(gc_graph g, int32_t dir, int32_t W, int32_t k, int32_t j) {
+  if (dir == GC_PUSH) return gcx::push_width(g->n, W) != W;
+  const int32_t B = static_cast<int32_t>((static_cast<int64_t>(g->n) + W - 1) / W);
+  const bool stream = W <= gcx::kLdsMaxWidth;
+  return gcx::merge_width(g->n, g->m, B, k, stream) == gcx::merge_width(g->n, g->m, B, j, stream);
+}
+
 // Times `iters` PageRank iterations on partition t (after one warm-up).
 hipError_t time_iters(gc_graph g, gc_tocab t, int32_t iters, float* ra, float* rb, hipStream_t s, double* ms) {
   GC_HIP_TRY(gcx::pagerank_run(g, t, t->dir, 0.85f, GC_DANGLING_UNIFORM, ra, rb, 1, s));
@@ -114,7 +122,7 @@ hipError_t autotune(gc_graph g, int32_t dir, int32_t min_W, int32_t* W_out, int3
   Candidate best = cand[0];
   if (best.ms == 0.0) GC_HIP_TRY(evaluate(best, iters));
   for (int32_t k : {2048, 8192, 16384}) {
-    if (!allowed(n, best.W, k)) continue;
+    if (!allowed(n, best.W, k) || same_ranges(g, dir, best.W, k, best.k)) continue;
     Candidate c{best.W, k};
     GC_HIP_TRY(evaluate(c, iters));
     Candidate b2 = best;

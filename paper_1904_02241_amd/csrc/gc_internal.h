@@ -225,12 +225,14 @@ constexpr int32_t kPushLdsMaxWidth = 1 << 14;
 // rows. PageRank, 20 iterations at 2^14, 13, 12, 11, 10: R-MAT of 16 arcs and
 // 20,000 vertices 1420, 954, 592, 477, 370 us; 300,007: 1690, 1073, 812, 698,
 // 725; 10^6: 2398, 1884, 1652, 2043, 2654; 3 M: 3182, 3799, 4334, 5062, 7938.
+// W itself where the width would be twice that: 15 % of a run, and a second
+// layout to build (a grid of 2 M vertices at 2^12 with its transpose 1457 us,
+// 2144 with one).
 constexpr int32_t kPushBlocks = 128;
 inline int32_t push_width(int32_t n, int32_t W) {
-  if (W > kPushLdsMaxWidth) return W;
-  W = kPushLdsMaxWidth;
-  while (W > 1024 && (static_cast<int64_t>(n) + W - 1) / W < kPushBlocks) W /= 2;
-  return W;
+  int32_t w = kPushLdsMaxWidth;
+  while (w > 1024 && (static_cast<int64_t>(n) + w - 1) / w < kPushBlocks) w /= 2;
+  return W > kPushLdsMaxWidth || w == 2 * W ? W : w;
 }
 // Most blocks of a push partition with expanded contributions (a work-group
 // keeps two run bounds per block in LDS).
@@ -286,6 +288,9 @@ struct PrBuffers {
 hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int32_t dangling,
                         const float* rank_in, float* rank_out, int32_t iters, hipStream_t s,
                         Converge* cv = nullptr, int32_t ladder = -1, const PrBuffers* bufs = nullptr);
+
+// Width of the ranges that the merges of a pull partition work in.
+int32_t merge_width(int32_t n, int64_t m, int32_t B, int32_t k, bool stream);
 
 // Small graphs (gc_pr_small.hip): whether all of g's iterations fit one
 // work-group's LDS, and that form of pagerank_run.
