@@ -117,8 +117,13 @@ int graph_free(gc_graph g);
  * merge_range k: power of two in [256, 16384], width of the merge ranges of
  * Figure 5 (0 = 4096, or the autotuned value when W = 0). Inside block s only rows with at least one arc there
  * get a local id, in ascending global order; id_map maps local to global.
+ * The merges of a GC_PULL partition may work in narrower ranges than k (its
+ * arrays and k stay as given).
  * A GC_PUSH partition with W <= 2^14 and k <= W (its block sums fit in LDS)
- * also holds the expanded-contribution form its PageRank iterations use:
+ * also holds the expanded-contribution form its PageRank iterations use, over
+ * its own blocks or over a second copy of its arcs in blocks of the width
+ * that they are fastest at (2^14, halved until there are 128; left out where
+ * there is no memory for it):
  * the local rows in source-major order (int32 + uint16 per row), two FP32
  * buffers of one contribution per local row (written each iteration by the
  * work-group that updates the row's source), and the arcs as streams (16-bit
@@ -131,7 +136,8 @@ int tocab_partition(gc_graph g, int32_t dir, int32_t block_width, int32_t merge_
  * size with a sweep, Section 4.3): candidate widths 2^12 .. min(2^22, n)
  * are timed on PageRank iterations of the graph itself with successive
  * halving (2, 4, 8, ... iterations; the faster half survives each round),
- * then merge ranges 2048 / 4096 / 8192 are compared for the winner. Builds
+ * then merge ranges 2048 / 4096 / 8192 / 16384 that run differently are
+ * compared for the winner. Builds
  * and frees candidate partitions (needs room for one at a time), allocates
  * two rank vectors, synchronises `stream`. The result is cached per graph
  * signature (n, m, sampled offsets) for the life of the process.

@@ -5,7 +5,7 @@
 //              paper's status array, at n/8 bytes: 2 MB at 2^24 vertices,
 //              so the random tests of a pull level stay in one XCD's L2)
 //   next       the same for the next level; all zero when a level starts
-//              (cleared through the old frontier's queue)
+//              (k_level_end clears the old frontier's)
 //   queue      list of the current frontier (size n_f), and the list being
 //              filled for the next level
 //   visited    bitmap of vertices with a final depth (BFS)
