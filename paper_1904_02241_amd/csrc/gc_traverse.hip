@@ -1718,15 +1718,16 @@ struct Heuristic {
   static constexpr double kAlpha = 14.0, kBeta = 24.0;
   static constexpr double kCacheBytes = 4.0 * 1024 * 1024;  // one XCD's L2
   // BFS over a stream-layout partition: TOCAB pull on graphs with at most
-  // kBfsTocabDegree arcs per vertex, while at least 1/64 of the arcs still
-  // end at unvisited vertices. Measured per level on the grid (4 arcs per
-  // vertex), uniform (8) and R-MAT 22 / 24 (16) graphs: a TOCAB pull level
-  // costs 3-6 ps per arc, a plain-pull level about 50 ps per vertex while
-  // many vertices are unvisited (one thread per vertex, early exit, status
-  // bits in L2), so TOCAB halves the grid's dense levels, gains a quarter
-  // on the uniform graph's and ties on R-MAT's; once fewer than 1/64 of the
-  // arcs end at unvisited vertices the plain pull is up to three times
-  // faster.
+  // kBfsTocabVertices vertices and kBfsTocabDegree arcs per vertex, while at
+  // least 1/64 of the arcs still end at unvisited vertices; else plain pull.
+  // The plain pull is the faster since a wave walks its rows end to end
+  // (early exit, status bits in L2). A whole BFS with the TOCAB arm and
+  // without: grids of 160,000, 10^6, 4 and 8 M vertices 501, 668, 1052, 1616
+  // us against 453, 553, 772, 1163; uniform of 8 arcs per vertex 229, 317, 604,
+  // 879 against 209, 273, 525, 758; R-MAT of 8 194, 252, 370, 440 against 174,
+  // 201, 300, 340. Up to 2^18 vertices that is some 10 us per level, and the
+  // blocked form, which the method is about, stays; beyond it grows with n.
+  static constexpr int64_t kBfsTocabVertices = int64_t{1} << 18;
   static constexpr double kBfsTocabShare = 1.0 / 64.0;
   static constexpr double kBfsTocabDegree = 10.0;
   bool pulling = false;
@@ -1738,7 +1739,7 @@ struct Heuristic {
     else if (pulling && static_cast<double>(n_f) < static_cast<double>(n) / kBeta) pulling = false;
     if (!pulling) return Mode::kPush;
     if (bfs && have_tocab && stream)
-      return static_cast<double>(m) <= kBfsTocabDegree * static_cast<double>(n) &&
+      return n <= kBfsTocabVertices && static_cast<double>(m) <= kBfsTocabDegree * static_cast<double>(n) &&
                      static_cast<double>(m_u_in) >= kBfsTocabShare * static_cast<double>(m)
                  ? Mode::kTocab
                  : Mode::kPull;
@@ -2246,7 +2247,8 @@ hipError_t traverse(gc_graph g, gc_tocab t, int32_t source, int32_t* value, int3
   // the working-set rule's BFS arm over a stream-layout partition reads the
   // unvisited vertices' in-arcs
   f.count_in = bfs && (policy == GC_POLICY_HEURISTIC || policy == GC_POLICY_LEARNED) && fall_t != nullptr &&
-               fall_t->col16 != nullptr && static_cast<double>(g->m) <= Heuristic::kBfsTocabDegree * n;
+               fall_t->col16 != nullptr && n <= Heuristic::kBfsTocabVertices &&
+               static_cast<double>(g->m) <= Heuristic::kBfsTocabDegree * n;
   std::vector<float> outs(static_cast<size_t>(std::max(K, 1)));
   while (f.n_f > 0) {
     if (!bfs && level > n) return hipErrorInvalidValue;  // cannot happen with positive weights

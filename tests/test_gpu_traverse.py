@@ -293,3 +293,20 @@ def test_pull_rows_of_every_length(rows, at, W):
     if part is not None:
         part.free()
     h.free()
+
+
+@pytest.mark.parametrize("side,tocab", [(512, True), (513, False)])
+def test_heuristic_bfs_arm_ends_at_2_18_vertices(side, tocab):
+    import paper_1904_02241_amd as gc
+    g = gg.grid(side, side, 0.05, seed=3)  # 2^18 vertices, and more
+    print(f"heuristic bfs arm grid{side}", flush=True)
+    h = load(g)
+    part = gc.tocab_partition(h, gc.GC_PULL, 1 << 14, 4096)
+    d = torch().empty(g.n, dtype=torch().int32, device="cuda")
+    s = int(gg.sources(g, 1, seed=5)[0])
+    gc.bfs_pull(h, part, s, d, gc.GC_POLICY_HEURISTIC)
+    np.testing.assert_array_equal(host(d), oracle.bfs(g.n, g.rowptr, g.colidx, s))
+    acts = set(gc.traversal_trace(h)[0].tolist())
+    assert acts == ({0, 1, 2} if tocab else {0, 1}), acts
+    part.free()
+    h.free()
