@@ -225,13 +225,12 @@ __device__ __forceinline__ double sum_slots(const double* p, int32_t count, int3
 // Finishes row v of an iteration from its in-arc sum s (lane = seed):
 // writes its next contribution and, on the last iteration, its rank; returns
 // its dangling mass (its rank when it has no out-arc).
-__device__ __forceinline__ double ppr_finish(const BPpr& p, int32_t v, double s, int32_t it, double d, double D,
-                                             int32_t seed, float* out) {
+__device__ __forceinline__ double ppr_finish(const BPpr& p, int32_t v, int32_t deg, double s, int32_t it, double d,
+                                             double D, int32_t seed, float* out) {
   const int lane = threadIdx.x & (kWave - 1);
   const double pv = (v == seed) ? 1.0 : 0.0;
   const double r = (1.0 - d) * pv + d * (s + D * pv);
   const float r32 = static_cast<float>(r);
-  const int32_t deg = p.rowptr[v + 1] - p.rowptr[v];
   p.c[(it + 1) & 1][static_cast<int64_t>(v) * kPprLanes + lane] =
       deg ? static_cast<float>(static_cast<double>(r32) / deg) : 0.0f;
   if (out && lane < p.S) out[static_cast<int64_t>(v) * p.S + lane] = r32;
@@ -257,13 +256,19 @@ __device__ double ppr_unit(const BPpr& p, const PprUnit& q, int32_t it, double d
   const bool run = q.r0 >= 0;
   int32_t v = run ? q.r0 : 0;  // current row
   const int32_t last = run ? q.r1 : 0;
-  // ends of rows base .. base + 63, one per lane
-  int32_t base = v;
-  int32_t ends = p.t_rowptr[min(base + 1 + lane, p.n)];
+  // ends and out-degrees of rows base .. base + 63, one per lane (a load of
+  // each row's own where it is finished is a round trip per row: one graph of
+  // 200,003 vertices and 8 seeds, 20 iterations, 3154 -> 2998 us)
+  int32_t base = v, ends, degs;
+  auto load_rows = [&] {
+    ends = p.t_rowptr[min(base + 1 + lane, p.n)];
+    degs = p.rowptr[min(base + 1 + lane, p.n)] - p.rowptr[min(base + lane, p.n)];
+  };
+  load_rows();
   auto row_end = [&](int32_t r) {
     if (r - base >= kWave) {
       base = r;
-      ends = p.t_rowptr[min(base + 1 + lane, p.n)];
+      load_rows();
     }
     return __builtin_amdgcn_readlane(ends, r - base);
   };
@@ -272,7 +277,7 @@ __device__ double ppr_unit(const BPpr& p, const PprUnit& q, int32_t it, double d
   // rows that end at or before arc a (empty ones included) are finished
   auto flush_to = [&](int32_t a) {
     while (v < last && vend <= a) {
-      dang += ppr_finish(p, v, s, it, d, D, seed, out);
+      dang += ppr_finish(p, v, __builtin_amdgcn_readlane(degs, v - base), s, it, d, D, seed, out);
       s = 0.0;
       ++v;
       vend = v < last ? row_end(v) : INT32_MAX;
@@ -353,7 +358,7 @@ __device__ void ppr_long_rows(const BPpr& p, int32_t item, int32_t it, double d,
     double s = 0.0;
 #pragma unroll 8
     for (int32_t c = l.p0; c < l.p1; ++c) s += p.piece[static_cast<int64_t>(c) * kPprLanes + lane];
-    mine = ppr_finish(p, l.row, s, it, d, D, seed, out);
+    mine = ppr_finish(p, l.row, p.rowptr[l.row + 1] - p.rowptr[l.row], s, it, d, D, seed, out);
   }
   ppr_dangling(p.dfix[it & 1] + static_cast<int64_t>(item) * kPprLanes, mine);
 }
