@@ -704,21 +704,37 @@ __device__ __forceinline__ void hold_raw(const RawTile& t, const uint32_t (&x)[k
   for (int e = 0; e < kArcsPerLane; ++e) asm volatile("" ::"v"(x[e]));
 }
 
+// The lane's arcs of tile q (bit e: arc e) that lie in [a0, a1) (indices
+// past the layout's end still fit 32 bits).
+__device__ __forceinline__ uint32_t arcs_inside(int32_t q, int lane, int32_t a0, int32_t a1) {
+  const int32_t b = q * kWaveTile + kArcsPerLane * lane;
+  const int32_t lo = min(max(a0 - b, 0), kArcsPerLane), hi = min(max(a1 - b, 0), kArcsPerLane);
+  return (0xFFu << lo) & ~(0xFFu << hi);
+}
+
 // The lane's candidates from the slice at ad. check (uniform): a path length
-// may reach INT32_MAX in this block; *ovf is set when one does.
-template <int kW>
-__device__ __forceinline__ void gather_min(const RawTile& r, const uint32_t* ad, bool check,
+// may reach INT32_MAX in this block; *ovf is set when one does over an arc of
+// the mask own(). The first and the last tile of a chunk also hold arcs of
+// the blocks beside it, whose columns are offsets into other slices: they are
+// left out of the mask.
+template <int kW, class Own>
+__device__ __forceinline__ void gather_min(const RawTile& r, const uint32_t* ad, bool check, Own&& own,
                                            uint32_t (&x)[kArcsPerLane], bool* ovf) {
 #pragma unroll
   for (int e = 0; e < kArcsPerLane; ++e) x[e] = ad[(r.cols[e >> 1] >> (16 * (e & 1))) & 0xFFFFu];
   if (kW == kWNone) return;
+  uint32_t w[kArcsPerLane];
 #pragma unroll
-  for (int e = 0; e < kArcsPerLane; ++e) {
-    const uint32_t w = kW == kW8 ? static_cast<uint32_t>(r.w8 >> (8 * e)) & 0xFFu
-                                 : static_cast<uint32_t>(e < 4 ? r.wa[e] : r.wb[e - 4]);
-    if (check) *ovf |= x[e] != 0u && w >= x[e];
-    x[e] = __builtin_elementwise_sub_sat(x[e], w);
+  for (int e = 0; e < kArcsPerLane; ++e)
+    w[e] = kW == kW8 ? static_cast<uint32_t>(r.w8 >> (8 * e)) & 0xFFu
+                     : static_cast<uint32_t>(e < 4 ? r.wa[e] : r.wb[e - 4]);
+  if (check) {
+    const uint32_t mine = own();
+#pragma unroll
+    for (int e = 0; e < kArcsPerLane; ++e) *ovf |= ((mine >> e) & 1u) && x[e] != 0u && w[e] >= x[e];
   }
+#pragma unroll
+  for (int e = 0; e < kArcsPerLane; ++e) x[e] = __builtin_elementwise_sub_sat(x[e], w[e]);
 }
 
 // Largest candidate over the tiles after tile q of the row open at q's end,
@@ -737,7 +753,7 @@ __device__ uint32_t finish_open_min(const uint16_t* __restrict__ col16, const gc
     const int mine = lane < first_lane ? kArcsPerLane : (lane == first_lane ? __ffs(my8) - 1 : 0);
     uint32_t x[kArcsPerLane];
     bool o = false;
-    gather_min<kW>(r, ad, check && mine == kArcsPerLane, x, &o);
+    gather_min<kW>(r, ad, check, [&] { return (1u << mine) - 1u; }, x, &o);
     *ovf |= o;
     uint32_t m = 0;
 #pragma unroll
@@ -766,7 +782,8 @@ __global__ __launch_bounds__(kLdsThreads) void k_sssp_tocab_lds(
   // issued before the block's LDS fill and overlap it.
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
-  const int32_t q0 = row_ptr[r0] / kWaveTile, q1 = (row_ptr[r1] - 1) / kWaveTile;
+  const int32_t a0 = row_ptr[r0], a1 = row_ptr[r1];  // the chunk's arcs
+  const int32_t q0 = a0 / kWaveTile, q1 = (a1 - 1) / kWaveTile;
   const int32_t nt = q1 - q0 + 1;
   const int32_t qa = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * wid / kLdsWaves);
   const int32_t qz = q0 + static_cast<int32_t>(static_cast<int64_t>(nt) * (wid + 1) / kLdsWaves) - 1;
@@ -846,9 +863,11 @@ __global__ __launch_bounds__(kLdsThreads) void k_sssp_tocab_lds(
   load_window(sb, sd, ns, lane, cr);
   cursor_from_window(cr);
   uint32_t x0[kArcsPerLane], x1[kArcsPerLane];
-  gather_min<kW>(t0, ad, check, x0, &ovf);
+  // the chunk's arcs of the wave's tile i (clamped to its last)
+  auto own = [&](int32_t i) { return [=] { return arcs_inside(min(i, qz), lane, a0, a1); }; };
+  gather_min<kW>(t0, ad, check, own(q), x0, &ovf);
 #define GC_MIN_STEP(cur, xcur, nxt, xnxt, k)                                       \
-  gather_min<kW>(nxt, ad, check, xnxt, &ovf);                                      \
+  gather_min<kW>(nxt, ad, check, own(q + (k + 1)), xnxt, &ovf);                    \
   reduce_wave_tile<MaxOp>(cur.hw, xcur, lane, sb, sd, ns, r0, r1, cr, out, stage); \
   hold_raw<kW>(cur, xcur);                                                         \
   cur = load_raw_tile<kW>(col16, heads, w_arcs, min(q + (k + kDepth), qz), lane);
@@ -868,12 +887,12 @@ __global__ __launch_bounds__(kLdsThreads) void k_sssp_tocab_lds(
   }
   const int32_t rest = nw % kDepth;
   if (rest > 0) {
-    if (kDepth > 2) gather_min<kW>(t1, ad, check, x1, &ovf);
+    if (kDepth > 2) gather_min<kW>(t1, ad, check, own(q + 1), x1, &ovf);
     reduce_wave_tile<MaxOp>(t0.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);
   }
   if constexpr (kDepth == 4) {
     if (rest > 1) {
-      gather_min<kW>(t2, ad, check, x0, &ovf);
+      gather_min<kW>(t2, ad, check, own(q + 2), x0, &ovf);
       reduce_wave_tile<MaxOp>(t1.hw, x1, lane, sb, sd, ns, r0, r1, cr, out, stage);
     }
     if (rest > 2) reduce_wave_tile<MaxOp>(t2.hw, x0, lane, sb, sd, ns, r0, r1, cr, out, stage);

@@ -310,3 +310,32 @@ def test_heuristic_bfs_arm_ends_at_2_18_vertices(side, tocab):
     assert acts == ({0, 1, 2} if tocab else {0, 1}), acts
     part.free()
     h.free()
+
+
+# a tile of 512 arcs that two blocks share: an arc of one block, taken with the slice of the other, would be a path
+# beyond INT32_MAX (1.5e9 + 1e9) where every distance is finite; and a real one is still reported
+@pytest.mark.parametrize("far", [5, 1024 + 5], ids=["last_tile", "first_tile"])
+@pytest.mark.parametrize("fill", [0, 700, 2000])
+@pytest.mark.parametrize("real", [False, True])
+def test_sssp_overflow_only_over_arcs_of_the_block(far, fill, real):
+    import paper_1904_02241_amd as gc
+    near = 5 + 1024 - (far - 5)  # the same place in the other block
+    arcs = {(0, far): 1500000000, (far, far + 1): 1000000000 if real else 1, (0, near): 1, (near, 2040): 1000000000}
+    src = np.array([a for a, _ in arcs] + [9] * fill, np.int64)  # vertex 9 is not reached
+    dst = np.array([b for _, b in arcs] + list(range(10, 10 + min(fill, 2000))), np.int64)
+    g = gg.from_edges(2100, src, dst, name=f"shared_tile{fill}")
+    owner = np.repeat(np.arange(g.n), np.diff(g.rowptr))
+    g.weights = np.array([arcs.get((int(a), int(b)), 1) for a, b in zip(owner, g.colidx)], np.int32)
+    print(f"sssp overflow far={far} fill={fill} real={real} m={g.m}", flush=True)
+    h = load(g, weights=True)
+    part = gc.tocab_partition(h, gc.GC_PULL, 1 << 10, 256)
+    d = torch().empty(g.n, dtype=torch().int32, device="cuda")
+    if real:
+        with pytest.raises(gc.GraphCageError) as e:
+            gc.sssp_pull(h, part, 0, d, gc.GC_POLICY_PULL)
+        assert e.value.code == gc.GC_EOVERFLOW
+    else:
+        gc.sssp_pull(h, part, 0, d, gc.GC_POLICY_PULL)
+        np.testing.assert_array_equal(host(d), oracle.dijkstra(g.n, g.rowptr, g.colidx, g.weights, 0))
+    part.free()
+    h.free()
