@@ -105,6 +105,10 @@ void mirror_put(int32_t* p) {
   (void)hipHostFree(p);
 }
 
+__global__ void k_mark(int32_t* word, int32_t seq) {
+  __hip_atomic_store(word, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 void free_graph(gc_graph g) {
   if (!g) return;
   void* bufs[] = {g->rowptr, g->colidx, g->w, g->t_rowptr, g->t_colidx, g->t_w, g->scratch, g->tile_row_in,
@@ -159,6 +163,13 @@ hipError_t wait_mirror(const int32_t* word, int32_t seq, hipStream_t s) {
   const hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
   return __atomic_load_n(word, __ATOMIC_ACQUIRE) == seq ? hipSuccess : hipErrorUnknown;
+}
+
+hipError_t wait_queued(gc_graph g, hipStream_t s) {
+  const int32_t seq = static_cast<int32_t>(++g->level_seq);
+  k_mark<<<1, 1, 0, s>>>(g->stats_host + kStatSeq, seq);
+  GC_HIP_TRY(hipGetLastError());
+  return wait_mirror(g->stats_host + kStatSeq, seq, s);
 }
 
 void dev_free(void* p, hipStream_t s) {

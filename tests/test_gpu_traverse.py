@@ -339,3 +339,32 @@ def test_sssp_overflow_only_over_arcs_of_the_block(far, fill, real):
         np.testing.assert_array_equal(host(d), oracle.dijkstra(g.n, g.rowptr, g.colidx, g.weights, 0))
     part.free()
     h.free()
+
+
+# a traversal is done with the handle when it returns, so the next one may come on another stream, with the GPU busy
+# on a third: pull levels to the end (the last level's end clears status words over all of the GPU), and push levels
+@pytest.mark.parametrize("policy", ["pull", "push", "heuristic"])
+def test_traversals_on_two_streams_in_turn(policy):
+    import paper_1904_02241_amd as gc
+    t = torch()
+    g = gg.uniform(1500007, 3000000, seed=9).with_weights(3)
+    pol = {"pull": gc.GC_POLICY_PULL, "push": gc.GC_POLICY_PUSH, "heuristic": gc.GC_POLICY_HEURISTIC}[policy]
+    h = load(g, weights=True)
+    srcs = [int(x) for x in gg.sources(g, 3, seed=11)]
+    want = [oracle.bfs(g.n, g.rowptr, g.colidx, s) for s in srcs]
+    want_d = oracle.dijkstra(g.n, g.rowptr, g.colidx, g.weights, srcs[0])
+    streams = [t.cuda.Stream(), t.cuda.Stream()]
+    other = t.cuda.Stream()
+    a = t.randn(4096, 4096, device="cuda")
+    out = [t.empty(g.n, dtype=t.int32, device="cuda") for _ in range(13)]
+    t.cuda.synchronize()
+    print(f"two streams {policy} n={g.n} m={g.m}", flush=True)
+    for i in range(12):
+        with t.cuda.stream(other):
+            a @ a
+        gc.bfs_pull(h, None, srcs[i % 3], out[i], pol, stream=streams[i & 1])
+    gc.sssp_pull(h, None, srcs[0], out[12], pol, stream=streams[0])
+    for i in range(12):
+        np.testing.assert_array_equal(host(out[i]), want[i % 3])
+    np.testing.assert_array_equal(host(out[12]), want_d)
+    h.free()
