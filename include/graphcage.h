@@ -17,8 +17,9 @@
  *    device faults surface as GC_EHIP from a later synchronising call.
  *  - A graph or partition handle keeps per-iteration scratch inside it, so
  *    one handle must not be used from two streams at the same time. Calls
- *    that wait for their stream (bfs_pull, sssp_pull, bc_accumulate) are done
- *    with the handle when they return: the next call may come on any stream.
+ *    that wait for their stream (pagerank_converge, bfs_pull, sssp_pull,
+ *    bc_accumulate) are done with the handle when they return: the next call
+ *    may come on any stream.
  *  - Vertex ids are int32 in [0, n); arc counts m < 2^31.
  *  - Device buffers the caller passes stay owned by the caller.
  *  - Memory the library needs comes from the allocator set with

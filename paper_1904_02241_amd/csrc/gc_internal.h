@@ -40,10 +40,11 @@ struct gc_graph_s {
   int32_t dpart_slots = 0;
   bool values_f32 = false;  // the weight arrays hold FP32 values (GC_VALUES_F32)
   // convergence mode (allocated by the first pagerank_converge call): FP64
-  // partials of the L1 change per update work-group, their total, and a
-  // second FP32 iterate
+  // partials of the L1 change per update work-group, results, and a second
+  // FP32 iterate
   double* lpart = nullptr;
-  double* ltotal = nullptr;
+  double* ltotal = nullptr;     // the one-work-group form's change and count; [2]: number (int64) of the last call that converged
+  int64_t conv_calls = 0;       // calls so far, which number them
   float* rank_tmp = nullptr;
   // traversal scratch
   uint32_t* front = nullptr;  // status arrays (Section 3.3), one bit per vertex

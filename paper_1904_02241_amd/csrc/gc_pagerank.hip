@@ -32,12 +32,13 @@ namespace {
 int g_cus = 256;  // compute units of the GPU (read once by pagerank_setup)
 
 // Convergence mode: an iteration's L1 change, from its partials to the host
-// (two words of the FP64 value, then `seq`, in pinned memory) and to the
-// stop flag.
+// (two words of the FP64 value, then `seq`, in pinned memory) and, when it
+// ends the run, this call's number to the stop word.
 struct Change {
-  const double* lpart = nullptr;  // null: clear the flag (when given)
+  const double* lpart = nullptr;  // null: no change to sum
   double tol = 0.0;
-  int32_t* stop = nullptr;
+  int64_t* word = nullptr;
+  int64_t call = 0;
   int32_t* host = nullptr;
   int32_t seq = 0;
 };
@@ -60,21 +61,19 @@ __device__ __forceinline__ double reduce_slots(const double* __restrict__ slots,
 // of the L1-change partials), in a fixed order.
 __global__ __launch_bounds__(1024) void k_reduce_dangling(const double* __restrict__ dpart, int32_t count,
                                                           double* __restrict__ dtotal, Change ch) {
-  if (ch.lpart && stopped(ch.stop)) return;  // uniform
+  if (ch.lpart && *ch.word >= ch.call) return;  // uniform
   __shared__ double part[1024 / kWave];
   const double t = reduce_slots(dpart, count, part);
   if (threadIdx.x == 0) *dtotal = t;
   if (ch.lpart) {
     const double l = reduce_slots(ch.lpart, count, part);
     if (threadIdx.x == 0) {
-      if (l <= ch.tol) *ch.stop = 1;
+      if (l <= ch.tol) *ch.word = ch.call;
       const uint64_t b = static_cast<uint64_t>(__double_as_longlong(l));
       for (int i = 0; i < 2; ++i)
         __hip_atomic_store(ch.host + i, static_cast<int32_t>(b >> (32 * i)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       __hip_atomic_store(ch.host + 2, ch.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-  } else if (ch.stop && threadIdx.x == 0) {
-    *ch.stop = 0;  // before the first iteration
   }
 }
 
@@ -103,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_tocab_pull(const int32_t* __res
                                                             const int32_t* __restrict__ tile_row,
                                                             const float* __restrict__ c,
                                                             float* __restrict__ partial,
-                                                            const int32_t* __restrict__ stop) {
+                                                            Stop stop) {
   if (stopped(stop)) return;
   __shared__ float vals[kStageCap];
   const int32_t r0 = tile_row[blockIdx.x], r1 = tile_row[blockIdx.x + 1];
@@ -222,7 +221,7 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
     const int32_t* __restrict__ chunk_end, const int32_t* __restrict__ chunk_blk,
     const int32_t* __restrict__ chunk_j0, const int32_t* __restrict__ chunk_ns, const int2* __restrict__ seg,
     int32_t R, int32_t log2W, int32_t n, const float* __restrict__ c, float* __restrict__ partial,
-    uint32_t partial_bytes, const int32_t* __restrict__ stop) {
+    uint32_t partial_bytes, Stop stop) {
   extern __shared__ float lds[];
   if (stopped(stop)) return;
   const int32_t W = 1 << log2W;
@@ -596,7 +595,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_push(const int32_t* __restrict_
                                                       const int32_t* __restrict__ id_map,
                                                       const int32_t* __restrict__ col,
                                                       const float* __restrict__ c, double* __restrict__ sums,
-                                                      int64_t rows, const int32_t* __restrict__ stop) {
+                                                      int64_t rows, Stop stop) {
   if (stopped(stop)) return;
   __shared__ int32_t start[kThreads];
   __shared__ int32_t first[kThreads];
@@ -1049,11 +1048,11 @@ hipError_t spmv_stream(gc_graph g, gc_tocab t, const float* x, const float* vals
       if (vals)
         k_pr_tocab_pull_lds<true><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, vals, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, nullptr);
+            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, Stop());
       else
         k_pr_tocab_pull_lds<false><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, nullptr);
+            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, Stop());
     }
   }
   ProfScope prof("spmv_merge", s);
@@ -1267,7 +1266,8 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   Change change;
   if (cv) {
     change.tol = cv->tol;
-    change.stop = reinterpret_cast<int32_t*>(g->ltotal + 2);
+    change.word = reinterpret_cast<int64_t*>(g->ltotal + 2);
+    change.call = ++g->conv_calls;
   }
   auto hand_over = [&](int32_t count, int slot) {
     const bool fused = few && count <= kDangFused;
@@ -1286,13 +1286,13 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   float* const iterate[2] = {rank_out, cv ? g->rank_tmp : nullptr};
   if (cv) {
     u.lpart = g->lpart;
-    u.stop = change.stop;
+    u.stop = Stop{change.word, change.call};
     change.lpart = g->lpart;
   }
   // Iteration `it` is queued before the host waits for the change of the one
   // before it (in a ring of four pinned slots), so the GPU does not idle
-  // while the host is told; past the last iteration its kernels find the stop
-  // flag set and leave. The change of iteration j: its slot, and the number
+  // while the host is told; past the last iteration its kernels find that this
+  // call has stopped and leave. The change of iteration j: its slot, and the number
   // that marks it.
   auto slot_of = [&](int32_t j) { return g->stats_host + kStatOut + 4 * (j & 3); };
   const uint32_t seq0 = g->level_seq + 1;
@@ -1402,8 +1402,10 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
       GC_HIP_TRY(converged(it, &done));
     }
   }
-  if (cv && (cv->iters & 1) == 0)  // the last iterate is in rank_tmp
+  if (cv && (cv->iters & 1) == 0) {  // the last iterate is in rank_tmp, which the next call may write on another stream
     GC_HIP_TRY(hipMemcpyAsync(rank_out, g->rank_tmp, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
+    return wait_queued(g, s);
+  }
   return hipSuccess;
 }
 

@@ -26,6 +26,17 @@ constexpr int kFlatB = gcm::kFlatB;              // merges over at most this man
 
 static_assert(kTileArcs <= kStageCap, "a tile's short rows must fit the stage");
 
+// Convergence mode queues an iteration before it knows the change of the one
+// before; the kernels of an iteration past the last do nothing. The word holds
+// the number of the last call that has converged, and calls are numbered
+// upwards, so the kernels that a call leaves behind stay stopped when the next
+// one runs, on whichever stream.
+struct Stop {
+  const int64_t* word = nullptr;  // null: never
+  int64_t call = 0;
+};
+__device__ __forceinline__ bool stopped(const Stop& s) { return s.word && *s.word >= s.call; }
+
 struct Update {
   double base;      // (1 - d) / n
   double d;         // damping
@@ -38,13 +49,9 @@ struct Update {
   float* rank_out;        // written on the last iteration only (else null)
   const float* rank_prev = nullptr;  // convergence mode: the previous iterate
   double* lpart = nullptr;           // convergence mode: L1 change per work-group
-  const int32_t* stop = nullptr;     // convergence mode: set once an iterate has converged
+  Stop stop;                         // convergence mode
   int32_t n;
 };
-
-// Convergence mode queues an iteration before it knows the change of the one
-// before; the kernels of an iteration past the last do nothing.
-__device__ __forceinline__ bool stopped(const int32_t* stop) { return stop && *stop; }
 
 // r'[v] from the neighbour sum; writes c'[v] (and r'[v] on the last pass),
 // returns r'[v] when v has no out-arcs (its share of the next D), else 0.

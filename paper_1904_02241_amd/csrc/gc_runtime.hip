@@ -718,12 +718,15 @@ int pagerank_converge(gc_graph g, gc_tocab t, int32_t dir_if_plain, float dampin
     g->lpart = static_cast<double*>(gcx::dev_alloc(sizeof(double) * g->dpart_slots, stream));
     g->ltotal = static_cast<double*>(gcx::dev_alloc(3 * sizeof(double), stream));
     g->rank_tmp = static_cast<float*>(gcx::dev_alloc(sizeof(float) * std::max<int32_t>(g->n, 1), stream));
-    if (!g->lpart || !g->ltotal || !g->rank_tmp) {
+    hipError_t e = hipSuccess;
+    if (g->ltotal) e = hipMemsetAsync(g->ltotal, 0, 3 * sizeof(double), stream);  // no call has converged
+    if (!g->lpart || !g->ltotal || !g->rank_tmp || e != hipSuccess) {
       for (void* p : {static_cast<void*>(g->lpart), static_cast<void*>(g->ltotal), static_cast<void*>(g->rank_tmp)})
         if (p) gcx::dev_free(p, stream);
       g->lpart = nullptr;
       g->ltotal = nullptr;
       g->rank_tmp = nullptr;
+      if (e != hipSuccess) return hip_fail(e, "pagerank_converge");
       return fail(GC_ENOMEM, "pagerank_converge: device allocation failed");
     }
   }

@@ -88,3 +88,41 @@ def test_converge_rejects_bad_arguments():
     with pytest.raises(gc.GraphCageError, match="overlap"):
         gc.pagerank_converge(h, None, gc.GC_PULL, 0.85, gc.GC_DANGLING_UNIFORM, rin, rin, 1e-3, 10)
     h.free()
+
+
+@pytest.mark.parametrize("form,W,K", FORMS, ids=lambda x: str(x))
+def test_converge_on_two_streams_in_turn(form, W, K):
+    """A run leaves kernels behind that must stay stopped when the next run of the handle, on another stream, has
+    not converged; an even count's last iterate comes from the handle's own buffer. Even and odd counts and runs
+    that end at their cap follow one another."""
+    import paper_1904_02241_amd as gc
+    t = torch()
+    g = gg.rmat(17, 8, seed=6)
+    h = load(g)
+    part = None
+    if form.startswith("tocab"):
+        part = gc.tocab_partition(h, gc.GC_PULL if form == "tocab_pull" else gc.GC_PUSH, W, K)
+    plain_dir = gc.GC_PUSH if form == "plain_push" else gc.GC_PULL
+    rin = dev(np.full(g.n, 1.0 / g.n, np.float32))
+    r0 = host(rin).astype(np.float64)
+    runs = [(1e-3, 200), (1e-4, 200), (0.0, 3), (1e-3, 200), (3e-5, 200), (0.0, 2)]
+    out = [t.empty(g.n, dtype=t.float32, device="cuda") for _ in runs]
+    streams = [t.cuda.Stream(), t.cuda.Stream()]
+    other = t.cuda.Stream()
+    a = t.randn(4096, 4096, device="cuda")
+    t.cuda.synchronize()
+    print(f"converge two streams {form} W={W} k={K}", flush=True)
+    iters = []
+    for i, (tol, cap) in enumerate(runs):
+        with t.cuda.stream(other):
+            a @ a
+        iters.append(gc.pagerank_converge(h, part, plain_dir, 0.85, gc.GC_DANGLING_UNIFORM, rin, out[i], tol, cap,
+                                          stream=streams[i & 1])[0])
+    t.cuda.synchronize()
+    assert iters[2] == 3 and iters[5] == 2 and iters[0] == iters[3]
+    for k, o in zip(iters, out):
+        want = oracle.pagerank(g.n, g.rowptr, g.colidx, 0.85, k, r0=r0)
+        assert float(np.abs(host(o).astype(np.float64) - want).sum()) <= L1_TOL
+    if part is not None:
+        part.free()
+    h.free()
