@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256) void k_local_rows(const int32_t* __restrict__ 
         const int32_t v = row[i];
         id_map[l] = v;
         row_ptr[l] = static_cast<int32_t>(i);
-        id16[l] = static_cast<uint16_t>(v & kmask);
+        if (id16) id16[l] = static_cast<uint16_t>(v & kmask);
       }
     }
     if (heads && w < head_words && lane == 0) {
@@ -1090,8 +1090,7 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
   // once (pull), and 32-bit arc indices past the padded end
   const bool pull_stream = t->dir == GC_PULL && t->W <= kLdsMaxWidth &&
                            static_cast<int64_t>(B) * (R + 1) <= (int64_t(1) << 25) && m + 1024 < INT32_MAX;
-  const bool push_stream = t->dir == GC_PUSH && !t->inner && t->W <= kPushLdsMaxWidth && t->k <= t->W && m > 0 &&
-                           m + 1024 < INT32_MAX && B <= kPushExpandMaxBlocks;
+  const bool push_stream = t->dir == GC_PUSH && !t->inner && push_expands(t->n_rows, m, t->W, t->k);
   t->mk = t->dir == GC_PULL ? merge_width(t->n_rows, m, B, t->k, t->W <= kLdsMaxWidth) : t->k;
   t->mR = (t->n_rows + t->mk - 1) / t->mk;
   const int64_t tile = wave_tile_arcs();
@@ -1180,10 +1179,13 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
   t->row_ptr = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (Pn + 1), s));
   // padded for 4-wide reads, and past the pull's buffer resource (its range
   // check leaves out a store's scalar offset, at most 512 floats)
-  t->partial = static_cast<float*>(dev_alloc(sizeof(float) * (Pn + 8 + 512), s));
-  t->pmin = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (Pn + 8), s));  // padded for 16-byte reads
-  t->id16 = static_cast<uint16_t*>(dev_alloc(sizeof(uint16_t) * Pn, s));
-  if (!t->id_map || !t->row_ptr || !t->partial || !t->pmin || !t->id16) return hipErrorOutOfMemory;
+  if (!t->ranks_only) {
+    t->partial = static_cast<float*>(dev_alloc(sizeof(float) * (Pn + 8 + 512), s));
+    t->pmin = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (Pn + 8), s));  // padded for 16-byte reads
+    t->id16 = static_cast<uint16_t*>(dev_alloc(sizeof(uint16_t) * Pn, s));
+    if (!t->partial || !t->pmin || !t->id16) return hipErrorOutOfMemory;
+  }
+  if (!t->id_map || !t->row_ptr) return hipErrorOutOfMemory;
   t->bytes = sizeof(int32_t) * ((R + 1 + (t->mk != t->k ? t->mR + 1 : 0)) * static_cast<int64_t>(B) + B + 1 + 4 * static_cast<int64_t>(Pn) + 1 +
                                 mn * (t->weighted ? 2 : 1)) +
              static_cast<int64_t>(sizeof(uint16_t)) * P;
@@ -1196,7 +1198,7 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
     k_range_rows<<<grid_for(static_cast<int64_t>(t->mR + 1) * B, 256, 65536), 256, 0, s>>>(
         t->id_map, t->blk_rowoff, B, t->mR, __builtin_ctz(t->mk), t->mrange);
   GC_HIP_TRY(hipGetLastError());
-  GC_HIP_TRY(build_tiles(t->row_ptr, P, m, pull_tile_arcs(), &t->tile_row, &t->n_tiles, s));
+  if (!t->ranks_only) GC_HIP_TRY(build_tiles(t->row_ptr, P, m, pull_tile_arcs(), &t->tile_row, &t->n_tiles, s));
   if (pull_stream && 4 * (P + 8) < (int64_t(1) << 31)) {
     GC_HIP_TRY(build_lds_stream(t, s));
   } else if (pull_stream) {  // too many local rows for the pull's 32-bit byte offsets
@@ -1208,7 +1210,16 @@ hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a
     t->m_pad = 0;
   }
   if (push_stream) GC_HIP_TRY(build_push_expand(t, s));
-  return hipStreamSynchronize(s);  // the Buf is released on return
+  GC_HIP_TRY(hipStreamSynchronize(s));  // the Buf is released on return
+  if (t->ranks_only) {  // what only the building has read
+    dev_free(t->col, s);
+    dev_free(t->id_map, s);
+    t->col = nullptr;
+    t->id_map = nullptr;
+    t->bytes -= static_cast<int64_t>(sizeof(int32_t)) * (static_cast<int64_t>(mn) + 3 * static_cast<int64_t>(Pn)) +
+                static_cast<int64_t>(sizeof(uint16_t)) * P;
+  }
+  return hipSuccess;
 }
 
 }  // namespace gcx

@@ -138,6 +138,7 @@ struct gc_tocab_s {
   // GC_PUSH: the same arcs in blocks of the width that PageRank is fastest
   // over (push_width), which it takes instead; null: W itself.
   gc_tocab inner = nullptr;
+  bool ranks_only = false;  // such a second layout: it keeps the expanded form alone
   // Expanded contributions of a GC_PUSH partition with block sums in LDS
   // (W <= kPushLdsMaxWidth, B <= kPushExpandMaxBlocks): the work-group that
   // updates source block s writes the new contribution of each local row
@@ -238,6 +239,12 @@ inline int32_t push_width(int32_t n, int32_t W) {
 // Most blocks of a push partition with expanded contributions (a work-group
 // keeps two run bounds per block in LDS).
 constexpr int32_t kPushExpandMaxBlocks = 4096;
+// Whether a push partition of k-wide ranges has the expanded form: block sums
+// in LDS, 16-bit offsets, and arc indices that fit 32 bits past the padded end.
+inline bool push_expands(int32_t n, int64_t m, int32_t W, int32_t k) {
+  return W <= kPushLdsMaxWidth && k <= W && m > 0 && m + 1024 < INT32_MAX &&
+         (static_cast<int64_t>(n) + W - 1) / W <= kPushExpandMaxBlocks;
+}
 // Average run length (local rows per (source block, block) pair) from which
 // the expanded push walks its runs in place rather than through a
 // source-major list.

@@ -463,27 +463,44 @@ int tocab_partition(gc_graph g, int32_t dir, int32_t block_width, int32_t merge_
     t->m = g->m;
     return t;
   };
-  gc_tocab t = make(block_width, merge_range);
-  if (!t) return fail(GC_ENOMEM, "tocab_partition: host allocation failed");
-  t->weighted = g->weighted;
   const int32_t* a_rowptr = dir == GC_PULL ? g->t_rowptr : g->rowptr;
   const int32_t* a_col = dir == GC_PULL ? g->t_colidx : g->colidx;
   const int32_t* a_w = dir == GC_PULL ? g->t_w : g->w;
-  // (graphs that run in one work-group need no second layout)
+  // a second layout for PageRank's push (graphs that run in one work-group
+  // need none), unless there is no memory for it or for what was asked for
+  // beside it
   const int32_t push_w =
       dir == GC_PUSH && !gcx::pr_small_fits(g, true) ? gcx::push_width(g->n, block_width) : block_width;
-  if (push_w != block_width && (t->inner = make(push_w, push_w)) != nullptr &&
-      gcx::build_partition(t->inner, a_rowptr, a_col, nullptr, stream) != hipSuccess) {
-    (void)hipGetLastError();  // no memory for a second layout: PageRank runs over the blocks as given
-    (void)hipStreamSynchronize(stream);
-    free_tocab(t->inner);
-    t->inner = nullptr;
+  gc_tocab inner = nullptr;
+  hipError_t e = hipSuccess;
+  if (push_w != block_width && gcx::push_expands(g->n, g->m, push_w, push_w)) {
+    inner = make(push_w, push_w);
+    if (inner) {
+      inner->ranks_only = true;
+      e = gcx::build_partition(inner, a_rowptr, a_col, nullptr, stream);
+    }
+    if (e != hipSuccess) {
+      (void)hipStreamSynchronize(stream);
+      free_tocab(inner);
+      inner = nullptr;
+    }
+    if (e != hipSuccess && e != hipErrorOutOfMemory) return hip_fail(e, "tocab_partition");
   }
-  hipError_t e = gcx::build_partition(t, a_rowptr, a_col, a_w, stream);
-  if (e != hipSuccess) {
+  gc_tocab t = nullptr;
+  for (;;) {
+    t = make(block_width, merge_range);
+    if (!t) {
+      free_tocab(inner);
+      return fail(GC_ENOMEM, "tocab_partition: host allocation failed");
+    }
+    t->weighted = g->weighted;
+    t->inner = inner;
+    e = gcx::build_partition(t, a_rowptr, a_col, a_w, stream);
+    if (e == hipSuccess) break;
     (void)hipStreamSynchronize(stream);
-    free_tocab(t);
-    return hip_fail(e, "tocab_partition");
+    free_tocab(t);  // and the second layout
+    if (e != hipErrorOutOfMemory || !inner) return hip_fail(e, "tocab_partition");
+    inner = nullptr;
   }
   if (t->inner) t->bytes += t->inner->bytes;
   *out = t;

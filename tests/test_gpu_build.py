@@ -134,3 +134,78 @@ def test_partition_rejects_bad_widths():
             gc.tocab_partition(h, gc.GC_PULL, W, k)
         assert e.value.code == gc.GC_EINVAL
     h.free()
+
+
+class _Capped:
+    """The library's allocator with a limit on the bytes held (no handle may be alive outside)."""
+
+    def __init__(self, gc):
+        import torch
+        self.gc, self.cap, self.live, self.peak, self.size = gc, None, 0, 0, {}
+
+        @gc._ALLOC_FN
+        def alloc(nbytes, stream, ctx):
+            if self.cap is not None and self.live + nbytes > self.cap:
+                return None
+            p = torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream or 0))
+            self.size[p] = int(nbytes)
+            self.live += int(nbytes)
+            self.peak = max(self.peak, self.live)
+            return p
+
+        @gc._FREE_FN
+        def release(ptr, stream, ctx):
+            self.live -= self.size.pop(int(ptr))
+            torch.cuda.caching_allocator_delete(int(ptr))
+
+        self.fns = alloc, release
+
+    def __enter__(self):
+        self.gc._check(self.gc.lib.gc_set_allocator(*self.fns, None), "gc_set_allocator")
+        return self
+
+    def __exit__(self, *a):
+        self.gc.use_torch_allocator(True)
+
+
+def test_push_partition_leaves_the_second_layout_out_where_memory_is_short():
+    """Whatever the limit: the partition as asked for where that fits, the second layout (blocks of 2^12 here)
+    beside it where both do, and an error with nothing kept where the first does not."""
+    import paper_1904_02241_amd as gc
+    from tests.gpu_util import dev, host
+    import torch
+    g = gg.uniform(600007, 3000000, seed=3)
+    n, W, k = g.n, 1 << 14, 4096
+    with _Capped(gc) as a:
+        h = gc.graph_load_csr(g.rowptr, g.colidx)
+        base = a.live
+        a.peak = 0
+        part = gc.tocab_partition(h, gc.GC_PUSH, W, k)
+        full, kept = a.peak, a.live - base
+        part.free()
+        assert a.live == base
+        rin = dev(np.full(n, 1.0 / n, np.float32))
+        want = oracle.pagerank(n, g.rowptr, g.colidx, 0.85, 3, r0=host(rin).astype(np.float64))
+        sizes = []
+        for cap in [full] + [base + (full - base) * i // 16 for i in range(15, 3, -1)] + [full - 1]:
+            a.cap = cap
+            print(f"push partition under {cap - base} of {full - base} bytes", flush=True)
+            try:
+                part = gc.tocab_partition(h, gc.GC_PUSH, W, k)
+            except gc.GraphCageError as e:
+                assert e.code == gc.GC_ENOMEM and a.live == base
+                sizes.append(0)
+                continue
+            sizes.append(a.live - base)
+            assert (part.info["W"], part.info["k"]) == (W, k)
+            out = torch.empty_like(rin)
+            gc.pagerank_iter(h, part, gc.GC_PULL, 0.85, 0, rin, out, 3)
+            assert float(np.abs(host(out).astype(np.float64) - want).sum()) <= 1e-6
+            part.free()
+            assert a.live == base
+        a.cap = None
+        h.free()
+    print(f"held {sizes}, {kept} without a limit", flush=True)
+    assert sizes[0] == kept          # room for both
+    assert 0 < sizes[-1] < kept      # a byte less than both take while they are built: the one asked for
+    assert sizes[-2] == 0            # and too little for either
