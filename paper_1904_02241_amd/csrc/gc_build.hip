@@ -130,6 +130,12 @@ constexpr int kRadixItems = 8;  // arcs per thread
 constexpr int kRadixTile = kRadixThreads * kRadixItems;
 constexpr int kRadixBits = 10;
 constexpr int kTransposeBits = 8;
+// Rows that a tile marks one by one; over more of them (long runs of empty
+// rows) its arcs search for theirs: 10^6 arcs at both ends of 16 M vertices
+// in blocks, push, 14.4 ms with one work-group marking the rows between, 0.18
+// so; 2 M arcs spread over them (32,000 rows a tile) 229 marked, 251 searched,
+// 10^6 spread 216 and 231, 500,000 269 and 218 us.
+constexpr int32_t kMarkRows = 24 * kRadixTile;
 
 // Digit counts of every tile, digit-major: counts[d * tiles + tile]. A
 // thread reads kRadixItems consecutive keys and adds each run of equal
@@ -248,36 +254,52 @@ __global__ __launch_bounds__(kRadixThreads) void k_radix_move(RadixArgs a) {
       const int32_t r = wave_owner_row(a.rowptr, a.n_rows, e0 + len - 1);
       if (lane == 0) row_last = r;
     }
-    for (int32_t i = threadIdx.x; i < kRadixTile; i += kRadixThreads) stage[i] = 0;
     __syncthreads();
     const int32_t rf = row_first, rl = row_last;
-    for (int32_t r = rf + 1 + static_cast<int32_t>(threadIdx.x); r <= rl; r += kRadixThreads) {
-      atomicMax(&stage[a.rowptr[r] - e0], r - rf);  // e0 < rowptr[r] < e0 + len
+    if (rl - rf > kMarkRows) {  // uniform
+      // mostly empty rows: every arc searches them
+      int64_t e[kRadixItems];
+#pragma unroll
+      for (int r = 0; r < kRadixItems; ++r) {
+        e[r] = e0 + min(p0 + r * kWave, len - 1);
+        row[r] = rf;
+      }
+      for (int32_t step = 1 << (31 - __builtin_clz(rl - rf)); step > 0; step >>= 1) {
+#pragma unroll
+        for (int r = 0; r < kRadixItems; ++r)
+          if (step <= rl - row[r] && a.rowptr[row[r] + step] <= e[r]) row[r] += step;
+      }
+    } else {
+      for (int32_t i = threadIdx.x; i < kRadixTile; i += kRadixThreads) stage[i] = 0;
+      __syncthreads();
+      for (int32_t r = rf + 1 + static_cast<int32_t>(threadIdx.x); r <= rl; r += kRadixThreads) {
+        atomicMax(&stage[a.rowptr[r] - e0], r - rf);  // e0 < rowptr[r] < e0 + len
+      }
+      __syncthreads();
+      int32_t v[kRadixItems];
+      const int32_t s0 = threadIdx.x * kRadixItems;
+#pragma unroll
+      for (int j = 0; j < kRadixItems; ++j) {
+        v[j] = stage[s0 + j];
+        if (j) v[j] = max(v[j], v[j - 1]);
+      }
+      int32_t incl = v[kRadixItems - 1];
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t t = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl = max(incl, t);
+      }
+      if (lane == kWave - 1) wave_tot[wid] = incl;
+      const int32_t up = __shfl_up(incl, 1, kWave);
+      __syncthreads();
+      int32_t before = lane ? up : 0;
+      for (int w = 0; w < wid; ++w) before = max(before, wave_tot[w]);
+#pragma unroll
+      for (int j = 0; j < kRadixItems; ++j) stage[s0 + j] = rf + max(before, v[j]);
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < kRadixItems; ++r) row[r] = stage[p0 + r * kWave];
     }
-    __syncthreads();
-    int32_t v[kRadixItems];
-    const int32_t s0 = threadIdx.x * kRadixItems;
-#pragma unroll
-    for (int j = 0; j < kRadixItems; ++j) {
-      v[j] = stage[s0 + j];
-      if (j) v[j] = max(v[j], v[j - 1]);
-    }
-    int32_t incl = v[kRadixItems - 1];
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int32_t t = __shfl_up(incl, o, kWave);
-      if (lane >= o) incl = max(incl, t);
-    }
-    if (lane == kWave - 1) wave_tot[wid] = incl;
-    const int32_t up = __shfl_up(incl, 1, kWave);
-    __syncthreads();
-    int32_t before = lane ? up : 0;
-    for (int w = 0; w < wid; ++w) before = max(before, wave_tot[w]);
-#pragma unroll
-    for (int j = 0; j < kRadixItems; ++j) stage[s0 + j] = rf + max(before, v[j]);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kRadixItems; ++r) row[r] = stage[p0 + r * kWave];
   }
   for (int32_t i = threadIdx.x; i < kRadixWaves * bins; i += kRadixThreads) cnt[i] = 0;
   __syncthreads();
@@ -385,23 +407,71 @@ __device__ __forceinline__ int32_t first_at_least(const int32_t* a, int32_t lo, 
   return lo;
 }
 
+// First arc in [0, m) with key >= v (m if none), by the whole wave.
+__device__ __forceinline__ int32_t wave_first_at_least(const int32_t* __restrict__ key, int64_t m, int32_t v) {
+  const int lane = gcd::lane_id();
+  int64_t lo = 0, hi = m;
+  while (lo < hi) {  // uniform
+    const int64_t step = (hi - lo + kWave - 1) / kWave;
+    const int64_t at = min(hi - 1, lo + (lane + 1) * step - 1);
+    const int cnt = __popcll(__ballot(key[at] < v));  // a prefix of the lanes
+    if (cnt == kWave) return static_cast<int32_t>(hi);
+    hi = min(hi - 1, lo + (cnt + 1) * step - 1);
+    lo += cnt * step;
+  }
+  return static_cast<int32_t>(lo);
+}
+
 // Row offsets of arcs sorted by row: rowptr[v] = first arc with key >= v. A
 // work-group stages kOffsetTile keys in LDS and writes the offsets of the
 // rows after the previous tile's last key up to its own last key (the last
-// tile: up to n), each by a binary search in LDS.
+// tile: up to n), each by a binary search in LDS, if they are at most
+// kWideRows. Where arcs are few or leave long runs of rows empty, one
+// work-group would walk most of the graph (16 M vertices, 10^6 arcs into the
+// last 65,536 of them: 62 ms to load): the rows of wider tiles are written by
+// the work-groups after those of the tiles, one per kOffsetTile rows, each by
+// a binary search in memory (0.29 ms). One of them meets two wide tiles at
+// most, with its first row and with its last. Arcs spread over 16 M vertices,
+// load with half this line and with this: 4 M 440, 398 us; 2 M 372, 380;
+// 250,000 309, 314 (1425 by tiles alone).
 constexpr int kOffsetTile = 4096;
+constexpr int32_t kWideRows = 8 * kOffsetTile;
 
 __global__ __launch_bounds__(256) void k_row_offsets(const int32_t* __restrict__ key, int64_t m, int32_t n,
-                                                     int32_t* __restrict__ rowptr) {
-  __shared__ int32_t k[kOffsetTile];
-  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kOffsetTile;
-  const int32_t len = static_cast<int32_t>(min<int64_t>(kOffsetTile, m - i0));
-  for (int32_t i = threadIdx.x; i < len; i += 256) k[i] = key[i0 + i];
-  const int32_t v0 = i0 ? key[i0 - 1] + 1 : 0;
+                                                     int32_t tiles, int32_t* __restrict__ rowptr) {
+  auto first_row = [&](int64_t t) { return t ? key[t * kOffsetTile - 1] + 1 : 0; };
+  auto last_row = [&](int64_t t) { return t == tiles - 1 ? n : key[(t + 1) * kOffsetTile - 1]; };
+  const int32_t tile = blockIdx.x;
+  if (tile < tiles) {
+    __shared__ int32_t k[kOffsetTile];
+    const int32_t v0 = first_row(tile), v1 = last_row(tile);
+    if (v1 - v0 >= kWideRows) return;  // uniform
+    const int64_t i0 = static_cast<int64_t>(tile) * kOffsetTile;
+    const int32_t len = static_cast<int32_t>(min<int64_t>(kOffsetTile, m - i0));
+    for (int32_t i = threadIdx.x; i < len; i += 256) k[i] = key[i0 + i];
+    __syncthreads();
+    for (int64_t v = static_cast<int64_t>(v0) + threadIdx.x; v <= v1; v += 256)
+      rowptr[v] = static_cast<int32_t>(i0) + first_at_least(k, 0, len, v);
+    return;
+  }
+  __shared__ int32_t end[2];  // arcs at which the first and the last row start
+  const int64_t c0 = static_cast<int64_t>(tile - tiles) * kOffsetTile, c1 = min<int64_t>(n, c0 + kOffsetTile - 1);
+  const int wid = static_cast<int>(threadIdx.x) / kWave;
+  if (wid < 2) {
+    const int32_t a = wave_first_at_least(key, m, static_cast<int32_t>(wid ? c1 : c0));
+    if (gcd::lane_id() == 0) end[wid] = a;
+  }
   __syncthreads();
-  const int32_t v1 = i0 + len == m ? n : k[len - 1];
-  for (int64_t v = static_cast<int64_t>(v0) + threadIdx.x; v <= v1; v += 256)
-    rowptr[v] = static_cast<int32_t>(i0) + first_at_least(k, 0, len, v);
+  const int32_t a0 = end[0], a1 = end[1];
+  auto tile_of = [&](int32_t a) { return min(a / kOffsetTile, tiles - 1); };
+  const int32_t t0 = tile_of(a0), t1 = tile_of(a1);
+  const bool wide0 = last_row(t0) - first_row(t0) >= kWideRows, wide1 = last_row(t1) - first_row(t1) >= kWideRows;
+  if (!wide0 && !wide1) return;  // uniform
+  for (int64_t v = c0 + threadIdx.x; v <= c1; v += 256) {
+    const int32_t a = first_at_least(key, a0, a1, v);
+    const int32_t t = tile_of(a);
+    if ((t == t0 && wide0) || (t == t1 && wide1)) rowptr[v] = a;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -830,7 +900,8 @@ hipError_t build_transpose(int32_t n, int64_t m, const int32_t* rowptr, const in
     a.row = rows[o];
     if (w) a.w = ws[o];
   }
-  k_row_offsets<<<grid_for(m, kOffsetTile), 256, 0, s>>>(keys[0], m, n, t_rowptr);
+  const int32_t tiles = grid_for(m, kOffsetTile);
+  k_row_offsets<<<tiles + grid_for(static_cast<int64_t>(n) + 1, kOffsetTile), 256, 0, s>>>(keys[0], m, n, tiles, t_rowptr);
   GC_HIP_TRY(hipGetLastError());
   return hipStreamSynchronize(s);  // the Buf is released on return
 }

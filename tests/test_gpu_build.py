@@ -209,3 +209,90 @@ def test_push_partition_leaves_the_second_layout_out_where_memory_is_short():
     assert sizes[0] == kept          # room for both
     assert 0 < sizes[-1] < kept      # a byte less than both take while they are built: the one asked for
     assert sizes[-2] == 0            # and too little for either
+
+
+def _rows(*parts):
+    return np.concatenate([np.asarray(p, np.int64) for p in parts])
+
+
+# rows whose arcs are few or stand far apart: a tile of 4096 arcs over 32,768 rows (as many as it takes itself) and
+# over one more, the same for the 98,304 rows that it marks, two such tiles in one run of 4096 rows, a hub before a
+# gap, rows at the edges of the runs, nothing but a tail
+_HOLLOW = {
+    "at_limit": (40000, lambda: _rows(np.linspace(0, 32767, 4096), [39999])),
+    "beyond": (40000, lambda: _rows(np.linspace(0, 32768, 4096), [39999])),
+    "marks_at_limit": (110000, lambda: _rows(np.linspace(0, 98304, 4096), [109999])),
+    "marks_beyond": (110000, lambda: _rows(np.linspace(0, 98305, 4096), [109999])),
+    "two_tiles": (160001, lambda: _rows(np.arange(4096) * 17, 4096 * 17 + np.arange(4096) * 19, 150000 + np.arange(300))),
+    "hub_gap": (300007, lambda: _rows(np.full(5000, 7), [8, 4095, 4096, 8191, 250000], np.full(4097, 299999))),
+    "dense_between": (400003, lambda: _rows(np.arange(0, 100000, 50), 100000 + np.arange(9000), [399999])),
+    "tail": (1000003, lambda: 1000003 - 1 - np.arange(6000)),
+    "head": (1000003, lambda: np.arange(6000)),
+    "few": (3000017, lambda: [4095, 4096, 12287, 2999999]),
+}
+
+
+@pytest.mark.parametrize("name", list(_HOLLOW))
+@pytest.mark.parametrize("side", ["dst", "src"])
+def test_hollow_graphs_bit_exact(name, side):
+    import paper_1904_02241_amd as gc
+    n, rows = _HOLLOW[name]
+    a = np.asarray(rows(), np.int64)
+    b = (a + 1 + np.arange(len(a)) % 6001) % n  # distinct (row, other end), no loops
+    g = gg.from_edges(n, *((b, a) if side == "dst" else (a, b)), name=f"hollow_{name}").with_weights(5)
+    print(f"hollow {name} {side} n={n} m={g.m}", flush=True)
+    h = load(g, weights=True)
+    ar, ac, aw = oracle.transpose(n, g.rowptr, g.colidx, g.weights)
+    tr, tc, tw = np.empty(n + 1, np.int32), np.empty(g.m, np.int32), np.empty(g.m, np.int32)
+    gc.graph_export_transpose(h, tr, tc, tw)
+    gc.gc_sync()
+    for got, want in ((tr, ar), (tc, ac), (tw, aw)):
+        np.testing.assert_array_equal(got, want)
+    for d, csr in ((gc.GC_PULL, (ar, ac, aw)), (gc.GC_PUSH, (g.rowptr, g.colidx, g.weights))):
+        part = gc.tocab_partition(h, d, 1 << 14, 4096)
+        got, B, P, R = export_partition(part, g)
+        part.free()
+        want = oracle.partition(n, n, csr[0], csr[1], 1 << 14, 4096, csr[2])
+        assert (B, P) == (want.B, want.P)
+        for key in ("blk_rowoff", "row_ptr"):
+            np.testing.assert_array_equal(got[key], getattr(want, key))
+        np.testing.assert_array_equal(got["id_map"][:P], want.id_map)
+        np.testing.assert_array_equal(got["col"], want.col)
+        np.testing.assert_array_equal(got["w"], want.w)
+    h.free()
+
+
+@pytest.mark.parametrize("where", ["head", "tail", "ends"])
+def test_empty_rows_cost_no_more_in_one_run_than_spread(where):
+    """16 M vertices and 10^6 arcs: among a few of them (any long run of empty rows has one work-group in front of
+    it and one behind) as fast to load and to partition as spread over all, within 8 times (0.5 ms each)."""
+    import time
+    import torch
+    import paper_1904_02241_amd as gc
+    n, m, few = 1 << 24, 1000000, 1 << 16
+    rng = np.random.default_rng(1)
+
+    def ends(kind):
+        x = rng.integers(0, n if kind == "spread" else few, m)
+        if kind == "tail":
+            return n - 1 - x
+        return np.where(rng.integers(0, 2, m) == 0, x, n - 1 - x) if kind == "ends" else x
+
+    def seconds(kind):
+        g = gg.from_edges(n, ends(kind), ends(kind), name=kind)
+        rp, ci = torch.from_numpy(g.rowptr).cuda(), torch.from_numpy(g.colidx).cuda()
+        took = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            h = gc.graph_load_csr(rp, ci)
+            parts = [gc.tocab_partition(h, d, 1 << 15, 4096) for d in (gc.GC_PULL, gc.GC_PUSH)]
+            took.append(time.perf_counter() - t0)
+            for p in parts:
+                p.free()
+            h.free()
+        return sorted(took)[1]
+
+    base, got = seconds("spread"), seconds(where)
+    print(f"empty rows {where}: {got * 1e6:.0f} us, spread {base * 1e6:.0f}", flush=True)
+    assert got <= 8 * base
