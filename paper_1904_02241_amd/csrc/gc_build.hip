@@ -602,6 +602,20 @@ __global__ void k_tile_rows(const int32_t* __restrict__ row_ptr, int32_t rows, i
   tile_row[t] = first_at_least(row_ptr, 0, rows, static_cast<int64_t>(t) * tile_arcs);
 }
 
+__global__ __launch_bounds__(1024) void k_longest_row(const int32_t* __restrict__ row_ptr, int32_t rows,
+                                                      int32_t* __restrict__ out) {
+  __shared__ int32_t top[1024 / kWave];
+  int32_t x = 0;
+  for (int32_t r = threadIdx.x; r < rows; r += 1024) x = max(x, row_ptr[r + 1] - row_ptr[r]);
+  x = gcd::wave_max(x);
+  if (gcd::lane_id() == 0) top[threadIdx.x / kWave] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 1024 / kWave; ++w) x = max(x, top[w]);
+    __hip_atomic_store(out, x, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 // Low 16 bits of (value & mask): a column inside its block, or a row inside
 // its merge range.
 __global__ void k_col16(const int32_t* __restrict__ col, int64_t m, int32_t mask, uint16_t* __restrict__ col16) {
@@ -847,6 +861,11 @@ hipError_t build_tiles(const int32_t* row_ptr, int64_t rows, int64_t arcs, int32
   if (!*out) return hipErrorOutOfMemory;
   k_tile_rows<<<grid_for(nt + 1, 256, INT_MAX), 256, 0, s>>>(row_ptr, static_cast<int32_t>(rows), tile_arcs,
                                                              static_cast<int32_t>(nt), *out);
+  return hipGetLastError();
+}
+
+hipError_t longest_row(const int32_t* row_ptr, int32_t rows, int32_t* out, hipStream_t s) {
+  k_longest_row<<<1, 1024, 0, s>>>(row_ptr, rows, out);
   return hipGetLastError();
 }
 

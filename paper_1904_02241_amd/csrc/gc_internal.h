@@ -32,6 +32,7 @@ struct gc_graph_s {
   double* sums = nullptr;     // push accumulators (FP64 atomics)
   int32_t* tile_row_in = nullptr;  // pull tiles over the transposed graph
   int32_t n_tiles_in = 0;
+  int32_t longest_in = 0;  // largest in-degree (only for graphs that fit one work-group's LDS)
   // one slot per update work-group; [1]: kDangSlots slots, used in turn with
   // [0] by updates of at most that many work-groups
   double* dpart[2] = {nullptr, nullptr};
@@ -210,6 +211,8 @@ hipError_t build_transpose(int32_t n, int64_t m, const int32_t* rowptr, const in
 // [i*tile_arcs, (i+1)*tile_arcs); out[i] = first such row, out[n_tiles] = rows.
 hipError_t build_tiles(const int32_t* row_ptr, int64_t rows, int64_t arcs, int32_t tile_arcs,
                        int32_t** out, int32_t* n_tiles, hipStream_t s);
+// Queues the length of the longest row into the pinned word `out`.
+hipError_t longest_row(const int32_t* row_ptr, int32_t rows, int32_t* out, hipStream_t s);
 // TOCAB partition of CSR A (see tocab_partition); fills t's arrays.
 hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a_col,
                            const int32_t* a_w, hipStream_t s);
@@ -300,9 +303,13 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
 // Width of the ranges that the merges of a pull partition work in.
 int32_t merge_width(int32_t n, int64_t m, int32_t B, int32_t k, bool stream);
 
-// Small graphs (gc_pr_small.hip): whether all of g's iterations fit one
-// work-group's LDS, and that form of pagerank_run.
-bool pr_small_fits(gc_graph g, bool conv);
+// Small graphs (gc_pr_small.hip): whether a graph fits the one-work-group
+// form's LDS, whether a call in `form` is faster there, and that form of
+// pagerank_run. (Push over a partition as asked for, or over its second
+// layout.)
+enum class PrForm { kPull, kPush, kTocabPull, kTocabPush, kTocabPushInner };
+bool pr_small_fits(int64_t n, int64_t m, bool conv);
+bool pr_small_pays(gc_graph g, PrForm form, bool conv, int32_t iters);
 hipError_t pr_small_run(gc_graph g, float damping, int32_t dangling, const float* rank_in, float* rank_out,
                         int32_t iters, hipStream_t s, Converge* cv);
 

@@ -1227,9 +1227,12 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   static const hipError_t setup = pagerank_setup();
   GC_HIP_TRY(setup);
   if (ladder >= 0) return ladder_run(g, t, ladder, damping, dangling, rank_in, rank_out, iters, s);
-  if (pr_small_fits(g, cv != nullptr))
-    return pr_small_run(g, damping, dangling, rank_in, rank_out, iters, s, cv);
   const bool push = t ? (t->dir == GC_PUSH) : (dir == GC_PUSH);
+  const PrForm form = !t ? (push ? PrForm::kPush : PrForm::kPull)
+                         : !push ? PrForm::kTocabPull
+                                 : t->inner ? PrForm::kTocabPushInner : PrForm::kTocabPush;
+  if (pr_small_pays(g, form, cv != nullptr, iters))
+    return pr_small_run(g, damping, dangling, rank_in, rank_out, iters, s, cv);
   if (t && t->inner) t = t->inner;
   Update u;
   u.d = damping;

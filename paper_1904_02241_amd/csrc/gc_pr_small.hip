@@ -14,17 +14,18 @@
 // that mostly have one to do. Row
 // sums are FP64, ranks and contributions FP32, as in the other forms, and
 // every form of the iteration (pull, push, blocked) has the same result, so
-// all of them come here. Measured (20 iterations of the plain pull, us per
-// call, tile kernels -> this one): R-MAT of 1000 vertices and 7,400 arcs 247
-// -> 54, of 2500 / 18,000 275 -> 109, of 2000 / 27,000 240 -> 124; uniform
-// graphs of 1000 / 8,000 152 -> 45, 3000 / 24,000 152 -> 108, 5000 / 20,000
-// 164 -> 140; grid of 4000 154 -> 107. The blocked forms launch two or three
-// kernels per iteration where the plain pull launches one. So every graph
-// that fits the LDS takes this form (about 16 n + 2 m bytes of 158 KB: 4,500
-// vertices at 16 arcs each).
+// all of them may come here. Measured (20 iterations of the plain pull, us
+// per call, tile kernels -> this one): R-MAT of 1000 vertices and 7,400 arcs
+// 247 -> 54, of 2500 / 18,000 275 -> 109, of 2000 / 27,000 240 -> 124; uniform
+// graphs of 1000 / 8,000 107 -> 46, 3000 / 24,000 124 -> 112, 5000 / 20,000
+// 132 -> 142 (these stay with the tile kernels). pr_small_pays says which
+// calls take this form; a graph must fit the LDS: 18 n + 2 m + 1028 bytes
+// (22 n in convergence mode) of 158 KB, 3,200 vertices at 16 arcs each.
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -292,10 +293,40 @@ hipError_t launch(const SmallArgs& a, size_t lds, hipStream_t s) {
 
 namespace gcx {
 
-// The rule: everything fits the LDS of one work-group (see the top of the
-// file for both sides' times over that range).
-bool pr_small_fits(gc_graph g, bool conv) {
-  return g->n <= 65536 && small_lds(g->n, g->m, conv) <= kSmallLds;
+bool pr_small_fits(int64_t n, int64_t m, bool conv) { return n <= 65536 && small_lds(n, m, conv) <= kSmallLds; }
+
+// Microseconds of both sides, fitted to graphs of 64 to 8,500 vertices and
+// 0.1 to 160 arcs each, uniform and R-MAT, in every form (a call's time is
+// within a quarter of these but for the plain push of hub graphs). This form
+// loads and sorts once per call (5 us per 1000 vertices), then pays per
+// vertex and arc with one CU's instructions; a row of more than 128 arcs
+// takes a whole wave's steps of 512, so beyond 112 arcs per row on average
+// rows count as such. The tile kernels cost their launches (one to start and
+// one to three per iteration) and little per arc, but for a tile's rows, one
+// thread each (where arcs are few, a tile has many), a row of more than 128
+// arcs, and the push's atomics. Calls at both sides of the line (this form,
+// tiles): plain pull, 20 iterations of 2000 / 32,000 122, 119; of 3000 /
+// 48,000 180, 121; of 8,500 / 850 207, 386; one iteration of 1000 / 8,000 10,
+// 10, of 3000 / 24,000 23, 11; push of 8,500 / 850 207, 125; pull over blocks,
+// 400 / 64,000 549, 351, 3000 / 48,000 180, 245.
+bool pr_small_pays(gc_graph g, PrForm form, bool conv, int32_t iters) {
+  if (!pr_small_fits(g->n, g->m, conv)) return false;
+  const double n = g->n * 1e-3, m = static_cast<double>(g->m) * 1e-3, deg = m / n;
+  const double it = conv ? std::min(iters, 20) : iters;  // (a run until convergence takes some 10 to 20)
+  const double arcs = deg > 112.0 ? n * 512.0 * std::ceil(deg / 512.0) : m;
+  const double small = 5.0 * n + it * (0.5 + (conv ? 1.2 : 0.9) * n + 0.11 * arcs);
+  double step = 0.0;
+  switch (form) {
+    case PrForm::kPull:
+      step = g->longest_in > 128 ? 10.0
+                                 : std::max(6.7, 3.5 + 1.8 * n / static_cast<double>(g->m / pull_tile_arcs() + 1));
+      break;
+    case PrForm::kPush: step = 5.6 + 0.75 * deg; break;
+    case PrForm::kTocabPull: step = 10.0; break;
+    case PrForm::kTocabPush: step = 16.0 + 0.5 * m; break;
+    default: step = 8.0 + 0.16 * m; break;  // kTocabPushInner
+  }
+  return small <= 5.0 + it * (step + (conv ? 4.5 : 0.0));
 }
 
 hipError_t pr_small_run(gc_graph g, float damping, int32_t dangling, const float* rank_in, float* rank_out,

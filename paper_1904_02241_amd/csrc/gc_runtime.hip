@@ -383,10 +383,17 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
     e = gcx::build_transpose(n, m, g->rowptr, g->colidx, g->w, g->t_rowptr, g->t_colidx, g->t_w, stream);
   if (e == hipSuccess)
     e = gcx::build_tiles(g->t_rowptr, n, m, gcx::pull_tile_arcs(), &g->tile_row_in, &g->n_tiles_in, stream);
+  const bool small = gcx::pr_small_fits(n, m, false);
+  int32_t* const longest = g->stats_host + gcx::kStatOut;
+  if (e == hipSuccess && small) e = gcx::longest_row(g->t_rowptr, n, longest, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
     free_graph(g);
     return hip_fail(e, "graph_load_csr");
+  }
+  if (small) {
+    g->longest_in = *longest;
+    *longest = 0;
   }
   *out = g;
   return GC_OK;
@@ -469,8 +476,9 @@ int tocab_partition(gc_graph g, int32_t dir, int32_t block_width, int32_t merge_
   // a second layout for PageRank's push (graphs that run in one work-group
   // need none), unless there is no memory for it or for what was asked for
   // beside it
-  const int32_t push_w =
-      dir == GC_PUSH && !gcx::pr_small_fits(g, true) ? gcx::push_width(g->n, block_width) : block_width;
+  const gcx::PrForm inner_form = gcx::PrForm::kTocabPushInner;
+  const bool one_group = gcx::pr_small_pays(g, inner_form, false, 20) && gcx::pr_small_pays(g, inner_form, true, 20);
+  const int32_t push_w = dir == GC_PUSH && !one_group ? gcx::push_width(g->n, block_width) : block_width;
   gc_tocab inner = nullptr;
   hipError_t e = hipSuccess;
   if (push_w != block_width && gcx::push_expands(g->n, g->m, push_w, push_w)) {

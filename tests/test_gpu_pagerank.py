@@ -213,3 +213,77 @@ def test_autotune_picks_a_valid_width_and_caches_it():
     assert l1(got, want) <= L1_TOL
     part.free()
     h.free()
+
+
+def _exact(n, m, seed, isolated=0):
+    """A graph of exactly m arcs (distinct, no loops) among n vertices, and `isolated` more."""
+    rng = np.random.default_rng(seed)
+    keys = rng.choice(n * (n - 1), m, replace=False)
+    u, v = keys // (n - 1), keys % (n - 1)
+    return gg.from_edges(n + isolated, u, v + (v >= u), name=f"arcs{n}_{m}")
+
+
+def _ran(gc, call):
+    """The kernels that call() launches."""
+    gc.gc_profile(True)
+    call()
+    gc.gc_profile(False)
+    return set(gc.gc_profile_read())
+
+
+LDS = 158 * 1024  # what the one-work-group form may take: 18 n + 2 m + 1028 bytes, 22 n until converged
+
+
+# the last graph that fits the LDS, bit for bit on its edge, and one arc more; 20 iterations and an odd number
+@pytest.mark.parametrize("n", [3000, 5001, 700])
+@pytest.mark.parametrize("conv", [False, True])
+def test_pagerank_one_work_group_lds_edge(n, conv):
+    import paper_1904_02241_amd as gc
+    from tests.gpu_util import dev, host, torch
+    per = 22 if conv else 18
+    m = (LDS - 1028 - per * n) // 2
+    assert per * n + 2 * m + 1028 == LDS
+    for arcs, fits in ((m, True), (m + 1, False)):
+        g = _exact(n, arcs, seed=n)
+        print(f"lds edge n={n} m={g.m} conv={conv} fits={fits}", flush=True)
+        h = load(g)
+        rin = dev(np.full(n, 1.0 / n, np.float32))
+        out = torch().empty_like(rin)
+        for iters in (20, 21):
+            if conv:
+                ran = _ran(gc, lambda: gc.pagerank_converge(h, None, gc.GC_PUSH, 0.85, 0, rin, out, 0.0, iters))
+            else:
+                ran = _ran(gc, lambda: gc.pagerank_iter(h, None, gc.GC_PUSH, 0.85, 0, rin, out, iters))
+            assert ("pr_small" in ran) == fits, ran
+            want = oracle.pagerank(n, g.rowptr, g.colidx, 0.85, iters, r0=host(rin).astype(np.float64))
+            assert l1(host(out), want) <= L1_TOL
+        h.free()
+
+
+# which calls take the one-work-group form: (n, arcs, form, iterations) well on either side of the line (both sides'
+# times stand at the rule); the result is the same on both
+@pytest.mark.parametrize("n,m,form,iters,small", [
+    (1000, 8000, "plain_pull", 20, True), (3000, 48000, "plain_pull", 20, False), (500, 70000, "plain_pull", 20, False),
+    (300, 70000, "tocab_pull", 20, False), (6000, 24000, "plain_pull", 20, False), (8500, 850, "plain_pull", 20, True),
+    (8500, 850, "plain_push", 20, False), (8500, 850, "tocab_push", 20, False), (3000, 48000, "plain_push", 20, True),
+    (1000, 60000, "tocab_push", 20, True), (3000, 24000, "tocab_pull", 20, True), (4000, 16000, "plain_pull", 1, False),
+    (8000, 8000, "tocab_push", 1, False), (600, 4800, "plain_pull", 1, True)])
+def test_pagerank_one_work_group_where_it_pays(n, m, form, iters, small):
+    import paper_1904_02241_amd as gc
+    from tests.gpu_util import dev, host, torch
+    g = _exact(n, m, seed=n + m)
+    print(f"one work-group n={n} m={m} {form} iters={iters}", flush=True)
+    h = load(g)
+    part = None
+    if form.startswith("tocab"):
+        part = gc.tocab_partition(h, gc.GC_PULL if form == "tocab_pull" else gc.GC_PUSH, 1 << 12, 1024)
+    rin = dev(np.full(n, 1.0 / n, np.float32))
+    out = torch().empty_like(rin)
+    d = gc.GC_PUSH if form == "plain_push" else gc.GC_PULL
+    ran = _ran(gc, lambda: gc.pagerank_iter(h, part, d, 0.85, 1, rin, out, iters))
+    assert ("pr_small" in ran) == small, ran
+    want = oracle.pagerank(n, g.rowptr, g.colidx, 0.85, iters, mode=oracle.LEAK, r0=host(rin).astype(np.float64))
+    assert l1(host(out), want) <= L1_TOL
+    if part is not None:
+        part.free()
+    h.free()
