@@ -240,15 +240,20 @@ __device__ double wg_row_sum(const int32_t* __restrict__ col, const float* __res
 // Section 3.2): the tile owns the rows whose first arc lies in its
 // kTileArcs-wide slice of the arc array. Their arcs are gathered into LDS
 // together; then each thread sums whole short rows serially in FP64, rows of
-// more than kThreadRow arcs are summed by their wave (a thread walking a
-// hub's row of up to 4096 arcs kept the tile waiting), and a last row too
-// long for the stage is summed by the whole work-group. No atomics.
-// emit(row, sum) is called once per owned row. Measured before and after
-// (with stage_gather's skipped loads): plain pull of a 1000-vertex R-MAT
-// graph 17.8 -> 11.4 us, pull over 2^18-wide blocks of a uniform graph of
-// 2.5 M vertices and 38 M arcs 203 -> 184 us (206 G gathers/s of the 274 an
-// L2-resident slice gives).
-constexpr int kThreadRow = 128;
+// more than kThreadRow arcs are summed by a wave (a thread walking a hub's row
+// of up to 4096 arcs kept the tile waiting), and a last row too long for the
+// stage is summed by the whole work-group. No atomics. emit(row, sum) is
+// called once per owned row. Measured before and after (with stage_gather's
+// skipped loads): plain pull of a 1000-vertex R-MAT graph 17.8 -> 11.4 us,
+// pull over 2^18-wide blocks of a uniform graph of 2.5 M vertices and 38 M
+// arcs 203 -> 184 us (206 G gathers/s of the 274 an L2-resident slice gives).
+// Where a tile's rows are about as long as that line, some threads walk theirs
+// and the wave then takes the others: so a tile of more than kMeanRow arcs per
+// row leaves its rows of more than kMeanWaveRow to the waves, all four of them.
+// PageRank by plain pull, 20 iterations, 100,000 vertices of 112, 136, 200
+// arcs: threads alone 1214, 1428, 2090 us; the one line for every tile and the
+// first wave 1216, 1624, 1914; so 1124, 1309, 1836 (of 64: 758, 744, 747).
+constexpr int kThreadRow = 128, kMeanRow = 80, kMeanWaveRow = 32;
 template <class Emit, class Arc = PlainArc>
 __device__ __forceinline__ void pull_tile(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                                           const float* __restrict__ c, int32_t r0, int32_t r1, float* vals,
@@ -257,25 +262,32 @@ __device__ __forceinline__ void pull_tile(const int32_t* __restrict__ row_ptr, c
   const int32_t last_b = row_ptr[r1 - 1];
   const int32_t a_end = row_ptr[r1];
   const bool long_last = (a_end - a0) > kStageCap;
+  const int lane = threadIdx.x & (kWave - 1);
+  // up to 64 rows go to the waves in turn, so that rows summed by a wave
+  // spread over all of them; more go to the threads in order (coalesced)
+  const bool few = r1 - r0 <= kWave;  // uniform
+  const int32_t slot =
+      few ? lane * (kThreads / kWave) + static_cast<int32_t>(threadIdx.x) / kWave : static_cast<int32_t>(threadIdx.x);
   // the bounds of the thread's first row, in flight with the tile's loads
   const int32_t r_short_end = long_last ? r1 - 1 : r1;
   int32_t rb = 0, re = 0;
-  if (r0 + static_cast<int32_t>(threadIdx.x) < r_short_end) {
-    rb = row_ptr[r0 + threadIdx.x];
-    re = row_ptr[r0 + threadIdx.x + 1];
+  if (r0 + slot < r_short_end) {
+    rb = row_ptr[r0 + slot];
+    re = row_ptr[r0 + slot + 1];
   }
-  stage_gather(col, c, a0, (long_last ? last_b : a_end) - a0, vals, arc);
+  const int32_t arcs = (long_last ? last_b : a_end) - a0;
+  const int32_t by_wave = arcs > kMeanRow * (r_short_end - r0) ? kMeanWaveRow : kThreadRow;
+  stage_gather(col, c, a0, arcs, vals, arc);
   __syncthreads();
-  const int lane = threadIdx.x & (kWave - 1);
   for (int32_t base = r0; base < r_short_end; base += kThreads) {  // uniform
-    const int32_t r = base + static_cast<int32_t>(threadIdx.x);
+    const int32_t r = base + slot;
     const bool mine = r < r_short_end;
     if (base != r0 && mine) {
       rb = row_ptr[r];
       re = row_ptr[r + 1];
     }
     const int32_t b = mine ? rb - a0 : 0, e = mine ? re - a0 : 0;
-    const bool whole_wave = e - b > kThreadRow;
+    const bool whole_wave = e - b > by_wave;
     double s = 0.0;
     if (mine && !whole_wave)
       for (int32_t i = b; i < e; ++i) s += static_cast<double>(vals[i]);

@@ -287,3 +287,29 @@ def test_pagerank_one_work_group_where_it_pays(n, m, form, iters, small):
     if part is not None:
         part.free()
     h.free()
+
+
+# rows summed by a thread or by a wave: tiles of rows all just under, at and over either line, of rows on both sides
+# of it, of few rows and of many, and short rows among long ones
+@pytest.mark.parametrize("rows", [(32,), (33,), (80,), (81,), (128, 129), (31, 300), (0, 1, 2000, 5), (64,), (4096, 4097),
+                                  (1, 130, 0)], ids=lambda r: "-".join(map(str, r)))
+@pytest.mark.parametrize("form", ["plain_pull", "tocab_wide"])
+def test_pagerank_tile_rows_by_thread_and_wave(rows, form):
+    import paper_1904_02241_amd as gc
+    from tests.gpu_util import dev, host, torch
+    n, live = 20011, min(1500, 300000 // max(rows))
+    deg = np.array([rows[i % len(rows)] for i in range(live)])
+    dst = np.repeat(np.arange(live), deg)
+    src = (dst + 1 + np.arange(len(dst)) - np.repeat(np.cumsum(deg) - deg, deg)) % n
+    g = gg.from_edges(n, src, dst, name="tile_rows")
+    print(f"tile rows {rows} {form} m={g.m}", flush=True)
+    h = load(g)
+    part = gc.tocab_partition(h, gc.GC_PULL, 1 << 16, 256) if form == "tocab_wide" else None
+    rin = dev(np.full(n, 1.0 / n, np.float32))
+    out = torch().empty_like(rin)
+    gc.pagerank_iter(h, part, gc.GC_PULL, 0.85, 0, rin, out, 3)
+    want = oracle.pagerank(n, g.rowptr, g.colidx, 0.85, 3, r0=host(rin).astype(np.float64))
+    assert l1(host(out), want) <= L1_TOL
+    if part is not None:
+        part.free()
+    h.free()
