@@ -591,28 +591,22 @@ __global__ void k_check_csr(const int32_t* __restrict__ rowptr, int32_t n, const
   }
 }
 
-__global__ void k_tile_rows(const int32_t* __restrict__ row_ptr, int32_t rows, int32_t tile_arcs, int32_t n_tiles,
-                            int32_t* __restrict__ tile_row) {
-  const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t > n_tiles) return;
-  if (t == n_tiles) {
-    tile_row[t] = rows;
-    return;
-  }
-  tile_row[t] = first_at_least(row_ptr, 0, rows, static_cast<int64_t>(t) * tile_arcs);
-}
-
-__global__ __launch_bounds__(1024) void k_longest_row(const int32_t* __restrict__ row_ptr, int32_t rows,
-                                                      int32_t* __restrict__ out) {
-  __shared__ int32_t top[1024 / kWave];
+__global__ __launch_bounds__(256) void k_tile_rows(const int32_t* __restrict__ row_ptr, int32_t rows,
+                                                   int32_t tile_arcs, int32_t n_tiles, int32_t* __restrict__ tile_row,
+                                                   int32_t* __restrict__ longest) {
+  const int32_t t = blockIdx.x * 256 + threadIdx.x;
+  if (t < n_tiles) tile_row[t] = first_at_least(row_ptr, 0, rows, static_cast<int64_t>(t) * tile_arcs);
+  if (t == n_tiles) tile_row[t] = rows;
+  if (!longest || blockIdx.x != 0) return;  // uniform
+  __shared__ int32_t top[256 / kWave];
   int32_t x = 0;
-  for (int32_t r = threadIdx.x; r < rows; r += 1024) x = max(x, row_ptr[r + 1] - row_ptr[r]);
+  for (int32_t r = threadIdx.x; r < rows; r += 256) x = max(x, row_ptr[r + 1] - row_ptr[r]);
   x = gcd::wave_max(x);
   if (gcd::lane_id() == 0) top[threadIdx.x / kWave] = x;
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 1024 / kWave; ++w) x = max(x, top[w]);
-    __hip_atomic_store(out, x, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (int w = 1; w < 256 / kWave; ++w) x = max(x, top[w]);
+    __hip_atomic_store(longest, x, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -854,18 +848,13 @@ hipError_t check_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t*
 }
 
 hipError_t build_tiles(const int32_t* row_ptr, int64_t rows, int64_t arcs, int32_t tile_arcs, int32_t** out,
-                       int32_t* n_tiles, hipStream_t s) {
+                       int32_t* n_tiles, hipStream_t s, int32_t* longest) {
   const int64_t nt = arcs / tile_arcs + 1;  // arc index `arcs` (trailing empty rows) falls in the last tile
   *n_tiles = static_cast<int32_t>(nt);
   *out = static_cast<int32_t*>(dev_alloc(sizeof(int32_t) * (nt + 1), s));
   if (!*out) return hipErrorOutOfMemory;
   k_tile_rows<<<grid_for(nt + 1, 256, INT_MAX), 256, 0, s>>>(row_ptr, static_cast<int32_t>(rows), tile_arcs,
-                                                             static_cast<int32_t>(nt), *out);
-  return hipGetLastError();
-}
-
-hipError_t longest_row(const int32_t* row_ptr, int32_t rows, int32_t* out, hipStream_t s) {
-  k_longest_row<<<1, 1024, 0, s>>>(row_ptr, rows, out);
+                                                             static_cast<int32_t>(nt), *out, longest);
   return hipGetLastError();
 }
 

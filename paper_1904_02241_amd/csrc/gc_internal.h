@@ -209,10 +209,10 @@ hipError_t build_transpose(int32_t n, int64_t m, const int32_t* rowptr, const in
                            hipStream_t s);
 // Pull tile table: tile i owns the rows whose first arc lies in
 // [i*tile_arcs, (i+1)*tile_arcs); out[i] = first such row, out[n_tiles] = rows.
+// The pinned word `longest`, where given, gets the longest row's arcs (found
+// by one work-group).
 hipError_t build_tiles(const int32_t* row_ptr, int64_t rows, int64_t arcs, int32_t tile_arcs,
-                       int32_t** out, int32_t* n_tiles, hipStream_t s);
-// Queues the length of the longest row into the pinned word `out`.
-hipError_t longest_row(const int32_t* row_ptr, int32_t rows, int32_t* out, hipStream_t s);
+                       int32_t** out, int32_t* n_tiles, hipStream_t s, int32_t* longest = nullptr);
 // TOCAB partition of CSR A (see tocab_partition); fills t's arrays.
 hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a_col,
                            const int32_t* a_w, hipStream_t s);

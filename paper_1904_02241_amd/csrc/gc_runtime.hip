@@ -381,17 +381,15 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
   if (e == hipSuccess) e = hipMemsetAsync(g->dtotal, 0, sizeof(double) * 2, stream);
   if (e == hipSuccess)
     e = gcx::build_transpose(n, m, g->rowptr, g->colidx, g->w, g->t_rowptr, g->t_colidx, g->t_w, stream);
+  int32_t* const longest = gcx::pr_small_fits(n, m, false) ? g->stats_host + gcx::kStatOut : nullptr;
   if (e == hipSuccess)
-    e = gcx::build_tiles(g->t_rowptr, n, m, gcx::pull_tile_arcs(), &g->tile_row_in, &g->n_tiles_in, stream);
-  const bool small = gcx::pr_small_fits(n, m, false);
-  int32_t* const longest = g->stats_host + gcx::kStatOut;
-  if (e == hipSuccess && small) e = gcx::longest_row(g->t_rowptr, n, longest, stream);
+    e = gcx::build_tiles(g->t_rowptr, n, m, gcx::pull_tile_arcs(), &g->tile_row_in, &g->n_tiles_in, stream, longest);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
     free_graph(g);
     return hip_fail(e, "graph_load_csr");
   }
-  if (small) {
+  if (longest) {
     g->longest_in = *longest;
     *longest = 0;
   }
