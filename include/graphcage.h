@@ -140,7 +140,9 @@ int tocab_partition(gc_graph g, int32_t dir, int32_t block_width, int32_t merge_
  * are timed on PageRank iterations of the graph itself with successive
  * halving (2, 4, 8, ... iterations; the faster half survives each round),
  * then merge ranges 2048 / 4096 / 8192 / 16384 that run differently are
- * compared for the winner. Builds
+ * compared for the winner; of widths that run alike (push
+ * partitions over one second layout, graphs that run as one work-group) the
+ * one that needs no second layout, or the least, stands for all. Builds
  * and frees candidate partitions (needs room for one at a time), allocates
  * two rank vectors, synchronises `stream`. The result is cached per graph
  * signature (n, m, sampled offsets) for the life of the process.

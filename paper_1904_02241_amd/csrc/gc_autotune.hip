@@ -28,12 +28,41 @@ bool allowed(int64_t n, int32_t W, int32_t k) {
   return B <= 32768 && B * (R + 1) <= (int64_t(1) << 28);
 }
 
+// The block width that PageRank runs over with a partition of width W: a
+// push partition's own, or its second layout's.
+int32_t run_width(gc_graph g, int32_t dir, int32_t W) {
+  if (dir == GC_PULL) return W;
+  const int32_t w = gcx::push_width(g->n, W);
+  return gcx::push_expands(g->n, g->m, w, w) ? w : W;
+}
+
+// Whether every partition of g runs as one work-group, which reads none.
+bool one_group(gc_graph g, int32_t dir) {
+  return gcx::pr_small_pays(g, dir == GC_PULL ? gcx::PrForm::kTocabPull : gcx::PrForm::kTocabPushInner, false, 20);
+}
+
 // Whether the partitions of width W with merge ranges k and j run alike.
 bool same_ranges(gc_graph g, int32_t dir, int32_t W, int32_t k, int32_t j) {
-  if (dir == GC_PUSH) return gcx::push_width(g->n, W) != W;
+  if (one_group(g, dir)) return true;
+  if (dir == GC_PUSH) return run_width(g, dir, W) != W;
   const int32_t B = static_cast<int32_t>((static_cast<int64_t>(g->n) + W - 1) / W);
   const bool stream = W <= gcx::kLdsMaxWidth;
   return gcx::merge_width(g->n, g->m, B, k, stream) == gcx::merge_width(g->n, g->m, B, j, stream);
+}
+
+// Leaves one candidate of those that run alike (timing them against each
+// other would pick by noise): the one whose own blocks are those run over,
+// which needs no second layout, else the first.
+void leave_one_of_each(gc_graph g, int32_t dir, std::vector<Candidate>& cand) {
+  std::vector<Candidate> left;
+  for (const Candidate& c : cand) {
+    auto alike = std::find_if(left.begin(), left.end(), [&](const Candidate& o) {
+      return one_group(g, dir) || run_width(g, dir, o.W) == run_width(g, dir, c.W);
+    });
+    if (alike == left.end()) left.push_back(c);
+    else if (!one_group(g, dir) && run_width(g, dir, c.W) == c.W) *alike = c;
+  }
+  cand.swap(left);
 }
 
 // Times `iters` PageRank iterations on partition t (after one warm-up).
@@ -93,6 +122,7 @@ hipError_t autotune(gc_graph g, int32_t dir, int32_t min_W, int32_t* W_out, int3
   for (int32_t W = lo; W <= std::max(top, lo); W <<= 1)
     if (allowed(n, W, 4096)) cand.push_back({W, 4096});
   if (cand.empty()) cand.push_back({std::max(1 << 22, lo), 4096});
+  leave_one_of_each(g, dir, cand);
   Buf ra(sizeof(float) * n, s), rb(sizeof(float) * n, s);
   if (!ra.p || !rb.p) return hipErrorOutOfMemory;
   // uniform start vector: any vector gives the same amount of work

@@ -313,3 +313,19 @@ def test_pagerank_tile_rows_by_thread_and_wave(rows, form):
     if part is not None:
         part.free()
     h.free()
+
+
+def test_autotune_does_not_choose_between_widths_that_run_alike():
+    """Push partitions of 2^12 to 2^14 run PageRank over blocks of one width, and a graph that runs as one work-group
+    over none: the width that needs no second layout, or the least, is chosen, not the one noise favours."""
+    import paper_1904_02241_amd as gc
+    for seed in range(4):
+        for n, m, directions, alike in ((600007 + seed, 3000000, (gc.GC_PUSH,), (1 << 12, 1 << 13, 1 << 14)),
+                                        (5000 + seed, 10000, (gc.GC_PULL, gc.GC_PUSH), (1 << 12, 1 << 13))):
+            h = load(gg.uniform(n, m, seed=seed))
+            for d in directions:
+                W, k, ms = gc.tocab_autotune(h, d)
+                print(f"autotune n={n} dir={d}: {W} {k} {ms:.4f}", flush=True)
+                assert W == alike[0] or W not in alike
+                assert ms > 0
+            h.free()
