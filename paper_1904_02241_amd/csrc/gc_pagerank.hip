@@ -887,7 +887,8 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
   // the update on them (a load per vertex inside it is a round trip per step)
   int32_t deg[kPer];
   float prev[kPer], cv[kPer];
-  const uint32_t last = static_cast<uint32_t>(u.n - 1 - v0);  // v0 < n: the block has vertices
+  // (clamped to the block: narrow ones would read the next blocks' too)
+  const uint32_t last = static_cast<uint32_t>(min(u.n - 1 - v0, W - 1));  // v0 < n: the block has vertices
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const uint32_t o = min(static_cast<uint32_t>(threadIdx.x + k * kPushLdsThreads), last);
