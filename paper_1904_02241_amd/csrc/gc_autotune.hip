@@ -45,9 +45,7 @@ bool one_group(gc_graph g, int32_t dir) {
 bool same_ranges(gc_graph g, int32_t dir, int32_t W, int32_t k, int32_t j) {
   if (one_group(g, dir)) return true;
   if (dir == GC_PUSH) return run_width(g, dir, W) != W;
-  const int32_t B = static_cast<int32_t>((static_cast<int64_t>(g->n) + W - 1) / W);
-  const bool stream = W <= gcx::kLdsMaxWidth;
-  return gcx::merge_width(g->n, g->m, B, k, stream) == gcx::merge_width(g->n, g->m, B, j, stream);
+  return gcx::merge_width(g->n, g->m, W, k) == gcx::merge_width(g->n, g->m, W, j);
 }
 
 // Leaves one candidate of those that run alike (timing them against each

@@ -1139,38 +1139,15 @@ hipError_t build_push_expand(gc_tocab t, hipStream_t s) {
   return hipSuccess;
 }
 
-// Width of the ranges that the merges of a pull partition work in, since a
-// merge gives each range one work-group: k, halved as follows while the range
-// table stays below an eighth of the arcs.
-// Stream layout: until there are 128 (or they are 256 wide). PageRank, 20
-// iterations, with ranges of k, with 64, 128 and 256: 10^6 vertices of 16
-// arcs, k = 2^14: 1461, 1081, 887, 894 us; 300,007 of 16, 2^14: 657, 386, 361,
-// 385; of 4, 2^12: 312, 312, 296, 331 (a tile of the pull that meets more
-// ranges takes longer).
-// Wider blocks: until they are 2048 wide, and on to 1024 while there are
-// fewer than 512. The merge of 256 threads holds a range's FP64 sums in LDS,
-// so 2048 of them let a CU run its work-groups: 2.5 M vertices of 16 arcs with
-// k = 2^13 5552 us, 4815 with 4096, 4501 with 2048, 4557 with 1024; 10^6 of 16,
-// k = 2^14: 3381, 2119, 1940, 1861.
-int32_t merge_width(int32_t n, int64_t m, int32_t B, int32_t k, bool stream) {
-  auto ranges = [&](int32_t w) { return (static_cast<int64_t>(n) + w - 1) / w; };
-  auto wanted = [&] { return stream ? k > 256 && ranges(k) < 128 : k > 2048 || (k > 1024 && ranges(k) < 512); };
-  while (wanted() && B * (ranges(k / 2) + 1) <= m / 8 + 65536) k /= 2;
-  return k;
-}
-
 hipError_t build_partition(gc_tocab t, const int32_t* a_rowptr, const int32_t* a_col, const int32_t* a_w,
                            hipStream_t s) {
   const int32_t B = t->B, R = t->R;
   const int64_t m = t->m;
   const size_t mn = static_cast<size_t>(std::max<int64_t>(m, 1));
   const int64_t words = (m + 63) / 64;  // of head bits
-  // the stream layouts need the whole range table of a block on the host
-  // once (pull), and 32-bit arc indices past the padded end
-  const bool pull_stream = t->dir == GC_PULL && t->W <= kLdsMaxWidth &&
-                           static_cast<int64_t>(B) * (R + 1) <= (int64_t(1) << 25) && m + 1024 < INT32_MAX;
+  const bool pull_stream = t->dir == GC_PULL && pull_streams(t->n_rows, m, t->W, t->k);
   const bool push_stream = t->dir == GC_PUSH && !t->inner && push_expands(t->n_rows, m, t->W, t->k);
-  t->mk = t->dir == GC_PULL ? merge_width(t->n_rows, m, B, t->k, t->W <= kLdsMaxWidth) : t->k;
+  t->mk = t->dir == GC_PULL ? merge_width(t->n_rows, m, t->W, t->k) : t->k;
   t->mR = (t->n_rows + t->mk - 1) / t->mk;
   const int64_t tile = wave_tile_arcs();
   const int64_t m_pad = (m / tile + 2) * tile, head_words = m_pad / 64 + 1;

@@ -300,8 +300,36 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
                         const float* rank_in, float* rank_out, int32_t iters, hipStream_t s,
                         Converge* cv = nullptr, int32_t ladder = -1, const PrBuffers* bufs = nullptr);
 
-// Width of the ranges that the merges of a pull partition work in.
-int32_t merge_width(int32_t n, int64_t m, int32_t B, int32_t k, bool stream);
+// Whether a pull partition has the stream layout: a slice that fits the LDS, a
+// range table of at most 2^25 entries (of a block, the whole of it goes
+// through the host once), and arc indices that fit 32 bits past the padded end.
+inline bool pull_streams(int32_t n, int64_t m, int32_t W, int32_t k) {
+  auto parts = [&](int32_t w) { return (static_cast<int64_t>(n) + w - 1) / w; };
+  return W <= kLdsMaxWidth && parts(W) * (parts(k) + 1) <= (int64_t(1) << 25) && m + 1024 < INT32_MAX;
+}
+
+// Width of the ranges that the merges of a pull partition work in, since a
+// merge gives each range one work-group: k, halved as follows while the range
+// table stays below an eighth of the arcs.
+// Stream layout: until there are 128 (or they are 256 wide). PageRank, 20
+// iterations, with ranges of k, with 64, 128 and 256: 10^6 vertices of 16
+// arcs, k = 2^14: 1461, 1081, 887, 894 us; 300,007 of 16, 2^14: 657, 386, 361,
+// 385; of 4, 2^12: 312, 312, 296, 331 (a tile of the pull that meets more
+// ranges takes longer).
+// Wider blocks: until they are 2048 wide, and on to 1024 while there are
+// fewer than 512. The merge of 256 threads holds a range's FP64 sums in LDS,
+// so 2048 of them let a CU run its work-groups: 2.5 M vertices of 16 arcs with
+// k = 2^13 5552 us, 4815 with 4096, 4501 with 2048, 4557 with 1024; 10^6 of 16,
+// k = 2^14: 3381, 2119, 1940, 1861.
+// (The batched form, whose ranges are 1024 wide, takes blocks of at most 2^15
+// without the stream layout as well: they are left at k.)
+inline int32_t merge_width(int32_t n, int64_t m, int32_t W, int32_t k) {
+  auto parts = [&](int32_t w) { return (static_cast<int64_t>(n) + w - 1) / w; };
+  const bool stream = pull_streams(n, m, W, k);
+  auto wanted = [&] { return stream ? k > 256 && parts(k) < 128 : k > 2048 || (k > 1024 && parts(k) < 512); };
+  while (wanted() && parts(W) * (parts(k / 2) + 1) <= m / 8 + 65536) k /= 2;
+  return k;
+}
 
 // Small graphs (gc_pr_small.hip): whether a graph fits the one-work-group
 // form's LDS, whether a call in `form` is faster there, and that form of
