@@ -296,3 +296,11 @@ def test_empty_rows_cost_no_more_in_one_run_than_spread(where):
     base, got = seconds("spread"), seconds(where)
     print(f"empty rows {where}: {got * 1e6:.0f} us, spread {base * 1e6:.0f}", flush=True)
     assert got <= 8 * base
+
+
+@pytest.mark.parametrize("m", [4095, 4096, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("n,W", [(1025, 1 << 10), (70001, 1 << 10)])
+def test_radix_tile_edges_bit_exact(n, W, m):
+    """One arc tile of the radix passes (4096) less one arc, full and one more, and two."""
+    test_radix_edges_bit_exact(n, m, W, 256, "pull")
+    test_radix_edges_bit_exact(n, m, W, 256, "push")

@@ -126,3 +126,41 @@ def test_converge_on_two_streams_in_turn(form, W, K):
     if part is not None:
         part.free()
     h.free()
+
+
+@pytest.mark.parametrize("form,W,K", FORMS, ids=lambda x: str(x))
+def test_converge_caps_and_one_iteration_beyond_one_work_group(form, W, K):
+    """The loop over the tile kernels: a cycle's start vector is its own iterate (an iteration is queued behind the
+    one that ends the run), and runs that reach their cap of 1, 2, 3 and 7 hold that iterate, in the caller's buffer
+    (odd) or copied from the handle's (even)."""
+    import paper_1904_02241_amd as gc
+    n = 1 << 14
+    rowptr = np.arange(n + 1, dtype=np.int32)
+    h = gc.graph_load_csr(rowptr, ((np.arange(n) + 1) % n).astype(np.int32))
+    g = gg.rmat(15, 8, seed=5)
+    h2 = load(g)
+    d = gc.GC_PUSH if form == "tocab_push" else gc.GC_PULL
+    parts = [gc.tocab_partition(x, d, W, K) if form.startswith("tocab") else None for x in (h, h2)]
+    print(f"converge caps {form} W={W} k={K}", flush=True)
+    got, k, delta, _ = run(gc, h, parts[0], form, n, 0.0, 50)
+    assert (k, delta) == (1, 0.0)
+    np.testing.assert_array_equal(got, np.full(n, np.float32(1.0 / n)))
+    got, k, delta, _ = run(gc, h, parts[0], form, n, 0.0, 1)
+    assert (k, delta) == (1, 0.0)
+    for cap in (1, 2, 3, 7):
+        got, k, delta, r0 = run(gc, h2, parts[1], form, g.n, 0.0, cap)
+        assert k == cap and delta > 0.0
+        want = oracle.pagerank(g.n, g.rowptr, g.colidx, 0.85, cap, r0=r0)
+        assert float(np.abs(got.astype(np.float64) - want).sum()) <= L1_TOL
+        _, _, deltas = oracle.pagerank_converge(g.n, g.rowptr, g.colidx, 0.0, cap, r0=r0)
+        assert abs(delta - deltas[cap - 1]) <= 1e-6
+    # two iterations to converge: the change of the second is the first not above this tolerance
+    got, k, delta, _ = run(gc, h2, parts[1], form, g.n, float(deltas[1]) * 1.001, 50)
+    assert k == 2
+    want = oracle.pagerank(g.n, g.rowptr, g.colidx, 0.85, 2, r0=r0)
+    assert float(np.abs(got.astype(np.float64) - want).sum()) <= L1_TOL
+    for p in parts:
+        if p is not None:
+            p.free()
+    h2.free()
+    h.free()

@@ -329,3 +329,39 @@ def test_autotune_does_not_choose_between_widths_that_run_alike():
                 assert W == alike[0] or W not in alike
                 assert ms > 0
             h.free()
+
+
+# the corner shapes of the small graphs, padded with isolated vertices past what one work-group holds, so that the
+# tiled, pushed and blocked kernels meet them: no arc, one row or one column of all arcs, chains, sinks
+@pytest.mark.parametrize("make", [lambda: graphs.edgeless(5), lambda: graphs.star_out(9), lambda: graphs.star_in(9),
+                                  lambda: graphs.star_in(5001), lambda: graphs.star_out(9000), lambda: graphs.chain(8),
+                                  lambda: graphs.chain(3000), lambda: graphs.complete(6), lambda: graphs.dangling_mix(),
+                                  lambda: graphs.two_components(), lambda: graphs.random_small(40, 120, 1)],
+                         ids=["edgeless", "star_out9", "star_in9", "star_in5001", "star_out9000", "chain8", "chain3000",
+                              "complete", "dangling_mix", "two_components", "random"])
+@pytest.mark.parametrize("form", FORMS + ["tocab_wide"])
+def test_pagerank_corner_shapes_beyond_one_work_group(make, form):
+    import paper_1904_02241_amd as gc
+    from tests.gpu_util import dev, host, torch
+    small = make()
+    n = 20011
+    src = np.repeat(np.arange(small.n), np.diff(small.rowptr))
+    for shift in (0, n - small.n):  # the shape among the first vertices, and among the last
+        g = gg.from_edges(n, src + shift, small.colidx.astype(np.int64) + shift, name=f"{small.name}_padded")
+        h = load(g)
+        part = None
+        if form.startswith("tocab"):
+            part = gc.tocab_partition(h, gc.GC_PUSH if form == "tocab_push" else gc.GC_PULL,
+                                      1 << 16 if form == "tocab_wide" else 1 << 11, 256)
+        rin = dev(np.full(n, 1.0 / n, np.float32))
+        out = torch().empty_like(rin)
+        d = gc.GC_PUSH if form == "plain_push" else gc.GC_PULL
+        for mode in (oracle.UNIFORM, oracle.LEAK):
+            print(f"padded {small.name} {form} shift={shift} mode={mode}", flush=True)
+            ran = _ran(gc, lambda: gc.pagerank_iter(h, part, d, 0.85, mode, rin, out, 5))
+            assert "pr_small" not in ran
+            want = oracle.pagerank(n, g.rowptr, g.colidx, 0.85, 5, mode=mode, r0=host(rin).astype(np.float64))
+            assert l1(host(out), want) <= L1_TOL
+        if part is not None:
+            part.free()
+        h.free()
