@@ -18,12 +18,6 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
-__device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, kWave));
-  return v;
-}
-
 __device__ __forceinline__ int wave_max(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, kWave));
@@ -67,16 +61,6 @@ __device__ __forceinline__ T ld_stream(const T* p) {
 template <class T>
 __device__ __forceinline__ void st_stream(T* p, T v) {
   __builtin_nontemporal_store(v, p);
-}
-
-// First index in [lo, hi) with a[idx] >= key (a ascending).
-__device__ __forceinline__ int32_t lower_bound(const int32_t* a, int32_t lo, int32_t hi, int32_t key) {
-  while (lo < hi) {
-    const int32_t mid = lo + ((hi - lo) >> 1);
-    if (a[mid] < key) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
 }
 
 }  // namespace gcd

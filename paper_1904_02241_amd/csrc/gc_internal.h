@@ -27,7 +27,7 @@ struct gc_graph_s {
   int32_t* t_w = nullptr;
   void* scratch = nullptr;  // holds the arrays from contrib to arc_pre (but not those allocated later)
   // PageRank scratch: contributions (two buffers for the fused plain pull),
-  // push accumulators, FP64 dangling partials / totals and a done counter
+  // push accumulators, FP64 dangling partials and totals
   float* contrib[2] = {nullptr, nullptr};
   double* sums = nullptr;     // push accumulators (FP64 atomics)
   int32_t* tile_row_in = nullptr;  // pull tiles over the transposed graph
@@ -37,7 +37,6 @@ struct gc_graph_s {
   // [0] by updates of at most that many work-groups
   double* dpart[2] = {nullptr, nullptr};
   double* dtotal = nullptr;   // [2] ping-pong dangling totals
-  unsigned* counter = nullptr;
   int32_t dpart_slots = 0;
   bool values_f32 = false;  // the weight arrays hold FP32 values (GC_VALUES_F32)
   // convergence mode (allocated by the first pagerank_converge call): FP64
@@ -119,8 +118,6 @@ struct gc_tocab_s {
   uint16_t* col16 = nullptr;      // [m_pad], zero past m
   gc_head_word* heads = nullptr;  // [m_pad/64 + 1], bits at and past m set
   int64_t m_pad = 0;              // multiple of wave_tile_arcs(), >= m + wave_tile_arcs()
-  int32_t* wtile_row = nullptr;   // unused by the stream layout
-  int32_t n_wtiles = 0;
   int2* seg = nullptr;            // [B][mR+1]: first local row of block b in range j, shift to range-major index
   int32_t* rstart = nullptr;      // [mR+1] range-major start of merge range j
   uint16_t* id16s = nullptr;      // [P] id16 in range-major order

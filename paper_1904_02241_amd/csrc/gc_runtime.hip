@@ -124,7 +124,7 @@ void free_tocab(gc_tocab t) {
   free_tocab(t->inner);
   if (t->mrange == t->range_ptr) t->mrange = nullptr;
   void* bufs[] = {t->blk_rowoff, t->mrange, t->row_ptr, t->id_map, t->col, t->w, t->range_ptr, t->partial, t->pmin,
-                  t->tile_row, t->col16, t->chunk_beg, t->wtile_row, t->id16,
+                  t->tile_row, t->col16, t->chunk_beg, t->id16,
                   t->heads, t->seg, t->rstart, t->id16s, t->bc_part,
                   t->val32, t->w_pad, t->w8, t->xid16, t->xperm, t->xstart, t->xc, t->pcol16, t->pheads};
   for (void* p : bufs)
@@ -323,7 +323,7 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
   const size_t contrib0 = slab.reserve(sizeof(float) * nn), contrib1 = slab.reserve(sizeof(float) * nn),
                sums = slab.reserve(sizeof(double) * nn), dpart0 = slab.reserve(sizeof(double) * g->dpart_slots),
                dpart1 = slab.reserve(sizeof(double) * gcx::kDangSlots), dtotal = slab.reserve(sizeof(double) * 2),
-               counter = slab.reserve(sizeof(unsigned) * 4), front = slab.reserve(sizeof(uint32_t) * words),
+               front = slab.reserve(sizeof(uint32_t) * words),
                next = slab.reserve(sizeof(uint32_t) * words), queue0 = slab.reserve(sizeof(int32_t) * nn),
                queue1 = slab.reserve(sizeof(int32_t) * nn), stats = slab.reserve(sizeof(int32_t) * gcx::kStatSlots),
                visited = slab.reserve(sizeof(uint32_t) * words), mark = slab.reserve(sizeof(int32_t) * nn),
@@ -337,7 +337,6 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
     g->dpart[0] = slab.take<double>(g->scratch, dpart0);
     g->dpart[1] = slab.take<double>(g->scratch, dpart1);
     g->dtotal = slab.take<double>(g->scratch, dtotal);
-    g->counter = slab.take<unsigned>(g->scratch, counter);
     g->front = slab.take<uint32_t>(g->scratch, front);
     g->next = slab.take<uint32_t>(g->scratch, next);
     g->queue[0] = slab.take<int32_t>(g->scratch, queue0);
@@ -377,7 +376,6 @@ int graph_load_csr(int32_t n, int64_t m, const int32_t* rowptr, const int32_t* c
     return fail(GC_EINVAL, "graph_load_csr: %s", (bad & 1) ? "rowptr is not a valid offset array for m arcs"
                                                             : "a column index is outside [0, n)");
   }
-  if (e == hipSuccess) e = hipMemsetAsync(g->counter, 0, sizeof(unsigned) * 4, stream);
   if (e == hipSuccess) e = hipMemsetAsync(g->dtotal, 0, sizeof(double) * 2, stream);
   if (e == hipSuccess)
     e = gcx::build_transpose(n, m, g->rowptr, g->colidx, g->w, g->t_rowptr, g->t_colidx, g->t_w, stream);
