@@ -87,7 +87,8 @@ const char* gc_last_error(void);
 /* Replaces the device allocator used for every buffer the library owns.
  * alloc(bytes, stream, ctx) returns device memory or NULL; release(ptr,
  * stream, ctx) gives it back. Both NULL restores hipMalloc / hipFree. Must
- * not be called while handles made with the previous allocator are alive. */
+ * not be called while handles made with the previous allocator are alive.
+ * Frees the pinned pages (up to 64) that freed graphs have left for the next. */
 int gc_set_allocator(void* (*alloc)(size_t bytes, hipStream_t stream, void* ctx),
                      void (*release)(void* ptr, hipStream_t stream, void* ctx), void* ctx);
 

@@ -72,19 +72,17 @@ bool is_device_ptr(const void* p) {
 // Pinned mirrors of the traversal counters, one per graph. Allocating and
 // freeing one costs 80 us, most of what the host does to load a small graph,
 // so up to kMirrorsKept of them wait here for the next graph (a graph is
-// freed after the device has finished with it).
-constexpr size_t kMirrorsKept = 64;
+// freed after the device has finished with it) or for gc_set_allocator, which
+// frees them.
+constexpr int kMirrorsKept = 64;
 std::mutex g_mirror_mu;
-std::vector<int32_t*> g_mirrors;
+int32_t* g_mirrors[kMirrorsKept];
+int g_mirrors_kept = 0;
 
 int32_t* mirror_get() {
   {
     std::lock_guard<std::mutex> lk(g_mirror_mu);
-    if (!g_mirrors.empty()) {
-      int32_t* p = g_mirrors.back();
-      g_mirrors.pop_back();
-      return p;
-    }
+    if (g_mirrors_kept > 0) return g_mirrors[--g_mirrors_kept];
   }
   void* p = nullptr;
   if (hipHostMalloc(&p, sizeof(int32_t) * gcx::kStatSlots, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
@@ -97,12 +95,17 @@ int32_t* mirror_get() {
 void mirror_put(int32_t* p) {
   {
     std::lock_guard<std::mutex> lk(g_mirror_mu);
-    if (g_mirrors.size() < kMirrorsKept) {
-      g_mirrors.push_back(p);
+    if (g_mirrors_kept < kMirrorsKept) {
+      g_mirrors[g_mirrors_kept++] = p;
       return;
     }
   }
   (void)hipHostFree(p);
+}
+
+void mirrors_free() {
+  std::lock_guard<std::mutex> lk(g_mirror_mu);
+  while (g_mirrors_kept > 0) (void)hipHostFree(g_mirrors[--g_mirrors_kept]);
 }
 
 __global__ void k_mark(int32_t* word, int32_t seq) {
@@ -261,6 +264,7 @@ int gc_set_allocator(void* (*alloc)(size_t, hipStream_t, void*), void (*release)
   g_alloc = alloc;
   g_release = release;
   g_ctx = alloc ? ctx : nullptr;
+  mirrors_free();
   return GC_OK;
 }
 
