@@ -43,8 +43,8 @@ struct gc_graph_s {
   // partials of the L1 change per update work-group, results, and a second
   // FP32 iterate
   double* lpart = nullptr;
-  double* ltotal = nullptr;     // the one-work-group form's change and count; [2]: number (int64) of the last call that converged
-  int64_t conv_calls = 0;       // calls so far, which number them
+  double* ltotal = nullptr;     // the one-work-group form's change and count; [2]: number (int32) of the last call that ended
+  uint32_t conv_calls = 0;      // calls so far, which number them
   float* rank_tmp = nullptr;
   // traversal scratch
   uint32_t* front = nullptr;  // status arrays (Section 3.3), one bit per vertex

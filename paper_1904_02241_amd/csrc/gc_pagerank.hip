@@ -37,10 +37,11 @@ int g_cus = 256;  // compute units of the GPU (read once by pagerank_setup)
 struct Change {
   const double* lpart = nullptr;  // null: no change to sum
   double tol = 0.0;
-  int64_t* word = nullptr;
-  int64_t call = 0;
+  int32_t* stop = nullptr;
   int32_t* host = nullptr;
   int32_t seq = 0;
+  int32_t call = 0;
+  int32_t last = 0;  // the run ends here whatever the change
 };
 
 // D for the next iteration: the partials summed in index order by one
@@ -61,14 +62,14 @@ __device__ __forceinline__ double reduce_slots(const double* __restrict__ slots,
 // of the L1-change partials), in a fixed order.
 __global__ __launch_bounds__(1024) void k_reduce_dangling(const double* __restrict__ dpart, int32_t count,
                                                           double* __restrict__ dtotal, Change ch) {
-  if (ch.lpart && *ch.word >= ch.call) return;  // uniform
+  if (ch.lpart && stopped(ch.stop, ch.call)) return;  // uniform
   __shared__ double part[1024 / kWave];
   const double t = reduce_slots(dpart, count, part);
   if (threadIdx.x == 0) *dtotal = t;
   if (ch.lpart) {
     const double l = reduce_slots(ch.lpart, count, part);
     if (threadIdx.x == 0) {
-      if (l <= ch.tol) *ch.word = ch.call;
+      if (l <= ch.tol || ch.last) *ch.stop = ch.call;
       const uint64_t b = static_cast<uint64_t>(__double_as_longlong(l));
       for (int i = 0; i < 2; ++i)
         __hip_atomic_store(ch.host + i, static_cast<int32_t>(b >> (32 * i)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -102,8 +103,8 @@ __global__ __launch_bounds__(kThreads) void k_pr_tocab_pull(const int32_t* __res
                                                             const int32_t* __restrict__ tile_row,
                                                             const float* __restrict__ c,
                                                             float* __restrict__ partial,
-                                                            Stop stop) {
-  if (stopped(stop)) return;
+                                                            const int32_t* __restrict__ stop, int32_t call) {
+  if (stopped(stop, call)) return;
   __shared__ float vals[kStageCap];
   const int32_t r0 = tile_row[blockIdx.x], r1 = tile_row[blockIdx.x + 1];
   if (r0 >= r1) return;
@@ -221,9 +222,9 @@ __global__ __launch_bounds__(kLdsThreads) void k_pr_tocab_pull_lds(
     const int32_t* __restrict__ chunk_end, const int32_t* __restrict__ chunk_blk,
     const int32_t* __restrict__ chunk_j0, const int32_t* __restrict__ chunk_ns, const int2* __restrict__ seg,
     int32_t R, int32_t log2W, int32_t n, const float* __restrict__ c, float* __restrict__ partial,
-    uint32_t partial_bytes, Stop stop) {
+    uint32_t partial_bytes, int32_t call, const int32_t* __restrict__ stop) {
   extern __shared__ float lds[];
-  if (stopped(stop)) return;
+  if (stopped(stop, call)) return;
   const int32_t W = 1 << log2W;
   const int lane = threadIdx.x & (kWave - 1);
   const int wid = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(kThreads) void k_pr_plain_pull(const int32_t* __res
                                                             const int32_t* __restrict__ t_col,
                                                             const int32_t* __restrict__ tile_row,
                                                             const float* __restrict__ c_in, Update u) {
-  if (stopped(u.stop)) return;
+  if (stopped(u.stop, u.call)) return;
   __shared__ float vals[kStageCap];
   const int32_t r0 = tile_row[blockIdx.x], r1 = tile_row[blockIdx.x + 1];
   double mine = 0.0, dl = 0.0;
@@ -372,7 +373,7 @@ template <int K, bool kFlat>
 __global__ __launch_bounds__(kThreads) void k_pr_merge(const int32_t* __restrict__ range_ptr, int32_t B,
                                                        const uint16_t* __restrict__ id16,
                                                        const float* __restrict__ partial, Update u) {
-  if (stopped(u.stop)) return;
+  if (stopped(u.stop, u.call)) return;
   __shared__ double acc[K];
   const double share = dangling_share(u);
   merge_accumulate<K, kFlat>(range_ptr, B, id16, partial, blockIdx.x, acc);
@@ -458,7 +459,7 @@ template <int K, int NT = merge_threads<K>()>
 __global__ __launch_bounds__(NT) void k_pr_merge_persist(const int32_t* __restrict__ rstart,
                                                          const uint16_t* __restrict__ id16s,
                                                          const float* __restrict__ partial, int32_t R, Update u) {
-  if (stopped(u.stop)) return;
+  if (stopped(u.stop, u.call)) return;
   __shared__ double acc[K];
   for (int i = threadIdx.x; i < K; i += NT) acc[i] = 0.0;
   __syncthreads();
@@ -595,8 +596,8 @@ __global__ __launch_bounds__(kThreads) void k_pr_push(const int32_t* __restrict_
                                                       const int32_t* __restrict__ id_map,
                                                       const int32_t* __restrict__ col,
                                                       const float* __restrict__ c, double* __restrict__ sums,
-                                                      int64_t rows, Stop stop) {
-  if (stopped(stop)) return;
+                                                      int64_t rows, const int32_t* __restrict__ stop, int32_t call) {
+  if (stopped(stop, call)) return;
   __shared__ int32_t start[kThreads];
   __shared__ int32_t first[kThreads];
   __shared__ float val[kThreads];
@@ -651,7 +652,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds(const int32_t* 
                                                                  const int32_t* __restrict__ id_map,
                                                                  const int32_t* __restrict__ col, int32_t log2W,
                                                                  const float* __restrict__ c, Update u) {
-  if (stopped(u.stop)) return;
+  if (stopped(u.stop, u.call)) return;
   extern __shared__ double acc[];  // the block's W sums
   const int32_t W = 1 << log2W;
   const int32_t v0 = static_cast<int32_t>(blockIdx.x) << log2W;
@@ -841,7 +842,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
     const int32_t* __restrict__ blk_rowoff, const int32_t* __restrict__ row_ptr,
     const uint16_t* __restrict__ pcol16, const gc_head_word* __restrict__ pheads, int32_t log2W,
     const float* __restrict__ xc_in, PushX x, float* __restrict__ xc_out, Update u) {
-  if (stopped(u.stop)) return;
+  if (stopped(u.stop, u.call)) return;
   extern __shared__ double acc[];  // the block's W sums, then (as FP32) its W new contributions
   constexpr int kPer = kPushLdsMaxWidth / kPushLdsThreads;
   constexpr int kWaves = kPushLdsThreads / kWave;
@@ -919,7 +920,7 @@ __global__ __launch_bounds__(kPushLdsThreads) void k_pr_push_lds_x(
 }
 
 __global__ __launch_bounds__(kThreads) void k_pr_apply(double* __restrict__ sums, Update u) {
-  if (stopped(u.stop)) return;
+  if (stopped(u.stop, u.call)) return;
   const int32_t v = blockIdx.x * kThreads + threadIdx.x;
   const double D = dangling_total(u, dangling_share(u));
   double mine = 0.0, dl = 0.0;
@@ -1049,11 +1050,11 @@ hipError_t spmv_stream(gc_graph g, gc_tocab t, const float* x, const float* vals
       if (vals)
         k_pr_tocab_pull_lds<true><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, vals, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, Stop());
+            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, 0, nullptr);
       else
         k_pr_tocab_pull_lds<false><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
             t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
-            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, Stop());
+            t->chunk_ns, t->seg, t->mR, t->log2W, g->n, x, t->partial, bytes, 0, nullptr);
     }
   }
   ProfScope prof("spmv_merge", s);
@@ -1270,8 +1271,8 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   Change change;
   if (cv) {
     change.tol = cv->tol;
-    change.word = reinterpret_cast<int64_t*>(g->ltotal + 2);
-    change.call = ++g->conv_calls;
+    change.stop = reinterpret_cast<int32_t*>(g->ltotal + 2);
+    change.call = static_cast<int32_t>(++g->conv_calls);
   }
   auto hand_over = [&](int32_t count, int slot) {
     const bool fused = few && count <= kDangFused;
@@ -1290,7 +1291,8 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
   float* const iterate[2] = {rank_out, cv ? g->rank_tmp : nullptr};
   if (cv) {
     u.lpart = g->lpart;
-    u.stop = Stop{change.word, change.call};
+    u.stop = change.stop;
+    u.call = change.call;
     change.lpart = g->lpart;
   }
   // Iteration `it` is queued before the host waits for the change of the one
@@ -1324,7 +1326,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
             k_pr_tocab_pull_lds<false><<<t->n_chunks, kLdsThreads, pull_lds_bytes(t), s>>>(
                 t->row_ptr, t->col16, t->heads, nullptr, t->chunk_beg, t->chunk_end, t->chunk_blk, t->chunk_j0,
                 t->chunk_ns, t->seg, t->mR, t->log2W, n, buf.contrib[0], buf.partial,
-                static_cast<uint32_t>(sizeof(float) * (t->P + 8)), u.stop);
+                static_cast<uint32_t>(sizeof(float) * (t->P + 8)), u.call, u.stop);
         }
         u.contrib = buf.contrib[0];
         ProfScope prof("pr_merge", s);
@@ -1339,7 +1341,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
         {
           ProfScope prof("pr_tocab_pull", s);
           k_pr_tocab_pull<<<t->n_tiles, kThreads, 0, s>>>(t->row_ptr, t->col, t->tile_row, buf.contrib[0],
-                                                          buf.partial, u.stop);
+                                                          buf.partial, u.stop, u.call);
         }
         u.contrib = buf.contrib[0];  // safe in place: the pull pass has finished reading c
         ProfScope prof("pr_merge", s);
@@ -1379,11 +1381,12 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
         if (P > 0) {
           ProfScope prof("pr_tocab_push", s);
           k_pr_push<<<static_cast<uint32_t>((P + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-              t->row_ptr, t->id_map, t->col, buf.contrib[0], buf.sums, P, u.stop);
+              t->row_ptr, t->id_map, t->col, buf.contrib[0], buf.sums, P, u.stop, u.call);
         }
       } else {
         ProfScope prof("pr_plain_push", s);
-        k_pr_push<<<vgrid, kThreads, 0, s>>>(g->rowptr, nullptr, g->colidx, buf.contrib[0], buf.sums, n, u.stop);
+        k_pr_push<<<vgrid, kThreads, 0, s>>>(g->rowptr, nullptr, g->colidx, buf.contrib[0], buf.sums, n, u.stop,
+                                             u.call);
       }
       u.contrib = buf.contrib[0];
       ProfScope prof("pr_apply", s);
@@ -1392,6 +1395,7 @@ hipError_t pagerank_run(gc_graph g, gc_tocab t, int32_t dir, float damping, int3
     if (cv) {
       change.host = slot_of(it);
       change.seq = seq_of(it);
+      change.last = it == iters - 1;
       ++g->level_seq;
     }
     hand_over(parts, (it + 1) & 1);

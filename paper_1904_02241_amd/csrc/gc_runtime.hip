@@ -744,7 +744,7 @@ int pagerank_converge(gc_graph g, gc_tocab t, int32_t dir_if_plain, float dampin
     g->ltotal = static_cast<double*>(gcx::dev_alloc(3 * sizeof(double), stream));
     g->rank_tmp = static_cast<float*>(gcx::dev_alloc(sizeof(float) * std::max<int32_t>(g->n, 1), stream));
     hipError_t e = hipSuccess;
-    if (g->ltotal) e = hipMemsetAsync(g->ltotal, 0, 3 * sizeof(double), stream);  // no call has converged
+    if (g->ltotal) e = hipMemsetAsync(g->ltotal, 0, 3 * sizeof(double), stream);  // no call has ended
     if (!g->lpart || !g->ltotal || !g->rank_tmp || e != hipSuccess) {
       for (void* p : {static_cast<void*>(g->lpart), static_cast<void*>(g->ltotal), static_cast<void*>(g->rank_tmp)})
         if (p) gcx::dev_free(p, stream);
