@@ -11,8 +11,10 @@
 //   s[v]  = sum over arcs u -> v of c[u]
 //   r'[v] = (1 - d)/n + d * (s[v] + D/n)
 // The update kernel of iteration t writes c for iteration t+1 and each of
-// its work-groups a partial of the next D; the last work-group to finish
-// adds the partials in a fixed order, so D is reproducible.
+// its work-groups a partial of the next D. Up to kDangSlots partials are
+// added by every work-group of the next update, more (and all of them in
+// convergence mode) by a kernel of one work-group; either adds them in a fixed
+// order, so D is reproducible.
 
 #include <climits>
 #include <cstdlib>

@@ -166,7 +166,8 @@ struct ValuedArc {
 
 // Arcs kFirst * kThreads + [0, kCount * kThreads) of a tile of len arcs
 // starting at a0: the columns (coalesced across the work-group, streamed
-// past the cache), then the gathers, into LDS through store(). Indices past
+// past the cache), then the gathers, times the arcs' values into `vals` (LDS);
+// between() runs while the gathers are in flight. Indices past
 // the end are clamped to the last arc instead of branched around, which
 // keeps the loads free of control flow (a branch per load would make each
 // one wait for the previous).

@@ -1027,7 +1027,7 @@ __global__ __launch_bounds__(NT) void k_sssp_merge_stream(const int32_t* __restr
     }
     // distance (or depth) and status bits, with one atomic per 32-bit status
     // word (a wave's 32 lanes hold one word's vertices, the range starts on
-    // a word), then one queue append for the work-group
+    // a word), then the new frontier's degrees, which are counted
     uint32_t took = 0;  // bit u: vertex v0 + tid + u NT entered the next frontier
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -1760,8 +1760,9 @@ struct Heuristic {
   // without: grids of 160,000, 10^6, 4 and 8 M vertices 501, 668, 1052, 1616
   // us against 453, 553, 772, 1163; uniform of 8 arcs per vertex 229, 317, 604,
   // 879 against 209, 273, 525, 758; R-MAT of 8 194, 252, 370, 440 against 174,
-  // 201, 300, 340. Up to 2^18 vertices that is some 10 us per level, and the
-  // blocked form, which the method is about, stays; beyond it grows with n.
+  // 201, 300, 340. So the arm is not the faster form at any size: up to 2^18
+  // vertices, where it costs some 10 us per level, it stays as the header
+  // describes it and traversal_trace shows it; beyond, its cost grows with n.
   static constexpr int64_t kBfsTocabVertices = int64_t{1} << 18;
   static constexpr double kBfsTocabShare = 1.0 / 64.0;
   static constexpr double kBfsTocabDegree = 10.0;
@@ -1877,9 +1878,6 @@ int32_t* g_range_flag() {
   return flag;
 }
 
-// Integer weights of a stream-layout partition in its arc order, padded with
-// zeros to the layout's length (built by the first SSSP round over it), and
-// the LDS limit of the kernel that reads them.
 // The LDS limit of the stream-layout traversal pull (a block's values and
 // its chunk's position table).
 hipError_t stream_pull_setup() {
@@ -1895,6 +1893,9 @@ hipError_t stream_pull_setup() {
   return attr;
 }
 
+// Integer weights of a stream-layout partition in its arc order, padded with
+// zeros to the layout's length (built by the first SSSP round over it), and
+// the LDS limit of the kernel that reads them.
 hipError_t stream_weights(gc_tocab t, hipStream_t s) {
   GC_HIP_TRY(stream_pull_setup());
   if (t->w_pad || t->w8) return hipSuccess;
@@ -2106,8 +2107,8 @@ hipError_t run_level(gc_graph g, Frontier& f, bool bfs, int32_t* value, int32_t 
         k_bfs_pull<kThreads><<<pull_grid(n), kThreads, 0, s>>>(g->t_rowptr, g->t_colidx, n, f.front(), value, level,
                                                                f.next(), g->visited, tally);
     } else if (t->col16) {
-      // stream layout: the block's frontier bits (as 0 / INT32_MAX) in LDS,
-      // per-(row, block) minima stored range-major (0: an in-neighbour of
+      // stream layout: the block's frontier bits (as 1 or 0) in LDS,
+      // per-(row, block) maxima stored range-major (1: an in-neighbour of
       // the row is in the frontier), merged as one stream per range
       GC_HIP_TRY(stream_pull_setup());
       {

@@ -88,7 +88,7 @@ def _arcs(n, m, seed):
     return gg.from_edges(n, u, v + (v >= u), name=f"arcs{n}_{m}")
 
 
-# the edges of the radix passes: one arc, a head word (64 arcs) and an arc tile (8192) less, full and more; one
+# the edges of the radix passes: one arc, a head word (64 arcs) and two arc tiles (8192) less, full and more; one
 # vertex bit, digits of equal and unequal width; one block, the largest one-pass block count and two passes;
 # rows and blocks far apart (long runs of empty rows)
 @pytest.mark.parametrize("n,m,W,k", [(2, 1, 1 << 10, 256), (2, 2, 1 << 10, 256), (300, 63, 1 << 10, 256),
