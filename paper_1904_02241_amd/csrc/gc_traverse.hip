@@ -166,14 +166,16 @@ __device__ __forceinline__ void reset_stats(int32_t* stats) {
 }
 
 // Writes the level's counters (the first 16 slots and `outs` scheduler
-// outputs) to the pinned mirror, clears them for the next level, then writes
-// `seq`, which the host waits for: once it is there, the counters are the
-// next user's. One wave.
-__device__ __forceinline__ void publish_stats(int32_t* stats, int32_t* host, int32_t seq, int outs) {
-  for (int i = gcd::lane_id(); i < gcx::kStatOut + outs; i += kWave)
-    if (i != gcx::kStatSeq)
-      __hip_atomic_store(host + i, __hip_atomic_load(stats + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+// outputs) and the clock t1 at its end to the pinned mirror, clears them for
+// the next level, then writes `seq`, which the host waits for: once it is
+// there, the counters are the next user's. One wave.
+__device__ __forceinline__ void publish_stats(int32_t* stats, int32_t* host, int32_t seq, int outs, uint64_t t1) {
+  for (int i = gcd::lane_id(); i < gcx::kStatOut + outs; i += kWave) {
+    int32_t v = __hip_atomic_load(stats + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (i == gcx::kStatT1) v = static_cast<int32_t>(t1);
+    if (i == gcx::kStatT1 + 1) v = static_cast<int32_t>(t1 >> 32);
+    if (i != gcx::kStatSeq) __hip_atomic_store(host + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   reset_stats(stats);
   // one fence for both (it waits for the stores of all lanes of the wave; a
   // second one between them, or a release here, costs 1.7 us a level)
@@ -364,9 +366,8 @@ __global__ __launch_bounds__(kThreads) void k_level_end(int32_t* __restrict__ st
       __syncthreads();
     }
     if (threadIdx.x < kWave) {
-      if (threadIdx.x == 0) *reinterpret_cast<uint64_t*>(stats + gcx::kStatT1) = t1;
-      __threadfence();  // the wave reads back what its lanes have written
-      publish_stats(stats, host, seq, dec.params ? dec.K : 0);
+      if (dec.params) __threadfence();  // the wave reads back the decision that its lanes have written
+      publish_stats(stats, host, seq, dec.params ? dec.K : 0, t1);
     }
   }
   if (!clear || first) return;
